@@ -257,7 +257,7 @@ __global__ __launch_bounds__(512) void dist_skinny_kernel(SkinnyArgs p)
 // whose pair is <= T (at most 32 R, see the file header; `cap` >= that bound), so only those
 // blocks' keys are read, 128 bytes each.  One workgroup of 1024 threads per query.
 // ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kThrThreads) void block_threshold_kernel(const uint64_t *bmin, int64_t nb, int r_sel,
+__global__ __launch_bounds__(kThrThreads) void block_threshold_kernel(const uint64_t *bmin, const int32_t *count, int64_t nb, int r_sel,
                                                                       const float *keys, int64_t n_pad, int n,
                                                                       uint64_t *cand, int32_t *cand_count, int cap)
 {
@@ -267,6 +267,7 @@ __global__ __launch_bounds__(kThrThreads) void block_threshold_kernel(const uint
     __shared__ int blk_n, cnt_s;
     __shared__ int32_t blk_s[kMaxRescore];
     const int q = blockIdx.x, tid = threadIdx.x;
+    if (count && q >= *count) return;   // uniform
     const uint64_t *bq = bmin + (size_t)q * nb;
     // fewer blocks than wanted entries: everything passes
     const uint64_t t = r_sel >= nb ? kSentinel : rth_smallest_of(bq, nb, r_sel, list, &sel_s, &list_n, tid);
@@ -364,12 +365,12 @@ hipError_t launch_skinny_stream(const SkinnyLaunch &a, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_select(const float *keys, const uint64_t *bmin, int64_t n_pad, int n, int b, int r,
+hipError_t launch_select(const float *keys, const uint64_t *bmin, int64_t n_pad, int n, int b, const int32_t *count, int r,
                          int32_t *cand_count, uint64_t *cand, hipStream_t s)
 {
     const int64_t nb = n_pad / 32;
     if (!select_supported(n_pad, r) || b < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(block_threshold_kernel, dim3(b), dim3(kThrThreads), 0, s, bmin, nb, r, keys, n_pad, n, cand, cand_count,
+    hipLaunchKernelGGL(block_threshold_kernel, dim3(b), dim3(kThrThreads), 0, s, bmin, count, nb, r, keys, n_pad, n, cand, cand_count,
                        32 * r);
     return hipGetLastError();
 }

@@ -827,6 +827,7 @@ void plan_stream_k(DistPlan &pl, int num_cus, int64_t d_pad)
 
 size_t dist_partial_bytes(const DistPlan &plan)
 {
+    if (plan.variant == 4) return plan.st_cut ? (size_t)plan.st_wgs * 2 * (size_t)plan.bm * kTileN * 4 : 0;
     return (size_t)plan.sk_wgs * plan.sk_slots * (size_t)plan.bm * kTileN * 4;
 }
 
@@ -890,6 +891,7 @@ hipError_t launch_dist_topr(const DistPlan &plan, const DistArgs &a, hipStream_t
     if (plan.r < 1 || plan.r > kMaxRescore || a.d_pad % kPadD != 0) return hipErrorInvalidValue;
     if (plan.variant == 3 && (!a.keys || (!a.bmin && !a.projection))) return hipErrorInvalidValue;
     switch (plan.variant) {
+    case 4: return launch_dist_stream(plan, a, s);
     case 0: return launch_variant<DistCfg<256, 32, 16, 4, 2>>(plan, a, s);
     case 1: return launch_variant<DistCfg<256, 32, 32, 3>>(plan, a, s);
     case 2: return launch_variant<DistCfg<128, 32, 64, 4>>(plan, a, s);

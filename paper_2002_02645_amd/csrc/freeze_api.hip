@@ -121,8 +121,15 @@ int lists_per_query(const DistPlan &pl, bool device_count)
     return pl.bal_f > 0 ? pl.bal_lists : pl.n_splits;
 }
 
+// The streaming kernel serves batches of at most this many queries (50,000 x 2,048: 128 queries 135 -> 113 us,
+// but 160 queries as two tiles of 128 would read the cache twice; the 256-row tile takes 137 us), and
+// batches up to 256 on caches so small that 256-row tiles would leave most CUs idle (256 x 2,000 x 512:
+// 52 -> 36 us, 256 x 3,000 x 4,096: 127 -> 81 us).
+constexpr int kStreamRows = 128;
+
+// small_ws: choose the decomposition with the smallest workspace (freeze_lookup_static)
 bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, int rescore_r, bool cascade,
-                  LookupShape *out)
+                  LookupShape *out, bool small_ws = false)
 {
     if (b < 0 || b > (int64_t)1 << 30 || k < 1 || k > L.n) return false;
     if (k > FREEZE_MAX_K && !(k == L.n && k <= FREEZE_MAX_RESCORE)) return false;
@@ -156,9 +163,13 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
         // moderate size: every workgroup of the fused kernel gets a few tiles only and spends most of
         // its time filling its empty candidate lists key by key, so the keys go out here too
         // (measured cross-over: about 2^26 keys; 256 x 2,000: 129 -> 69 us, 200 x 50,000 x 512: 209 -> 80 us).
-        out->keys = !cascade && b <= 256 && (b * 20 <= L.d_pad || b * L.n_pad <= ((int64_t)1 << 26)) &&
+        out->keys = b <= (cascade ? kStreamRows : 256) && (b * 20 <= L.d_pad || b * L.n_pad <= ((int64_t)1 << 26)) &&
                     select_supported(L.n_pad, r);
-        out->plan = plan_dist(b, L.n, r, ctx->num_cus, out->keys, L.d_pad);
+        const int64_t k_steps = (L.n_pad / kTileN) * (L.d_pad / kKB);   // per query tile
+        if (out->keys && (b <= kStreamRows || 2 * k_steps < 16 * (int64_t)ctx->num_cus))
+            out->plan = plan_stream(b, L.n, r, ctx->num_cus, L.d_pad, small_ws);
+        else
+            out->plan = plan_dist(b, L.n, r, ctx->num_cus, out->keys, L.d_pad);
         out->ws_bytes = align_up((size_t)out->plan.b_pad * L.d_pad * 2);
         if (out->keys)
             out->ws_bytes += select_workspace_bytes(out->plan.b_pad, L.n_pad, r, kAlign) +
@@ -300,11 +311,11 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
             da.bmin = ws.take<uint64_t>(rows * (L.n_pad / 32));
             int32_t *cand_count = ws.take<int32_t>(rows);
             uint64_t *cand = ws.take<uint64_t>(rows * 32 * sh.r);
-            da.partial = sh.plan.sk_wgs > 0 ? ws.take<float>(dist_partial_bytes(sh.plan) / 4) : nullptr;
+            da.partial = dist_partial_bytes(sh.plan) > 0 ? ws.take<float>(dist_partial_bytes(sh.plan) / 4) : nullptr;
             if (launch_dist_topr(sh.plan, da, s) != hipSuccess) return FREEZE_EHIP;
             marks.mark(2);
             marked2 = true;
-            if (launch_select(da.keys, da.bmin, L.n_pad, (int)L.n, (int)b, sh.r, cand_count, cand, s) != hipSuccess)
+            if (launch_select(da.keys, da.bmin, L.n_pad, (int)L.n, (int)b, count, sh.r, cand_count, cand, s) != hipSuccess)
                 return FREEZE_EHIP;
             fa.part = cand;
             fa.part_count = cand_count;
@@ -419,13 +430,13 @@ int confidence_rule_for(const freeze_ctx *ctx, int layer, int k, int *kind)
 
 int lookup_checked(freeze_ctx *ctx, int layer, const float *queries, int64_t b, int k, const HitRule &rule,
                    int rescore_r, int32_t *out_labels, uint8_t *out_hit, int32_t *out_votes, int32_t *out_nbr_idx,
-                   float *out_nbr_dist, void *workspace, size_t workspace_bytes, void *stream)
+                   float *out_nbr_dist, void *workspace, size_t workspace_bytes, void *stream, bool small_ws = false)
 {
     int err;
     const LayerCache *L = get_layer(ctx, layer, &err);
     if (!L) return err;
     LookupShape sh;
-    if (!lookup_shape(ctx, *L, b, k, rescore_r, false, &sh)) return FREEZE_EINVAL;
+    if (!lookup_shape(ctx, *L, b, k, rescore_r, false, &sh, small_ws)) return FREEZE_EINVAL;
     if (b == 0) return FREEZE_OK;   // nothing to look up: data pointers may be null
     if (!queries || !out_labels || !out_hit || !out_votes || !out_nbr_idx || !out_nbr_dist || !workspace)
         return FREEZE_EINVAL;
@@ -697,6 +708,9 @@ int freeze_lookup_static(freeze_ctx *ctx, int layer, const float *queries, int64
     if (!L) return err;
     LookupShape sh;
     if (!lookup_shape(ctx, *L, b, k, rescore_r, false, &sh)) return FREEZE_EINVAL;
+    // a decomposition with accumulator slots that do not fit gives way to one without
+    const bool small_ws = sh.ws_bytes > (size_t)FREEZE_STATIC_SCRATCH_BYTES;
+    if (small_ws && !lookup_shape(ctx, *L, b, k, rescore_r, false, &sh, true)) return FREEZE_EINVAL;
     if (sh.ws_bytes > (size_t)FREEZE_STATIC_SCRATCH_BYTES) return FREEZE_ESCRATCH;
     if (b == 0) return FREEZE_OK;
     hipError_t herr;
@@ -704,7 +718,7 @@ int freeze_lookup_static(freeze_ctx *ctx, int layer, const float *queries, int64
     if (!ws) return FREEZE_EHIP;
     const HitRule rule{0, vote_threshold, 0.f, nullptr};
     return lookup_checked(ctx, layer, queries, b, k, rule, rescore_r, out_labels, out_hit, out_votes, out_nbr_idx,
-                          out_nbr_dist, ws, (size_t)FREEZE_STATIC_SCRATCH_BYTES, stream);
+                          out_nbr_dist, ws, (size_t)FREEZE_STATIC_SCRATCH_BYTES, stream, small_ws);
 }
 
 int freeze_lookup_confidence(freeze_ctx *ctx, int layer, const float *queries, int64_t b, int k, float conf_threshold,

@@ -131,7 +131,8 @@ __host__ __device__ inline int splits_for(int live_mt, int n_tiles, int num_cus,
 
 // Which distance kernel variant serves a re-scoring width.
 struct DistPlan {
-    int variant;    // 0: R<=16, 1: R<=32, 2: R<=64 (fused top-R); 3: keys-out (selection by separate kernels)
+    int variant;    // 0: R<=16, 1: R<=32, 2: R<=64 (fused top-R); 3: keys-out (selection by separate kernels);
+                    // 4: keys-out by the streaming kernel (small query tiles)
     int bm;         // queries per tile
     int r;          // entries kept per (query, split)
     int m_tiles;    // ceil(b / bm)
@@ -152,12 +153,19 @@ struct DistPlan {
     // bal_f more cut the flattened remainder of all query tiles, so every CU gets the same number of
     // tiles (+-1); a query then has bal_lists candidate lists.  bal_f == 0: off.
     int bal_f, bal_nfull, bal_wgs, bal_lists;
+    // streaming kernel (variant 4): st_wgs workgroups take st_len k-steps each of the flattened
+    // (query tile, cache tile, k-step) space; st_cut: some tiles are cut by the ends of ranges
+    int64_t st_len;
+    int st_wgs;
+    bool st_cut;
 };
 
 // d_pad decides stream-K for the keys-out variant (pass 0 to leave it off).
 DistPlan plan_dist(int64_t b, int64_t n, int r, int num_cus, bool keys_out, int64_t d_pad = 0);
 void plan_stream_k(DistPlan &pl, int num_cus, int64_t d_pad);   // sets the sk_* fields of a keys-out plan
-size_t dist_partial_bytes(const DistPlan &plan);   // stream-K accumulator slots (0 when off)
+// Streaming kernel; whole: never cut a tile (needs no accumulator slots).
+DistPlan plan_stream(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad, bool whole);
+size_t dist_partial_bytes(const DistPlan &plan);   // accumulator slots of cut tiles (0 when none are cut)
 
 struct DistArgs {
     const uint16_t *q_bf;   // b_pad x d_pad, tiled layout (tiles of plan.bm rows)
@@ -191,6 +199,7 @@ hipError_t launch_query_prep(const float *queries, const int32_t *sel, const int
                              int32_t *tickets, const float *mu, hipStream_t s);
 
 hipError_t launch_dist_topr(const DistPlan &plan, const DistArgs &a, hipStream_t s);
+hipError_t launch_dist_stream(const DistPlan &plan, const DistArgs &a, hipStream_t s);   // variant 4
 
 // Small-batch (bandwidth-bound) path: streaming kernel + threshold + filter; the result is a
 // candidate list per query for the finishing kernel.
@@ -212,8 +221,8 @@ bool skinny_supported(int64_t b, int64_t n_pad, int64_t d_pad, int r, int num_cu
 // block minima, then the candidate lists.  b queries, rows of n_pad keys.
 bool select_supported(int64_t n_pad, int r);
 size_t select_workspace_bytes(int64_t rows, int64_t n_pad, int r, size_t align);
-hipError_t launch_select(const float *keys, const uint64_t *bmin, int64_t n_pad, int n, int b, int r,
-                         int32_t *cand_count, uint64_t *cand, hipStream_t s);
+hipError_t launch_select(const float *keys, const uint64_t *bmin, int64_t n_pad, int n, int b, const int32_t *count, int r,
+                         int32_t *cand_count, uint64_t *cand, hipStream_t s);   // count (device): live queries, or null (= b)
 int plan_skinny_splits(int64_t n, int num_cus);
 size_t skinny_workspace_bytes(int64_t n_pad, int r, size_t align);
 hipError_t launch_skinny_stream(const SkinnyLaunch &a, hipStream_t s);   // block minima
