@@ -1322,7 +1322,337 @@ hipError_t launch_skinny_finish(const FinishArgs &a, const uint64_t *bmin, const
     return hipGetLastError();
 }
 
-hipError_t launch_finish(const FinishArgs &a, int num_cus, hipStream_t s)
+// ---------------------------------------------------------------------------------------
+// Finishing kernel of the keys-out routes (at most 256 queries): selection, exact re-scoring,
+// final top-k, certificate and vote in one launch, one workgroup of 1,024 threads per query.
+//  1. Selection.  The block minima are dealt into 256 groups (value j belongs to group j mod 256);
+//     T = the r_sel-th smallest group minimum.  At least r_sel blocks have a minimum <= T, so at
+//     least r_sel entries are <= T, and every entry <= T lies in one of those blocks: their keys
+//     (128 bytes a block) give the candidates.  r_sel is twice the re-scoring width, so that a query
+//     the certificate does not confirm has candidates left for the wider re-scoring.  Usually T leaves
+//     few more than r_sel blocks; with more than 64, T falls to the r_sel-th smallest minimum itself.
+//  2. The candidates (usually up to 64: one wave sorts them in registers) in order of their keys; the
+//     first r are re-scored by all sixteen waves: rows of 16,384 values and more by the whole block,
+//     from 4,096 on a quarter of the candidates by each group of four waves, shorter ones a candidate
+//     per wave.  Same order of additions as in finish_kernel.
+//  3. As in finish_kernel.
+// A dependent launch costs about 6 us here and the serial chain of small steps is what bounds the rest.
+// A 1,024-thread kernel for the selection and finish_kernel after it took 11 + 28 us on 32 queries x
+// 50,000 x 8,192 and 11 + 10 us on 256 x 2,000 x 512 (whole look-ups 203 and 35.9 us); this kernel takes 19
+// and 11 us (185 and 26.0 us).
+// ---------------------------------------------------------------------------------------
+struct KeysFinishArgs {
+    FinishArgs a;
+    const uint64_t *bmin;   // [b, nb] smallest (ordered key, index) of every block of 32 entries
+    const float *keys;      // [b, n_pad]
+    int64_t nb, n_pad;
+    int r_sel;              // blocks the threshold lets in at least (<= kMaxRescore)
+    uint64_t *cand;         // [b, a.part_stride] candidates left for the wider re-scoring of an unconfirmed query
+    int32_t *cand_count;    // [b]
+    int two_steps;          // re-score the last quarter only when the first three do not confirm the result
+};
+
+// dist_s[0 .. m) for rows of d values (a multiple of 8), 1,024 threads: group g of four waves takes
+// candidates g * per .. (RG of them at most); per-thread sums, butterfly and the sum over the four waves as in
+// rescore_block_all<256, .>.
+template <int RG>
+__device__ __forceinline__ void rescore_groups(const FinishArgs &a, const float *qrow, const int32_t *idx_s, float *dist_s,
+                                               float (*red)[RG], int m, int tid)
+{
+    const int per = (m + 3) / 4, g = tid >> 8, t = tid & 255;
+    const int c0 = g * per, mine = m - c0 < per ? m - c0 : per;   // candidates of this group (may be <= 0)
+    float acc[RG];
+#pragma unroll
+    for (int j = 0; j < RG; ++j) acc[j] = 0.f;
+    if (mine > 0) {
+        for (int64_t i = (int64_t)t * 8; i < a.d; i += 256 * 8) {
+            const f32x4 q0 = *reinterpret_cast<const f32x4 *>(qrow + i);
+            const f32x4 q1 = *reinterpret_cast<const f32x4 *>(qrow + i + 4);
+            const float qv[8] = {q0[0], q0[1], q0[2], q0[3], q1[0], q1[1], q1[2], q1[3]};
+            if (a.c_f32) {
+#pragma unroll
+                for (int j = 0; j < RG; ++j) {
+                    const float *c = a.c_f32 + (int64_t)idx_s[c0 + (j < mine ? j : mine - 1)] * a.d_pad + i;
+                    const f32x4 c0v = *reinterpret_cast<const f32x4 *>(c);
+                    const f32x4 c1v = *reinterpret_cast<const f32x4 *>(c + 4);
+                    const float cv[8] = {c0v[0], c0v[1], c0v[2], c0v[3], c1v[0], c1v[1], c1v[2], c1v[3]};
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float df = qv[e] - cv[e];
+                        acc[j] = __builtin_fmaf(df, df, acc[j]);
+                    }
+                }
+            } else {
+                uint4 cb[RG];
+#pragma unroll
+                for (int j = 0; j < RG; ++j)
+                    cb[j] = *reinterpret_cast<const uint4 *>(a.c_rows + (int64_t)idx_s[c0 + (j < mine ? j : mine - 1)] * a.d_pad + i);
+#pragma unroll
+                for (int j = 0; j < RG; ++j) {
+                    const uint32_t wv[4] = {cb[j].x, cb[j].y, cb[j].z, cb[j].w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float d0 = qv[2 * e] - __uint_as_float(wv[e] << 16);
+                        acc[j] = __builtin_fmaf(d0, d0, acc[j]);
+                        const float d1 = qv[2 * e + 1] - __uint_as_float(wv[e] & 0xffff0000u);
+                        acc[j] = __builtin_fmaf(d1, d1, acc[j]);
+                    }
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < RG; ++j) {
+        float v = acc[j];
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+        if ((tid & 63) == 0) red[tid >> 6][j] = v;
+    }
+    __syncthreads();
+    if (t < RG && t < mine)
+        dist_s[c0 + t] = 0.f + ((red[4 * g][t] + red[4 * g + 1][t]) + (red[4 * g + 2][t] + red[4 * g + 3][t]));
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(kThrThreads) void keys_finish_kernel(KeysFinishArgs ka)
+{
+    const FinishArgs &a = ka.a;
+    __shared__ uint64_t list[kThrList];          // gathered minima, then the candidates
+    __shared__ uint64_t pick_s[kMaxRescore];     // minima of the selected blocks
+    __shared__ uint64_t grp_s[kThrGroups];
+    __shared__ int rank_s[kThrGroups];
+    __shared__ uint64_t sel_s;
+    __shared__ int list_n, blk_n, cand_n, distinct_s, verdict_s;
+    __shared__ float red16[16][16];
+    __shared__ float dist_s[kMaxRescore];
+    __shared__ int32_t idx_s[kMaxRescore];
+    __shared__ int32_t lab_s[kMaxK], cnt_s[kMaxK];
+    __shared__ float dsel_s[kMaxK];
+    __shared__ double conf_s[kMaxK];
+    __shared__ int32_t nearest_s;
+    const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if (a.count && q >= *a.count) return;   // uniform
+    const int64_t nb = ka.nb;
+    const int r = a.r, r_sel = ka.r_sel;
+    const uint64_t *bq = ka.bmin + (size_t)q * nb;
+
+    // ---- 1. blocks that can hold a candidate ----
+    if (tid == 0) {
+        list_n = 0;
+        blk_n = 0;
+        cand_n = 0;
+        distinct_s = 0;
+    }
+    if (tid < kThrGroups) rank_s[tid] = 0;
+    uint64_t t = kSentinel;   // threshold on (key, index) pairs
+    int nblk;
+    if (r_sel >= nb) {        // fewer blocks than that: all of them, everything passes
+        if (tid < (int)nb) pick_s[tid] = bq[tid];
+        nblk = (int)nb;
+        __syncthreads();
+    } else {
+        constexpr int NV = 8;   // minima per thread kept in registers
+        uint64_t v[NV], m = kSentinel;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int64_t j = (int64_t)i * kThrThreads + tid;
+            v[i] = j < nb ? bq[j] : kSentinel;
+            m = v[i] < m ? v[i] : m;
+        }
+        for (int64_t j = (int64_t)NV * kThrThreads + tid; j < nb; j += kThrThreads) {
+            const uint64_t x = bq[j];
+            m = x < m ? x : m;
+        }
+        list[tid] = m;
+        __syncthreads();
+        if (tid < kThrGroups) {
+            uint64_t g = list[tid];
+#pragma unroll
+            for (int i = 1; i < kThrThreads / kThrGroups; ++i) {
+                const uint64_t x = list[tid + i * kThrGroups];
+                g = x < g ? x : g;
+            }
+            grp_s[tid] = g;
+        }
+        __syncthreads();
+        {   // rank of every group minimum: four threads count a quarter of the others each
+            const uint64_t mine = grp_s[tid & (kThrGroups - 1)];
+            const int part = tid / kThrGroups * (kThrGroups / 4);
+            int c = 0;
+#pragma unroll 16
+            for (int j = 0; j < kThrGroups / 4; ++j) c += grp_s[part + j] < mine;
+            atomicAdd(&rank_s[tid & (kThrGroups - 1)], c);
+        }
+        __syncthreads();
+        // (groups without a value hold the marker; r_sel < nb values exist, but they may lie in fewer than
+        // r_sel groups: then T stays the marker and everything passes)
+        if (tid == 0) sel_s = kSentinel;
+        __syncthreads();
+        if (tid < kThrGroups && rank_s[tid] == r_sel - 1 && grp_s[tid] != kSentinel) sel_s = grp_s[tid];
+        __syncthreads();
+        t = sel_s;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if (v[i] <= t && v[i] != kSentinel) {
+                const int pos = atomicAdd(&list_n, 1);
+                if (pos < kThrList) list[pos] = v[i];
+            }
+        }
+        for (int64_t j = (int64_t)NV * kThrThreads + tid; j < nb; j += kThrThreads) {
+            const uint64_t x = bq[j];
+            if (x <= t) {
+                const int pos = atomicAdd(&list_n, 1);
+                if (pos < kThrList) list[pos] = x;
+            }
+        }
+        __syncthreads();
+        const int cnt = list_n < kThrList ? list_n : kThrList;
+        if (cnt <= kMaxRescore) {
+            if (tid < cnt) pick_s[tid] = list[tid];
+            nblk = cnt;
+        } else {   // uniform
+            t = rth_of_list(list, cnt, r_sel, &sel_s, tid);
+            __syncthreads();
+            for (int i = tid; i < cnt; i += kThrThreads) {
+                const uint64_t x = list[i];
+                if (x <= t) {
+                    const int pos = atomicAdd(&blk_n, 1);
+                    if (pos < kMaxRescore) pick_s[pos] = x;
+                }
+            }
+            nblk = r_sel;
+        }
+        __syncthreads();
+    }
+
+    // ---- their entries at or under the threshold, in order of their keys ----
+    const float *kq = ka.keys + (size_t)q * ka.n_pad;
+    for (int c = tid; c < nblk * 32; c += kThrThreads) {
+        const uint32_t idx = ((uint32_t)pick_s[c >> 5] & ~31u) + (c & 31);
+        const uint64_t pr = ((uint64_t)ordered_bits(kq[idx]) << 32) | idx;
+        if (pr <= t && idx < (uint32_t)a.n) list[atomicAdd(&cand_n, 1)] = pr;   // <= 64 * 32 entries
+    }
+    __syncthreads();
+    const int real = cand_n;
+    int have = real;
+    if (have <= 64) {
+        if (w == 0) list[lane] = wave_sort64(lane < have ? list[lane] : kSentinel, lane);
+        __syncthreads();
+    } else {
+        int n2 = 128;
+        while (n2 < have) n2 <<= 1;
+        for (int i = have + tid; i < n2; i += kThrThreads) list[i] = kSentinel;
+        __syncthreads();
+        bitonic_sort_lds(list, n2, tid, kThrThreads);
+    }
+
+    // ---- 2. exact re-scoring of the first r ----
+    if (tid < r) {
+        // (fewer than r candidates, i.e. markers here, only with non-finite inputs: mapped to row 0)
+        const uint32_t ci = (uint32_t)list[tid];
+        idx_s[tid] = ci < (uint32_t)a.n ? (int32_t)ci : 0;
+    }
+    __syncthreads();
+    const float *qrow = a.queries + (int64_t)(a.sel ? a.sel[q] : q) * a.d;
+    auto rescore = [&](int c0, int m) {
+        if (a.d >= 16384 && a.d % 8 == 0) {
+            float(*red)[8] = reinterpret_cast<float(*)[8]>(&red16[0][0]);
+            if (m <= 16) {
+                rescore_block_all<1024, 16>(a, qrow, idx_s + c0, dist_s + c0, red, m, tid);
+            } else {
+                for (int c = 0; c < m; c += 32)
+                    rescore_block_all<1024, 32>(a, qrow, idx_s + c0 + c, dist_s + c0 + c, red, m - c < 32 ? m - c : 32, tid);
+            }
+        } else if (a.d >= 4096 && a.d % 8 == 0) {
+            if (m <= 16)
+                rescore_groups<4>(a, qrow, idx_s + c0, dist_s + c0, reinterpret_cast<float(*)[4]>(&red16[0][0]), m, tid);
+            else if (m <= 32)
+                rescore_groups<8>(a, qrow, idx_s + c0, dist_s + c0, reinterpret_cast<float(*)[8]>(&red16[0][0]), m, tid);
+            else
+                rescore_groups<16>(a, qrow, idx_s + c0, dist_s + c0, red16, m, tid);
+        } else {
+            if (m <= 16)
+                rescore_wave<1>(a, qrow, idx_s + c0, dist_s + c0, m, w, lane, 16);
+            else if (m <= 32)
+                rescore_wave<2>(a, qrow, idx_s + c0, dist_s + c0, m, w, lane, 16);
+            else
+                rescore_wave<4>(a, qrow, idx_s + c0, dist_s + c0, m, w, lane, 16);
+        }
+        __syncthreads();
+    };
+    const int m_first = ka.two_steps ? r - r / 4 : r;
+    rescore(0, m_first);
+
+    // ---- 3. final order, certificate, vote ----
+    // every entry that is no candidate has a key at or above the largest candidate's
+    const uint32_t excl0 = real >= a.n || real < 1 ? 0xffffffffu : (uint32_t)(list[real - 1] >> 32);
+    auto confirm = [&](int m) {
+        rank_and_emit(a, q, m, tid, kThrThreads, dist_s, idx_s, lab_s, dsel_s, &nearest_s, &distinct_s);
+        __syncthreads();
+        uint32_t excl = excl0;
+        if (real > m) {
+            const uint32_t nxt = (uint32_t)(list[m] >> 32);
+            excl = nxt < excl ? nxt : excl;
+        }
+        return certificate(list, dist_s, m, dsel_s[a.k - 1], excl, distinct_s, tid, &verdict_s);
+    };
+    bool ok = confirm(m_first);
+    if (!ok && m_first < r) {   // uniform
+        rescore(m_first, r - m_first);
+        if (tid == 0) distinct_s = 0;
+        __syncthreads();
+        ok = confirm(r);
+    }
+    if (!ok) {
+        // unconfirmed: the wider re-scoring, or the exact scan, redoes this query
+        const int keep = real < a.part_stride ? real : a.part_stride;
+        for (int i = tid; i < keep; i += kThrThreads) ka.cand[(size_t)q * a.part_stride + i] = list[i];
+        if (tid == 0) {
+            ka.cand_count[q] = keep;
+            const int next = keep <= r ? 1 : 0;
+            const int pos = atomicAdd(a.flag_count + next, 1);
+            (next ? a.flag_list2 : a.flag_list)[pos] = q;
+            if (a.stats && next == 1) atomicAdd(a.stats + 2, 1ull);
+        }
+    } else if (tid == 0 && a.stats) {
+        atomicAdd(a.stats, 1ull);
+    }
+    decide_and_write(a, q, tid, lab_s, dsel_s, cnt_s, conf_s, nearest_s);
+}
+
+bool keys_finish_supported(int64_t n_pad, int r)
+{
+    const int64_t nb = n_pad / 32;
+    return ((nb + kThrGroups - 1) / kThrGroups) * r <= kThrList;
+}
+
+int keys_finish_cand(int r) { return 32 * r < kTier1 ? 32 * r : kTier1; }
+
+size_t keys_finish_workspace_bytes(int64_t rows, int64_t n_pad, int r, size_t align)
+{
+    auto up = [&](size_t x) { return (x + align - 1) / align * align; };
+    const size_t b = (size_t)rows;
+    return up(b * (size_t)n_pad * 4) + up(b * (size_t)(n_pad / 32) * 8) + up(b * 4) + up(b * (size_t)keys_finish_cand(r) * 8);
+}
+
+// a.part / a.part_count (stride keys_finish_cand(a.r)) are the kernel's outputs for the wider re-scoring
+hipError_t launch_keys_finish(const FinishArgs &a, const float *keys, const uint64_t *bmin, int64_t n_pad, uint64_t *cand,
+                              int32_t *cand_count, hipStream_t s)
+{
+    if (!keys_finish_supported(n_pad, a.r) || a.r < 1 || a.r > kMaxRescore || a.k > kMaxK || a.k > a.r || a.b < 1 || !a.flag_count ||
+        !a.flag_list || !a.flag_list2 || a.part_stride != keys_finish_cand(a.r))
+        return hipErrorInvalidValue;
+    const int64_t nb = n_pad / 32, per_group = (nb + kThrGroups - 1) / kThrGroups;
+    int r_sel = 2 * a.r < kMaxRescore ? 2 * a.r : kMaxRescore;
+    while (r_sel > a.r && per_group * r_sel > kThrList) --r_sel;   // the gathered minima fit the list
+    // few queries: fetching the last quarter at once costs less than a second round of latency
+    const int two = (a.r == 16 || a.r == 32) && a.k <= a.r / 2 + a.r / 8 && a.d >= 4096 && a.d % 8 == 0 && a.b > 64;
+    KeysFinishArgs ka{a, bmin, keys, nb, n_pad, r_sel, cand, cand_count, two};
+    hipLaunchKernelGGL(keys_finish_kernel, dim3((unsigned)a.b), dim3(kThrThreads), 0, s, ka);
+    return hipGetLastError();
+}
+
+hipError_t launch_finish(const FinishArgs &a, hipStream_t s)
 {
     const int total = a.part_count ? a.part_stride : a.alloc_splits * a.r;
     if (total > kMaxMergeEntries || a.r > kMaxRescore || a.k > kMaxK || a.k > a.r) return hipErrorInvalidValue;
@@ -1335,8 +1665,16 @@ hipError_t launch_finish(const FinishArgs &a, int num_cus, hipStream_t s)
         hipLaunchKernelGGL((finish_kernel<1024, false>), dim3((unsigned)a.b), dim3(1024), lds, s, fa);
     else
         hipLaunchKernelGGL((finish_kernel<256, false>), dim3((unsigned)a.b), dim3(256), lds, s, fa);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    return hipGetLastError();
+}
+
+hipError_t launch_wider(const FinishArgs &a, int num_cus, hipStream_t s)
+{
+    const int total = a.part_count ? a.part_stride : a.alloc_splits * a.r;
+    if (total > kMaxMergeEntries || a.r > kMaxRescore || a.k > kMaxK || a.k > a.r) return hipErrorInvalidValue;
+    FinishKernelArgs fa{a, 2};
+    while (fa.sort_cap < total) fa.sort_cap <<= 1;
+    const size_t lds = (size_t)fa.sort_cap * sizeof(uint64_t);
     // the wider round for the queries on list 0: a fixed grid shares them (usually there are none)
     const int grid = a.b < 2 * num_cus ? a.b : 2 * num_cus;
     hipLaunchKernelGGL((finish_kernel<256, true>), dim3((unsigned)grid), dim3(256), lds, s, fa);

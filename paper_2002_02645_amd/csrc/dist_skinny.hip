@@ -16,11 +16,6 @@
 //     blocks: their 32 R entries are a superset of the R best.  It re-scores all of them
 //     exactly in fp32 (d <= 1024: one KiB or two per entry), keeps the k nearest, and checks
 //     that no entry outside those blocks can be nearer (every one has a key >= T).
-// The threshold kernel at the end of this file serves the keys-out variant of the tiled kernel
-// (one query tile), where the keys are materialised: block_threshold_kernel finds, per query, the
-// R-th smallest block minimum T and collects the entries with (key, index) <= T (at most 32 R,
-// all of them in the R blocks whose minimum is <= T) into a candidate list, which the general
-// finishing kernel sorts, cuts to R and re-scores.
 //
 // Paper: Sec. 3 (k nearest neighbours of the layer output), Sec. 5 "Cache lookup
 // performance" (look-up latency decides whether freezing pays off).
@@ -251,59 +246,7 @@ __global__ __launch_bounds__(512) void dist_skinny_kernel(SkinnyArgs p)
     }
 }
 
-// ---------------------------------------------------------------------------------------
-// Per query: T = the R-th smallest of the NB block minima (pairs (ordered key, index), all
-// distinct), then the candidate list: exactly R blocks have a minimum <= T and they hold every entry
-// whose pair is <= T (at most 32 R, see the file header; `cap` >= that bound), so only those
-// blocks' keys are read, 128 bytes each.  One workgroup of 1024 threads per query.
-// ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kThrThreads) void block_threshold_kernel(const uint64_t *bmin, const int32_t *count, int64_t nb, int r_sel,
-                                                                      const float *keys, int64_t n_pad, int n,
-                                                                      uint64_t *cand, int32_t *cand_count, int cap)
-{
-    __shared__ uint64_t list[kThrList];
-    __shared__ uint64_t sel_s;
-    __shared__ int list_n;
-    __shared__ int blk_n, cnt_s;
-    __shared__ int32_t blk_s[kMaxRescore];
-    const int q = blockIdx.x, tid = threadIdx.x;
-    if (count && q >= *count) return;   // uniform
-    const uint64_t *bq = bmin + (size_t)q * nb;
-    // fewer blocks than wanted entries: everything passes
-    const uint64_t t = r_sel >= nb ? kSentinel : rth_smallest_of(bq, nb, r_sel, list, &sel_s, &list_n, tid);
-    if (tid == 0) {
-        blk_n = 0;
-        cnt_s = 0;
-    }
-    __syncthreads();
-    for (int64_t i = tid; i < nb; i += kThrThreads) {
-        if (bq[i] <= t) {
-            const int pos = atomicAdd(&blk_n, 1);
-            if (pos < kMaxRescore) blk_s[pos] = (int32_t)i;
-        }
-    }
-    __syncthreads();
-    const int nblk = blk_n < kMaxRescore ? blk_n : kMaxRescore;   // = min(r_sel, nb)
-    const float *kq = keys + (size_t)q * n_pad;
-    for (int c = tid; c < nblk * 32; c += kThrThreads) {
-        const int64_t idx = (int64_t)blk_s[c >> 5] * 32 + (c & 31);
-        const uint64_t pr = ((uint64_t)ordered_bits(kq[idx]) << 32) | (uint32_t)idx;
-        if (pr <= t && idx < n) {
-            const int pos = atomicAdd(&cnt_s, 1);
-            if (pos < cap) cand[(size_t)q * cap + pos] = pr;
-        }
-    }
-    __syncthreads();
-    if (tid == 0) cand_count[q] = cnt_s;
-}
-
 }  // namespace
-
-bool select_supported(int64_t n_pad, int r)
-{
-    const int64_t nb = n_pad / 32;
-    return ((nb + kThrGroups - 1) / kThrGroups) * r <= kThrList;
-}
 
 bool skinny_supported(int64_t b, int64_t n_pad, int64_t d_pad, int r, int num_cus)
 {
@@ -314,13 +257,6 @@ bool skinny_supported(int64_t b, int64_t n_pad, int64_t d_pad, int r, int num_cu
     const int64_t groups = plan_skinny_splits(n_pad, num_cus);
     const int64_t bpg = ((n_tiles + groups - 1) / groups) * (kTileN / 32);
     return b >= 1 && b <= kSkinnyRows && d_pad <= kSkinnyMaxD && groups <= kThrThreads && bpg * r <= kThrList;
-}
-
-size_t select_workspace_bytes(int64_t rows, int64_t n_pad, int r, size_t align)
-{
-    auto up = [&](size_t x) { return (x + align - 1) / align * align; };
-    const size_t b = (size_t)rows;
-    return up(b * (size_t)n_pad * 4) + up(b * (size_t)(n_pad / 32) * 8) + up(b * 4) + up(b * (size_t)(32 * r) * 8);
 }
 
 int plan_skinny_splits(int64_t n, int num_cus)
@@ -362,16 +298,6 @@ hipError_t launch_skinny_stream(const SkinnyLaunch &a, hipStream_t s)
         hipLaunchKernelGGL((dist_skinny_kernel<SkinnyCfg<512, 3>>), dim3(a.n_splits), dim3(512), 0, s, k);
     else
         hipLaunchKernelGGL((dist_skinny_kernel<SkinnyCfg<1024, 2>>), dim3(a.n_splits), dim3(512), 0, s, k);
-    return hipGetLastError();
-}
-
-hipError_t launch_select(const float *keys, const uint64_t *bmin, int64_t n_pad, int n, int b, const int32_t *count, int r,
-                         int32_t *cand_count, uint64_t *cand, hipStream_t s)
-{
-    const int64_t nb = n_pad / 32;
-    if (!select_supported(n_pad, r) || b < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(block_threshold_kernel, dim3(b), dim3(kThrThreads), 0, s, bmin, count, nb, r, keys, n_pad, n, cand, cand_count,
-                       32 * r);
     return hipGetLastError();
 }
 

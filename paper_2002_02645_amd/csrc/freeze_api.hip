@@ -164,7 +164,7 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
         // its time filling its empty candidate lists key by key, so the keys go out here too
         // (measured cross-over: about 2^26 keys; 256 x 2,000: 129 -> 69 us, 200 x 50,000 x 512: 209 -> 80 us).
         out->keys = b <= (cascade ? kStreamRows : 256) && (b * 20 <= L.d_pad || b * L.n_pad <= ((int64_t)1 << 26)) &&
-                    select_supported(L.n_pad, r);
+                    keys_finish_supported(L.n_pad, r);
         const int64_t k_steps = (L.n_pad / kTileN) * (L.d_pad / kKB);   // per query tile
         if (out->keys && (b <= kStreamRows || 2 * k_steps < 16 * (int64_t)ctx->num_cus))
             out->plan = plan_stream(b, L.n, r, ctx->num_cus, L.d_pad, small_ws);
@@ -172,7 +172,7 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
             out->plan = plan_dist(b, L.n, r, ctx->num_cus, out->keys, L.d_pad);
         out->ws_bytes = align_up((size_t)out->plan.b_pad * L.d_pad * 2);
         if (out->keys)
-            out->ws_bytes += select_workspace_bytes(out->plan.b_pad, L.n_pad, r, kAlign) +
+            out->ws_bytes += keys_finish_workspace_bytes(out->plan.b_pad, L.n_pad, r, kAlign) +
                              align_up(dist_partial_bytes(out->plan));
         else
             out->ws_bytes += align_up((size_t)out->plan.b_pad * lists_per_query(out->plan, cascade) * r * 8);
@@ -269,7 +269,10 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
 
     FinishArgs fa{};
     marks.mark(1);
-    bool marked2 = false;
+    const float *keys = nullptr;
+    const uint64_t *keys_bmin = nullptr;
+    uint64_t *keys_cand = nullptr;
+    int32_t *keys_cand_count = nullptr;
     const uint64_t *skinny_bmin = nullptr, *skinny_wgmin = nullptr;
     uint64_t *skinny_cand = nullptr, *skinny_samp = nullptr;
     if (sh.skinny) {
@@ -290,8 +293,6 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
         sl.n_splits = sh.plan.n_splits;
         sl.n_pad = L.n_pad;
         if (launch_skinny_stream(sl, s) != hipSuccess) return FREEZE_EHIP;
-        marks.mark(2);
-        marked2 = true;
         skinny_bmin = sl.bmin;
         skinny_wgmin = sl.wgmin;
         skinny_cand = ws.take<uint64_t>((size_t)kSkinnyRows * ((sh.r + 1) / 2) * 64);
@@ -310,16 +311,16 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
             da.keys = ws.take<float>(rows * L.n_pad);
             da.bmin = ws.take<uint64_t>(rows * (L.n_pad / 32));
             int32_t *cand_count = ws.take<int32_t>(rows);
-            uint64_t *cand = ws.take<uint64_t>(rows * 32 * sh.r);
+            uint64_t *cand = ws.take<uint64_t>(rows * keys_finish_cand(sh.r));
             da.partial = dist_partial_bytes(sh.plan) > 0 ? ws.take<float>(dist_partial_bytes(sh.plan) / 4) : nullptr;
             if (launch_dist_topr(sh.plan, da, s) != hipSuccess) return FREEZE_EHIP;
-            marks.mark(2);
-            marked2 = true;
-            if (launch_select(da.keys, da.bmin, L.n_pad, (int)L.n, (int)b, count, sh.r, cand_count, cand, s) != hipSuccess)
-                return FREEZE_EHIP;
+            keys = da.keys;
+            keys_bmin = da.bmin;
+            keys_cand = cand;
+            keys_cand_count = cand_count;
             fa.part = cand;
             fa.part_count = cand_count;
-            fa.part_stride = 32 * sh.r;
+            fa.part_stride = keys_finish_cand(sh.r);
             fa.n_splits = 1;
         } else {
             // the workspace was sized by sh.cascade; the balanced decomposition only goes with it off
@@ -339,7 +340,7 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
             fa.max_splits = sh.plan.max_splits;
         }
     }
-    if (!marked2) marks.mark(2);
+    marks.mark(2);
 
     fa.r = sh.r;
     fa.queries = queries;
@@ -371,8 +372,11 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
         if (launch_skinny_finish(fa, skinny_bmin, skinny_wgmin, L.n_pad / 32, sh.plan.n_splits,
                                  (int)(L.n_pad / kTileN), skinny_cand, skinny_samp, tickets + kSkinnyRows, s) != hipSuccess)
             return FREEZE_EHIP;
-    } else if (launch_finish(fa, ctx->num_cus, s) != hipSuccess) {
-        return FREEZE_EHIP;
+    } else {
+        if ((keys ? launch_keys_finish(fa, keys, keys_bmin, L.n_pad, keys_cand, keys_cand_count, s) : launch_finish(fa, s)) !=
+            hipSuccess)
+            return FREEZE_EHIP;
+        if (launch_wider(fa, ctx->num_cus, s) != hipSuccess) return FREEZE_EHIP;
     }
     // the queries whose result the certificate did not confirm (usually none) are redone exactly
     if (launch_exact_scan(fa, tickets, scan_lists, ctx->num_cus, s) != hipSuccess) return FREEZE_EHIP;

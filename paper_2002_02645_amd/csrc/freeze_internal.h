@@ -217,12 +217,6 @@ struct SkinnyLaunch {
     int64_t n_pad;
 };
 bool skinny_supported(int64_t b, int64_t n_pad, int64_t d_pad, int r, int num_cus);
-// Selection from materialised keys (keys-out variant of the tiled kernel): threshold from the
-// block minima, then the candidate lists.  b queries, rows of n_pad keys.
-bool select_supported(int64_t n_pad, int r);
-size_t select_workspace_bytes(int64_t rows, int64_t n_pad, int r, size_t align);
-hipError_t launch_select(const float *keys, const uint64_t *bmin, int64_t n_pad, int n, int b, const int32_t *count, int r,
-                         int32_t *cand_count, uint64_t *cand, hipStream_t s);   // count (device): live queries, or null (= b)
 int plan_skinny_splits(int64_t n, int num_cus);
 size_t skinny_workspace_bytes(int64_t n_pad, int r, size_t align);
 hipError_t launch_skinny_stream(const SkinnyLaunch &a, hipStream_t s);   // block minima
@@ -265,7 +259,17 @@ struct FinishArgs {
                                  // the wider one, and queries handed to the exact scan (added to, never cleared)
 };
 
-hipError_t launch_finish(const FinishArgs &a, int num_cus, hipStream_t s);
+hipError_t launch_finish(const FinishArgs &a, hipStream_t s);
+// Keys-out routes: selection from the materialised keys and block minima, and everything launch_finish
+// does.  rows = query rows of the key buffers; cand [b, keys_finish_cand(r)] and cand_count [b] receive the
+// candidates of unconfirmed queries.
+bool keys_finish_supported(int64_t n_pad, int r);
+int keys_finish_cand(int r);
+size_t keys_finish_workspace_bytes(int64_t rows, int64_t n_pad, int r, size_t align);
+hipError_t launch_keys_finish(const FinishArgs &a, const float *keys, const uint64_t *bmin, int64_t n_pad, uint64_t *cand,
+                              int32_t *cand_count, hipStream_t s);
+// The wider re-scoring of the queries on list 0.
+hipError_t launch_wider(const FinishArgs &a, int num_cus, hipStream_t s);
 // Exact scan of the flagged queries (a.flag_list2 / a.flag_count[1]): brute-force fp32 distances to every
 // entry, the k nearest, the label and hit decision, written over the outputs of those queries.
 // tickets [b] int32 (zero on entry, zero again afterwards), part_x scan_scratch_entries(b, k, num_cus) u64.
