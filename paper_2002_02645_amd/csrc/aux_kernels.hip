@@ -353,9 +353,9 @@ __global__ __launch_bounds__(256) void query_prep_kernel(const float *queries, c
     const int row0 = blockIdx.x * 2;   // bm is even: both rows lie in one tile
     // counters of the kernels that follow in this look-up (the list of flagged queries, the exact
     // scan's tickets) start at zero
-    if (blockIdx.y == 0 && threadIdx.x < 2) {
-        if (tickets && row0 + (int)threadIdx.x < b) tickets[row0 + threadIdx.x] = 0;
-        if (flag_count && blockIdx.x == 0) flag_count[threadIdx.x] = 0;   // both lists' counts
+    if (blockIdx.y == 0 && threadIdx.x < kFlagCounts) {
+        if (threadIdx.x < 2 && tickets && row0 + (int)threadIdx.x < b) tickets[row0 + threadIdx.x] = 0;
+        if (flag_count && blockIdx.x == 0) flag_count[threadIdx.x] = 0;
     }
     const int live_pad = ((nq + bm - 1) / bm) * bm;
     if (row0 >= live_pad) return;
@@ -798,6 +798,57 @@ __device__ __forceinline__ void rank_and_emit(const FinishArgs &a, int q, int m,
     }
 }
 
+// The gathered candidates of query q in ent (marker-padded to a power of two); returns how many slots
+// they take.  *real_s = real cache entries among them; *excl_s = a lower bound (ordered bits) of the keys of
+// all entries that were not gathered (valid when the candidates are per-split lists; else the marker).
+__device__ __forceinline__ int gather_entries(const FinishArgs &a, int q, int nq, uint64_t *ent, int *real_s, uint32_t *excl_s,
+                                              int tid, int nthreads)
+{
+    const int r = a.r;
+    int n_splits = a.n_splits;
+    if (a.count && !a.part_count)   // cascade: the distance pass derived its splits from the live count
+        n_splits = splits_for((nq + a.bm - 1) / a.bm, a.n_tiles, a.num_cus, a.max_splits);
+    int total = n_splits * r, stride = a.alloc_splits * r;
+    if (a.part_count) {
+        stride = a.part_stride;
+        total = a.part_count[q] < stride ? a.part_count[q] : stride;
+    }
+    int sort_n = 2;
+    while (sort_n < total) sort_n <<= 1;
+    const uint64_t *src = a.part + (size_t)q * stride;
+    if (tid == 0) {
+        *real_s = 0;
+        *excl_s = 0xffffffffu;
+    }
+    __syncthreads();
+    int mine = 0;
+    for (int i = tid; i < sort_n; i += nthreads) {
+        const uint64_t x = (i < total) ? src[i] : kSentinel;
+        ent[i] = x;
+        mine += (uint32_t)x < (uint32_t)a.n;   // a real cache entry (the "no entry" marker carries index 2^32 - 1)
+    }
+    if (mine) atomicAdd(real_s, mine);
+    __syncthreads();
+    if (!a.part_count) {
+        // Per-split lists: a split that filled its list kept its r smallest keys, so every entry
+        // of its range that it dropped has a key >= the list's largest.  The smallest of these
+        // bounds every entry outside the gathered lists.  (Slots rotate with the thread
+        // number so that neighbouring threads read different LDS banks.)
+        for (int sp = tid; sp < n_splits; sp += nthreads) {
+            uint32_t mx = 0;
+            int jj = sp % r;
+            for (int j = 0; j < r; ++j) {
+                const uint32_t kb = (uint32_t)(ent[sp * r + jj] >> 32);
+                mx = kb > mx ? kb : mx;
+                jj = jj + 1 == r ? 0 : jj + 1;
+            }
+            atomicMin(excl_s, mx);   // a list with an empty slot dropped nothing: its largest is the marker
+        }
+        __syncthreads();
+    }
+    return total;
+}
+
 struct FinishKernelArgs {
     FinishArgs a;
     int sort_cap;   // power of two >= the largest number of entries gathered per query (LDS allocation)
@@ -865,21 +916,16 @@ __device__ __forceinline__ bool certificate(const uint64_t *ent, const float *di
 // would take 169 and leave two blocks per CU, too few to cover one block's merge and final
 // phases with the other blocks' re-scoring loads (0.55 -> 0.45 ms on 10,000 queries x 8,192).
 //
-// WIDER = false: one block per live query, the r best by the coarse key are re-scored; a query
-// the certificate does not confirm goes on list 0 (or straight on list 1 when no further
-// entries were gathered for it).  WIDER = true (a launch of its own, so that its code and registers
-// stay out of the kernel every query runs through; usually it finds list 0 empty): the blocks
-// share the queries of list 0 and re-score up to kTier1 of the gathered entries; what is still
-// unconfirmed goes on list 1, the exact scan's.
-template <int NT, bool WIDER>
+// One block per live query; a query the certificate does not confirm goes on list 0, the wider
+// re-scoring's (or straight on list 1, the exact scan's, when no further entries were gathered for it).
+template <int NT>
 __global__ __launch_bounds__(NT, NT == 256 ? 4 : 1) void finish_kernel(FinishKernelArgs fa)
 {
     const FinishArgs &a = fa.a;
-    constexpr int MAXC = WIDER ? kTier1 : kMaxRescore;   // candidates re-scored per query at most
     extern __shared__ uint64_t ent[];   // sort_cap entries (dynamic: small merges keep occupancy high)
     __shared__ float red[NT / 64][8];
-    __shared__ float dist_s[MAXC];
-    __shared__ int32_t idx_s[MAXC];
+    __shared__ float dist_s[kMaxRescore];
+    __shared__ int32_t idx_s[kMaxRescore];
     __shared__ int32_t lab_s[kMaxK];
     __shared__ int32_t cnt_s[kMaxK];
     __shared__ float dsel_s[kMaxK];
@@ -889,164 +935,94 @@ __global__ __launch_bounds__(NT, NT == 256 ? 4 : 1) void finish_kernel(FinishKer
     __shared__ uint32_t excl_s;
 
     const int nq = a.count ? *a.count : a.b;
-    const int todo = WIDER ? a.flag_count[0] : nq;   // queries this launch works on
-    const int tid = threadIdx.x;
+    const int q = blockIdx.x, tid = threadIdx.x;
+    if (q >= nq) return;   // uniform
     const int r = a.r;
-    auto one_query = [&](int job) {
-        const int q = WIDER ? a.flag_list[job] : job;
 
-        // 1. merge the per-split lists (or sort the query's candidate list)
-        int n_splits = a.n_splits;
-        if (a.count && !a.part_count)   // cascade: the distance pass derived its splits from the live count
-            n_splits = splits_for((nq + a.bm - 1) / a.bm, a.n_tiles, a.num_cus, a.max_splits);
-        int total = n_splits * r, stride = a.alloc_splits * r;
-        if (a.part_count) {
-            stride = a.part_stride;
-            total = a.part_count[q] < stride ? a.part_count[q] : stride;
-        }
-        int sort_n = 2;
-        while (sort_n < total) sort_n <<= 1;   // <= fa.sort_cap, the LDS allocation
-        const uint64_t *src = a.part + (size_t)q * stride;
-        if (tid == 0) {
-            real_s = 0;
-            excl_s = 0xffffffffu;
-            distinct_s = 0;
-        }
-        __syncthreads();
-        int mine = 0;
-        for (int i = tid; i < sort_n; i += NT) {
-            const uint64_t x = (i < total) ? src[i] : kSentinel;
-            ent[i] = x;
-            mine += (uint32_t)x < (uint32_t)a.n;   // a real cache entry (the "no entry" marker carries index 2^32 - 1)
-        }
-        if (mine) atomicAdd(&real_s, mine);
-        __syncthreads();
-        if (!a.part_count) {
-            // Per-split lists: a split that filled its list kept its r smallest keys, so every entry
-            // of its range that it dropped has a key >= the list's largest.  The smallest of these
-            // bounds every entry outside the gathered lists.  (Slots rotate with the thread
-            // number so that neighbouring threads read different LDS banks.)
-            for (int sp = tid; sp < n_splits; sp += NT) {
-                uint32_t mx = 0;
-                int jj = sp % r;
-                for (int j = 0; j < r; ++j) {
-                    const uint32_t kb = (uint32_t)(ent[sp * r + jj] >> 32);
-                    mx = kb > mx ? kb : mx;
-                    jj = jj + 1 == r ? 0 : jj + 1;
-                }
-                atomicMin(&excl_s, mx);   // a list with an empty slot dropped nothing: its largest is the marker
-            }
-            __syncthreads();
-        }
-        for (int size = 2; size <= sort_n; size <<= 1) {
-            for (int stride2 = size >> 1; stride2 > 0; stride2 >>= 1) {
-                for (int i = tid; i < (sort_n >> 1); i += NT) {
-                    const int lo = ((i & ~(stride2 - 1)) << 1) | (i & (stride2 - 1));   // stride2 is a power of two
-                    const int hi = lo + stride2;
-                    const bool up = ((lo & size) == 0);
-                    const uint64_t x = ent[lo], y = ent[hi];
-                    if ((x > y) == up) {
-                        ent[lo] = y;
-                        ent[hi] = x;
-                    }
-                }
-                __syncthreads();
-            }
-        }
-        const float *qrow = a.queries + (int64_t)(a.sel ? a.sel[q] : q) * a.d;
-        // candidates of this round: the best by the coarse key (real entries sort in front of the markers)
-        int m = WIDER ? (real_s < kTier1 ? real_s : kTier1) : r;
-        // Long activations, a width of 16 (or 32) that leaves room: the last quarter of the candidates
-        // is re-scored only when the certificate over the first twelve (24), which then counts the
-        // others among the excluded entries, does not confirm the result; most queries are spared a
-        // quarter of the rows (C2: 92 % of the queries, 0.42 -> 0.36 ms for the batch).
-        const bool two_steps = !WIDER && (r == 16 || r == 32) && a.k <= r / 2 + r / 8 && a.d >= 4096 && a.d % 8 == 0;
-        const int m_first = two_steps ? r - r / 4 : m;
+    // 1. merge the per-split lists
+    const int total = gather_entries(a, q, nq, ent, &real_s, &excl_s, tid, NT);
+    int sort_n = 2;
+    while (sort_n < total) sort_n <<= 1;   // <= fa.sort_cap, the LDS allocation
+    if (tid == 0) distinct_s = 0;
+    bitonic_sort_lds(ent, sort_n, tid, NT);
+    const float *qrow = a.queries + (int64_t)(a.sel ? a.sel[q] : q) * a.d;
+    // Long activations, a width of 16 (or 32) that leaves room: the last quarter of the candidates
+    // is re-scored only when the certificate over the first twelve (24), which then counts the
+    // others among the excluded entries, does not confirm the result; most queries are spared a
+    // quarter of the rows (C2: 92 % of the queries, 0.42 -> 0.36 ms for the batch).
+    const bool two_steps = (r == 16 || r == 32) && a.k <= r / 2 + r / 8 && a.d >= 4096 && a.d % 8 == 0;
+    const int m_first = two_steps ? r - r / 4 : r;
 
-        for (int c = tid; c < m; c += NT) {
-            // With finite inputs every one of the first r entries is a real cache row.  Non-finite
-            // inputs (outside the contract) can leave "no entry" markers here: map them to row 0 so
-            // that nothing is read out of bounds.
-            const uint32_t ci = (uint32_t)(ent[c] & 0xffffffffu);
-            idx_s[c] = ci < (uint32_t)a.n ? (int32_t)ci : 0;
-        }
-        __syncthreads();
-
-        // 2. exact fp32 re-scoring: each wave takes a group of candidates and needs no block barrier
-        if (a.d >= 4096 && a.d % 8 == 0) {
-            // long activations: the whole block per candidate, the query row read once
-            if (WIDER) {
-                for (int c0 = 0; c0 < m; c0 += 32)
-                    rescore_block_all<NT, 32>(a, qrow, idx_s + c0, dist_s + c0, red, m - c0 < 32 ? m - c0 : 32, tid);
-            } else if (m <= 16) {
-                rescore_block_all<NT, 16>(a, qrow, idx_s, dist_s, red, m_first, tid);
-            } else if (m <= 32) {
-                rescore_block_all<NT, 32>(a, qrow, idx_s, dist_s, red, m_first, tid);
-            } else {
-                // (two passes of 32: 64 accumulators per thread spill, and the pass is 8 % slower for it)
-                rescore_block_all<NT, 32>(a, qrow, idx_s, dist_s, red, 32, tid);
-                rescore_block_all<NT, 32>(a, qrow, idx_s + 32, dist_s + 32, red, m - 32, tid);
-            }
-        } else if (tid < 256) {   // short activations: four waves, one group of candidates each
-            if (m <= 16)
-                rescore_wave<4>(a, qrow, idx_s, dist_s, m, tid >> 6, tid & 63);
-            else if (m <= 32)
-                rescore_wave<8>(a, qrow, idx_s, dist_s, m, tid >> 6, tid & 63);
-            else
-                rescore_wave<16>(a, qrow, idx_s, dist_s, m, tid >> 6, tid & 63);
-        }
-        __syncthreads();
-
-        // 3. final order (dist, index) and the first k
-        const int real = real_s;   // real entries gathered
-        const int wider = real < kTier1 ? real : kTier1;
-        // the certificate: is any entry that was not re-scored possibly nearer than the k-th?
-        // (a candidate list of the keys-out selection holds every entry up to its largest pair)
-        const uint32_t excl0 = a.part_count ? (real >= a.n || real < 1 ? 0xffffffffu : (uint32_t)(ent[real - 1] >> 32)) : excl_s;
-        bool ok = false;
-        if (two_steps) {
-            rank_and_emit(a, q, m_first, tid, NT, dist_s, idx_s, lab_s, dsel_s, &nearest_s, &distinct_s);
-            __syncthreads();
-            const uint32_t nxt = (uint32_t)(ent[m_first] >> 32);   // (real >= r > m_first with finite inputs; else the marker)
-            ok = certificate(ent, dist_s, m_first, dsel_s[a.k - 1], nxt < excl0 ? nxt : excl0, distinct_s, tid, &verdict_s);
-            if (!ok) {   // uniform
-                rescore_block_all<NT, 16>(a, qrow, idx_s + m_first, dist_s + m_first, red, m - m_first, tid);
-                if (tid == 0) distinct_s = 0;
-                __syncthreads();
-            }
-        }
-        if (!ok) {
-            rank_and_emit(a, q, m, tid, NT, dist_s, idx_s, lab_s, dsel_s, &nearest_s, &distinct_s);
-            __syncthreads();
-            uint32_t excl = excl0;
-            if (real > m) {
-                const uint32_t nxt = (uint32_t)(ent[m] >> 32);
-                excl = nxt < excl ? nxt : excl;
-            }
-            ok = certificate(ent, dist_s, m, dsel_s[a.k - 1], excl, distinct_s, tid, &verdict_s);
-        }
-        if (tid == 0) {
-            // unconfirmed: the wider round, or the exact scan, redoes this query (the outputs written
-            // here stand until then)
-            const int next = (WIDER || wider <= r) ? 1 : 0;
-            if (!ok) {
-                const int pos = atomicAdd(a.flag_count + next, 1);
-                (next ? a.flag_list2 : a.flag_list)[pos] = q;
-            }
-            if (a.stats && (ok || next == 1)) atomicAdd(a.stats + (ok ? (WIDER ? 1 : 0) : 2), 1ull);
-        }
-
-        // 4. vote and hit decision
-        decide_and_write(a, q, tid, lab_s, dsel_s, cnt_s, conf_s, nearest_s);
-    };
-    if constexpr (WIDER) {
-        for (int job = blockIdx.x; job < todo; job += gridDim.x) {
-            one_query(job);
-            __syncthreads();   // the next job reuses the shared arrays
-        }
-    } else {
-        if ((int)blockIdx.x < todo) one_query(blockIdx.x);
+    for (int c = tid; c < r; c += NT) {
+        // With finite inputs every one of the first r entries is a real cache row.  Non-finite
+        // inputs (outside the contract) can leave "no entry" markers here: map them to row 0 so
+        // that nothing is read out of bounds.
+        const uint32_t ci = (uint32_t)(ent[c] & 0xffffffffu);
+        idx_s[c] = ci < (uint32_t)a.n ? (int32_t)ci : 0;
     }
+    __syncthreads();
+
+    // 2. exact fp32 re-scoring: each wave takes a group of candidates and needs no block barrier
+    if (a.d >= 4096 && a.d % 8 == 0) {
+        // long activations: the whole block per candidate, the query row read once
+        if (r <= 16) {
+            rescore_block_all<NT, 16>(a, qrow, idx_s, dist_s, red, m_first, tid);
+        } else if (r <= 32) {
+            rescore_block_all<NT, 32>(a, qrow, idx_s, dist_s, red, m_first, tid);
+        } else {
+            // (two passes of 32: 64 accumulators per thread spill, and the pass is 8 % slower for it)
+            rescore_block_all<NT, 32>(a, qrow, idx_s, dist_s, red, 32, tid);
+            rescore_block_all<NT, 32>(a, qrow, idx_s + 32, dist_s + 32, red, r - 32, tid);
+        }
+    } else if (tid < 256) {   // short activations: four waves, one group of candidates each
+        if (r <= 16)
+            rescore_wave<4>(a, qrow, idx_s, dist_s, r, tid >> 6, tid & 63);
+        else if (r <= 32)
+            rescore_wave<8>(a, qrow, idx_s, dist_s, r, tid >> 6, tid & 63);
+        else
+            rescore_wave<16>(a, qrow, idx_s, dist_s, r, tid >> 6, tid & 63);
+    }
+    __syncthreads();
+
+    // 3. final order (dist, index) and the first k
+    const int real = real_s;   // real entries gathered
+    const int wider = real < kTier1 ? real : kTier1;
+    // the certificate: is any entry that was not re-scored possibly nearer than the k-th?
+    bool ok = false;
+    if (two_steps) {
+        rank_and_emit(a, q, m_first, tid, NT, dist_s, idx_s, lab_s, dsel_s, &nearest_s, &distinct_s);
+        __syncthreads();
+        const uint32_t nxt = (uint32_t)(ent[m_first] >> 32);   // (real >= r > m_first with finite inputs; else the marker)
+        ok = certificate(ent, dist_s, m_first, dsel_s[a.k - 1], nxt < excl_s ? nxt : excl_s, distinct_s, tid, &verdict_s);
+        if (!ok) {   // uniform
+            rescore_block_all<NT, 16>(a, qrow, idx_s + m_first, dist_s + m_first, red, r - m_first, tid);
+            if (tid == 0) distinct_s = 0;
+            __syncthreads();
+        }
+    }
+    if (!ok) {
+        rank_and_emit(a, q, r, tid, NT, dist_s, idx_s, lab_s, dsel_s, &nearest_s, &distinct_s);
+        __syncthreads();
+        uint32_t excl = excl_s;
+        if (real > r) {
+            const uint32_t nxt = (uint32_t)(ent[r] >> 32);
+            excl = nxt < excl ? nxt : excl;
+        }
+        ok = certificate(ent, dist_s, r, dsel_s[a.k - 1], excl, distinct_s, tid, &verdict_s);
+    }
+    if (tid == 0) {
+        // unconfirmed: the wider round, or the exact scan, redoes this query (the outputs written
+        // here stand until then)
+        const int next = wider <= r ? 1 : 0;
+        if (!ok) {
+            const int pos = atomicAdd(a.flag_count + next, 1);
+            (next ? a.flag_list2 : a.flag_list)[pos] = q;
+        }
+        if (a.stats && (ok || next == 1)) atomicAdd(a.stats + (ok ? 0 : 2), 1ull);
+    }
+
+    // 4. vote and hit decision
+    decide_and_write(a, q, tid, lab_s, dsel_s, cnt_s, conf_s, nearest_s);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1662,47 +1638,48 @@ hipError_t launch_finish(const FinishArgs &a, hipStream_t s)
     const size_t lds = (size_t)fa.sort_cap * sizeof(uint64_t);
     // a block per query: with few queries and long activations use 1024-thread blocks
     if (a.b <= 1024 && a.d >= 16384 && a.d % 8 == 0)
-        hipLaunchKernelGGL((finish_kernel<1024, false>), dim3((unsigned)a.b), dim3(1024), lds, s, fa);
+        hipLaunchKernelGGL((finish_kernel<1024>), dim3((unsigned)a.b), dim3(1024), lds, s, fa);
     else
-        hipLaunchKernelGGL((finish_kernel<256, false>), dim3((unsigned)a.b), dim3(256), lds, s, fa);
-    return hipGetLastError();
-}
-
-hipError_t launch_wider(const FinishArgs &a, int num_cus, hipStream_t s)
-{
-    const int total = a.part_count ? a.part_stride : a.alloc_splits * a.r;
-    if (total > kMaxMergeEntries || a.r > kMaxRescore || a.k > kMaxK || a.k > a.r) return hipErrorInvalidValue;
-    FinishKernelArgs fa{a, 2};
-    while (fa.sort_cap < total) fa.sort_cap <<= 1;
-    const size_t lds = (size_t)fa.sort_cap * sizeof(uint64_t);
-    // the wider round for the queries on list 0: a fixed grid shares them (usually there are none)
-    const int grid = a.b < 2 * num_cus ? a.b : 2 * num_cus;
-    hipLaunchKernelGGL((finish_kernel<256, true>), dim3((unsigned)grid), dim3(256), lds, s, fa);
+        hipLaunchKernelGGL((finish_kernel<256>), dim3((unsigned)a.b), dim3(256), lds, s, fa);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------------
-// Exact scan of the queries whose result the certificate did not confirm (Sec. 3: the look-up
-// returns THE k nearest neighbours): brute-force fp32 distances sum (q_i - c_i)^2 to every
-// stored entry, the same arithmetic as the re-scoring above, no bf16 anywhere.  A fixed grid of
-// workgroups shares the flagged queries: with nf of them, each is cut into S = grid / nf
-// ranges of at least 16 entries (at least one range, at most max_splits); a workgroup scans its range 256 entries
-// at a time and keeps the k nearest by (distance, index); the last workgroup of a query to finish
-// (a ticket per query) merges the S lists and writes the neighbours, the label and the hit
-// decision over that query's outputs.  Nothing is flagged on the paper's kind of data, and then
-// the kernel reads one counter and returns.
+// Follow-up of a look-up, one launch: the queries whose result the certificate did not confirm.
+// Nothing is flagged on the paper's kind of data, and then the kernel reads two counters and returns;
+// an empty launch costs 4.6 us and the gap before it, so the two rounds share one (256 x 2,000 x 512: whole
+// look-up 26.0 -> 24.4 us).
+//
+// Round 1, the wider re-scoring (list 0): up to kTier1 of the candidates gathered by the distance pass
+// are re-scored and the certificate is taken again.  Workgroups take items off a queue: a query, or, with
+// few flagged queries, a sixteenth of a query's candidates; the last of its sixteen to finish (a ticket
+// per query) decides.  (One request of a 65,536-value layer, 32 MB of rows, kept a single workgroup busy
+// for 630 us; shared it takes 70.  20 queries
+// of 512 values: 63 -> 48 us.)  What is still unconfirmed goes on list 1.
+// A workgroup that finds the queue empty waits until every item taken off it is done: those are all held
+// by running workgroups, which wait for nothing while they hold one, so the wait ends whatever part of
+// the grid is resident.
+//
+// Round 2, the exact scan (list 1; Sec. 3: the look-up returns THE k nearest neighbours):
+// brute-force fp32 distances sum (q_i - c_i)^2 to every stored entry, the same arithmetic as the
+// re-scoring above, no bf16 anywhere.  The grid shares the flagged queries: with nf of them, each is cut
+// into S = grid / nf ranges of at least 16 entries (at least one range, at most max_splits); a workgroup
+// scans its range 256 entries at a time and keeps the k nearest by (distance, index); the last workgroup
+// of a query to finish (a ticket per query) merges the S lists and writes the neighbours, the label and
+// the hit decision over that query's outputs.
 // ---------------------------------------------------------------------------------------
 struct ScanArgs {
     FinishArgs a;
     int32_t *tickets;    // [b], zero on entry; left zero
     uint64_t *part_x;    // [items, k] the k nearest of each (query, range), packed (ordered distance, index)
     int max_splits;
+    int64_t part_bytes;  // size of part_x
 };
 
-__global__ __launch_bounds__(256) void exact_scan_kernel(ScanArgs sa)
+__global__ __launch_bounds__(256) void follow_up_kernel(ScanArgs sa)
 {
     const FinishArgs &a = sa.a;
-    extern __shared__ uint64_t ent[];   // >= 512 entries and >= max_splits * k
+    extern __shared__ uint64_t ent[];   // >= 512 entries, >= max_splits * k, >= the gathered candidates of a query
     __shared__ float red[4][8];
     __shared__ float dist_s[256];
     __shared__ int32_t idx_s[256];
@@ -1712,12 +1689,123 @@ __global__ __launch_bounds__(256) void exact_scan_kernel(ScanArgs sa)
     __shared__ float dsel_s[kMaxK];
     __shared__ double conf_s[kMaxK];
     __shared__ int32_t nearest_s;
-    __shared__ int surv_s, last_s;
+    __shared__ int surv_s, last_s, job_s, real_s, distinct_s, verdict_s;
+    __shared__ uint32_t excl_s;
 
-    const int nf = a.flag_count[1];
-    if (nf <= 0) return;   // the usual case
+    const int n_wider = a.flag_count[0];
+    int nf = a.flag_count[1];
+    if (n_wider <= 0 && nf <= 0) return;   // the usual case
     const int tid = threadIdx.x;
     const int grid = (int)gridDim.x, k = a.k;
+
+    // ---- round 1: wider re-scoring ----
+    if (n_wider > 0) {   // uniform
+        const int nq = a.count ? *a.count : a.b;
+        // few flagged queries: kWiderParts workgroups share each, the distances meet in round 2's scratch
+        const bool split = n_wider * kWiderParts <= grid && (int64_t)n_wider * kTier1 * 4 <= sa.part_bytes;
+        const int items = split ? n_wider * kWiderParts : n_wider;
+        bool held = false;   // an item taken off the queue is finished, but not yet counted
+        while (true) {
+            // (thread 0 counts the last item and takes the next in one place, with barriers on both sides: a
+            // branch of thread 0 at the loop's end and another at its top would be joined by the compiler into
+            // a path on which the other threads run ahead to the next barrier)
+            if (tid == 0) {
+                if (held) atomicAdd(a.flag_count + 3, 1);
+                job_s = atomicAdd(a.flag_count + 2, 1);
+            }
+            __syncthreads();
+            const int job = __builtin_amdgcn_readfirstlane(job_s);
+            if (job >= items) break;   // uniform
+            held = true;
+            const int j = split ? job / kWiderParts : job;
+            const int q = __builtin_amdgcn_readfirstlane(a.flag_list[j]);
+            const int total = gather_entries(a, q, nq, ent, &real_s, &excl_s, tid, 256);
+            int sort_n = 2;
+            while (sort_n < total) sort_n <<= 1;
+            bitonic_sort_lds(ent, sort_n, tid, 256);
+            const int real = __builtin_amdgcn_readfirstlane(real_s);
+            const int most = real < kTier1 ? real : kTier1;   // (real entries sort in front of the markers)
+            const float *qrow = a.queries + (int64_t)(a.sel ? a.sel[q] : q) * a.d;
+            const bool whole_block = a.d >= 4096 && a.d % 8 == 0;
+            // a candidate list (keys-out routes) holds every entry up to its largest pair
+            const uint32_t excl0 = a.part_count ? (real >= a.n || real < 1 ? 0xffffffffu : (uint32_t)(ent[real - 1] >> 32)) : excl_s;
+            if (tid < most) idx_s[tid] = (int32_t)(uint32_t)ent[tid];   // < n: counted as real
+            __syncthreads();
+            auto rescore = [&](int m0, int m) {   // candidates [m0, m)
+                if (whole_block) {
+                    for (int c0 = m0; c0 < m; c0 += 16)
+                        rescore_block_all<256, 16>(a, qrow, idx_s + c0, dist_s + c0, red, m - c0 < 16 ? m - c0 : 16, tid);
+                } else {
+                    rescore_wave<4>(a, qrow, idx_s + m0, dist_s + m0, m - m0, tid >> 6, tid & 63);
+                    __syncthreads();
+                }
+            };
+            auto confirm = [&](int m) {
+                if (tid == 0) distinct_s = 0;
+                __syncthreads();
+                rank_and_emit(a, q, m, tid, 256, dist_s, idx_s, lab_s, dsel_s, &nearest_s, &distinct_s);
+                __syncthreads();
+                uint32_t excl = excl0;
+                if (real > m) {
+                    const uint32_t nxt = (uint32_t)(ent[m] >> 32);
+                    excl = nxt < excl ? nxt : excl;
+                }
+                return __builtin_amdgcn_readfirstlane(
+                           (int)certificate(ent, dist_s, m, dsel_s[k - 1], excl, distinct_s, tid, &verdict_s)) != 0;
+            };
+            bool mine = true, ok = false;   // mine: this workgroup decides the query
+            if (split) {
+                constexpr int per = kTier1 / kWiderParts;
+                float *meet = reinterpret_cast<float *>(sa.part_x) + (size_t)j * kTier1;
+                const int m0 = (job % kWiderParts) * per, m = m0 + per < most ? m0 + per : most;
+                if (m0 < m) rescore(m0, m);
+                // device-coherent stores, complete before the ticket is taken, and device-coherent loads: no fence,
+                // which would write back the whole L2 (a fence per wave took 100 us in place of 45 on 20 queries)
+                if (tid >= m0 && tid < m) __hip_atomic_store(meet + tid, dist_s[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();
+                if (tid == 0) {
+                    last_s = (atomicAdd(&sa.tickets[j], 1) == kWiderParts - 1);
+                    if (last_s) atomicExch(&sa.tickets[j], 0);   // round 2 finds it zero
+                }
+                __syncthreads();
+                mine = __builtin_amdgcn_readfirstlane(last_s) != 0;
+                if (mine) {
+                    if (tid < most) dist_s[tid] = __hip_atomic_load(meet + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    ok = confirm(most);
+                }
+            } else {
+                // many flagged queries: a workgroup each; of long rows twice as many at a time, until the
+                // certificate, whose bound grows with the first key left out, confirms the result
+                for (int m0 = 0, m = whole_block ? 64 : most; !ok && m0 < most; m0 = m, m *= 2) {
+                    m = m < most ? m : most;
+                    rescore(m0, m);
+                    ok = confirm(m);
+                }
+            }
+            if (mine) {
+                if (tid == 0) {
+                    if (!ok)
+                        __hip_atomic_store(a.flag_list2 + atomicAdd(a.flag_count + 1, 1), q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (a.stats) atomicAdd(a.stats + (ok ? 1 : 2), 1ull);
+                }
+                decide_and_write(a, q, tid, lab_s, dsel_s, cnt_s, conf_s, nearest_s);
+                // round 2 overwrites the outputs of an unconfirmed query, perhaps from another XCD: these
+                // stores leave this one's L2 before the query counts as done
+                if (!ok) __threadfence();
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+        }
+        __syncthreads();
+        if (tid == 0)
+            while (__hip_atomic_load(a.flag_count + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < items) __builtin_amdgcn_s_sleep(16);
+        __syncthreads();
+        nf = __builtin_amdgcn_readfirstlane(__hip_atomic_load(a.flag_count + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        if (nf <= 0) return;   // uniform
+    }
+
+    // ---- round 2: exact scan ----
     int S = grid / nf;
     const int by_size = (a.n + 15) / 16;   // a range holds at least 16 entries
     S = S > sa.max_splits ? sa.max_splits : S;
@@ -1726,7 +1814,7 @@ __global__ __launch_bounds__(256) void exact_scan_kernel(ScanArgs sa)
     const int64_t items = (int64_t)nf * S;
     for (int64_t item = blockIdx.x; item < items; item += grid) {
         const int j = (int)(item / S), sp = (int)(item - (int64_t)j * S);
-        const int q = a.flag_list2[j];
+        const int q = __builtin_amdgcn_readfirstlane(__hip_atomic_load(a.flag_list2 + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
         const float *qrow = a.queries + (int64_t)(a.sel ? a.sel[q] : q) * a.d;
         const int row0 = (int)((int64_t)a.n * sp / S), row1 = (int)((int64_t)a.n * (sp + 1) / S);
         if (tid < kMaxK) best_s[tid] = kSentinel;
@@ -1809,14 +1897,17 @@ size_t scan_scratch_entries(int64_t b, int k, int num_cus)
     return (size_t)items * (size_t)k;
 }
 
-hipError_t launch_exact_scan(const FinishArgs &a, int32_t *tickets, uint64_t *part_x, int num_cus, hipStream_t s)
+hipError_t launch_follow_up(const FinishArgs &a, int32_t *tickets, uint64_t *part_x, int num_cus, hipStream_t s)
 {
-    if (!a.flag_count || !a.flag_list2 || !tickets || !part_x || a.k < 1 || a.k > kMaxK) return hipErrorInvalidValue;
+    if (!a.flag_count || !a.flag_list || !a.flag_list2 || !tickets || !part_x || a.k < 1 || a.k > kMaxK) return hipErrorInvalidValue;
+    const int total = a.part_count ? a.part_stride : a.alloc_splits * a.r;   // (0: nothing goes on list 0)
+    if (total > kMaxMergeEntries) return hipErrorInvalidValue;
     const int grid = scan_grid(num_cus, a.b);
-    ScanArgs sa{a, tickets, part_x, scan_max_splits(a.k) < grid ? scan_max_splits(a.k) : grid};
+    ScanArgs sa{a, tickets, part_x, scan_max_splits(a.k) < grid ? scan_max_splits(a.k) : grid,
+                (int64_t)(scan_scratch_entries(a.b, a.k, num_cus) * 8)};
     int cap = 512;
-    while (cap < sa.max_splits * a.k) cap <<= 1;
-    hipLaunchKernelGGL(exact_scan_kernel, dim3((unsigned)grid), dim3(256), (size_t)cap * sizeof(uint64_t), s, sa);
+    while (cap < sa.max_splits * a.k || cap < total) cap <<= 1;
+    hipLaunchKernelGGL(follow_up_kernel, dim3((unsigned)grid), dim3(256), (size_t)cap * sizeof(uint64_t), s, sa);
     return hipGetLastError();
 }
 

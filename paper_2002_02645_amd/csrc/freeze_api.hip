@@ -141,7 +141,7 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
     out->cascade = cascade;
     // list and count of the queries the certificate flags, the exact scan's tickets and lists
     const size_t bb = (size_t)(b > 0 ? b : 1);
-    const size_t scan_bytes = align_up(8) + 3 * align_up((bb > 2 * kSkinnyRows ? bb : 2 * kSkinnyRows) * 4) +
+    const size_t scan_bytes = align_up(kFlagCounts * 4) + 3 * align_up((bb > 2 * kSkinnyRows ? bb : 2 * kSkinnyRows) * 4) +
                               align_up(scan_scratch_entries(b, k, ctx->num_cus) * 8);
     out->skinny = !cascade && skinny_supported(b, L.n_pad, L.d_pad, r, ctx->num_cus);
     out->keys = false;
@@ -249,7 +249,7 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
     Carver ws(workspace);
     uint16_t *q_bf = ws.take<uint16_t>((size_t)sh.plan.b_pad * L.d_pad);
     const size_t bb = (size_t)b > 2 * (size_t)kSkinnyRows ? (size_t)b : 2 * (size_t)kSkinnyRows;
-    int32_t *flag_count = ws.take<int32_t>(2);
+    int32_t *flag_count = ws.take<int32_t>(kFlagCounts);
     int32_t *flag_list = ws.take<int32_t>(bb);
     int32_t *flag_list2 = ws.take<int32_t>(bb);
     int32_t *tickets = ws.take<int32_t>(bb);   // the exact scan's; the small-batch finishing kernel's follow at + kSkinnyRows
@@ -261,7 +261,7 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
     // look-up also clears the flag count and the tickets
     if (!sh.skinny && prepared) {
         // only the flag counts start over (the exact scan leaves its tickets at zero)
-        if (launch_fill_i32(flag_count, 0, 2, s) != hipSuccess) return FREEZE_EHIP;
+        if (launch_fill_i32(flag_count, 0, kFlagCounts, s) != hipSuccess) return FREEZE_EHIP;
     } else if (!sh.skinny && launch_query_prep(queries, sel, count, b, sh.plan.b_pad, sh.plan.bm, L.d, L.d_pad, q_bf,
                                                flag_count, tickets, L.mu, s) != hipSuccess) {
         return FREEZE_EHIP;
@@ -372,14 +372,12 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
         if (launch_skinny_finish(fa, skinny_bmin, skinny_wgmin, L.n_pad / 32, sh.plan.n_splits,
                                  (int)(L.n_pad / kTileN), skinny_cand, skinny_samp, tickets + kSkinnyRows, s) != hipSuccess)
             return FREEZE_EHIP;
-    } else {
-        if ((keys ? launch_keys_finish(fa, keys, keys_bmin, L.n_pad, keys_cand, keys_cand_count, s) : launch_finish(fa, s)) !=
-            hipSuccess)
-            return FREEZE_EHIP;
-        if (launch_wider(fa, ctx->num_cus, s) != hipSuccess) return FREEZE_EHIP;
+    } else if ((keys ? launch_keys_finish(fa, keys, keys_bmin, L.n_pad, keys_cand, keys_cand_count, s) : launch_finish(fa, s)) !=
+               hipSuccess) {
+        return FREEZE_EHIP;
     }
     // the queries whose result the certificate did not confirm (usually none) are redone exactly
-    if (launch_exact_scan(fa, tickets, scan_lists, ctx->num_cus, s) != hipSuccess) return FREEZE_EHIP;
+    if (launch_follow_up(fa, tickets, scan_lists, ctx->num_cus, s) != hipSuccess) return FREEZE_EHIP;
     marks.mark(3);
     marks.done();
     return FREEZE_OK;

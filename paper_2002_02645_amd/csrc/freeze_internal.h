@@ -75,8 +75,10 @@ constexpr uint64_t kSentinel = ~0ull;   // "no entry" in (key, index) lists; lar
 // first certificate fails, the width of the error margin in estimated standard deviations, and the
 // fewest (distinct) samples an estimate is taken from.
 constexpr int kTier1 = 256;
+constexpr int kWiderParts = 16;         // workgroups that share a flagged query when few are flagged
 constexpr double kCertZ = 8.0;
 constexpr int kCertMinSamples = 8;
+constexpr int kFlagCounts = 4;          // counters of the follow-up kernel (see FinishArgs)
 constexpr int kScanMaxSplits = 512;     // exact scan of a flagged query: at most this many workgroups share it
 
 // One layer's cache inside the caller's storage buffer.
@@ -191,7 +193,7 @@ hipError_t launch_cache_build(const void *entries, int dtype, int64_t n, int64_t
                               uint16_t *c_bf, float *norm, float *c_f32, uint16_t *c_rows, const int32_t *labels_in,
                               int32_t *labels_out, float *mu, double *stats, int centre_mode, hipStream_t s);
 
-// Also clears what the later kernels of the look-up count in: flag_count[0 .. 2) and tickets[0 .. b)
+// Also clears what the later kernels of the look-up count in: flag_count[0 .. kFlagCounts) and tickets[0 .. b)
 // (each may be null).
 // mu: the cache's centring vector [d_pad] (subtracted before the rounding) or null.
 hipError_t launch_query_prep(const float *queries, const int32_t *sel, const int32_t *count, int64_t b,
@@ -251,8 +253,9 @@ struct FinishArgs {
     float *out_nbr_dist;    // [b, k]
     // Queries whose result the certificate could not confirm, by their (compact) positions: list 0
     // (flag_list, counted in flag_count[0]) is redone by the wider re-scoring, list 1 (flag_list2,
-    // flag_count[1]) by the exact scan.  The first kernel of the look-up clears both counts.
-    int32_t *flag_count;    // [2]
+    // flag_count[1]) by the exact scan.  flag_count[2] and [3] count the queries of list 0 taken and done.
+    // The first kernel of the look-up clears all four.
+    int32_t *flag_count;    // [kFlagCounts]
     int32_t *flag_list;     // [b]
     int32_t *flag_list2;    // [b]
     unsigned long long *stats;   // device, [3] or null: queries confirmed after the first re-scoring, after
@@ -268,13 +271,12 @@ int keys_finish_cand(int r);
 size_t keys_finish_workspace_bytes(int64_t rows, int64_t n_pad, int r, size_t align);
 hipError_t launch_keys_finish(const FinishArgs &a, const float *keys, const uint64_t *bmin, int64_t n_pad, uint64_t *cand,
                               int32_t *cand_count, hipStream_t s);
-// The wider re-scoring of the queries on list 0.
-hipError_t launch_wider(const FinishArgs &a, int num_cus, hipStream_t s);
-// Exact scan of the flagged queries (a.flag_list2 / a.flag_count[1]): brute-force fp32 distances to every
-// entry, the k nearest, the label and hit decision, written over the outputs of those queries.
+// Follow-up for the flagged queries, both lists: the wider re-scoring of list 0, then the exact scan of
+// list 1 (brute-force fp32 distances to every entry, the k nearest, the label and hit decision, written
+// over the outputs of those queries).
 // tickets [b] int32 (zero on entry, zero again afterwards), part_x scan_scratch_entries(b, k, num_cus) u64.
 size_t scan_scratch_entries(int64_t b, int k, int num_cus);
-hipError_t launch_exact_scan(const FinishArgs &a, int32_t *tickets, uint64_t *part_x, int num_cus, hipStream_t s);
+hipError_t launch_follow_up(const FinishArgs &a, int32_t *tickets, uint64_t *part_x, int num_cus, hipStream_t s);
 // Small-batch path: from the block minima [b, nb] and the per-group minima to the outputs (takes
 // a.r blocks).  cand and samp are scratch (skinny_finish_workspace_bytes covers both); tickets
 // [16] int32 must be zero on entry and are left zero.
