@@ -870,8 +870,10 @@ struct FinishKernelArgs {
 // one.  z = kCertZ; the estimate needs kCertMinSamples samples from as many distinct distances
 // (duplicated rows repeat one sample).  Otherwise the verdict is "unconfirmed" and the caller
 // widens the candidate set or hands the query to the exact scan.
+// floor_ulps: the margin is at least this many fp32 ulps of the quantities involved (ties; rounding that the
+// samples do not show).
 __device__ __forceinline__ bool certificate(const uint64_t *ent, const float *dist_s, int m, float dk, uint32_t excl_bits,
-                                            int distinct, int tid, int *verdict_s)
+                                            int distinct, int tid, int *verdict_s, double floor_ulps = 4.0)
 {
     if (tid < 64) {
         const double e0 = (double)from_ordered_bits((uint32_t)(ent[0] >> 32)) - (double)dist_s[0];
@@ -901,7 +903,7 @@ __device__ __forceinline__ bool certificate(const uint64_t *ent, const float *di
                 // z standard deviations of (an excluded entry's error minus the sample mean), widened by
                 // 1 + 4/m for the uncertainty of a standard deviation estimated from m samples
                 double margin = kCertZ * (1.0 + 4.0 / m) * __builtin_sqrt(var * (1.0 + 1.0 / m));
-                const double floor_ = 4.0 * 5.9604644775390625e-8 * (__builtin_fabs(kex) + __builtin_fabs(mean) + (double)dk);
+                const double floor_ = floor_ulps * 5.9604644775390625e-8 * (__builtin_fabs(kex) + __builtin_fabs(mean) + (double)dk);
                 margin = margin > floor_ ? margin : floor_;
                 ok = (kex - mean - margin > (double)dk) ? 1 : 0;   // false for NaN
             }
@@ -1628,6 +1630,436 @@ hipError_t launch_keys_finish(const FinishArgs &a, const float *keys, const uint
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------------------
+// Finishing kernel of the block-minima route (batches on short activations), one workgroup of 128 or
+// 256 threads per query, from the smallest coarse key of every block of eight entries:
+//  1. Selection.  Every wave takes the (2 R / waves)-th smallest of its 64 lanes' minima; T = the largest of
+//     these.  At least 2 R block minima are <= T, usually a few more: those are gathered and sorted.  The
+//     first m of them hold the m best entries by the coarse key: each holds one that is no worse than any
+//     entry outside them.
+//  2. Exact re-scoring of the entries of the first k + 2 blocks, a block per wave at a time: eight rows in flight per lane, and
+//     one transposed reduction for the eight sums (ten shuffles instead of 48) that adds in the order of
+//     rescore_wave's butterfly.
+//  3. The k nearest by (distance, index).
+//  4. The certificate.  Which entry of a block had the smallest key is not known; the coarse key of
+//     the block's nearest entry is formed again from the same bf16 values (the query's and the row's,
+//     relative to the cache's mean where the matrix cores' copy is), which gives a sample of the key's
+//     error per block.  What they do not show is the rounding of the matrix cores' additions, at most one ulp of a
+//     partial sum per k-step: the margin's floor covers that.  Entries outside the blocks taken have a key
+//     at or above the next minimum.  A query that fails takes R blocks, then all that were gathered (up to
+//     64), then goes on the exact scan's list.
+// Bound by the rows it reads, 8 per block: 4,096 queries x 12 blocks x 8 rows of 1 KB are 0.4 GB, beyond L2 for
+// a cache of 50,000 x 512 (51 MB); 112 us with the minima's 103 MB, 80 us on a cache of 5,000 rows.
+// ---------------------------------------------------------------------------------------
+struct BlockFinishArgs {
+    FinishArgs a;
+    const float *bkey;   // [b, nb] smallest coarse key of every block
+    const float *norm;   // [n_pad]
+    const float *mu;     // [d_pad] centring vector or null
+    int64_t nb;
+    int nk;              // k-steps of the matrix-core pass
+    int first;           // blocks re-scored at first
+    int gather;          // blocks the threshold lets in at least
+};
+
+// first of the eight entries of block blk: entries first + e and first + 16 + e, e < 4
+__device__ __forceinline__ int block_first_entry(int blk)
+{
+    return (blk >> 5) * kTileN + ((blk >> 3) & 3) * 64 + (blk & 1) * 32 + ((blk >> 1) & 3) * 4;
+}
+
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+// two values rounded to bf16 (nearest even) and widened again
+__device__ __forceinline__ f32x2 through_bf16(float x, float y)
+{
+    const uint32_t u = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x, y}, bf16x2));
+    return f32x2{__uint_as_float(u << 16), __uint_as_float(u & 0xffff0000u)};
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void block_finish_kernel(BlockFinishArgs ba)
+{
+    const FinishArgs &a = ba.a;
+    constexpr int NW = NT / 64;
+    constexpr int RMAX = kMaxRescore;                 // blocks taken at most
+    constexpr int kBlkList = 4 * NT;                  // gathered minima at most
+    __shared__ uint64_t list[kBlkList];
+    __shared__ uint64_t ent[RMAX * 8], ent2[RMAX * 8 < 128 ? 128 : RMAX * 8];
+    __shared__ uint64_t samp_s[RMAX];
+    __shared__ float sdist_s[RMAX];
+    __shared__ int32_t sidx_s[RMAX];
+    __shared__ uint32_t wave_s[4];
+    __shared__ int32_t lab_s[kMaxK], cnt_s[kMaxK];
+    __shared__ float dsel_s[kMaxK];
+    __shared__ double conf_s[kMaxK];
+    __shared__ int32_t nearest_s;
+    __shared__ uint64_t kth_s;
+    __shared__ int list_n, near_n, distinct_s, verdict_s;
+    const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (a.count && q >= *a.count) return;   // uniform
+    const int r = a.r;
+    const float *bq = ba.bkey + (size_t)q * ba.nb;
+    constexpr uint32_t kInf = 0xff800000u;   // ordered bits of +inf: a block of padding rows, or no block
+    const float inf = __builtin_inff();
+
+    // ---- 1. selection ----
+    if (tid == 0) list_n = 0;
+    uint32_t t1;
+    {
+        // group j of a thread: four consecutive minima, or with few blocks a single one, so that every lane has some
+        const bool by_four = ba.nb > 8 * NT;
+        const int64_t ng = by_four ? ba.nb / 4 : ba.nb;
+        auto fetch = [&](int64_t j) {
+            if (by_four) return reinterpret_cast<const f32x4 *>(bq)[j];
+            return f32x4{bq[j], inf, inf, inf};
+        };
+        // the minimum of every group; those of a thread's first G groups stay in registers, so that the second
+        // look fetches the few groups that hold something (further ones are read again: caches of more than
+        // 65,536 entries)
+        constexpr int G = 2048 / NT, U = 8;   // U groups in flight
+        float gm[G], m = inf;
+        auto group_min = [&](int64_t j) {
+            const f32x4 v = j < ng ? fetch(j) : f32x4{inf, inf, inf, inf};
+            return __builtin_fminf(__builtin_fminf(v[0], v[1]), __builtin_fminf(v[2], v[3]));
+        };
+#pragma unroll
+        for (int i0 = 0; i0 < G; i0 += U) {
+#pragma unroll
+            for (int i = i0; i < i0 + U; ++i) gm[i] = group_min((int64_t)i * NT + tid);
+        }
+#pragma unroll
+        for (int i = 0; i < G; ++i) m = __builtin_fminf(m, gm[i]);
+        for (int64_t j0 = (int64_t)G * NT + tid; j0 < ng; j0 += (int64_t)U * NT) {
+            float t[U];
+#pragma unroll
+            for (int i = 0; i < U; ++i) t[i] = group_min(j0 + (int64_t)i * NT);
+#pragma unroll
+            for (int i = 0; i < U; ++i) m = __builtin_fminf(m, t[i]);
+        }
+        const uint32_t s = wave_sort32(ordered_bits(m), lane);
+        const uint32_t c = (uint32_t)__shfl((int)s, (ba.gather + NW - 1) / NW - 1, 64);
+        if constexpr (NW == 1) {
+            t1 = c;
+        } else {
+            if (lane == 0) wave_s[w] = c;
+            __syncthreads();
+            t1 = wave_s[0];
+#pragma unroll
+            for (int i = 1; i < NW; ++i) t1 = wave_s[i] > t1 ? wave_s[i] : t1;
+        }
+        const float t1f = t1 >= kInf ? 3.4028235e38f : from_ordered_bits(t1);   // (blocks without an entry, +inf, never pass)
+        __syncthreads();
+        auto take = [&](int64_t j) {
+            const f32x4 v = fetch(j);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (v[e] <= t1f) {
+                    const int pos = atomicAdd(&list_n, 1);
+                    if (pos < kBlkList) list[pos] = ((uint64_t)ordered_bits(v[e]) << 32) | (uint32_t)(by_four ? j * 4 + e : j);
+                }
+            }
+        };
+        uint32_t hit = 0;   // groups of this thread that hold something
+#pragma unroll
+        for (int i = 0; i < G; ++i) hit |= (uint32_t)(gm[i] <= t1f) << i;
+        while (hit) {
+            const int i = __builtin_ctz(hit);
+            hit &= hit - 1;
+            take((int64_t)i * NT + tid);
+        }
+        for (int64_t j0 = (int64_t)G * NT + tid; j0 < ng; j0 += (int64_t)U * NT) {
+            float t[U];
+#pragma unroll
+            for (int i = 0; i < U; ++i) t[i] = group_min(j0 + (int64_t)i * NT);
+#pragma unroll
+            for (int i = 0; i < U; ++i)
+                if (t[i] <= t1f) take(j0 + (int64_t)i * NT);
+        }
+    }
+    __syncthreads();
+    const int cnt = __builtin_amdgcn_readfirstlane(list_n);
+    // (uniform) that many minima under T, which takes equal ones that the certificate could not tell apart
+    // either; or none, which takes non-finite inputs
+    if (cnt > kBlkList || cnt == 0) {
+        if (tid == 0) {
+            a.flag_list2[atomicAdd(a.flag_count + 1, 1)] = q;
+            if (a.stats) atomicAdd(a.stats + 2, 1ull);
+        }
+        return;
+    }
+    if (cnt <= 64) {
+        if (w == 0) {
+            const uint64_t x = wave_sort64(lane < cnt ? list[lane] : kSentinel, lane);
+            list[lane] = x;
+        }
+        __syncthreads();
+    } else {
+        int n2 = 128;
+        while (n2 < cnt) n2 <<= 1;
+        for (int i = cnt + tid; i < n2; i += NT) list[i] = kSentinel;
+        __syncthreads();
+        bitonic_sort_lds(list, n2, tid, NT);
+    }
+
+    const float *qrow = a.queries + (int64_t)(a.sel ? a.sel[q] : q) * a.d;
+    // the query's elements i .. i + 7 (zeros past d, where the cache's rows are zero too)
+    const bool whole = (a.d % 8) == 0, quads = (a.d % 4) == 0;
+    auto load_q = [&](int64_t i, float (&x)[8]) {
+        if (whole || (quads && i + 8 <= a.d)) {
+            const f32x4 q0 = *reinterpret_cast<const f32x4 *>(qrow + i), q1 = *reinterpret_cast<const f32x4 *>(qrow + i + 4);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = e < 4 ? q0[e & 3] : q1[e & 3];
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = i + e < a.d ? qrow[i + e] : 0.f;
+        }
+    };
+    bool ok = false;
+    // first ba.first blocks, unconfirmed queries R, then all that were gathered
+    int done = 0, nblk = ba.first < cnt ? ba.first : cnt;
+    while (true) {
+        // ---- 2. exact re-scoring of blocks [done, nblk): packed (distance, index) of their entries ----
+        for (int b = done + w; b < nblk; b += NW) {
+            const int e0 = block_first_entry(__builtin_amdgcn_readfirstlane((int)(uint32_t)list[b]));
+            // the row's place in the cache (uniform); rows past it (padding) are read as the last row and dropped below
+            auto row_of = [&](int j) {
+                const int e = e0 + (j & 3) + (j >> 2) * 16;
+                return (int64_t)(e < a.n ? e : a.n - 1) * a.d_pad;
+            };
+            float acc[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+            for (int64_t i = (int64_t)lane * 8; i < a.d; i += 512) {
+                float qv[8];
+                load_q(i, qv);
+                if (a.c_f32) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const f32x4 c0 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row_of(j) + i);
+                        const f32x4 c1 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row_of(j) + i + 4);
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const float df = qv[e] - (e < 4 ? c0[e & 3] : c1[e & 3]);
+                            acc[j] = __builtin_fmaf(df, df, acc[j]);
+                        }
+                    }
+                } else {
+                    uint4 cb[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) cb[j] = *reinterpret_cast<const uint4 *>(a.c_rows + row_of(j) + i);
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const uint32_t wv[4] = {cb[j].x, cb[j].y, cb[j].z, cb[j].w};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float d0 = qv[2 * e] - __uint_as_float(wv[e] << 16);
+                            acc[j] = __builtin_fmaf(d0, d0, acc[j]);
+                            const float d1 = qv[2 * e + 1] - __uint_as_float(wv[e] & 0xffff0000u);
+                            acc[j] = __builtin_fmaf(d1, d1, acc[j]);
+                        }
+                    }
+                }
+            }
+            // transposed reduction: after the steps over lane bits 5, 4 and 3 a lane holds the partial sum of
+            // row 4 b5 + 2 b4 + b3, the rest is a butterfly
+            float s4[4], s2[2], s1;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool hi = lane & 32;
+                s4[j] = (hi ? acc[4 + j] : acc[j]) + __shfl_xor(hi ? acc[j] : acc[4 + j], 32, 64);
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const bool hi = lane & 16;
+                s2[j] = (hi ? s4[2 + j] : s4[j]) + __shfl_xor(hi ? s4[j] : s4[2 + j], 16, 64);
+            }
+            {
+                const bool hi = lane & 8;
+                s1 = (hi ? s2[1] : s2[0]) + __shfl_xor(hi ? s2[0] : s2[1], 8, 64);
+            }
+#pragma unroll
+            for (int off = 4; off >= 1; off >>= 1) s1 += __shfl_xor(s1, off, 64);
+            // lane >> 3 = 4 b5 + 2 b4 + b3: the row; the block's nearest entry is the certificate's sample
+            const int e = e0 + ((lane >> 3) & 3) + (lane >> 5) * 16;
+            uint64_t x = e < a.n ? ((uint64_t)ordered_bits(s1) << 32) | (uint32_t)e : kSentinel;
+            if ((lane & 7) == 0) ent[b * 8 + (lane >> 3)] = x;
+#pragma unroll
+            for (int off = 32; off >= 8; off >>= 1) {
+                const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)x, off, 64);
+                const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(x >> 32), off, 64);
+                const uint64_t y = ((uint64_t)hi << 32) | lo;
+                x = y < x ? y : x;
+            }
+            if (lane == 0) {
+                // (a block that was taken holds a real entry; the marker only with non-finite inputs)
+                sidx_s[b] = (uint32_t)x < (uint32_t)a.n ? (int32_t)(uint32_t)x : 0;
+                sdist_s[b] = from_ordered_bits((uint32_t)(x >> 32));
+            }
+        }
+        if (tid == 0) {
+            distinct_s = 0;
+            near_n = 0;
+        }
+        __syncthreads();
+
+        // ---- 3. the k nearest ----
+        // The k-th smallest of the blocks' nearest distances bounds the k-th neighbour: usually a few more
+        // than k entries are left under it, and one wave sorts them.
+        const int total = nblk * 8;
+        uint64_t *res = ent2;
+        int near = 1 << 30;
+        if (a.k <= nblk) {   // uniform
+            if (w == 0) {
+                const uint64_t x = wave_sort64(
+                    lane < nblk ? ((uint64_t)ordered_bits(sdist_s[lane]) << 32) | (uint32_t)sidx_s[lane] : kSentinel, lane);
+                if (lane == a.k - 1) kth_s = x;
+            }
+            __syncthreads();
+            const uint64_t kth = kth_s;
+            for (int c = tid; c < total; c += NT) {
+                const uint64_t x = ent[c];
+                if (x <= kth) {
+                    const int pos = atomicAdd(&near_n, 1);
+                    if (pos < 64) ent2[pos] = x;
+                }
+            }
+            __syncthreads();
+            near = __builtin_amdgcn_readfirstlane(near_n);
+        }
+        if (near <= 64) {
+            if (w == 0) ent2[lane] = wave_sort64(lane < near ? ent2[lane] : kSentinel, lane);
+            __syncthreads();
+        } else {   // all of them (a second round needs ent again: the sort works on a copy)
+            int n2 = 64;
+            while (n2 < total) n2 <<= 1;   // <= RMAX * 8
+            for (int i = tid; i < n2; i += NT) ent2[i] = i < total ? ent[i] : kSentinel;
+            __syncthreads();
+            bitonic_sort_lds(ent2, n2, tid, NT);
+        }
+        if (tid < a.k) {
+            const uint64_t x = res[tid];
+            // with finite inputs the first k are real entries; a "no entry" marker maps to row 0
+            const int32_t im = x == kSentinel ? 0 : (int32_t)(uint32_t)x;
+            const float dm = from_ordered_bits((uint32_t)(x >> 32));
+            a.out_nbr_idx[(int64_t)q * a.k + tid] = im;
+            a.out_nbr_dist[(int64_t)q * a.k + tid] = dm;
+            lab_s[tid] = a.labels[im];
+            dsel_s[tid] = dm;
+            if (tid == 0) nearest_s = im;
+        }
+
+        // ---- 4. the certificate ----
+        for (int b0 = done + w * 4; b0 < nblk; b0 += 4 * NW) {
+            int64_t row[4];
+            float dot[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                row[j] = (int64_t)__builtin_amdgcn_readfirstlane(sidx_s[b0 + j < nblk ? b0 + j : nblk - 1]) * a.d_pad;
+                dot[j] = 0.f;
+            }
+            for (int64_t i = (int64_t)lane * 8; i < a.d; i += 512) {
+                float qv[8], mv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                load_q(i, qv);
+                if (ba.mu) {
+                    const f32x4 m0 = *reinterpret_cast<const f32x4 *>(ba.mu + i), m1 = *reinterpret_cast<const f32x4 *>(ba.mu + i + 4);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) mv[e] = e < 4 ? m0[e & 3] : m1[e & 3];
+                }
+#pragma unroll
+                for (int e = 0; e < 8; e += 2) {
+                    const f32x2 v = through_bf16(qv[e] - mv[e], qv[e + 1] - mv[e + 1]);
+                    qv[e] = v[0];
+                    qv[e + 1] = v[1];
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    float cv[8];
+                    if (a.c_f32) {
+                        const f32x4 c0 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row[j] + i);
+                        const f32x4 c1 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row[j] + i + 4);
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) cv[e] = e < 4 ? c0[e & 3] : c1[e & 3];
+                    } else {
+                        const uint4 cb = *reinterpret_cast<const uint4 *>(a.c_rows + row[j] + i);
+                        const uint32_t wv[4] = {cb.x, cb.y, cb.z, cb.w};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            cv[2 * e] = __uint_as_float(wv[e] << 16);
+                            cv[2 * e + 1] = __uint_as_float(wv[e] & 0xffff0000u);
+                        }
+                    }
+#pragma unroll
+                    for (int e = 0; e < 8; e += 2) {
+                        const f32x2 v = through_bf16(cv[e] - mv[e], cv[e + 1] - mv[e + 1]);
+                        dot[j] = __builtin_fmaf(qv[e], v[0], dot[j]);
+                        dot[j] = __builtin_fmaf(qv[e + 1], v[1], dot[j]);
+                    }
+                }
+            }
+            // the four sums, transposed: lane bits 5 and 4 name the row
+            float s2[2], s1;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const bool hi = lane & 32;
+                s2[j] = (hi ? dot[2 + j] : dot[j]) + __shfl_xor(hi ? dot[j] : dot[2 + j], 32, 64);
+            }
+            {
+                const bool hi = lane & 16;
+                s1 = (hi ? s2[1] : s2[0]) + __shfl_xor(hi ? s2[0] : s2[1], 16, 64);
+            }
+#pragma unroll
+            for (int off = 8; off >= 1; off >>= 1) s1 += __shfl_xor(s1, off, 64);
+            const int bj = b0 + (lane >> 4);
+            if ((lane & 15) == 0 && bj < nblk) samp_s[bj] = (uint64_t)ordered_bits(__builtin_fmaf(-2.f, s1, ba.norm[sidx_s[bj]])) << 32;
+        }
+        if (tid < nblk) {
+            int twin = 0;
+            for (int j = 0; j < tid; ++j) twin |= (sdist_s[j] == sdist_s[tid]);
+            if (!twin) atomicAdd(&distinct_s, 1);
+        }
+        __syncthreads();
+        // what was not gathered has a key above T (nothing is left out when T is infinite)
+        uint32_t excl = t1 >= kInf ? 0xffffffffu : t1;
+        if (cnt > nblk) {
+            const uint32_t nxt = (uint32_t)(list[nblk] >> 32);
+            excl = nxt < excl ? nxt : excl;
+        }
+        ok = __builtin_amdgcn_readfirstlane(
+                 (int)certificate(samp_s, sdist_s, nblk, dsel_s[a.k - 1], excl, distinct_s, tid, &verdict_s, 4.0 + 2.0 * ba.nk)) != 0;
+        const int most = cnt < RMAX ? cnt : RMAX;
+        if (ok || nblk >= most) break;   // uniform
+        done = nblk;
+        nblk = nblk < r && r < most ? r : most;
+        __syncthreads();
+    }
+    if (tid == 0) {
+        if (!ok) a.flag_list2[atomicAdd(a.flag_count + 1, 1)] = q;
+        if (a.stats) atomicAdd(a.stats + (ok ? (nblk > r ? 1 : 0) : 2), 1ull);
+    }
+    decide_and_write(a, q, tid, lab_s, dsel_s, cnt_s, conf_s, nearest_s);
+}
+
+hipError_t launch_block_finish(const FinishArgs &a, const float *bkey, const float *norm, const float *mu, int64_t n_pad, hipStream_t s)
+{
+    if (a.r < 1 || a.r > kMaxRescore || a.k > kMaxK || a.k > a.r || a.b < 1 || !a.flag_count || !a.flag_list2 || n_pad % kTileN != 0)
+        return hipErrorInvalidValue;
+    // two blocks more than neighbours confirm most queries (4,096 x 50,000 x 512, k = 10: 112 us with 12 blocks at
+    // first, 115 with 11 or 14, 123 with 16); the certificate wants eight samples at least
+    int first = a.k + 2 > kCertMinSamples ? a.k + 2 : kCertMinSamples;
+    first = first < a.r ? first : a.r;
+    const int gather = 2 * a.r < kMaxRescore ? 2 * a.r : kMaxRescore;
+    BlockFinishArgs ba{a, bkey, norm, mu, n_pad / 8, (int)(a.d_pad / kKB), first, gather};
+    // Two waves per query where the batch fills the chip with them, four where it does not (50,000 x 512: 1,500
+    // queries 52 against 57 us, 600 queries 37 against 28 us; one wave per query is slower than two at both).
+    if (a.b >= 1024)
+        hipLaunchKernelGGL(block_finish_kernel<128>, dim3((unsigned)a.b), dim3(128), 0, s, ba);
+    else
+        hipLaunchKernelGGL(block_finish_kernel<256>, dim3((unsigned)a.b), dim3(256), 0, s, ba);
+    return hipGetLastError();
+}
+
 hipError_t launch_finish(const FinishArgs &a, hipStream_t s)
 {
     const int total = a.part_count ? a.part_stride : a.alloc_splits * a.r;
@@ -1689,6 +2121,7 @@ __global__ __launch_bounds__(256) void follow_up_kernel(ScanArgs sa)
     __shared__ float dsel_s[kMaxK];
     __shared__ double conf_s[kMaxK];
     __shared__ int32_t nearest_s;
+    __shared__ uint64_t bound_s;
     __shared__ int surv_s, last_s, job_s, real_s, distinct_s, verdict_s;
     __shared__ uint32_t excl_s;
 
@@ -1857,12 +2290,37 @@ __global__ __launch_bounds__(256) void follow_up_kernel(ScanArgs sa)
         }
         __syncthreads();
         if (last_s) {   // uniform: this workgroup finished the query's last range
+            // The lists are sorted.  The k-th smallest of their heads (of S >= k lists) bounds the k-th entry:
+            // k lists have a head at or under it, so at most k * k entries are, usually a few more than k.
+            // (A sort of all S * k took 150 us of a scan of 50,000 x 1,024.)
             const int total = S * k;
-            int n2 = 2;
-            while (n2 < total) n2 <<= 1;
             const uint64_t *src = sa.part_x + (size_t)j * S * k;
-            for (int i = tid; i < n2; i += 256)
-                ent[i] = i < total ? __hip_atomic_load(src + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kSentinel;
+            uint64_t bound = kSentinel;
+            if (S > k) {   // uniform
+                for (int i = tid; i < S; i += 256)
+                    ent[i] = __hip_atomic_load(src + (size_t)i * k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (tid == 0) bound_s = kSentinel;
+                __syncthreads();
+                for (int i = tid; i < S; i += 256) {
+                    const uint64_t x = ent[i];
+                    int rank = 0;
+                    for (int l = 0; l < S; ++l) rank += ent[l] < x;
+                    if (rank == k - 1 && x != kSentinel) bound_s = x;   // (heads are distinct entries)
+                }
+                __syncthreads();
+                bound = bound_s;
+            }
+            if (tid == 0) surv_s = 0;
+            __syncthreads();
+            for (int i = tid; i < total; i += 256) {
+                const uint64_t x = __hip_atomic_load(src + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (x <= bound) ent[atomicAdd(&surv_s, 1)] = x;
+            }
+            __syncthreads();
+            const int got = __builtin_amdgcn_readfirstlane(surv_s);
+            int n2 = 2;
+            while (n2 < got || n2 < k) n2 <<= 1;   // got <= total <= the allocation
+            for (int i = got + tid; i < n2; i += 256) ent[i] = kSentinel;
             __syncthreads();
             bitonic_sort_lds(ent, n2, tid, 256);
             if (tid < k) {

@@ -1,0 +1,312 @@
+// Distance pass for batches on short activations: block minima instead of candidate lists.
+//
+// The fused kernel folds every 256 x 256 tile of keys into per-query lists in LDS.  That takes 12 us a
+// tile once the lists have settled and 60 us for a workgroup's first one, whatever the activation's
+// length; a tile's matrix work takes 11 us at 512 values (4,096 queries x 50,000 x 512: 399 us for 140 us
+// of matrix work).  Here a tile leaves one number per query and block of eight entries, the smallest key
+// of the block (4 bytes per 8 entries and query), and nothing in the kernel depends on the data: four
+// max3 per block in registers, one 8-byte store per two blocks, no LDS, no barrier.  block_finish_kernel
+// then finds the R blocks with the smallest minima, which hold the R best entries by the coarse key
+// and more, and re-scores their 8 R entries exactly: cheap as long as rows are short, which is what
+// limits this route (block_route in the API file).
+//
+//   - The accumulators start at -|c|^2 / 2 (the first matrix instruction of a tile takes the norms as its
+//     third operand), so a finished accumulator is q.c - |c|^2 / 2 = -key / 2: no arithmetic on the way out
+//     but the maximum and an exact scaling by -2.
+//   - The matrix instruction takes entries as its rows and queries as its columns: a lane holds four
+//     consecutive entries of one query per instruction, and a block is the lane's eight entries of two
+//     instructions 16 entries apart, so that its maximum needs no other lane.
+//   - 8 waves (2 x 4), each 128 queries x 64 entries, the k-step in two halves as in the batched kernel's
+//     8-wave loop; the ring of four stages runs on from one tile to the next (a tile has as few as two
+//     k-steps), so a tile costs no prologue and no drain.  Loads and stores are counted by the kernel.
+//   - Work: whole tiles, dealt evenly and contiguously to one workgroup per CU in the order (group of
+//     query tiles, cache tile, query tile of the group): a workgroup uses a cache tile for all query tiles
+//     of a group in a row, and a group's queries (at most 1 MB) stay in the XCD's L2.
+//
+// 4,096 x 50,000 x 512, k = 10: this kernel 180 us = 1.17 PFLOP/s and 103 MB of minima (399 us with lists), the
+// whole look-up 510 -> 324 us; 300 queries 170 -> 64 us; 1,500 queries, k = 40 726 -> 222 us.
+//
+// Paper: Sec. 3 (k nearest neighbours), Sec. 4 "Computational Complexity".
+#include "freeze_internal.h"
+#include "select_common.h"
+
+#include <type_traits>
+
+namespace fz {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((address_space(3))) void *lds_void_ptr;
+
+namespace {
+
+constexpr int kStageHalf = kTileN * kKB * 2;    // 16 KiB: one k-block of 256 rows
+constexpr int kStageBytes = 2 * kStageHalf;     // queries, then entries
+constexpr int NS = 4;                           // stages
+constexpr int LPS = 4, LB = 2;                  // loads per wave and stage; issued in the half-step that frees the stage
+constexpr int AM = 8, AH = 4, BNB = 4;          // 16-query blocks per wave (and half), 16-entry blocks per wave
+constexpr int STORES = AM;                      // per wave and tile
+constexpr int kNorms = NS * kStageBytes;        // byte offset of the norm buffers: per tile parity and wave, 64 floats
+constexpr int kLds = kNorms + 2 * 8 * 256;
+static_assert(kLds <= 163840, "LDS budget");
+
+struct BlockArgs {
+    const uint16_t *q_bf;   // tiled, tiles of 256 rows
+    const uint16_t *c_bf;
+    const float *norm;
+    float *bkey;            // [b_pad, n_pad / 8] smallest key of every block
+    const int32_t *count;   // device: live queries, or null (= b)
+    int b, n_tiles, nk, group;   // nk k-steps per tile (even); group: query tiles that share a cache tile in a row
+};
+
+template <class T>
+__device__ __forceinline__ T max3(T a, T b, T c)
+{
+    T r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+__global__ __launch_bounds__(512) void dist_block_kernel(BlockArgs p)
+{
+    __shared__ __attribute__((aligned(16))) unsigned char smem[kLds];
+    const bf16x8 *smem16 = reinterpret_cast<const bf16x8 *>(smem);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = w >> 2, wn = w & 3;
+    const int nq = p.count ? *p.count : p.b;
+    const int live_mt = (nq + 255) / 256;
+    const int64_t tiles = (int64_t)live_mt * p.n_tiles;
+    // contiguous shares, neighbouring shares on one XCD (block id modulo 8)
+    const int W = (int)gridDim.x, x8 = blockIdx.x & 7, a8 = W >> 3, rem8 = W & 7;
+    const int xid = x8 * a8 + (x8 < rem8 ? x8 : rem8) + ((int)blockIdx.x >> 3);
+    const int64_t t0 = tiles * xid / W, t1 = tiles * (xid + 1) / W;
+    if (t0 >= t1) return;   // uniform
+    const int steps = (int)(t1 - t0) * p.nk;
+
+    // cursor over (tile, k-step): tile t = ((query tile group, cache tile), query tile of the group)
+    struct Cursor {
+        int g0, gn, mt, nt, kb;   // first query tile and size of the group, query tile, cache tile, k-step
+    };
+    auto cursor_at = [&](int64_t t) {
+        Cursor c;
+        const int64_t per_group = (int64_t)p.group * p.n_tiles;
+        const int g = (int)(t / per_group);
+        const int64_t r = t - g * per_group;
+        c.g0 = g * p.group;
+        c.gn = live_mt - c.g0 < p.group ? live_mt - c.g0 : p.group;
+        c.nt = (int)(r / c.gn);
+        c.mt = c.g0 + (int)(r - (int64_t)c.nt * c.gn);
+        c.kb = 0;
+        return c;
+    };
+    auto next_tile = [&](Cursor &c) {
+        c.kb = 0;
+        if (++c.mt == c.g0 + c.gn) {
+            c.mt = c.g0;
+            if (++c.nt == p.n_tiles) {
+                c.nt = 0;
+                c.g0 += c.gn;
+                c.gn = live_mt - c.g0 < p.group ? live_mt - c.g0 : p.group;
+                c.mt = c.g0;
+            }
+        }
+    };
+    Cursor cur = cursor_at(t0), ld = cur;
+    int ld_left = steps;    // the loads' cursor stops at the last k-step, which the refills past the end repeat
+    auto advance = [&]() {
+        if (ld_left > 1) {
+            --ld_left;
+            if (++ld.kb == p.nk) next_tile(ld);
+        }
+    };
+    const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_void_ptr)smem;
+    const uint32_t lane_off = w * 1024 + lane * 16;
+    const uint64_t qbase = (uint64_t)(uintptr_t)p.q_bf, cbase = (uint64_t)(uintptr_t)p.c_bf;
+    // load l of the stage at the loads' cursor: two of queries, two of entries, 8 KiB of the workgroup each
+    auto issue_one = [&](int stage, int l) {
+        const uint64_t src = l < 2 ? uniform_u64(qbase + ((uint64_t)ld.mt * p.nk + ld.kb) * kStageHalf)
+                                   : uniform_u64(cbase + ((uint64_t)ld.nt * p.nk + ld.kb) * kStageHalf);
+        load16_global_to_lds(src + (l & 1) * 8192, lane_off, smem_base + stage * kStageBytes + w * 1024 + l * 8192);
+    };
+    auto issue_norms = [&](int nt, int par) {
+        const uint64_t src = uniform_u64((uint64_t)(uintptr_t)(p.norm + (size_t)nt * kTileN + wn * 64));
+        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" ::"s"(smem_base + kNorms + (par * 8 + w) * 256), "v"(lane * 4), "s"(src)
+                     : "memory", "m0");
+    };
+
+    const int rowA = wm * 128 + (lane & 15), rowB = wn * 64 + (lane & 15);
+    const int rdA = rowA * 4 + ((lane >> 4) ^ tiled_chunk_swizzle(rowA));
+    const int rdB = kStageHalf / 16 + rowB * 4 + ((lane >> 4) ^ tiled_chunk_swizzle(rowB));
+    bf16x8 af[2][AH], bfr[2][BNB];
+    auto read_a = [&](int h, int stage, int i) { af[h][i] = smem16[stage * (kStageBytes / 16) + rdA + (h * AH + i) * 64]; };
+    auto read_b = [&](int set, int stage, int j) { bfr[set][j] = smem16[stage * (kStageBytes / 16) + rdB + j * 64]; };
+    f32x4 acc[AM][BNB], nrm[BNB];
+    // accumulator starts of the tile whose norms lie in buffer `par`: -|c|^2 / 2 (padding entries: -inf)
+    auto read_norms = [&](int par) {
+        const f32x4 *src = reinterpret_cast<const f32x4 *>(smem + kNorms + (par * 8 + w) * 256);
+#pragma unroll
+        for (int j = 0; j < BNB; ++j) {
+            const f32x4 v = src[j * 4 + (lane >> 4)];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) nrm[j][e] = -0.5f * v[e];
+        }
+    };
+
+    int par = 0, stores_at = NS;   // stores_at: k-steps since the last tile's stores
+    issue_norms(cur.nt, 0);
+#pragma unroll
+    for (int ps = 0; ps < NS; ++ps) {
+#pragma unroll
+        for (int l = 0; l < (ps == NS - 1 ? LB : LPS); ++l) issue_one(ps, l);
+        if (ps < NS - 1) advance();
+    }
+    wait_global_loads_le<(NS - 2) * LPS + LB>();
+    __syncthreads();
+    read_norms(0);
+#pragma unroll
+    for (int i = 0; i < AH; ++i) read_a(0, 0, i);
+#pragma unroll
+    for (int j = 0; j < BNB; ++j) read_b(0, 0, j);
+
+    int st = 0;
+    // The k-step of the batched kernel's 8-wave loop: half the wave's query blocks against all its entry
+    // blocks, then, past the step's only barrier, the other half.  The second half's A fragments are read
+    // during the first half; the next stage's first fragments and the refill of the stage just freed leave
+    // between the second half's matrix instructions, the rest of the refill between the next step's first ones.
+    auto k_step = [&](auto set_tag, auto first_tag) {
+        constexpr int set = decltype(set_tag)::value;
+        constexpr bool first = decltype(first_tag)::value;   // the tile's first k-step: the accumulators start at the norms
+        const int nst = (st + 1 == NS) ? 0 : st + 1;
+        const int pst = (st == 0) ? NS - 1 : st - 1;
+#pragma unroll
+        for (int i = 0; i < AH; ++i) read_a(1, st, i);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < AH; ++i) {
+#pragma unroll
+            for (int j = 0; j < BNB; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[set][j], af[0][i], first ? nrm[j] : acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int l = LB + i * (LPS - LB) / AH; l < LB + (i + 1) * (LPS - LB) / AH; ++l) issue_one(pst, l);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        advance();
+        // own part of the next k-block has landed; younger than it are NS - 2 stages and, for NS - 2 steps
+        // after a tile's end, that tile's stores
+        if (stores_at <= NS - 2) wait_global_loads_le<(NS - 2) * LPS + STORES>();
+        else wait_global_loads_le<(NS - 2) * LPS>();
+        ++stores_at;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __syncthreads();                                // ... everyone's; and stage st is free
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < AH; ++i) {
+#pragma unroll
+            for (int j = 0; j < BNB; ++j)
+                acc[AH + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[set][j], af[1][i], first ? nrm[j] : acc[AH + i][j], 0, 0, 0);
+#pragma unroll
+            for (int rr = i * 8 / 3; rr < (i + 1) * 8 / 3 && rr < AH + BNB && i < 3; ++rr) {
+                if (rr < AH)
+                    read_a(0, nst, rr);
+                else
+                    read_b(set ^ 1, nst, rr - AH);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int l = i * LB / AH; l < (i + 1) * LB / AH; ++l) issue_one(st, l);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        st = nst;
+    };
+    using S0 = std::integral_constant<int, 0>;
+    using S1 = std::integral_constant<int, 1>;
+
+    for (int64_t t = t0; t < t1; ++t) {
+        // the next tile's norms, older than every stage in flight when they are read
+        Cursor nxt = cur;
+        next_tile(nxt);
+        if (t + 1 < t1) issue_norms(nxt.nt, par ^ 1);
+        k_step(S0{}, std::true_type{});
+        k_step(S1{}, std::false_type{});
+        for (int kb = 2; kb < p.nk; kb += 2) {
+            k_step(S0{}, std::false_type{});
+            k_step(S1{}, std::false_type{});
+        }
+        // ---- the tile is finished: the block minima ----
+        if (t + 1 < t1) {
+            if (p.nk <= 6) wait_global_loads_le<0>();   // a short tile: the norms may still be on their way
+            read_norms(par ^ 1);
+        }
+        int elane = lane;
+        asm volatile("" : "+v"(elane));   // opaque: the addresses are formed here, not kept across the loop
+        // (the compiler does not see that max3 reads matrix results: the no-ops are the distance the hardware
+        // wants, and the operands keep every maximum behind them)
+        asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7"
+                     : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[0][2]), "+v"(acc[0][3]), "+v"(acc[1][0]), "+v"(acc[1][1]),
+                       "+v"(acc[1][2]), "+v"(acc[1][3]), "+v"(acc[2][0]), "+v"(acc[2][1]), "+v"(acc[2][2]), "+v"(acc[2][3]),
+                       "+v"(acc[3][0]), "+v"(acc[3][1]), "+v"(acc[3][2]), "+v"(acc[3][3]));
+        asm volatile(""
+                     : "+v"(acc[4][0]), "+v"(acc[4][1]), "+v"(acc[4][2]), "+v"(acc[4][3]), "+v"(acc[5][0]), "+v"(acc[5][1]),
+                       "+v"(acc[5][2]), "+v"(acc[5][3]), "+v"(acc[6][0]), "+v"(acc[6][1]), "+v"(acc[6][2]), "+v"(acc[6][3]),
+                       "+v"(acc[7][0]), "+v"(acc[7][1]), "+v"(acc[7][2]), "+v"(acc[7][3]));
+        const int64_t nb = (int64_t)p.n_tiles * (kTileN / 8);
+        float *dst = p.bkey + ((int64_t)cur.mt * 256 + wm * 128 + (elane & 15)) * nb + cur.nt * (kTileN / 8) + wn * 8 + (elane >> 4) * 2;
+#pragma unroll
+        for (int i = 0; i < AM; ++i) {
+            f32x2 v;
+#pragma unroll
+            for (int j2 = 0; j2 < 2; ++j2) {
+                const f32x4 a = acc[i][2 * j2], b = acc[i][2 * j2 + 1];
+                const float m = max3(max3(a[0], a[1], a[2]), max3(a[3], b[0], b[1]), __builtin_fmaxf(b[2], b[3]));
+                v[j2] = -2.f * m;
+            }
+            // (rows past the batch are written too: the buffer has whole tiles of rows)
+            asm volatile("global_store_dwordx2 %0, %1, off" ::"v"(dst + i * 16 * nb), "v"(v) : "memory");
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        stores_at = 1;
+        cur = nxt;
+        par ^= 1;
+    }
+    wait_global_loads_le<0>();   // the refills past the end land before the workgroup gives its LDS back
+}
+
+}  // namespace
+
+DistPlan plan_block(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad)
+{
+    DistPlan pl{};
+    pl.variant = 5;
+    pl.bm = 256;
+    pl.r = r;
+    pl.m_tiles = (int)((b + 255) / 256);
+    if (pl.m_tiles < 1) pl.m_tiles = 1;
+    pl.n_tiles = (int)((n + kTileN - 1) / kTileN);
+    pl.n_splits = pl.alloc_splits = 1;
+    pl.max_splits = pl.n_tiles;
+    pl.num_cus = num_cus;
+    pl.b_pad = (int64_t)pl.m_tiles * 256;
+    const int64_t tiles = (int64_t)pl.m_tiles * pl.n_tiles;
+    pl.grid_units = (int)(tiles < num_cus ? tiles : num_cus);
+    // query tiles of a group: their bf16 rows take at most a quarter of an XCD's 4 MB of L2 (10,000 x 50,000 x
+    // 512: 676 us at 1 MB, 701 at 2, 728 at 4)
+    const int64_t tile_bytes = 256 * d_pad * 2;
+    int64_t g = (1 << 20) / tile_bytes;
+    g = g < 1 ? 1 : g;
+    pl.bal_f = (int)(g < pl.m_tiles ? g : pl.m_tiles);
+    return pl;
+}
+
+hipError_t launch_dist_block(const DistPlan &pl, const DistArgs &a, hipStream_t s)
+{
+    if (pl.variant != 5 || !a.keys || a.d_pad < 64 || a.d_pad % kPadD != 0 || a.b < 1 || a.b > pl.b_pad || pl.bal_f < 1 || pl.grid_units < 1)
+        return hipErrorInvalidValue;
+    BlockArgs k{a.q_bf, a.c_bf, a.norm, a.keys, a.count, a.b, pl.n_tiles, a.d_pad / kKB, pl.bal_f};
+    hipLaunchKernelGGL(dist_block_kernel, dim3((unsigned)pl.grid_units), dim3(512), 0, s, k);
+    return hipGetLastError();
+}
+
+}  // namespace fz

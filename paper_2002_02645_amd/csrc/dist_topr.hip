@@ -892,6 +892,7 @@ hipError_t launch_dist_topr(const DistPlan &plan, const DistArgs &a, hipStream_t
     if (plan.variant == 3 && (!a.keys || (!a.bmin && !a.projection))) return hipErrorInvalidValue;
     switch (plan.variant) {
     case 4: return launch_dist_stream(plan, a, s);
+    case 5: return launch_dist_block(plan, a, s);
     case 0: return launch_variant<DistCfg<256, 32, 16, 4, 2>>(plan, a, s);
     case 1: return launch_variant<DistCfg<256, 32, 32, 3>>(plan, a, s);
     case 2: return launch_variant<DistCfg<128, 32, 64, 4>>(plan, a, s);

@@ -109,6 +109,7 @@ struct LookupShape {
     int r;
     bool skinny;   // small-batch bandwidth-bound kernel instead of the tiled matrix-core kernel
     bool keys;     // tiled kernel writes every key; selection by the threshold / filter kernels
+    bool blocks;   // tiled kernel writes block minima; selection and re-scoring by block_finish_kernel
     bool cascade;  // sized for a look-up whose live count may sit on the device
     DistPlan plan;
     size_t ws_bytes;
@@ -119,6 +120,28 @@ int lists_per_query(const DistPlan &pl, bool device_count)
 {
     if (device_count) return pl.alloc_splits;
     return pl.bal_f > 0 ? pl.bal_lists : pl.n_splits;
+}
+
+// Whether a batch goes through block minima instead of per-query lists: where what the lists cost
+// is more than what re-scoring whole blocks of eight costs.  Both are times in microseconds, fitted to
+// measurements of both routes over 2,000 .. 300,000 entries, 256 .. 3,072 values, 300 .. 10,000 queries:
+//   lists   filling every workgroup's empty lists, 110 at 16 slots, 180 at 32, 500 at 64, and 10 per
+//           256 x 256 tile of a workgroup;
+//   blocks  8 (k + 2) rows per query, 64 at least, at 5.3 TB/s (8 when the cache is small enough for the L2s), 20, and a
+//           twelfth of the matrix work (the 8-wave loop against the 4-wave one of the lists at R <= 16).
+// 4,096 x 50,000, k = 10: 512 values 474 us with lists, 296 with blocks; 1,024: 583, 502; 1,536: 724, 722;
+// 2,048: 834, 914.  300 queries x 50,000 x 3,072: 271, 208.
+bool block_route(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, int r)
+{
+    // 1 GiB of minima at most; longer rows than measured lose more to the re-scoring (259 x 13,556 x 8,192, k = 20:
+    // 345 us with lists, 415 with blocks)
+    if (b * L.n_pad > (int64_t)1 << 31 || L.d_pad > 3072) return false;
+    const double tiles = (double)((b + 255) / 256) * (double)(L.n_pad / kTileN);
+    const double lists = (r <= 16 ? 110.0 : (r <= 32 ? 180.0 : 500.0)) + 10.0 * (1.0 + (double)(int64_t)(tiles / ctx->num_cus));
+    const double row = (double)L.d_pad * (L.entries_dtype == FREEZE_F32 ? 4.0 : 2.0);
+    const double per_us = (double)L.n * row <= 16e6 ? 8e6 : 5.3e6;
+    const double matrix = tiles * 256.0 * 256.0 * 2.0 * (double)L.d_pad / 1.4e9;
+    return 20.0 + matrix / 12.0 + (double)b * 8.0 * (k + 2 > 8 ? k + 2 : 8) * row / per_us < lists;
 }
 
 // The streaming kernel serves batches of at most this many queries (50,000 x 2,048: 128 queries 135 -> 113 us,
@@ -145,6 +168,7 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
                               align_up(scan_scratch_entries(b, k, ctx->num_cus) * 8);
     out->skinny = !cascade && skinny_supported(b, L.n_pad, L.d_pad, r, ctx->num_cus);
     out->keys = false;
+    out->blocks = false;
     if (out->skinny) {
         DistPlan pl{};
         pl.variant = -1;
@@ -165,15 +189,25 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
         // (measured cross-over: about 2^26 keys; 256 x 2,000: 129 -> 69 us, 200 x 50,000 x 512: 209 -> 80 us).
         out->keys = b <= (cascade ? kStreamRows : 256) && (b * 20 <= L.d_pad || b * L.n_pad <= ((int64_t)1 << 26)) &&
                     keys_finish_supported(L.n_pad, r);
+        // (batches of 129 to 256 queries on large caches: the keys' traffic costs more than the blocks' rows;
+        // 160 x 300,000 x 512: 183 against 136 us)
+        if ((!out->keys || (b > kStreamRows && b * L.n_pad > (int64_t)1 << 25)) && !small_ws && block_route(ctx, L, b, k, r)) {
+            out->keys = false;
+            out->blocks = true;
+        }
         const int64_t k_steps = (L.n_pad / kTileN) * (L.d_pad / kKB);   // per query tile
         if (out->keys && (b <= kStreamRows || 2 * k_steps < 16 * (int64_t)ctx->num_cus))
             out->plan = plan_stream(b, L.n, r, ctx->num_cus, L.d_pad, small_ws);
+        else if (out->blocks)
+            out->plan = plan_block(b, L.n, r, ctx->num_cus, L.d_pad);
         else
             out->plan = plan_dist(b, L.n, r, ctx->num_cus, out->keys, L.d_pad);
         out->ws_bytes = align_up((size_t)out->plan.b_pad * L.d_pad * 2);
         if (out->keys)
             out->ws_bytes += keys_finish_workspace_bytes(out->plan.b_pad, L.n_pad, r, kAlign) +
                              align_up(dist_partial_bytes(out->plan));
+        else if (out->blocks)
+            out->ws_bytes += align_up((size_t)out->plan.b_pad * (L.n_pad / 8) * 4);
         else
             out->ws_bytes += align_up((size_t)out->plan.b_pad * lists_per_query(out->plan, cascade) * r * 8);
         out->ws_bytes += scan_bytes;
@@ -270,6 +304,7 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
     FinishArgs fa{};
     marks.mark(1);
     const float *keys = nullptr;
+    const float *bkey = nullptr;
     const uint64_t *keys_bmin = nullptr;
     uint64_t *keys_cand = nullptr;
     int32_t *keys_cand_count = nullptr;
@@ -322,6 +357,10 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
             fa.part_count = cand_count;
             fa.part_stride = keys_finish_cand(sh.r);
             fa.n_splits = 1;
+        } else if (sh.blocks) {
+            da.keys = ws.take<float>((size_t)sh.plan.b_pad * (L.n_pad / 8));
+            if (launch_dist_topr(sh.plan, da, s) != hipSuccess) return FREEZE_EHIP;
+            bkey = da.keys;
         } else {
             // the workspace was sized by sh.cascade; the balanced decomposition only goes with it off
             const int alloc = lists_per_query(sh.plan, sh.cascade);
@@ -372,6 +411,8 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
         if (launch_skinny_finish(fa, skinny_bmin, skinny_wgmin, L.n_pad / 32, sh.plan.n_splits,
                                  (int)(L.n_pad / kTileN), skinny_cand, skinny_samp, tickets + kSkinnyRows, s) != hipSuccess)
             return FREEZE_EHIP;
+    } else if (bkey) {
+        if (launch_block_finish(fa, bkey, L.norm, L.mu, L.n_pad, s) != hipSuccess) return FREEZE_EHIP;
     } else if ((keys ? launch_keys_finish(fa, keys, keys_bmin, L.n_pad, keys_cand, keys_cand_count, s) : launch_finish(fa, s)) !=
                hipSuccess) {
         return FREEZE_EHIP;

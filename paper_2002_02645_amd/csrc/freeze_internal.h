@@ -134,7 +134,7 @@ __host__ __device__ inline int splits_for(int live_mt, int n_tiles, int num_cus,
 // Which distance kernel variant serves a re-scoring width.
 struct DistPlan {
     int variant;    // 0: R<=16, 1: R<=32, 2: R<=64 (fused top-R); 3: keys-out (selection by separate kernels);
-                    // 4: keys-out by the streaming kernel (small query tiles)
+                    // 4: keys-out by the streaming kernel (small query tiles); 5: block minima only (short activations)
     int bm;         // queries per tile
     int r;          // entries kept per (query, split)
     int m_tiles;    // ceil(b / bm)
@@ -167,6 +167,8 @@ DistPlan plan_dist(int64_t b, int64_t n, int r, int num_cus, bool keys_out, int6
 void plan_stream_k(DistPlan &pl, int num_cus, int64_t d_pad);   // sets the sk_* fields of a keys-out plan
 // Streaming kernel; whole: never cut a tile (needs no accumulator slots).
 DistPlan plan_stream(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad, bool whole);
+// Block minima; bal_f = query tiles per group, grid_units = workgroups.
+DistPlan plan_block(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad);
 size_t dist_partial_bytes(const DistPlan &plan);   // accumulator slots of cut tiles (0 when none are cut)
 
 struct DistArgs {
@@ -202,6 +204,7 @@ hipError_t launch_query_prep(const float *queries, const int32_t *sel, const int
 
 hipError_t launch_dist_topr(const DistPlan &plan, const DistArgs &a, hipStream_t s);
 hipError_t launch_dist_stream(const DistPlan &plan, const DistArgs &a, hipStream_t s);   // variant 4
+hipError_t launch_dist_block(const DistPlan &plan, const DistArgs &a, hipStream_t s);    // variant 5; keys: the block minima
 
 // Small-batch (bandwidth-bound) path: streaming kernel + threshold + filter; the result is a
 // candidate list per query for the finishing kernel.
@@ -271,6 +274,9 @@ int keys_finish_cand(int r);
 size_t keys_finish_workspace_bytes(int64_t rows, int64_t n_pad, int r, size_t align);
 hipError_t launch_keys_finish(const FinishArgs &a, const float *keys, const uint64_t *bmin, int64_t n_pad, uint64_t *cand,
                               int32_t *cand_count, hipStream_t s);
+// Block-minima route: from the smallest key of every block of eight entries [b, n_pad / 8] to the outputs.
+hipError_t launch_block_finish(const FinishArgs &a, const float *bkey, const float *norm, const float *mu, int64_t n_pad,
+                               hipStream_t s);
 // Follow-up for the flagged queries, both lists: the wider re-scoring of list 0, then the exact scan of
 // list 1 (brute-force fp32 distances to every entry, the k nearest, the label and hit decision, written
 // over the outputs of those queries).

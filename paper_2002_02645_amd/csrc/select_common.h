@@ -63,8 +63,23 @@ __device__ __forceinline__ uint64_t wave_sort64(uint64_t x, int lane)
             const uint64_t y = ((uint64_t)hi << 32) | lo;
             const bool up = (lane & size) == 0 || size == 64;
             const bool lower = (lane & stride) == 0;
-            const uint64_t mn = x < y ? x : y, mx = x < y ? y : x;
-            x = (lower == up) ? mn : mx;
+            x = ((x < y) == (lower == up)) ? x : y;   // keep the smaller where lower == up, else the larger
+        }
+    }
+    return x;
+}
+
+// The same for 32-bit values.
+__device__ __forceinline__ uint32_t wave_sort32(uint32_t x, int lane)
+{
+#pragma unroll
+    for (int size = 2; size <= 64; size <<= 1) {
+#pragma unroll
+        for (int stride = size >> 1; stride > 0; stride >>= 1) {
+            const uint32_t y = (uint32_t)__shfl_xor((int)x, stride, 64);
+            const bool up = (lane & size) == 0 || size == 64;
+            const bool lower = (lane & stride) == 0;
+            x = ((x < y) == (lower == up)) ? x : y;
         }
     }
     return x;
