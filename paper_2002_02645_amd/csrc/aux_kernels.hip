@@ -1301,7 +1301,7 @@ hipError_t launch_skinny_finish(const FinishArgs &a, const uint64_t *bmin, const
 }
 
 // ---------------------------------------------------------------------------------------
-// Finishing kernel of the keys-out routes (at most 256 queries): selection, exact re-scoring,
+// Finishing kernel of the keys-out routes (at most 1,024 queries): selection, exact re-scoring,
 // final top-k, certificate and vote in one launch, one workgroup of 1,024 threads per query.
 //  1. Selection.  The block minima are dealt into 256 groups (value j belongs to group j mod 256);
 //     T = the r_sel-th smallest group minimum.  At least r_sel blocks have a minimum <= T, so at

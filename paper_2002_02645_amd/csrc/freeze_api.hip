@@ -181,7 +181,7 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
         out->plan = pl;
         out->ws_bytes = align_up((size_t)pl.b_pad * L.d_pad * 2) + skinny_workspace_bytes(L.n_pad, r, kAlign) + scan_bytes;
     } else {
-        // One query tile and a long activation: materialising the keys (4 B per entry and query)
+        // At most 256 queries (one tile) and a long activation: materialising the keys (4 B per entry and query)
         // is cheap next to the cache stream (2 d B per entry), lets the tile be 256 queries wide for
         // any R, and keeps the selection out of the streaming kernel.  One query tile and a cache of
         // moderate size: every workgroup of the fused kernel gets a few tiles only and spends most of
@@ -194,6 +194,18 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
         if ((!out->keys || (b > kStreamRows && b * L.n_pad > (int64_t)1 << 25)) && !small_ws && block_route(ctx, L, b, k, r)) {
             out->keys = false;
             out->blocks = true;
+        }
+        // Batches of 257 to 1,024 queries: the lists of the fused kernel would fill from empty in workgroups that
+        // see few tiles, and whole tiles fill the chip badly, where the keys-out kernel cuts them along the
+        // depth (300 / 600 / 1,000 x 10,000 x 16,384: 471 -> 233, 516 -> 358, 587 -> 406 us; 1,000 x 50,000 x 8,192: 839 ->
+        // 770).  At 1,537 queries its finishing kernel, a workgroup of 1,024 threads per query, has caught up
+        // (20,011 x 4,104: 464 -> 476).  Block minima give way where their whole tiles leave half the chip idle
+        // (300 x 5,000 x 2,048: 94 -> 65 us; 1,000 x 2,000 x 2,048 goes the other way: 110, 136).
+        const int64_t tiles = ((b + 255) / 256) * (L.n_pad / kTileN);
+        if (!cascade && !small_ws && b > 256 && b <= 1024 && b * L.n_pad <= ((int64_t)1 << 26) && keys_finish_supported(L.n_pad, r) &&
+            (!out->blocks || (2 * tiles <= ctx->num_cus && L.d_pad >= 1024 && b <= 640))) {
+            out->keys = true;
+            out->blocks = false;
         }
         const int64_t k_steps = (L.n_pad / kTileN) * (L.d_pad / kKB);   // per query tile
         if (out->keys && (b <= kStreamRows || 2 * k_steps < 16 * (int64_t)ctx->num_cus))

@@ -41,6 +41,18 @@ def test_stream_shapes(n, d, b, k, dtype):
     check_case(L.entries, L.labels, q, 10, k, max(1, k - 2))
 
 
+@pytest.mark.parametrize("n,d,b,k,dtype", [
+    (2900, 4100, 257, 10, torch.bfloat16),   # keys-out kernel, two query tiles cut along the depth
+    (2900, 4100, 600, 20, torch.float32),
+    (1500, 2048, 1024, 10, torch.bfloat16),  # four query tiles, the last batch size of this route
+    (1500, 2048, 1025, 10, torch.bfloat16),  # ... and the first beyond it
+    (5000, 1024, 640, 5, torch.bfloat16),    # whole tiles (32 k-steps), in place of block minima
+])
+def test_keys_out_for_several_query_tiles(n, d, b, k, dtype):
+    L, q = _inputs(n, d, b, k, dtype, 900 + n + b)
+    check_case(L.entries, L.labels, q, 10, k, max(1, k - 2))
+
+
 @pytest.mark.parametrize("batch,thresholds", [(1, (8, 8, 8, 8)), (40, (10, 10, 10, 10)), (128, (8, 8, 8, 8))])
 def test_small_cascade(batch, thresholds):
     """All layers by the streaming kernel; with thresholds of 10 of 10 many requests go all the way."""
