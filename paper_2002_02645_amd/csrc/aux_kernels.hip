@@ -59,12 +59,53 @@ __global__ __launch_bounds__(256) void col_stats_kernel(const void *entries, int
     const int64_t per = (ns + gridDim.y - 1) / gridDim.y;
     const int64_t i0 = (int64_t)blockIdx.y * per, i1 = i0 + per < ns ? i0 + per : ns;
     const bool vec = (reinterpret_cast<uintptr_t>(entries) % 16) == 0 && (dtype == 0 ? d % 4 == 0 : d % 8 == 0) && col + 8 <= d;
+    const uint64_t step = ((uint64_t)n << 32) / (uint64_t)ns;   // ns <= 8,192, i < ns: no overflow below 2^31 rows
     double s1[8], s2[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) s1[e] = s2[e] = 0.0;
     if (col < d) {
-        for (int64_t i = i0 + w; i < i1; i += 4) {
-            const int64_t r = i * n / ns;   // sample i of ns (distinct rows: ns <= n)
+        int64_t i = i0 + w;
+        if (vec) {
+            // whole groups of values, four rows in flight; sample i of ns is row i * n / ns (n / ns in 32.32 fixed
+            // point: distinct rows, for ns <= n)
+            for (; i + 12 < i1; i += 16) {
+                f32x4 f[4][2];
+                uint4 u[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int64_t r = (int64_t)(((uint64_t)(i + 4 * t) * step) >> 32);
+                    if (dtype == 0) {
+                        const float *src = reinterpret_cast<const float *>(entries) + r * d + col;
+                        f[t][0] = *reinterpret_cast<const f32x4 *>(src);
+                        f[t][1] = *reinterpret_cast<const f32x4 *>(src + 4);
+                    } else {
+                        u[t] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(entries) + r * d + col);
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    float v[8];
+                    if (dtype == 0) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) v[e] = f[t][e >> 2][e & 3];
+                    } else {
+                        const uint32_t wv[4] = {u[t].x, u[t].y, u[t].z, u[t].w};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            v[2 * e] = __uint_as_float(wv[e] << 16);
+                            v[2 * e + 1] = __uint_as_float(wv[e] & 0xffff0000u);
+                        }
+                    }
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        s1[e] += (double)v[e];
+                        s2[e] += (double)v[e] * (double)v[e];
+                    }
+                }
+            }
+        }
+        for (; i < i1; i += 4) {
+            const int64_t r = (int64_t)(((uint64_t)i * step) >> 32);
             float v[8];
             if (vec && dtype == 0) {
                 const float *src = reinterpret_cast<const float *>(entries) + r * d + col;
@@ -156,7 +197,8 @@ __global__ __launch_bounds__(1024) void col_mean_kernel(const double *stats, int
 template <int RB>
 __global__ __launch_bounds__(256) void cache_build_kernel(const void *entries, int dtype, int64_t n, int64_t d,
                                                           int64_t d_pad, uint16_t *c_bf, float *norm, float *c_f32,
-                                                          uint16_t *c_rows, const float *mu)
+                                                          uint16_t *c_rows, const float *mu, const int32_t *labels_in,
+                                                          int32_t *labels_out)
 {
     // the matrix cores' copy of the block's rows, 64 chunks (512 elements) of every row at a time, on its
     // way from row order to the tiled order (rows padded by one chunk against bank conflicts)
@@ -166,6 +208,7 @@ __global__ __launch_bounds__(256) void cache_build_kernel(const void *entries, i
     const int64_t row0 = (int64_t)blockIdx.x * RB;
     const int64_t tile = row0 / kTileN;
     const int rit0 = (int)(row0 % kTileN);
+    if (threadIdx.x < RB && row0 + threadIdx.x < n) labels_out[row0 + threadIdx.x] = labels_in[row0 + threadIdx.x];
     uint4 *tile_base = reinterpret_cast<uint4 *>(c_bf + tile * kTileN * d_pad);
     const int64_t chunks = d_pad / 8;
     // rows start 16-byte aligned when the batch does and d is a multiple of 8 (bf16) or 4 (fp32):
@@ -297,12 +340,6 @@ __global__ __launch_bounds__(256) void cache_build_kernel(const void *entries, i
     }
 }
 
-__global__ void copy_i32_kernel(const int32_t *src, int32_t *dst, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] = src[i];
-}
-
 hipError_t launch_cache_build(const void *entries, int dtype, int64_t n, int64_t d, int64_t n_pad, int64_t d_pad,
                               uint16_t *c_bf, float *norm, float *c_f32, uint16_t *c_rows, const int32_t *labels_in,
                               int32_t *labels_out, float *mu, double *stats, int centre_mode, hipStream_t s)
@@ -313,8 +350,10 @@ hipError_t launch_cache_build(const void *entries, int dtype, int64_t n, int64_t
         if ((e = launch_fill_i32(reinterpret_cast<int32_t *>(stats), 0, 4 * d_pad, s)) != hipSuccess) return e;
         const int64_t ns = n < kStatRows ? n : kStatRows;   // sampled rows
         const int64_t col_blocks = (d + 511) / 512;
-        int64_t row_chunks = 2048 / col_blocks;
-        if (row_chunks > (ns + 31) / 32) row_chunks = (ns + 31) / 32;
+        // enough workgroups to fill the chip, but at least 128 rows each: every workgroup ends with 1,024 fp64
+        // atomic additions, and 227 per column took most of the time (8,192 x 4,104 sampled: 136 us, now 54; 8,192 x 517: 62, now 45)
+        int64_t row_chunks = 512 / col_blocks;
+        if (row_chunks > (ns + 127) / 128) row_chunks = (ns + 127) / 128;
         if (row_chunks < 1) row_chunks = 1;
         if (row_chunks > 65535) row_chunks = 65535;
         hipLaunchKernelGGL(col_stats_kernel, dim3((unsigned)col_blocks, (unsigned)row_chunks), dim3(256), 0, s, entries,
@@ -326,13 +365,10 @@ hipError_t launch_cache_build(const void *entries, int dtype, int64_t n, int64_t
     static_assert(kTileN % 16 == 0, "a workgroup's rows lie in one tile");
     if (n_pad / 16 >= 512)
         hipLaunchKernelGGL(cache_build_kernel<16>, dim3((unsigned)(n_pad / 16)), dim3(256), 0, s, entries, dtype, n, d, d_pad,
-                           c_bf, norm, c_f32, c_rows, mu);
+                           c_bf, norm, c_f32, c_rows, mu, labels_in, labels_out);
     else
         hipLaunchKernelGGL(cache_build_kernel<4>, dim3((unsigned)(n_pad / 4)), dim3(256), 0, s, entries, dtype, n, d, d_pad,
-                           c_bf, norm, c_f32, c_rows, mu);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(copy_i32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, labels_in, labels_out, n);
+                           c_bf, norm, c_f32, c_rows, mu, labels_in, labels_out);
     return hipGetLastError();
 }
 
