@@ -973,8 +973,14 @@ __global__ __launch_bounds__(NT, NT == 256 ? 4 : 1) void finish_kernel(FinishKer
     __shared__ uint32_t excl_s;
 
     const int nq = a.count ? *a.count : a.b;
-    const int q = blockIdx.x, tid = threadIdx.x;
-    if (q >= nq) return;   // uniform
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x >= nq) return;   // uniform
+    int q = blockIdx.x;
+    if (a.order) {
+        // neighbours of the order on one XCD (block id modulo 8)
+        const int x8 = q & 7, a8 = nq >> 3, rem8 = nq & 7;
+        q = a.order[x8 * a8 + (x8 < rem8 ? x8 : rem8) + (q >> 3)];
+    }
     const int r = a.r;
 
     // 1. merge the per-split lists

@@ -290,7 +290,7 @@ struct HitRule {
 int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, const float *queries, const int32_t *sel,
                    const int32_t *count, int64_t b, int k, const HitRule &rule, int32_t *out_labels, uint8_t *out_hit,
                    int32_t *out_votes, int32_t *out_nbr_idx, float *out_nbr_dist, void *workspace, hipStream_t s,
-                   bool prepared = false)
+                   bool prepared = false, const int32_t *order = nullptr)
 {
     Carver ws(workspace);
     uint16_t *q_bf = ws.take<uint16_t>((size_t)sh.plan.b_pad * L.d_pad);
@@ -397,6 +397,7 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
     fa.queries = queries;
     fa.sel = sel;
     fa.count = count;
+    fa.order = order;
     fa.b = (int)b;
     fa.n = (int)L.n;
     fa.d = L.d;
@@ -931,6 +932,11 @@ int freeze_kmeans_build(freeze_ctx *ctx, int layer, const float *points, int64_t
     // rounds of (centres -> cache, every point looked up with k = 1, centres <- means); a last
     // assignment to the final centres gives the majority labels and their shares
     const HitRule rule{0, 1, 0.f, nullptr};
+    // The points' candidates are re-scored against fp32 centres.  Where those exceed an XCD's L2 (4 MB) the
+    // points are taken, from the second round on, in the order of the centre they were assigned to in the
+    // round before, in which the update has grouped them anyway: neighbours share candidates (50,000 x 8,192,
+    // 200 centres: 895 -> 840 us a round).
+    const bool grouped = (double)kc * (double)d * 4.0 > 4e6;
     for (int it = 0; it <= iters; ++it) {
         const float *cur = cen[it & 1];
         int rc = cache_build_impl(ctx, layer, cur, FREEZE_F32, kc, d, zero_labels, num_classes, storage, cl.bytes, stream, false);
@@ -941,7 +947,7 @@ int freeze_kmeans_build(freeze_ctx *ctx, int layer, const float *points, int64_t
         // the points do not change from round to round: their bf16 copy is made once (the shape of
         // the look-up, and with it the layout of its workspace, is the same in every round)
         rc = enqueue_lookup(ctx, L, sh, points, nullptr, nullptr, n, 1, rule, t_labels, t_hit, t_votes, assign, t_dist,
-                            lookup_ws, s, it > 0);
+                            lookup_ws, s, it > 0, grouped && it > 0 ? grp_members : nullptr);
         if (rc != FREEZE_OK) return rc;
         if (it < iters &&
             launch_kmeans_update(points, assign, n, d, kc, cur, cen[(it + 1) & 1], grp_sizes, grp_offsets, grp_members, s) !=

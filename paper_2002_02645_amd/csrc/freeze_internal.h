@@ -237,6 +237,8 @@ struct FinishArgs {
     const float *queries;   // [*, d] fp32 (original batch)
     const int32_t *sel;     // compact position -> row of `queries`, or null
     const int32_t *count;   // device live-query count or null
+    const int32_t *order;   // a permutation of [0, b) the queries are taken in, or null (fused route, host-side count):
+                            // queries that share candidates next to each other
     int b;
     int n;                  // cache entries (candidate indices are checked against it)
     int64_t d, d_pad;
@@ -304,6 +306,9 @@ hipError_t launch_cascade_scatter(const int32_t *labels, const uint8_t *hit, con
 hipError_t launch_kmeans_update(const float *points, const int32_t *assign, int64_t n, int64_t d, int64_t k,
                                 const float *old_centers, float *new_centers, int32_t *sizes, int32_t *offsets,
                                 int32_t *members, hipStream_t s);
+// members = the ids 0 .. n-1 grouped by key (in [0, k)), each group ascending
+hipError_t launch_kmeans_group(const int32_t *key, int64_t n, int64_t k, int32_t *sizes, int32_t *offsets, int32_t *members,
+                               hipStream_t s);
 hipError_t launch_kmeans_majority(const int32_t *assign, const int32_t *labels, int64_t n, int num_classes, int64_t k,
                                   int32_t *majority, float *fraction, int64_t *sizes, hipStream_t s);
 hipError_t launch_copy_rows_f32(const float *src, int64_t src_stride, float *dst, int64_t rows, int64_t d, hipStream_t s);

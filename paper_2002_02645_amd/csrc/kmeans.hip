@@ -17,13 +17,27 @@ namespace fz {
 // rows in that order in fp64 and rounds the mean once to fp32, so the result does not depend on
 // scheduling; every point row is read exactly once, in 1 KiB pieces, eight rows in flight per
 // thread.  A cluster without points keeps its centre.
+// Histogram of the keys, up to kCountBins of them in LDS first (one global atomic per point and a few
+// hundred addresses: 48 us for 50,000 points).
+constexpr int kCountBins = 4096;
 __global__ __launch_bounds__(256) void kmeans_count_kernel(const int32_t *assign, int64_t n, int64_t k, int32_t *sizes)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) {
+    __shared__ int hist[kCountBins];
+    const int bins = (int)(k < kCountBins ? k : kCountBins);
+    for (int c = threadIdx.x; c < bins; c += 256) hist[c] = 0;
+    __syncthreads();
+    const int64_t per = (n + gridDim.x - 1) / gridDim.x;
+    const int64_t i1 = (blockIdx.x + 1) * per < n ? (blockIdx.x + 1) * per : n;
+    for (int64_t i = blockIdx.x * per + threadIdx.x; i < i1; i += 256) {
         const int32_t c = assign[i];
-        if ((uint32_t)c < (uint64_t)k) atomicAdd(&sizes[c], 1);
+        if (c >= 0 && c < bins)
+            atomicAdd(&hist[c], 1);
+        else if ((uint32_t)c < (uint64_t)k)
+            atomicAdd(&sizes[c], 1);
     }
+    __syncthreads();
+    for (int c = threadIdx.x; c < bins; c += 256)
+        if (hist[c]) atomicAdd(&sizes[c], hist[c]);
 }
 
 // offsets[c] = sizes[0] + .. + sizes[c-1], offsets[k] = total; one workgroup
@@ -101,20 +115,68 @@ __global__ __launch_bounds__(256) void kmeans_update_kernel(const float *points,
     new_centers[(int64_t)c * d + dim] = m1 > m0 ? (float)(acc / (double)(m1 - m0)) : old_centers[(int64_t)c * d + dim];
 }
 
+// The same for rows of whole 16-byte pieces: one wave per (centre, 256 dimensions), four dimensions per lane, so
+// that a wave reads 1 KiB of a row at a time, sixteen rows in flight.
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+__global__ __launch_bounds__(64) void kmeans_update4_kernel(const float *points, const int32_t *offsets, const int32_t *members,
+                                                            int64_t d, const float *old_centers, float *new_centers)
+{
+    constexpr int U = 16;
+    const int c = blockIdx.x;
+    const int64_t dim = (int64_t)blockIdx.y * 256 + threadIdx.x * 4;
+    if (dim >= d) return;
+    const int m0 = offsets[c], m1 = offsets[c + 1];
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    int j = m0;
+    for (; j + U <= m1; j += U) {
+        f32x4 v[U];
+#pragma unroll
+        for (int e = 0; e < U; ++e) v[e] = *reinterpret_cast<const f32x4 *>(points + (int64_t)members[j + e] * d + dim);
+#pragma unroll
+        for (int e = 0; e < U; ++e)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) acc[x] += (double)v[e][x];   // in point order
+    }
+    for (; j < m1; ++j) {
+        const f32x4 v = *reinterpret_cast<const f32x4 *>(points + (int64_t)members[j] * d + dim);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) acc[x] += (double)v[x];
+    }
+    f32x4 o = *reinterpret_cast<const f32x4 *>(old_centers + (int64_t)c * d + dim);
+    if (m1 > m0) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) o[x] = (float)(acc[x] / (double)(m1 - m0));
+    }
+    *reinterpret_cast<f32x4 *>(new_centers + (int64_t)c * d + dim) = o;
+}
+
+hipError_t launch_kmeans_group(const int32_t *key, int64_t n, int64_t k, int32_t *sizes, int32_t *offsets, int32_t *members,
+                               hipStream_t s)
+{
+    hipError_t e = launch_fill_i32(sizes, 0, k, s);
+    if (e != hipSuccess) return e;
+    const int64_t blocks = (n + 2047) / 2048 < 256 ? (n + 2047) / 2048 : 256;
+    hipLaunchKernelGGL(kmeans_count_kernel, dim3((unsigned)blocks), dim3(256), 0, s, key, n, k, sizes);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(kmeans_offsets_kernel, dim3(1), dim3(1024), 0, s, sizes, k, offsets);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(kmeans_members_kernel, dim3((unsigned)k), dim3(1024), 0, s, key, n, offsets, members);
+    return hipGetLastError();
+}
+
 hipError_t launch_kmeans_update(const float *points, const int32_t *assign, int64_t n, int64_t d, int64_t k,
                                 const float *old_centers, float *new_centers, int32_t *sizes, int32_t *offsets,
                                 int32_t *members, hipStream_t s)
 {
-    hipError_t e = launch_fill_i32(sizes, 0, k, s);
+    hipError_t e = launch_kmeans_group(assign, n, k, sizes, offsets, members, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kmeans_count_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, assign, n, k, sizes);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(kmeans_offsets_kernel, dim3(1), dim3(1024), 0, s, sizes, k, offsets);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(kmeans_members_kernel, dim3((unsigned)k), dim3(1024), 0, s, assign, n, offsets, members);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(kmeans_update_kernel, dim3((unsigned)k, (unsigned)((d + 255) / 256)), dim3(256), 0, s, points,
-                       offsets, members, d, old_centers, new_centers);
+    // (points, centres: 16-byte aligned by contract and by the workspace's layout)
+    if (d % 4 == 0)
+        hipLaunchKernelGGL(kmeans_update4_kernel, dim3((unsigned)k, (unsigned)((d + 255) / 256)), dim3(64), 0, s, points,
+                           offsets, members, d, old_centers, new_centers);
+    else
+        hipLaunchKernelGGL(kmeans_update_kernel, dim3((unsigned)k, (unsigned)((d + 255) / 256)), dim3(256), 0, s, points,
+                           offsets, members, d, old_centers, new_centers);
     return hipGetLastError();
 }
 
@@ -134,7 +196,21 @@ __global__ __launch_bounds__(256) void kmeans_majority_kernel(const int32_t *ass
     if (tid == 0) size_s = 0;
     __syncthreads();
     int mine = 0;
-    for (int64_t i = tid; i < n; i += 256) {
+    int64_t i = tid;
+    for (; i + 7 * 256 < n; i += 8 * 256) {   // eight loads in flight; most points belong to other clusters
+        int32_t as[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) as[u] = assign[i + u * 256];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (as[u] == c) {
+                const int l = labels[i + u * 256];
+                if ((unsigned)l < (unsigned)num_classes) atomicAdd(&hist[l], 1);   // labels outside the contract are not counted
+                ++mine;
+            }
+        }
+    }
+    for (; i < n; i += 256) {
         if (assign[i] == c) {
             const int l = labels[i];
             if ((unsigned)l < (unsigned)num_classes) atomicAdd(&hist[l], 1);   // labels outside the contract are not counted
