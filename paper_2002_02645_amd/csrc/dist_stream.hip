@@ -12,7 +12,7 @@
 //     ranges, one per workgroup, two workgroups per CU (one's end of a tile overlaps the other's
 //     stream).  A tile that lies in one range is finished in place; a tile cut by a range's end
 //     leaves its accumulators, BM x 256 fp32 (16 - 128 KiB), in a slot per piece, and
-//     stream_fixup_kernel adds the pieces up in the order of the ranges.
+//     stream_fixup_kernel adds the pieces up in a fixed order.
 //   - A k-step's stage in LDS is 16 KiB of cache and BM x 64 bytes of queries, both exact copies of
 //     the tiled layout, fetched with LDS-direct loads into a ring of NS stages.  The ring runs on
 //     across tile boundaries; the kernel counts its own loads and stores (stores are issued through
@@ -73,6 +73,10 @@ struct StreamArgs {
     int64_t len;            // k-steps per workgroup
     int64_t n_pad;
     int once;               // one query tile: the cache is read once and its loads carry the non-temporal hint
+    // as a projection: keys [b, ld] = acc + norm[col] (the bias), optionally through ReLU; no block minima,
+    // nothing is written past row b or column n
+    int projection, relu, n;
+    int64_t ld;
 };
 
 __device__ __forceinline__ void load4_to_lds(uint64_t sbase, uint32_t voff, uint32_t lds_byte_addr)
@@ -102,6 +106,35 @@ __device__ __forceinline__ void emit_tile(const f32x4 (&acc)[C::EB][C::QB], cons
                                           int nt, int we, int wq, int lane)
 {
     const int e0 = nt * kTileN + we * C::EB * 16 + (lane >> 4) * 4;   // first of the lane's entries in block 0
+    if (p.projection) {   // uniform
+        const bool vec = (p.ld % 4) == 0;   // rows of whole 16-byte pieces (the buffer is 16-byte aligned)
+        const int nq = p.count ? *p.count : p.b;
+#pragma unroll
+        for (int qb = 0; qb < C::QB; ++qb) {
+            const int64_t row = (int64_t)mt * C::BM + (wq * C::QB + qb) * 16 + (lane & 15);
+            if (row < nq) {
+#pragma unroll
+                for (int cb = 0; cb < C::EB; ++cb) {
+                    const int col = e0 + cb * 16;
+                    f32x4 v;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        v[e] = acc[cb][qb][e] + nrm[cb][e];
+                        if (p.relu) v[e] = __builtin_fmaxf(v[e], 0.f);
+                    }
+                    float *dst = p.keys + row * p.ld + col;
+                    if (vec && col + 4 <= p.n) {
+                        *reinterpret_cast<f32x4 *>(dst) = v;
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (col + e < p.n) dst[e] = v[e];
+                    }
+                }
+            }
+        }
+        return;
+    }
 #pragma unroll
     for (int qb = 0; qb < C::QB; ++qb) {
         const int64_t row = (int64_t)mt * C::BM + (wq * C::QB + qb) * 16 + (lane & 15);
@@ -253,7 +286,7 @@ __global__ __launch_bounds__(512, 4) void dist_stream_kernel(StreamArgs p)
 #pragma unroll
             for (int i = 0; i < C::EB; ++i) nrm[i] = nb[i * 4 + (elane >> 4)];
             emit_tile<C>(acc, nrm, p, mt, nt, we, wq, elane);
-            since = 1;
+            since = p.projection ? NS : 1;   // (a projection's stores are not counted)
         } else {
             // slot 0: the piece that does not hold the tile's first k-step, slot 1: the one that does
             f32x4 *dst = reinterpret_cast<f32x4 *>(p.partial) +
@@ -277,11 +310,14 @@ __global__ __launch_bounds__(512, 4) void dist_stream_kernel(StreamArgs p)
     wait_global_loads_le<0>();   // the refills past the end land before the workgroup gives its LDS back
 }
 
-// The tiles cut by the ends of ranges: add up the pieces in the order of the ranges, then emit.
-// Block (x, w): wave part w of the tile whose first k-step, but not its last, lies in range x.
+// The tiles cut by the ends of ranges: add up the pieces, then emit.  Block (x, w): wave part w of the tile whose
+// first k-step, but not its last, lies in range x.  Its four waves take a quarter of the pieces each, in the
+// order of the ranges, and the first adds the quarters up in order (one wave reading the 128 pieces of a
+// 32,768-value projection one after the other took 70 us).
 template <class C>
-__global__ __launch_bounds__(64) void stream_fixup_kernel(StreamArgs p)
+__global__ __launch_bounds__(256) void stream_fixup_kernel(StreamArgs p)
 {
+    __shared__ f32x4 part[3][C::EB * C::QB][64];
     const int nq = p.count ? *p.count : p.b;
     const int live_mt = (nq + C::BM - 1) / C::BM;
     const int64_t total = (int64_t)live_mt * p.n_tiles * p.nk;
@@ -291,31 +327,48 @@ __global__ __launch_bounds__(64) void stream_fixup_kernel(StreamArgs p)
     const int64_t tile = (g1 - 1) / p.nk;
     const int64_t t0 = tile * p.nk, t1 = t0 + p.nk;
     if (g1 == t1 || t0 < g0) return;   // uniform: the range ends with a tile, or its last tile starts earlier
-    const int w = blockIdx.y, lane = threadIdx.x;
+    const int w = blockIdx.y, lane = threadIdx.x & 63;
+    const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int we = w % C::WE, wq = w / C::WE;
-    const int x_last = (int)((t1 - 1) / p.len);
+    const int pieces = (int)((t1 - 1) / p.len) - (int)blockIdx.x + 1;
     f32x4 acc[C::EB][C::QB];
+#pragma unroll
+    for (int i = 0; i < C::EB; ++i)
+#pragma unroll
+        for (int j = 0; j < C::QB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const size_t piece = (size_t)(C::BM * kTileN / 4);
     const f32x4 *src = reinterpret_cast<const f32x4 *>(p.partial) + (size_t)w * C::EB * C::QB * 64 + lane;
-    {
-        const f32x4 *s1 = src + ((size_t)blockIdx.x * 2 + 1) * piece;
-#pragma unroll
-        for (int i = 0; i < C::EB; ++i)
-#pragma unroll
-            for (int j = 0; j < C::QB; ++j) acc[i][j] = s1[(i * C::QB + j) * 64];
-    }
-#pragma unroll 4
-    for (int x = (int)blockIdx.x + 1; x <= x_last; ++x) {
-        const f32x4 *s0 = src + (size_t)x * 2 * piece;
+#pragma unroll 2
+    for (int n = pieces * v / 4; n < pieces * (v + 1) / 4; ++n) {
+        // the first piece is its range's slot 1, the others are slot 0 of theirs
+        const f32x4 *s0 = src + ((size_t)(blockIdx.x + n) * 2 + (n == 0 ? 1 : 0)) * piece;
 #pragma unroll
         for (int i = 0; i < C::EB; ++i)
 #pragma unroll
             for (int j = 0; j < C::QB; ++j) {
-                const f32x4 v = s0[(i * C::QB + j) * 64];
+                const f32x4 x = s0[(i * C::QB + j) * 64];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[i][j][e] += v[e];
+                for (int e = 0; e < 4; ++e) acc[i][j][e] += x[e];
             }
     }
+    if (v > 0) {
+#pragma unroll
+        for (int i = 0; i < C::EB; ++i)
+#pragma unroll
+            for (int j = 0; j < C::QB; ++j) part[v - 1][i * C::QB + j][lane] = acc[i][j];
+    }
+    __syncthreads();
+    if (v > 0) return;
+#pragma unroll
+    for (int u = 0; u < 3; ++u)
+#pragma unroll
+        for (int i = 0; i < C::EB; ++i)
+#pragma unroll
+            for (int j = 0; j < C::QB; ++j) {
+                const f32x4 x = part[u][i * C::QB + j][lane];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[i][j][e] += x[e];
+            }
     const int mt = (int)(tile / p.n_tiles), nt = (int)(tile % p.n_tiles);
     f32x4 nrm[C::EB];
 #pragma unroll
@@ -340,11 +393,15 @@ hipError_t launch_cfg(const DistPlan &pl, const DistArgs &a, hipStream_t s)
     k.nk = a.d_pad / kKB;
     k.len = pl.st_len;
     k.n_pad = (int64_t)pl.n_tiles * kTileN;
-    k.once = pl.m_tiles == 1;
+    k.once = pl.m_tiles == 1 && !a.projection;   // (weights are small and stay in the caches)
+    k.projection = a.projection ? 1 : 0;
+    k.relu = a.relu ? 1 : 0;
+    k.n = a.n;
+    k.ld = a.projection ? a.ld : k.n_pad;
     hipLaunchKernelGGL((dist_stream_kernel<C>), dim3((unsigned)pl.st_wgs), dim3(512), 0, s, k);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !pl.st_cut) return e;
-    hipLaunchKernelGGL((stream_fixup_kernel<C>), dim3((unsigned)pl.st_wgs, 8), dim3(64), 0, s, k);
+    hipLaunchKernelGGL((stream_fixup_kernel<C>), dim3((unsigned)pl.st_wgs, 8), dim3(256), 0, s, k);
     return hipGetLastError();
 }
 
@@ -374,7 +431,9 @@ DistPlan plan_stream(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad, bo
     pl.b_pad = (int64_t)pl.m_tiles * bm;
     const int64_t all = (int64_t)pl.m_tiles * pl.n_tiles * nk;
     int64_t len = (all + wgs - 1) / wgs;
-    if (len < 8) len = 8;
+    // at least 8 k-steps a workgroup, 16 where a cut tile's slot is 128 KiB
+    const int64_t least = bm == 128 ? 16 : 8;
+    if (len < least) len = least;
     // whole tiles where a tile is short (a second launch costs more than the idle workgroups) or where a
     // range holds so many that cutting one gains little
     if (whole || nk <= 32 || len >= 16 * (int64_t)nk) len = (len + nk - 1) / nk * nk;
@@ -386,7 +445,7 @@ DistPlan plan_stream(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad, bo
 
 hipError_t launch_dist_stream(const DistPlan &pl, const DistArgs &a, hipStream_t s)
 {
-    if (pl.variant != 4 || pl.st_wgs < 1 || pl.st_len < 1 || a.d_pad < 64 || a.d_pad % kPadD != 0 || !a.keys || !a.bmin || a.b < 1 ||
+    if (pl.variant != 4 || pl.st_wgs < 1 || pl.st_len < 1 || a.d_pad < 64 || a.d_pad % kPadD != 0 || !a.keys || (!a.bmin && !a.projection) || (a.projection && a.ld < a.n) || a.b < 1 ||
         a.b > pl.b_pad || (pl.st_cut && !a.partial))
         return hipErrorInvalidValue;
     switch (pl.bm) {

@@ -817,9 +817,11 @@ void plan_stream_k(DistPlan &pl, int num_cus, int64_t d_pad)
     const int64_t rounds = (tiles + num_cus - 1) / num_cus;
     const double fill = (double)tiles / ((double)rounds * num_cus);
     const int64_t total = tiles * nk;
-    if (fill < 0.9 && rounds <= 4 && nk >= 64 && total >= 16 * (int64_t)num_cus) {
-        pl.sk_wgs = num_cus;
-        pl.sk_len = (int)((total + num_cus - 1) / num_cus);
+    if (fill < 0.9 && rounds <= 4 && nk >= 64 && total >= 4 * (int64_t)num_cus) {
+        // (at least 16 k-steps a workgroup: with 12 x 256 k-steps, 700 inputs x 8,192 -> 1,024
+        // outputs, whole tiles take 158 us and this 81)
+        pl.sk_wgs = (int)(total / 16 < num_cus ? total / 16 : num_cus);
+        pl.sk_len = (int)((total + pl.sk_wgs - 1) / pl.sk_wgs);
         pl.sk_len += pl.sk_len & 1;   // the kernel takes k-steps in pairs (nk is even: d_pad is a multiple of 64)
         pl.sk_slots = (pl.sk_len - 1) / nk + 2;
     }

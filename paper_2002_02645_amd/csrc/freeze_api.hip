@@ -611,9 +611,13 @@ const LayerCache *get_projection(const freeze_ctx *ctx, int slot, int *err)
     *err = FREEZE_OK;
     return &ctx->layers[slot];
 }
-// one workgroup per (tile of 256 inputs, tile of 256 outputs), whole depth
+// Up to 256 inputs, and up to 512 where their 256 x 256 tiles would go without stream-K: the streaming kernel, which
+// cuts the few output tiles along the depth for small input tiles too (8,192 -> 1,024 outputs: 1 input 155 -> 20 us,
+// 128 inputs 155 -> 39 us; 384 x 16,384, where stream-K applies: 124 us against 133).  Else a workgroup per (tile
+// of 256 inputs, tile of 256 outputs), whole depth or stream-K.
 DistPlan projection_plan(const freeze_ctx *ctx, const LayerCache &P, int64_t b)
 {
+    if (b <= 256) return plan_stream(b > 0 ? b : 1, P.n, 1, ctx->num_cus, P.d_pad, false);
     DistPlan pl{};
     pl.variant = 3;
     pl.bm = 256;
@@ -627,6 +631,7 @@ DistPlan projection_plan(const freeze_ctx *ctx, const LayerCache &P, int64_t b)
     pl.num_cus = ctx->num_cus;
     pl.b_pad = (int64_t)pl.m_tiles * 256;
     plan_stream_k(pl, ctx->num_cus, P.d_pad);
+    if (b <= 512 && pl.sk_wgs == 0) return plan_stream(b, P.n, 1, ctx->num_cus, P.d_pad, false);
     return pl;
 }
 
@@ -1014,8 +1019,9 @@ size_t freeze_project_workspace_bytes(const freeze_ctx *ctx, int slot, int64_t b
     int err;
     const LayerCache *P = get_projection(ctx, slot, &err);
     if (!P || b < 0 || b > (int64_t)1 << 30) return 0;
-    const int64_t b_pad = (b + 255) / 256 * 256 + (b == 0 ? 256 : 0);
     const DistPlan pl = projection_plan(ctx, *P, b);
+    if (pl.variant == 4) return align_up((size_t)pl.b_pad * P->d_pad * 2) + align_up(dist_partial_bytes(pl));
+    const int64_t b_pad = (b + 255) / 256 * 256 + (b == 0 ? 256 : 0);
     return align_up((size_t)b_pad * P->d_pad * 2) + align_up((size_t)(b > 0 ? b : 1) * P->n_pad * 4) +
            align_up(dist_partial_bytes(pl));
 }
@@ -1037,11 +1043,13 @@ int freeze_project(freeze_ctx *ctx, int slot, const float *x, int64_t b, int rel
     const DistPlan pl = projection_plan(ctx, *P, b);
     Carver ws(workspace);
     uint16_t *x_bf = ws.take<uint16_t>((size_t)pl.b_pad * P->d_pad);
-    float *tmp = ws.take<float>((size_t)b * P->n_pad);
-    float *partial = pl.sk_wgs > 0 ? ws.take<float>(dist_partial_bytes(pl) / 4) : nullptr;
+    const bool streamed = pl.variant == 4;
+    float *tmp = streamed ? nullptr : ws.take<float>((size_t)b * P->n_pad);
+    float *partial = dist_partial_bytes(pl) > 0 ? ws.take<float>(dist_partial_bytes(pl) / 4) : nullptr;
     if (launch_query_prep(x, nullptr, nullptr, b, pl.b_pad, pl.bm, P->d, P->d_pad, x_bf, nullptr, nullptr, nullptr, s) != hipSuccess)
         return FREEZE_EHIP;
-    const bool direct = P->n == P->n_pad;   // the output rows are then exactly what the kernel writes
+    // the output rows are what the kernel writes (the 256-input tiles write whole tiles of columns)
+    const bool direct = streamed || P->n == P->n_pad;
     DistArgs da{};
     da.q_bf = x_bf;
     da.c_bf = P->c_bf;
@@ -1052,6 +1060,7 @@ int freeze_project(freeze_ctx *ctx, int slot, const float *x, int64_t b, int rel
     da.d_pad = (int)P->d_pad;
     da.projection = true;
     da.relu = relu != 0;
+    da.ld = P->n;
     da.partial = partial;
     if (launch_dist_topr(pl, da, s) != hipSuccess) return FREEZE_EHIP;
     if (!direct && launch_copy_rows_f32(tmp, P->n_pad, out, b, P->n, s) != hipSuccess) return FREEZE_EHIP;

@@ -181,6 +181,7 @@ struct DistArgs {
     float *partial;         // dist_partial_bytes(plan) bytes of scratch (keys-out variant under stream-K)
     bool projection;        // keys-out variant as a projection: keys = acc + norm[col] (norm holds the bias), no bmin
     bool relu;              // ... through max(., 0)
+    int64_t ld;             // ... row stride of `keys` in the streaming kernel's projection
     bool balanced;          // use the plan's balanced decomposition (needs lists >= plan.bal_lists)
     int lists;              // candidate lists per query `part` has room for (their stride); fused variants
     const int32_t *count;   // device: number of live queries, or null (= b)
