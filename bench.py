@@ -238,7 +238,9 @@ def run_workload(torch, np, binding, synth, dev, name, steps, warmup, cache_copi
         achieved = cache_bytes / (dist_ms * 1e-3) / 1e9
         roofline = dict(bound="hbm", achieved=round(achieved, 1), peak=PEAK_HBM_GBS, unit="GB/s",
                         frac=round(achieved / PEAK_HBM_GBS, 4), traffic=None)
-    roofline["kernel"] = "dist_skinny_kernel" if skinny else "dist_topr_kernel"
+    # (a small cache is streamed against small query tiles: the library's rule is on 256-row tiles x k-steps)
+    streamed = not cascade and not skinny and (b <= 128 or (b <= 256 and 2 * -(-spec.n // 256) * -(-spec.d // 64) * 2 < 4096))
+    roofline["kernel"] = "dist_skinny_kernel" if skinny else ("dist_stream_kernel" if streamed else "dist_topr_kernel")
     roofline["kernel_ms"] = round(dist_ms, 4)
     # (a cascade's profile averages the kernel over its four layers: no per-layer traffic figure)
     roofline["traffic"] = None if cascade else measured_traffic(roofline["kernel"], wl.name)
