@@ -149,7 +149,8 @@ int freeze_lookup(freeze_ctx *ctx, int layer, const float *queries, int64_t b, i
 /*
  * freeze_lookup for callers that cannot allocate device memory or hand over a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
- * arguments, kernels and results as freeze_lookup, except that the workspace is a buffer of
+ * arguments and results as freeze_lookup (where the faster decomposition of the work needs more
+ * scratch than the buffer holds, a smaller one is taken), except that the workspace is a buffer of
  * FREEZE_STATIC_SCRATCH_BYTES bytes that lives inside the library's device code (every GPU the
  * library runs on holds one until the process ends).  The call allocates nothing, on the
  * device or through any library.  A look-up whose freeze_lookup_workspace_bytes() exceeds
