@@ -802,14 +802,18 @@ DistPlan plan_dist(int64_t b, int64_t n, int r, int num_cus, bool keys_out, int6
         }
     }
     pl.sk_wgs = pl.sk_len = pl.sk_slots = 0;
-    if (keys_out) plan_stream_k(pl, num_cus, d_pad);
+    if (keys_out) plan_stream_k(pl, num_cus, d_pad, 90.0);
     return pl;
 }
 
 // Stream-K for the keys-out variant when whole (query tile, cache tile) units fill the CUs badly
 // (196 units on 256 CUs leave a quarter of the chip idle; 4 units nearly all of it) and the depth
-// is long enough to be worth cutting.
-void plan_stream_k(DistPlan &pl, int num_cus, int64_t d_pad)
+// is long enough to be worth cutting.  Writing, reading and adding up the slots takes about 50 us whatever the
+// depth, so for a look-up it pays only where whole tiles would leave the average CU idle for more k-steps
+// (0.55 us each) than that: 96 pay (1,000 x 10,000 x 8,192: 281 us whole, 256 cut), 60 do not (256 x 50,000 x
+// 8,192: 269 whole, 302 cut).  A projection is cut wherever whole tiles fill badly: shorter chains of additions
+// are part of its precision.
+void plan_stream_k(DistPlan &pl, int num_cus, int64_t d_pad, double least_idle)
 {
     pl.sk_wgs = pl.sk_len = pl.sk_slots = 0;
     const int nk = (int)(d_pad / 32);   // k-steps per tile of the keys-out variant
@@ -817,7 +821,8 @@ void plan_stream_k(DistPlan &pl, int num_cus, int64_t d_pad)
     const int64_t rounds = (tiles + num_cus - 1) / num_cus;
     const double fill = (double)tiles / ((double)rounds * num_cus);
     const int64_t total = tiles * nk;
-    if (fill < 0.9 && rounds <= 4 && nk >= 64 && total >= 4 * (int64_t)num_cus) {
+    const double idle = (double)rounds * nk * (1.0 - fill);   // k-steps
+    if (fill < 0.9 && idle > least_idle && rounds <= 4 && nk >= 64 && total >= 4 * (int64_t)num_cus) {
         // (at least 16 k-steps a workgroup: with 12 x 256 k-steps, 700 inputs x 8,192 -> 1,024
         // outputs, whole tiles take 158 us and this 81)
         pl.sk_wgs = (int)(total / 16 < num_cus ? total / 16 : num_cus);

@@ -630,7 +630,7 @@ DistPlan projection_plan(const freeze_ctx *ctx, const LayerCache &P, int64_t b)
     pl.grid_units = pl.m_tiles * pl.n_tiles;
     pl.num_cus = ctx->num_cus;
     pl.b_pad = (int64_t)pl.m_tiles * 256;
-    plan_stream_k(pl, ctx->num_cus, P.d_pad);
+    plan_stream_k(pl, ctx->num_cus, P.d_pad, 0.0);
     if (b <= 512 && pl.sk_wgs == 0) return plan_stream(b, P.n, 1, ctx->num_cus, P.d_pad, false);
     return pl;
 }

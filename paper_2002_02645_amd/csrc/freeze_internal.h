@@ -164,7 +164,8 @@ struct DistPlan {
 
 // d_pad decides stream-K for the keys-out variant (pass 0 to leave it off).
 DistPlan plan_dist(int64_t b, int64_t n, int r, int num_cus, bool keys_out, int64_t d_pad = 0);
-void plan_stream_k(DistPlan &pl, int num_cus, int64_t d_pad);   // sets the sk_* fields of a keys-out plan
+// Sets the sk_* fields of a keys-out plan; least_idle: k-steps the average CU must be idle under whole tiles.
+void plan_stream_k(DistPlan &pl, int num_cus, int64_t d_pad, double least_idle);
 // Streaming kernel; whole: never cut a tile (needs no accumulator slots).
 DistPlan plan_stream(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad, bool whole);
 // Block minima; bal_f = query tiles per group, grid_units = workgroups.
