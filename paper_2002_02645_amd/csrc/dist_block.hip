@@ -21,7 +21,7 @@
 //     k-steps), so a tile costs no prologue and no drain.  Loads and stores are counted by the kernel.
 //   - Work: whole tiles, dealt evenly and contiguously to one workgroup per CU in the order (group of
 //     query tiles, cache tile, query tile of the group): a workgroup uses a cache tile for all query tiles
-//     of a group in a row, and a group's queries (at most 1 MB) stay in the XCD's L2.
+//     of a group in a row, and a group's queries (1 or 2 MB) stay in the XCD's L2.
 //
 // 4,096 x 50,000 x 512, k = 10: this kernel 180 us = 1.17 PFLOP/s and 103 MB of minima (399 us with lists), the
 // whole look-up 510 -> 324 us; 300 queries 170 -> 64 us; 1,500 queries, k = 40 726 -> 222 us.
@@ -294,7 +294,10 @@ DistPlan plan_block(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad)
     // query tiles of a group: their bf16 rows take at most a quarter of an XCD's 4 MB of L2 (10,000 x 50,000 x
     // 512: 676 us at 1 MB, 701 at 2, 728 at 4)
     const int64_t tile_bytes = 256 * d_pad * 2;
-    int64_t g = (1 << 20) / tile_bytes;
+    // ... at 2 MB where the cache exceeds the memory-side cache (256 MB) and every group reads it from HBM again (640 x
+    // 520,980 x 1,100: 988 us at 1 MB, 832 at 2)
+    const int64_t cache_bytes = (int64_t)pl.n_tiles * kTileN * d_pad * 2;
+    int64_t g = (cache_bytes > ((int64_t)256 << 20) ? 2 << 20 : 1 << 20) / tile_bytes;
     g = g < 1 ? 1 : g;
     pl.bal_f = (int)(g < pl.m_tiles ? g : pl.m_tiles);
     return pl;

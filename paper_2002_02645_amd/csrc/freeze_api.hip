@@ -136,6 +136,8 @@ bool block_route(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, i
     // 1 GiB of minima at most; longer rows than measured lose more to the re-scoring (259 x 13,556 x 8,192, k = 20:
     // 345 us with lists, 415 with blocks)
     if (b * L.n_pad > (int64_t)1 << 31 || L.d_pad > 3072) return false;
+    // (600 x 250,000 x 3,000: 1,011 us with lists, 1,091 with blocks)
+    if (L.d_pad > 2048 && L.n_pad * L.d_pad * 2 > (int64_t)512 << 20) return false;
     const double tiles = (double)((b + 255) / 256) * (double)(L.n_pad / kTileN);
     const double lists = (r <= 16 ? 110.0 : (r <= 32 ? 180.0 : 500.0)) + 10.0 * (1.0 + (double)(int64_t)(tiles / ctx->num_cus));
     const double row = (double)L.d_pad * (L.entries_dtype == FREEZE_F32 ? 4.0 : 2.0);
