@@ -1699,13 +1699,14 @@ struct BlockFinishArgs {
     const float *norm;   // [n_pad]
     const float *mu;     // [d_pad] centring vector or null
     int64_t nb;
+    int64_t real_blocks; // blocks that hold an entry (the others hold padding rows)
     int nk;              // k-steps of the matrix-core pass
     int first;           // blocks re-scored at first
     int gather;          // blocks the threshold lets in at least
 };
 
 // first of the eight entries of block blk: entries first + e and first + 16 + e, e < 4
-__device__ __forceinline__ int block_first_entry(int blk)
+__host__ __device__ inline int block_first_entry(int blk)
 {
     return (blk >> 5) * kTileN + ((blk >> 3) & 3) * 64 + (blk & 1) * 32 + ((blk >> 1) & 3) * 4;
 }
@@ -1823,8 +1824,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
     __syncthreads();
     const int cnt = __builtin_amdgcn_readfirstlane(list_n);
     // (uniform) that many minima under T, which takes equal ones that the certificate could not tell apart
-    // either; or none, which takes non-finite inputs
-    if (cnt > kBlkList || cnt == 0) {
+    // either; or none, which takes non-finite inputs; or, with T infinite, fewer than there are: the key of some
+    // block's every entry overflowed, and those entries rank by their index
+    if (cnt > kBlkList || cnt == 0 || (t1 >= kInf && cnt < ba.real_blocks)) {
         if (tid == 0) {
             a.flag_list2[atomicAdd(a.flag_count + 1, 1)] = q;
             if (a.stats) atomicAdd(a.stats + 2, 1ull);
@@ -2062,7 +2064,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
             if (!twin) atomicAdd(&distinct_s, 1);
         }
         __syncthreads();
-        // what was not gathered has a key above T (nothing is left out when T is infinite)
+        // what was not gathered has a key above T (nothing is left out when T is infinite: see above)
         uint32_t excl = t1 >= kInf ? 0xffffffffu : t1;
         if (cnt > nblk) {
             const uint32_t nxt = (uint32_t)(list[nblk] >> 32);
@@ -2092,7 +2094,9 @@ hipError_t launch_block_finish(const FinishArgs &a, const float *bkey, const flo
     int first = a.k + 2 > kCertMinSamples ? a.k + 2 : kCertMinSamples;
     first = first < a.r ? first : a.r;
     const int gather = 2 * a.r < kMaxRescore ? 2 * a.r : kMaxRescore;
-    BlockFinishArgs ba{a, bkey, norm, mu, n_pad / 8, (int)(a.d_pad / kKB), first, gather};
+    int64_t real_blocks = (n_pad / kTileN - 1) * (kTileN / 8);
+    for (int blk = 0; blk < kTileN / 8; ++blk) real_blocks += n_pad - kTileN + block_first_entry(blk) < a.n;
+    BlockFinishArgs ba{a, bkey, norm, mu, n_pad / 8, real_blocks, (int)(a.d_pad / kKB), first, gather};
     // Two waves per query where the batch fills the chip with them, four where it does not (50,000 x 512: 1,500
     // queries 52 against 57 us, 600 queries 37 against 28 us; one wave per query is slower than two at both).
     if (a.b >= 1024)

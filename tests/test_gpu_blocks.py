@@ -8,7 +8,7 @@ import torch
 from oracle import freeze_oracle as fo
 from paper_2002_02645_amd import binding, synth
 from tests import parity
-from tests.test_gpu_parity import check_case
+from tests.test_gpu_parity import check_case, run_lookup
 
 pytestmark = pytest.mark.gpu
 
@@ -80,3 +80,25 @@ def test_blocks_in_a_cascade():
                                         wl.k, [9] * nl)
     assert np.array_equal(got["label"], exp_l) and np.array_equal(got["exit_layer"], exp_x)
     assert np.array_equal(got["hits_per_layer"], exp_h)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_entries_whose_norm_overflows(dtype):
+    """Finite values whose squares overflow in fp32: the distance is +inf, and such entries rank behind all
+    others in the order of their indices.  Only five of 300 entries are nearer here, none of them
+    in a block with the first indices."""
+    n, d, b, k = 300, 64, 300, 10
+    g = torch.Generator().manual_seed(99)
+    ent = torch.randn(n, d, generator=g) * 1e25
+    near = [100, 130, 200, 255, 290]
+    ent[near] = torch.randn(5, d, generator=g)
+    ent = ent.to(dtype)
+    q = torch.randn(b, d, generator=g)
+    labels = torch.randint(0, 10, (n,), generator=g, dtype=torch.int32)
+    got = run_lookup(ent, labels, q, 10, k, 3)
+    dist = ((q.double()[:, None, :] - ent[near].double()[None]) ** 2).sum(2)
+    order = dist.argsort(dim=1)
+    assert np.array_equal(got["idx"][:, :5], np.array(near)[order.numpy()])
+    np.testing.assert_allclose(got["dist"][:, :5], dist.sort(dim=1).values.numpy(), rtol=1e-5)
+    assert np.array_equal(got["idx"][:, 5:], np.broadcast_to(np.arange(5), (b, 5)))
+    assert np.isposinf(got["dist"][:, 5:]).all()
