@@ -7,6 +7,8 @@
 #include "freeze_internal.h"
 #include "select_common.h"
 
+#include <type_traits>
+
 namespace fz {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -1680,8 +1682,8 @@ hipError_t launch_keys_finish(const FinishArgs &a, const float *keys, const uint
 //     first m of them hold the m best entries by the coarse key: each holds one that is no worse than any
 //     entry outside them.
 //  2. Exact re-scoring of the entries of the first k + 2 blocks, a block per wave at a time: eight rows in flight per lane, and
-//     one transposed reduction for the eight sums (ten shuffles instead of 48) that adds in the order of
-//     rescore_wave's butterfly.
+//     one transposed reduction for the eight sums (ten shuffles instead of 48).  Same order of additions as in
+//     rescore_wave, for rows of any length, hence the same distances bit for bit.
 //  3. The k nearest by (distance, index).
 //  4. The certificate.  Which entry of a block had the smallest key is not known; the coarse key of
 //     the block's nearest entry is formed again from the same bf16 values (the query's and the row's,
@@ -1875,56 +1877,147 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
             float acc[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-            for (int64_t i = (int64_t)lane * 8; i < a.d; i += 512) {
-                float qv[8];
-                load_q(i, qv);
-                if (a.c_f32) {
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const f32x4 c0 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row_of(j) + i);
-                        const f32x4 c1 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row_of(j) + i + 4);
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            const float df = qv[e] - (e < 4 ? c0[e & 3] : c1[e & 3]);
-                            acc[j] = __builtin_fmaf(df, df, acc[j]);
+            if (whole) {   // uniform
+                for (int64_t i = (int64_t)lane * 8; i < a.d; i += 512) {
+                    float qv[8];
+                    load_q(i, qv);
+                    if (a.c_f32) {
+    #pragma unroll
+                        for (int j = 0; j < 8; ++j) {
+                            const f32x4 c0 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row_of(j) + i);
+                            const f32x4 c1 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row_of(j) + i + 4);
+    #pragma unroll
+                            for (int e = 0; e < 8; ++e) {
+                                const float df = qv[e] - (e < 4 ? c0[e & 3] : c1[e & 3]);
+                                acc[j] = __builtin_fmaf(df, df, acc[j]);
+                            }
                         }
-                    }
-                } else {
-                    uint4 cb[8];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) cb[j] = *reinterpret_cast<const uint4 *>(a.c_rows + row_of(j) + i);
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const uint32_t wv[4] = {cb[j].x, cb[j].y, cb[j].z, cb[j].w};
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const float d0 = qv[2 * e] - __uint_as_float(wv[e] << 16);
-                            acc[j] = __builtin_fmaf(d0, d0, acc[j]);
-                            const float d1 = qv[2 * e + 1] - __uint_as_float(wv[e] & 0xffff0000u);
-                            acc[j] = __builtin_fmaf(d1, d1, acc[j]);
+                    } else {
+                        uint4 cb[8];
+    #pragma unroll
+                        for (int j = 0; j < 8; ++j) cb[j] = *reinterpret_cast<const uint4 *>(a.c_rows + row_of(j) + i);
+    #pragma unroll
+                        for (int j = 0; j < 8; ++j) {
+                            const uint32_t wv[4] = {cb[j].x, cb[j].y, cb[j].z, cb[j].w};
+    #pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const float d0 = qv[2 * e] - __uint_as_float(wv[e] << 16);
+                                acc[j] = __builtin_fmaf(d0, d0, acc[j]);
+                                const float d1 = qv[2 * e + 1] - __uint_as_float(wv[e] & 0xffff0000u);
+                                acc[j] = __builtin_fmaf(d1, d1, acc[j]);
+                            }
                         }
                     }
                 }
-            }
-            // transposed reduction: after the steps over lane bits 5, 4 and 3 a lane holds the partial sum of
-            // row 4 b5 + 2 b4 + b3, the rest is a butterfly
-            float s4[4], s2[2], s1;
+            } else if (a.c_f32) {
+                // Rows of another length: rescore_wave's order, chain l of 64 takes elements l, l + 64, .., so that a
+                // distance does not depend on the kernel that formed it.  A chain per lane; four steps' loads of all
+                // eight rows in flight (whole look-ups, 20,011 x 517, 1,537 queries, k = 20: 242 us with eight elements per lane, 189 so).
+                auto steps = [&](int64_t i, auto count) {
+                    constexpr int U = decltype(count)::value;
+                    float qv[U], cv[8][U];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const bool hi = lane & 32;
-                s4[j] = (hi ? acc[4 + j] : acc[j]) + __shfl_xor(hi ? acc[j] : acc[4 + j], 32, 64);
-            }
+                    for (int u = 0; u < U; ++u) {
+                        qv[u] = qrow[i + u * 64];
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const bool hi = lane & 16;
-                s2[j] = (hi ? s4[2 + j] : s4[j]) + __shfl_xor(hi ? s4[j] : s4[2 + j], 16, 64);
-            }
-            {
-                const bool hi = lane & 8;
-                s1 = (hi ? s2[1] : s2[0]) + __shfl_xor(hi ? s2[0] : s2[1], 8, 64);
-            }
+                        for (int j = 0; j < 8; ++j) cv[j][u] = a.c_f32[row_of(j) + i + u * 64];
+                    }
 #pragma unroll
-            for (int off = 4; off >= 1; off >>= 1) s1 += __shfl_xor(s1, off, 64);
+                    for (int u = 0; u < U; ++u)
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) {
+                            const float df = qv[u] - cv[j][u];
+                            acc[j] = __builtin_fmaf(df, df, acc[j]);
+                        }
+                };
+                int64_t i = lane;
+                for (; i + 3 * 64 < a.d; i += 4 * 64) steps(i, std::integral_constant<int, 4>{});
+                for (; i < a.d; i += 64) steps(i, std::integral_constant<int, 1>{});
+            }
+            float s1;
+            if (whole || a.c_f32) {   // uniform
+                // transposed reduction: after the steps over lane bits 5, 4 and 3 a lane holds the partial sum of
+                // row 4 b5 + 2 b4 + b3, the rest is a butterfly
+                float s4[4], s2[2];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const bool hi = lane & 32;
+                    s4[j] = (hi ? acc[4 + j] : acc[j]) + __shfl_xor(hi ? acc[j] : acc[4 + j], 32, 64);
+                }
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const bool hi = lane & 16;
+                    s2[j] = (hi ? s4[2 + j] : s4[j]) + __shfl_xor(hi ? s4[j] : s4[2 + j], 16, 64);
+                }
+                {
+                    const bool hi = lane & 8;
+                    s1 = (hi ? s2[1] : s2[0]) + __shfl_xor(hi ? s2[0] : s2[1], 8, 64);
+                }
+#pragma unroll
+                for (int off = 4; off >= 1; off >>= 1) s1 += __shfl_xor(s1, off, 64);
+            } else {
+                // The same order on bf16 rows: half a wave per row, chains 2 p and 2 p + 1 in lane p of the half, so that a
+                // lane's load is 4 bytes (50,000 x 517, 4,096 queries: 363 us with eight elements per lane, 708 with a chain per lane
+                // and 2-byte loads, 350 so).  Lane bit 5 and jp
+                // name the row; elements past d are zeros on both sides and leave a chain as it is.
+                const int p = lane & 31, hf = lane >> 5;
+                const uint32_t *row[4];
+#pragma unroll
+                for (int jp = 0; jp < 4; ++jp) {
+                    const int e = e0 + jp + hf * 16;
+                    row[jp] = reinterpret_cast<const uint32_t *>(a.c_rows + (int64_t)(e < a.n ? e : a.n - 1) * a.d_pad) + p;
+                }
+                float ch[4][2];   // [jp][chain of the lane]
+#pragma unroll
+                for (int jp = 0; jp < 4; ++jp) ch[jp][0] = ch[jp][1] = 0.f;
+                auto steps = [&](int64_t i0, auto count) {   // elements [i0, i0 + 64 U), i0 + 64 U <= d_pad
+                    constexpr int U = decltype(count)::value;
+                    float qv[U][2];
+                    uint32_t cv[4][U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int64_t i = i0 + u * 64 + 2 * p;
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) qv[u][h] = i + h < a.d ? qrow[i + h] : 0.f;
+#pragma unroll
+                        for (int jp = 0; jp < 4; ++jp) cv[jp][u] = row[jp][(i0 >> 1) + u * 32];
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+#pragma unroll
+                        for (int jp = 0; jp < 4; ++jp) {
+                            const float d0 = qv[u][0] - __uint_as_float(cv[jp][u] << 16);
+                            ch[jp][0] = __builtin_fmaf(d0, d0, ch[jp][0]);
+                            const float d1 = qv[u][1] - __uint_as_float(cv[jp][u] & 0xffff0000u);
+                            ch[jp][1] = __builtin_fmaf(d1, d1, ch[jp][1]);
+                        }
+                };
+                int64_t i0 = 0;
+                for (; i0 + 4 * 64 <= a.d_pad; i0 += 4 * 64) steps(i0, std::integral_constant<int, 4>{});
+                for (; i0 < a.d_pad; i0 += 64) steps(i0, std::integral_constant<int, 1>{});
+                // the butterfly over chains 32, 16, 8, 4, 2 and 1 apart: lanes 16, 8, 4, 2 and 1 apart, then the
+                // lane's two chains; transposed over lane bits 4 and 3 (jp) and 2 (the chain)
+                float t4[2][2], t2[2];
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const bool hi = lane & 16;
+                        t4[j][h] = (hi ? ch[2 + j][h] : ch[j][h]) + __shfl_xor(hi ? ch[j][h] : ch[2 + j][h], 16, 64);
+                    }
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const bool hi = lane & 8;
+                    t2[h] = (hi ? t4[1][h] : t4[0][h]) + __shfl_xor(hi ? t4[0][h] : t4[1][h], 8, 64);
+                }
+                {
+                    const bool hi = lane & 4;
+                    s1 = (hi ? t2[1] : t2[0]) + __shfl_xor(hi ? t2[0] : t2[1], 4, 64);
+                }
+                s1 += __shfl_xor(s1, 2, 64);
+                s1 += __shfl_xor(s1, 1, 64);
+                s1 += __shfl_xor(s1, 4, 64);
+            }
             // lane >> 3 = 4 b5 + 2 b4 + b3: the row; the block's nearest entry is the certificate's sample
             const int e = e0 + ((lane >> 3) & 3) + (lane >> 5) * 16;
             uint64_t x = e < a.n ? ((uint64_t)ordered_bits(s1) << 32) | (uint32_t)e : kSentinel;

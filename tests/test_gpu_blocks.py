@@ -102,3 +102,31 @@ def test_entries_whose_norm_overflows(dtype):
     np.testing.assert_allclose(got["dist"][:, :5], dist.sort(dim=1).values.numpy(), rtol=1e-5)
     assert np.array_equal(got["idx"][:, 5:], np.broadcast_to(np.arange(5), (b, 5)))
     assert np.isposinf(got["dist"][:, 5:]).all()
+
+@pytest.mark.parametrize("n,d,dtype", [
+    (3000, 512, torch.bfloat16),
+    (3000, 517, torch.float32),
+    (3000, 517, torch.bfloat16),
+    (3000, 100, torch.bfloat16),     # a multiple of 4 only
+    (2500, 20, torch.float32),
+    (20000, 1030, torch.float32),
+    (20000, 2053, torch.bfloat16),
+])
+def test_distances_do_not_depend_on_the_batch(n, d, dtype):
+    """The same queries in one batch (block minima), in batches of 100 and of 16 (other finishing kernels):
+    the same distances bit for bit, which is also what the exact scan of an unconfirmed query gives."""
+    b, k = 300, 10
+    L, q = _inputs(n, d, b, k, dtype, 5 + n + d)
+    fc = binding.FreezeCache(1)
+    try:
+        fc.build_layer(0, L.entries.cuda(), L.labels.cuda(), 10)
+        q = q.cuda()
+        whole = fc.lookup(0, q, k, 8)
+        for step in (100, 16):
+            for i in range(0, b, step):
+                part = fc.lookup(0, q[i:i + step].contiguous(), k, 8)
+                torch.cuda.synchronize()
+                for key in ("idx", "dist"):
+                    assert torch.equal(part[key], whole[key][i:i + step]), (key, step, i)
+    finally:
+        fc.close()
