@@ -153,9 +153,9 @@ int freeze_lookup(freeze_ctx *ctx, int layer, const float *queries, int64_t b, i
  * scratch than the buffer holds, a smaller one is taken), except that the workspace is a buffer of
  * FREEZE_STATIC_SCRATCH_BYTES bytes that lives inside the library's device code (every GPU the
  * library runs on holds one until the process ends).  The call allocates nothing, on the
- * device or through any library.  A look-up whose freeze_lookup_workspace_bytes() exceeds
- * FREEZE_STATIC_SCRATCH_BYTES is refused with FREEZE_ESCRATCH before anything is enqueued
- * (32 MiB covers e.g. 16 queries against 1,000,000 x 512 entries, or 256 queries against
+ * device or through any library.  A look-up that no decomposition fits into
+ * FREEZE_STATIC_SCRATCH_BYTES is refused with FREEZE_ESCRATCH before anything is enqueued; one whose
+ * freeze_lookup_workspace_bytes() is at most that size never is (32 MiB covers e.g. 16 queries against 1,000,000 x 512 entries, or 256 queries against
  * 2,000 x 512).  All calls on one GPU share that GPU's buffer, whatever context or stream they
  * use: calls that overlap in time on one GPU race; order them on one stream.  The buffer keeps
  * the last call's contents; nothing in it needs to be zero when a call starts.

@@ -215,7 +215,7 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
         else if (out->blocks)
             out->plan = plan_block(b, L.n, r, ctx->num_cus, L.d_pad);
         else
-            out->plan = plan_dist(b, L.n, r, ctx->num_cus, out->keys, L.d_pad);
+            out->plan = plan_dist(b, L.n, r, ctx->num_cus, out->keys, small_ws ? 0 : L.d_pad);   // depth 0: no cut tiles, no slots
         out->ws_bytes = align_up((size_t)out->plan.b_pad * L.d_pad * 2);
         if (out->keys)
             out->ws_bytes += keys_finish_workspace_bytes(out->plan.b_pad, L.n_pad, r, kAlign) +
