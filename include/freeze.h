@@ -103,7 +103,12 @@ int freeze_cache_build(freeze_ctx *ctx, int layer, const void *entries, int entr
  */
 int freeze_set_centring(freeze_ctx *ctx, int mode);
 
-/* Bytes of workspace freeze_lookup needs for a batch of b queries. 0 on invalid arguments. */
+/* Bytes of workspace with which freeze_lookup runs a batch of b queries at full speed. 0 on invalid
+ * arguments.  The keys or block minima of a batch (4,096 queries against 300,000 x 512 entries: 0.6 GiB; minima take
+ * 2 GiB at most) and the accumulators of tiles that several workgroups share lie in it, and a smaller batch
+ * may ask for more than a larger one (50,000 x 8,192: 1,024 queries 546 MiB, 10,000 queries 171 MiB).  The look-up takes a smaller workspace too as long as a slower
+ * decomposition of the same work fits it (candidate lists, tiles of one workgroup each; the results are the
+ * same), and else returns FREEZE_EWORKSPACE. */
 size_t freeze_lookup_workspace_bytes(const freeze_ctx *ctx, int layer, int64_t b, int k, int rescore_r);
 
 /*
@@ -136,7 +141,7 @@ size_t freeze_lookup_workspace_bytes(const freeze_ctx *ctx, int layer, int64_t b
  *   out_nbr_idx    [b, k] int32  entry indices, nearest first.
  *   out_nbr_dist   [b, k] fp32   squared distances, computed as sum (q_i - c_i)^2
  *                  in fp32 (exactly 0 for an entry identical to the query).
- *   workspace      >= freeze_lookup_workspace_bytes() bytes, 256-byte aligned;
+ *   workspace      freeze_lookup_workspace_bytes() bytes (less: see there), 256-byte aligned;
  *                  scratch only, contents undefined afterwards.
  * b == 0 is a no-op (the data pointers may then be NULL).  Calls that share a workspace must
  * be ordered on one stream.
@@ -165,7 +170,8 @@ int freeze_lookup_static(freeze_ctx *ctx, int layer, const float *queries, int64
                          int vote_threshold, int rescore_r, int32_t *out_labels, uint8_t *out_hit,
                          int32_t *out_votes, int32_t *out_nbr_idx, float *out_nbr_dist, void *stream);
 
-/* Bytes of workspace freeze_lookup_cascade needs. `layers` is a host array. 0 on invalid arguments. */
+/* Bytes of workspace with which freeze_lookup_cascade runs at full speed (a smaller one is taken as by
+ * freeze_lookup). `layers` is a host array. 0 on invalid arguments. */
 size_t freeze_cascade_workspace_bytes(const freeze_ctx *ctx, int num_layers, const int *layers, int64_t b,
                                       int k, int rescore_r);
 
@@ -249,7 +255,8 @@ int freeze_compute_thresholds(freeze_ctx *ctx, int num_layers, const int *layers
  *                 num_classes <= 8192.
  *   init_centers  [num_centers, d] fp32; 1 <= num_centers <= n.
  *   storage       >= freeze_kmeans_storage_bytes() bytes, 256-byte aligned; must outlive the
- *                 look-ups on this layer.   workspace  >= freeze_kmeans_workspace_bytes().
+ *                 look-ups on this layer.   workspace  freeze_kmeans_workspace_bytes() (a smaller one
+ *                 is taken as by freeze_lookup).
  * On such a layer freeze_lookup (k = 1) returns the nearest centre and its majority label, and
  * the confidence entry points (freeze_lookup_confidence, freeze_lookup_cascade_confidence,
  * freeze_compute_thresholds; k must be 1) use the paper's k-means confidence: the majority
@@ -276,7 +283,8 @@ int freeze_kmeans_read(freeze_ctx *ctx, int layer, float *out_centers, int32_t *
  *   storage  >= freeze_projection_storage_bytes() bytes, 256-byte aligned, must outlive the
  *            calls of freeze_project on the slot; build workspace: >= 256 + 4 m bytes.
  *   x        [b, d] fp32, 16-byte aligned;  out [b, m] fp32, 16-byte aligned.
- *   workspace of freeze_project: >= freeze_project_workspace_bytes() bytes.
+ *   workspace of freeze_project: freeze_project_workspace_bytes() bytes; a smaller one is taken while it
+ *            holds the bf16 copy of x and, for larger batches, the padded outputs.
  * b == 0 is a no-op.
  */
 size_t freeze_projection_storage_bytes(int64_t m, int64_t d, int weights_dtype);

@@ -133,7 +133,7 @@ int lists_per_query(const DistPlan &pl, bool device_count)
 // 2,048: 834, 914.  300 queries x 50,000 x 3,072: 271, 208.
 bool block_route(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, int r)
 {
-    // 1 GiB of minima at most; longer rows than measured lose more to the re-scoring (259 x 13,556 x 8,192, k = 20:
+    // 1 GiB of minima at most (2 with the padding of the last query tile); longer rows than measured lose more to the re-scoring (259 x 13,556 x 8,192, k = 20:
     // 345 us with lists, 415 with blocks)
     if (b * L.n_pad > (int64_t)1 << 31 || L.d_pad > 3072) return false;
     // (600 x 250,000 x 3,000: 1,011 us with lists, 1,091 with blocks)
@@ -152,9 +152,15 @@ bool block_route(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, i
 // 52 -> 36 us, 256 x 3,000 x 4,096: 127 -> 81 us).
 constexpr int kStreamRows = 128;
 
-// small_ws: choose the decomposition with the smallest workspace (freeze_lookup_static)
+// Which decomposition of the work a look-up is planned with; the result does not depend on it.
+enum class Decomp {
+    best,    // the fastest
+    small,   // whole tiles only, no accumulator slots, no block minima: where the workspace does not hold the fastest
+    plain    // the 256-query kernel alone, as `small` (only its size is asked for: see asked_bytes)
+};
+
 bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, int rescore_r, bool cascade,
-                  LookupShape *out, bool small_ws = false)
+                  LookupShape *out, Decomp how = Decomp::best)
 {
     if (b < 0 || b > (int64_t)1 << 30 || k < 1 || k > L.n) return false;
     if (k > FREEZE_MAX_K && !(k == L.n && k <= FREEZE_MAX_RESCORE)) return false;
@@ -189,11 +195,11 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
         // moderate size: every workgroup of the fused kernel gets a few tiles only and spends most of
         // its time filling its empty candidate lists key by key, so the keys go out here too
         // (measured cross-over: about 2^26 keys; 256 x 2,000: 129 -> 69 us, 200 x 50,000 x 512: 209 -> 80 us).
-        out->keys = b <= (cascade ? kStreamRows : 256) && (b * 20 <= L.d_pad || b * L.n_pad <= ((int64_t)1 << 26)) &&
+        out->keys = b <= (cascade ? kStreamRows : 256) && !(cascade && how != Decomp::best) && (b * 20 <= L.d_pad || b * L.n_pad <= ((int64_t)1 << 26)) &&
                     keys_finish_supported(L.n_pad, r);
         // (batches of 129 to 256 queries on large caches: the keys' traffic costs more than the blocks' rows;
         // 160 x 300,000 x 512: 183 against 136 us)
-        if ((!out->keys || (b > kStreamRows && b * L.n_pad > (int64_t)1 << 25)) && !small_ws && block_route(ctx, L, b, k, r)) {
+        if ((!out->keys || (b > kStreamRows && b * L.n_pad > (int64_t)1 << 25)) && how == Decomp::best && block_route(ctx, L, b, k, r)) {
             out->keys = false;
             out->blocks = true;
         }
@@ -204,18 +210,18 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
         // (20,011 x 4,104: 464 -> 476).  Block minima give way where their whole tiles leave half the chip idle
         // (300 x 5,000 x 2,048: 94 -> 65 us; 1,000 x 2,000 x 2,048 goes the other way: 110, 136).
         const int64_t tiles = ((b + 255) / 256) * (L.n_pad / kTileN);
-        if (!cascade && !small_ws && b > 256 && b <= 1024 && b * L.n_pad <= ((int64_t)1 << 26) && keys_finish_supported(L.n_pad, r) &&
+        if (!cascade && how == Decomp::best && b > 256 && b <= 1024 && b * L.n_pad <= ((int64_t)1 << 26) && keys_finish_supported(L.n_pad, r) &&
             (!out->blocks || (2 * tiles <= ctx->num_cus && L.d_pad >= 1024 && b <= 640))) {
             out->keys = true;
             out->blocks = false;
         }
         const int64_t k_steps = (L.n_pad / kTileN) * (L.d_pad / kKB);   // per query tile
-        if (out->keys && (b <= kStreamRows || 2 * k_steps < 16 * (int64_t)ctx->num_cus))
-            out->plan = plan_stream(b, L.n, r, ctx->num_cus, L.d_pad, small_ws);
+        if (out->keys && how != Decomp::plain && (b <= kStreamRows || 2 * k_steps < 16 * (int64_t)ctx->num_cus))
+            out->plan = plan_stream(b, L.n, r, ctx->num_cus, L.d_pad, how == Decomp::small);
         else if (out->blocks)
             out->plan = plan_block(b, L.n, r, ctx->num_cus, L.d_pad);
         else
-            out->plan = plan_dist(b, L.n, r, ctx->num_cus, out->keys, small_ws ? 0 : L.d_pad);   // depth 0: no cut tiles, no slots
+            out->plan = plan_dist(b, L.n, r, ctx->num_cus, out->keys, how == Decomp::best ? L.d_pad : 0);   // depth 0: no cut tiles, no slots
         out->ws_bytes = align_up((size_t)out->plan.b_pad * L.d_pad * 2);
         if (out->keys)
             out->ws_bytes += keys_finish_workspace_bytes(out->plan.b_pad, L.n_pad, r, kAlign) +
@@ -226,6 +232,28 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
             out->ws_bytes += align_up((size_t)out->plan.b_pad * lists_per_query(out->plan, cascade) * r * 8);
         out->ws_bytes += scan_bytes;
     }
+    return true;
+}
+
+// The fastest decomposition whose workspace is at most `room` bytes.  False: there is none (or bad arguments).
+bool fit_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, int rescore_r, bool cascade, size_t room,
+               LookupShape *out)
+{
+    return (lookup_shape(ctx, L, b, k, rescore_r, cascade, out) && out->ws_bytes <= room) ||
+           (lookup_shape(ctx, L, b, k, rescore_r, cascade, out, Decomp::small) && out->ws_bytes <= room);
+}
+
+// Workspace the library asks for: what the fastest decomposition takes, and at least what the 256-query
+// kernel alone would.  The faster kernels take less for some batches than `small` does for a smaller one (62
+// queries on 124 entries: 0.4 MB, five: 0.46 MB), and a buffer sized for the full batch has to go on serving the
+// last, partial one.
+bool asked_bytes(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, int rescore_r, bool cascade, size_t *bytes)
+{
+    LookupShape best, plain;
+    if (!lookup_shape(ctx, L, b, k, rescore_r, cascade, &best) ||
+        !lookup_shape(ctx, L, b, k, rescore_r, cascade, &plain, Decomp::plain))
+        return false;
+    *bytes = best.ws_bytes > plain.ws_bytes ? best.ws_bytes : plain.ws_bytes;
     return true;
 }
 
@@ -439,13 +467,21 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
     return FREEZE_OK;
 }
 
-struct CascadeLayout {
-    size_t lookup_ws;   // largest per-layer look-up workspace
+// Workspace of a call that runs look-ups and keeps buffers of its own.
+struct CallLayout {
+    size_t lookup_ws;   // asked for the look-ups (they share it)
+    size_t rest;        // bytes of everything behind it
     size_t bytes;
+    // what a buffer of `have` bytes leaves for the look-ups (0: not even the rest fits)
+    size_t room(size_t have) const
+    {
+        if (have < rest) return 0;
+        return have >= bytes ? lookup_ws : (have - rest) / kAlign * kAlign;
+    }
 };
 
 bool cascade_layout(const freeze_ctx *ctx, int num_layers, const int *layers, int64_t b, int k, int rescore_r,
-                    CascadeLayout *out, int *err)
+                    CallLayout *out, int *err)
 {
     if (!ctx || !layers || num_layers < 1 || num_layers > 1024) {
         *err = FREEZE_EINVAL;
@@ -457,19 +493,19 @@ bool cascade_layout(const freeze_ctx *ctx, int num_layers, const int *layers, in
         if (!L) return false;
         // a layer is looked up either with the live count on the device (later layers of a cascade)
         // or with all b requests (its first layer; every layer while thresholds are calibrated)
-        LookupShape sh, sh_all;
-        if (!lookup_shape(ctx, *L, b, k, rescore_r, true, &sh) || !lookup_shape(ctx, *L, b, k, rescore_r, false, &sh_all)) {
+        size_t live, all;
+        if (!asked_bytes(ctx, *L, b, k, rescore_r, true, &live) || !asked_bytes(ctx, *L, b, k, rescore_r, false, &all)) {
             *err = FREEZE_EINVAL;
             return false;
         }
-        if (sh.ws_bytes > mx) mx = sh.ws_bytes;
-        if (sh_all.ws_bytes > mx) mx = sh_all.ws_bytes;
+        if (live > mx) mx = live;
+        if (all > mx) mx = all;
     }
     out->lookup_ws = mx;
     const size_t bb = (size_t)(b > 0 ? b : 1);
     // per-layer outputs in compact order + two miss lists + two counters
-    out->bytes = mx + 3 * align_up(bb * 4) + align_up(bb) + 2 * align_up(bb * k * 4) + 2 * align_up(bb * 4) +
-                 2 * align_up(4);
+    out->rest = 3 * align_up(bb * 4) + align_up(bb) + 2 * align_up(bb * k * 4) + 2 * align_up(bb * 4) + 2 * align_up(4);
+    out->bytes = mx + out->rest;
     *err = FREEZE_OK;
     return true;
 }
@@ -488,18 +524,18 @@ int confidence_rule_for(const freeze_ctx *ctx, int layer, int k, int *kind)
 
 int lookup_checked(freeze_ctx *ctx, int layer, const float *queries, int64_t b, int k, const HitRule &rule,
                    int rescore_r, int32_t *out_labels, uint8_t *out_hit, int32_t *out_votes, int32_t *out_nbr_idx,
-                   float *out_nbr_dist, void *workspace, size_t workspace_bytes, void *stream, bool small_ws = false)
+                   float *out_nbr_dist, void *workspace, size_t workspace_bytes, void *stream)
 {
     int err;
     const LayerCache *L = get_layer(ctx, layer, &err);
     if (!L) return err;
     LookupShape sh;
-    if (!lookup_shape(ctx, *L, b, k, rescore_r, false, &sh, small_ws)) return FREEZE_EINVAL;
+    if (!lookup_shape(ctx, *L, b, k, rescore_r, false, &sh)) return FREEZE_EINVAL;
     if (b == 0) return FREEZE_OK;   // nothing to look up: data pointers may be null
     if (!queries || !out_labels || !out_hit || !out_votes || !out_nbr_idx || !out_nbr_dist || !workspace)
         return FREEZE_EINVAL;
     if ((reinterpret_cast<uintptr_t>(queries) % 16) != 0) return FREEZE_EINVAL;
-    if (workspace_bytes < sh.ws_bytes || (reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0)
+    if ((reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0 || !fit_shape(ctx, *L, b, k, rescore_r, false, workspace_bytes, &sh))
         return FREEZE_EWORKSPACE;
     return enqueue_lookup(ctx, *L, sh, queries, nullptr, nullptr, b, k, rule, out_labels, out_hit, out_votes,
                           out_nbr_idx, out_nbr_dist, workspace, static_cast<hipStream_t>(stream));
@@ -512,7 +548,7 @@ int cascade_checked(freeze_ctx *ctx, int num_layers, const int *layers, const fl
                     int32_t *out_exit_layer, int64_t *out_hits_per_layer, void *workspace, size_t workspace_bytes,
                     void *stream)
 {
-    CascadeLayout cl;
+    CallLayout cl;
     int err;
     if (!cascade_layout(ctx, num_layers, layers, b, k, rescore_r, &cl, &err)) return err;
     if (!queries_per_layer || !out_hits_per_layer || !workspace) return FREEZE_EINVAL;
@@ -521,12 +557,18 @@ int cascade_checked(freeze_ctx *ctx, int num_layers, const int *layers, const fl
         if (b > 0 && (!queries_per_layer[l] || (reinterpret_cast<uintptr_t>(queries_per_layer[l]) % 16) != 0))
             return FREEZE_EINVAL;
     }
-    if (workspace_bytes < cl.bytes || (reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0)
-        return FREEZE_EWORKSPACE;
+    // Every request enters the first layer: its look-up is planned like a single-layer one, with
+    // the count known on the host (any route, any decomposition); the later layers are sized for
+    // b and read the live count on the device.
+    const size_t room = cl.room(workspace_bytes);
+    LookupShape sh;
+    if ((reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0) return FREEZE_EWORKSPACE;
+    for (int l = 0; l < num_layers; ++l)
+        if (!fit_shape(ctx, ctx->layers[layers[l]], b, k, rescore_r, l != 0, room, &sh)) return FREEZE_EWORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
 
     Carver ws(workspace);
-    unsigned char *lookup_ws = ws.take<unsigned char>(cl.lookup_ws);
+    unsigned char *lookup_ws = ws.take<unsigned char>(room);
     const size_t bb = (size_t)(b > 0 ? b : 1);
     int32_t *t_labels = ws.take<int32_t>(bb);
     int32_t *t_votes = ws.take<int32_t>(bb);
@@ -551,11 +593,7 @@ int cascade_checked(freeze_ctx *ctx, int num_layers, const int *layers, const fl
     const int32_t *count = nullptr;
     for (int l = 0; l < num_layers; ++l) {
         const LayerCache &L = ctx->layers[layers[l]];
-        // Every request enters the first layer: its look-up is planned like a single-layer one, with
-        // the count known on the host (any route, any decomposition); the later layers are sized for
-        // b and read the live count on the device.
-        LookupShape sh;
-        lookup_shape(ctx, L, b, k, rescore_r, l != 0, &sh);
+        fit_shape(ctx, L, b, k, rescore_r, l != 0, room, &sh);
         HitRule rule = rules[(size_t)l];
         rule.out_conf = t_conf;
         int rc = enqueue_lookup(ctx, L, sh, queries_per_layer[l], sel, count, b, k, rule, t_labels, t_hit, t_votes,
@@ -573,26 +611,28 @@ int cascade_checked(freeze_ctx *ctx, int num_layers, const int *layers, const fl
     return FREEZE_OK;
 }
 
-struct KmeansLayout {
-    size_t lookup_ws;
-    size_t bytes;
-};
-// workspace: two centre buffers, dummy labels, the look-up's outputs for n points and its workspace
-bool kmeans_layout(const freeze_ctx *ctx, int64_t n, int64_t d, int64_t kc, KmeansLayout *out)
+// the centres as a cache, as far as the plan of a look-up depends on it
+bool centres_shape(int64_t kc, int64_t d, LayerCache *out)
 {
     CacheLayout cl;
-    if (!ctx || n < 1 || n > (int64_t)1 << 30 || kc < 1 || kc > n || !cache_layout(kc, d, FREEZE_F32, &cl)) return false;
-    LayerCache tmp;   // shape of the centres as a cache
-    tmp.n = kc;
-    tmp.d = d;
-    tmp.n_pad = cl.n_pad;
-    tmp.d_pad = cl.d_pad;
-    LookupShape sh;
-    if (!lookup_shape(ctx, tmp, n, 1, 0, false, &sh)) return false;
-    out->lookup_ws = sh.ws_bytes;
-    out->bytes = sh.ws_bytes + 2 * align_up((size_t)kc * d * 4) + align_up((size_t)kc * 4) + 3 * align_up((size_t)n * 4) +
+    if (!cache_layout(kc, d, FREEZE_F32, &cl)) return false;
+    out->n = kc;
+    out->d = d;
+    out->n_pad = cl.n_pad;
+    out->d_pad = cl.d_pad;
+    out->entries_dtype = FREEZE_F32;
+    return true;
+}
+// workspace: two centre buffers, dummy labels, the look-up's outputs for n points and its workspace
+bool kmeans_layout(const freeze_ctx *ctx, int64_t n, int64_t d, int64_t kc, CallLayout *out)
+{
+    LayerCache centres;
+    if (!ctx || n < 1 || n > (int64_t)1 << 30 || kc < 1 || kc > n || !centres_shape(kc, d, &centres)) return false;
+    if (!asked_bytes(ctx, centres, n, 1, 0, false, &out->lookup_ws)) return false;
+    out->rest = 2 * align_up((size_t)kc * d * 4) + align_up((size_t)kc * 4) + 3 * align_up((size_t)n * 4) +
                  align_up((size_t)n) + 2 * align_up((size_t)n * 4) +
                  align_up((size_t)kc * 4) + align_up((size_t)(kc + 1) * 4) + align_up((size_t)n * 4);   // grouping by centre
+    out->bytes = out->lookup_ws + out->rest;
     return true;
 }
 
@@ -616,10 +656,10 @@ const LayerCache *get_projection(const freeze_ctx *ctx, int slot, int *err)
 // Up to 256 inputs, and up to 512 where their 256 x 256 tiles would go without stream-K: the streaming kernel, which
 // cuts the few output tiles along the depth for small input tiles too (8,192 -> 1,024 outputs: 1 input 155 -> 20 us,
 // 128 inputs 155 -> 39 us; 384 x 16,384, where stream-K applies: 124 us against 133).  Else a workgroup per (tile
-// of 256 inputs, tile of 256 outputs), whole depth or stream-K.
-DistPlan projection_plan(const freeze_ctx *ctx, const LayerCache &P, int64_t b)
+// of 256 inputs, tile of 256 outputs), whole depth or stream-K.  whole: no cut tiles (no accumulator slots).
+DistPlan projection_plan(const freeze_ctx *ctx, const LayerCache &P, int64_t b, bool whole)
 {
-    if (b <= 256) return plan_stream(b > 0 ? b : 1, P.n, 1, ctx->num_cus, P.d_pad, false);
+    if (b <= 256) return plan_stream(b > 0 ? b : 1, P.n, 1, ctx->num_cus, P.d_pad, whole);
     DistPlan pl{};
     pl.variant = 3;
     pl.bm = 256;
@@ -632,9 +672,16 @@ DistPlan projection_plan(const freeze_ctx *ctx, const LayerCache &P, int64_t b)
     pl.grid_units = pl.m_tiles * pl.n_tiles;
     pl.num_cus = ctx->num_cus;
     pl.b_pad = (int64_t)pl.m_tiles * 256;
-    plan_stream_k(pl, ctx->num_cus, P.d_pad, 0.0);
-    if (b <= 512 && pl.sk_wgs == 0) return plan_stream(b, P.n, 1, ctx->num_cus, P.d_pad, false);
+    if (!whole) plan_stream_k(pl, ctx->num_cus, P.d_pad, 0.0);
+    if (b <= 512 && pl.sk_wgs == 0) return plan_stream(b, P.n, 1, ctx->num_cus, P.d_pad, whole);
     return pl;
+}
+
+// bf16 copy of the inputs, whole rows of outputs for the 256-input tiles, accumulator slots
+size_t projection_bytes(const LayerCache &P, int64_t b, const DistPlan &pl)
+{
+    const size_t rows = pl.variant == 4 ? 0 : align_up((size_t)(b > 0 ? b : 1) * P.n_pad * 4);
+    return align_up((size_t)pl.b_pad * P.d_pad * 2) + rows + align_up(dist_partial_bytes(pl));
 }
 
 }  // namespace
@@ -746,9 +793,9 @@ size_t freeze_lookup_workspace_bytes(const freeze_ctx *ctx, int layer, int64_t b
 {
     int err;
     const LayerCache *L = get_layer(ctx, layer, &err);
-    LookupShape sh;
-    if (!L || !lookup_shape(ctx, *L, b, k, rescore_r, false, &sh)) return 0;
-    return sh.ws_bytes;
+    size_t bytes;
+    if (!L || !asked_bytes(ctx, *L, b, k, rescore_r, false, &bytes)) return 0;
+    return bytes;
 }
 
 int freeze_lookup(freeze_ctx *ctx, int layer, const float *queries, int64_t b, int k, int vote_threshold,
@@ -771,17 +818,14 @@ int freeze_lookup_static(freeze_ctx *ctx, int layer, const float *queries, int64
     if (!L) return err;
     LookupShape sh;
     if (!lookup_shape(ctx, *L, b, k, rescore_r, false, &sh)) return FREEZE_EINVAL;
-    // a decomposition with accumulator slots that do not fit gives way to one without
-    const bool small_ws = sh.ws_bytes > (size_t)FREEZE_STATIC_SCRATCH_BYTES;
-    if (small_ws && !lookup_shape(ctx, *L, b, k, rescore_r, false, &sh, true)) return FREEZE_EINVAL;
-    if (sh.ws_bytes > (size_t)FREEZE_STATIC_SCRATCH_BYTES) return FREEZE_ESCRATCH;
+    if (!fit_shape(ctx, *L, b, k, rescore_r, false, (size_t)FREEZE_STATIC_SCRATCH_BYTES, &sh)) return FREEZE_ESCRATCH;
     if (b == 0) return FREEZE_OK;
     hipError_t herr;
     void *ws = static_scratch_ptr(&herr);
     if (!ws) return FREEZE_EHIP;
     const HitRule rule{0, vote_threshold, 0.f, nullptr};
     return lookup_checked(ctx, layer, queries, b, k, rule, rescore_r, out_labels, out_hit, out_votes, out_nbr_idx,
-                          out_nbr_dist, ws, (size_t)FREEZE_STATIC_SCRATCH_BYTES, stream, small_ws);
+                          out_nbr_dist, ws, (size_t)FREEZE_STATIC_SCRATCH_BYTES, stream);
 }
 
 int freeze_lookup_confidence(freeze_ctx *ctx, int layer, const float *queries, int64_t b, int k, float conf_threshold,
@@ -801,7 +845,7 @@ int freeze_lookup_confidence(freeze_ctx *ctx, int layer, const float *queries, i
 size_t freeze_cascade_workspace_bytes(const freeze_ctx *ctx, int num_layers, const int *layers, int64_t b, int k,
                                       int rescore_r)
 {
-    CascadeLayout cl;
+    CallLayout cl;
     int err;
     return cascade_layout(ctx, num_layers, layers, b, k, rescore_r, &cl, &err) ? cl.bytes : 0;
 }
@@ -844,7 +888,7 @@ int freeze_compute_thresholds(freeze_ctx *ctx, int num_layers, const int *layers
                               const int32_t *model_labels, float *out_thresholds, void *workspace,
                               size_t workspace_bytes, void *stream)
 {
-    CascadeLayout cl;
+    CallLayout cl;
     int err;
     if (!cascade_layout(ctx, num_layers, layers, b, k, rescore_r, &cl, &err)) return err;
     if (!queries_per_layer || !out_thresholds || !workspace) return FREEZE_EINVAL;
@@ -852,12 +896,15 @@ int freeze_compute_thresholds(freeze_ctx *ctx, int num_layers, const int *layers
     for (int l = 0; l < num_layers; ++l)
         if (b > 0 && (!queries_per_layer[l] || (reinterpret_cast<uintptr_t>(queries_per_layer[l]) % 16) != 0))
             return FREEZE_EINVAL;
-    if (workspace_bytes < cl.bytes || (reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0)
-        return FREEZE_EWORKSPACE;
+    const size_t room = cl.room(workspace_bytes);
+    LookupShape sh;
+    if ((reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0) return FREEZE_EWORKSPACE;
+    for (int l = 0; l < num_layers; ++l)
+        if (!fit_shape(ctx, ctx->layers[layers[l]], b, k, rescore_r, false, room, &sh)) return FREEZE_EWORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
 
     Carver ws(workspace);
-    unsigned char *lookup_ws = ws.take<unsigned char>(cl.lookup_ws);
+    unsigned char *lookup_ws = ws.take<unsigned char>(room);
     const size_t bb = (size_t)(b > 0 ? b : 1);
     int32_t *t_labels = ws.take<int32_t>(bb);
     int32_t *t_votes = ws.take<int32_t>(bb);
@@ -871,8 +918,7 @@ int freeze_compute_thresholds(freeze_ctx *ctx, int num_layers, const int *layers
     // every validation item is looked up at every layer (no early exit while calibrating)
     for (int l = 0; l < num_layers; ++l) {
         const LayerCache &L = ctx->layers[layers[l]];
-        LookupShape sh;
-        lookup_shape(ctx, L, b, k, rescore_r, false, &sh);
+        fit_shape(ctx, L, b, k, rescore_r, false, room, &sh);
         int kind = 1;
         if (int rck = confidence_rule_for(ctx, layers[l], k, &kind)) return rck;
         const HitRule rule{kind, 1, 0.f, t_conf};
@@ -894,7 +940,7 @@ size_t freeze_kmeans_storage_bytes(int64_t num_centers, int64_t d)
 
 size_t freeze_kmeans_workspace_bytes(const freeze_ctx *ctx, int64_t n, int64_t d, int64_t num_centers)
 {
-    KmeansLayout kl;
+    CallLayout kl;
     return kmeans_layout(ctx, n, d, num_centers, &kl) ? kl.bytes : 0;
 }
 
@@ -906,17 +952,24 @@ int freeze_kmeans_build(freeze_ctx *ctx, int layer, const float *points, int64_t
         num_classes < 1 || num_classes > 8192)
         return FREEZE_EINVAL;
     if (layer < 0 || layer >= (int)ctx->layers.size()) return FREEZE_ELAYER;
-    KmeansLayout kl;
+    CallLayout kl;
     if (!kmeans_layout(ctx, n, d, num_centers, &kl)) return FREEZE_EINVAL;
     if ((reinterpret_cast<uintptr_t>(points) % 16) != 0) return FREEZE_EINVAL;
     const size_t st_bytes = freeze_kmeans_storage_bytes(num_centers, d);
     if (storage_bytes < st_bytes || (reinterpret_cast<uintptr_t>(storage) % kAlign) != 0) return FREEZE_EWORKSPACE;
-    if (workspace_bytes < kl.bytes || (reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0) return FREEZE_EWORKSPACE;
-    hipStream_t s = static_cast<hipStream_t>(stream);
+    // the points do not change from round to round: their bf16 copy is made once (the shape of
+    // the look-up, and with it the layout of its workspace, is the same in every round)
     const int64_t kc = num_centers;
+    const size_t room = kl.room(workspace_bytes);
+    LayerCache centres;
+    LookupShape sh;
+    centres_shape(kc, d, &centres);
+    if ((reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0 || !fit_shape(ctx, centres, n, 1, 0, false, room, &sh))
+        return FREEZE_EWORKSPACE;
+    hipStream_t s = static_cast<hipStream_t>(stream);
 
     Carver ws(workspace);
-    unsigned char *lookup_ws = ws.take<unsigned char>(kl.lookup_ws);
+    unsigned char *lookup_ws = ws.take<unsigned char>(room);
     float *cen[2] = {ws.take<float>((size_t)kc * d), ws.take<float>((size_t)kc * d)};
     int32_t *zero_labels = ws.take<int32_t>((size_t)kc);
     int32_t *t_labels = ws.take<int32_t>((size_t)n);
@@ -949,10 +1002,6 @@ int freeze_kmeans_build(freeze_ctx *ctx, int layer, const float *points, int64_t
         int rc = cache_build_impl(ctx, layer, cur, FREEZE_F32, kc, d, zero_labels, num_classes, storage, cl.bytes, stream, false);
         if (rc != FREEZE_OK) return rc;
         const LayerCache &L = ctx->layers[layer];
-        LookupShape sh;
-        if (!lookup_shape(ctx, L, n, 1, 0, false, &sh)) return FREEZE_EINVAL;
-        // the points do not change from round to round: their bf16 copy is made once (the shape of
-        // the look-up, and with it the layout of its workspace, is the same in every round)
         rc = enqueue_lookup(ctx, L, sh, points, nullptr, nullptr, n, 1, rule, t_labels, t_hit, t_votes, assign, t_dist,
                             lookup_ws, s, it > 0, grouped && it > 0 ? grp_members : nullptr);
         if (rc != FREEZE_OK) return rc;
@@ -1021,11 +1070,11 @@ size_t freeze_project_workspace_bytes(const freeze_ctx *ctx, int slot, int64_t b
     int err;
     const LayerCache *P = get_projection(ctx, slot, &err);
     if (!P || b < 0 || b > (int64_t)1 << 30) return 0;
-    const DistPlan pl = projection_plan(ctx, *P, b);
-    if (pl.variant == 4) return align_up((size_t)pl.b_pad * P->d_pad * 2) + align_up(dist_partial_bytes(pl));
-    const int64_t b_pad = (b + 255) / 256 * 256 + (b == 0 ? 256 : 0);
-    return align_up((size_t)b_pad * P->d_pad * 2) + align_up((size_t)(b > 0 ? b : 1) * P->n_pad * 4) +
-           align_up(dist_partial_bytes(pl));
+    // at least what the 256-input tiles take whole, which any smaller batch can do with
+    const int64_t b1 = b > 0 ? b : 1, b_pad = (b1 + 255) / 256 * 256;
+    const size_t plain = align_up((size_t)b_pad * P->d_pad * 2) + align_up((size_t)b1 * P->n_pad * 4);
+    const size_t best = projection_bytes(*P, b, projection_plan(ctx, *P, b, false));
+    return best > plain ? best : plain;
 }
 
 int freeze_project(freeze_ctx *ctx, int slot, const float *x, int64_t b, int relu, float *out, void *workspace,
@@ -1039,10 +1088,11 @@ int freeze_project(freeze_ctx *ctx, int slot, const float *x, int64_t b, int rel
     if (!x || !out || !workspace || (reinterpret_cast<uintptr_t>(x) % 16) != 0 ||
         (reinterpret_cast<uintptr_t>(out) % 16) != 0)
         return FREEZE_EINVAL;
-    if (workspace_bytes < freeze_project_workspace_bytes(ctx, slot, b) || (reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0)
+    DistPlan pl = projection_plan(ctx, *P, b, false);
+    if (projection_bytes(*P, b, pl) > workspace_bytes) pl = projection_plan(ctx, *P, b, true);
+    if (projection_bytes(*P, b, pl) > workspace_bytes || (reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0)
         return FREEZE_EWORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const DistPlan pl = projection_plan(ctx, *P, b);
     Carver ws(workspace);
     uint16_t *x_bf = ws.take<uint16_t>((size_t)pl.b_pad * P->d_pad);
     const bool streamed = pl.variant == 4;

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from paper_2002_02645_amd import binding, synth
+from tests.test_gpu_guard_bands import Guarded
 
 pytestmark = pytest.mark.gpu
 
@@ -40,5 +41,122 @@ def test_fixed_buffer_serves_whole_tiles_of_the_batched_kernel(n, d, b, k, dtype
         got = fc.alloc_outputs(b, k)
         binding.freeze_lookup_static(fc.ctx, 0, q, k, thr, 0, got["label"], got["hit"], got["votes"], got["idx"], got["dist"])
         _equal(got, want)
+    finally:
+        fc.close()
+
+
+@pytest.mark.parametrize("n,d,dtype,full,last,k", [
+    (2900, 4104, torch.bfloat16, 1100, 700, 10),   # lists; 700 queries would rather have keys and accumulator slots
+    (2900, 4100, torch.float32, 1100, 300, 20),
+    (124, 23, torch.float32, 62, 5, 45),           # the streaming kernel; five queries are the small-batch kernel's
+    (5000, 260, torch.bfloat16, 4096, 250, 10),    # block minima; 250 queries materialise their keys
+])
+def test_buffer_sized_for_the_full_batch_serves_the_last(n, d, dtype, full, last, k):
+    L, q = _layer(n, d, full, k, dtype, 17 + n)
+    thr = max(1, k - 2)
+    fc = binding.FreezeCache(1)
+    try:
+        fc.build_layer(0, L.entries.cuda(), L.labels.cuda(), 10)
+        ws = Guarded(binding.freeze_lookup_workspace_bytes(fc.ctx, 0, full, k))
+        q = q.cuda()
+        for b in (full, last):
+            part = q[full - b:].clone()      # (a slice need not start on 16 bytes)
+            want = fc.lookup(0, part, k, thr)
+            got = fc.alloc_outputs(b, k)
+            binding.freeze_lookup(fc.ctx, 0, part, k, thr, 0, got["label"], got["hit"], got["votes"], got["idx"], got["dist"],
+                                  ws.payload)
+            _equal(got, want)
+            assert ws.intact()
+    finally:
+        fc.close()
+
+
+@pytest.mark.parametrize("n,d,b,k,r,dtype", [
+    (2900, 4104, 700, 10, 0, torch.bfloat16),    # keys and slots -> lists of 16
+    (2901, 1500, 300, 20, 0, torch.float32),     # ... of 32, ragged depth
+    (3000, 2050, 333, 40, 64, torch.bfloat16),   # ... of 64
+    (20000, 517, 1300, 10, 0, torch.bfloat16),   # block minima -> lists
+    (50000, 2048, 64, 10, 0, torch.bfloat16),    # cut tiles -> whole tiles, 64 queries per tile
+    (36000, 2080, 200, 10, 64, torch.float32),   # ... of the 256-query kernel
+    (300, 40, 1, 1, 0, torch.float32),
+])
+def test_smaller_buffers_give_the_same_result_or_are_refused(n, d, b, k, r, dtype):
+    L, q = _layer(n, d, b, k, dtype, 23 + n)
+    thr = max(1, k - 2)
+    fc = binding.FreezeCache(1)
+    try:
+        fc.build_layer(0, L.entries.cuda(), L.labels.cuda(), 10)
+        q = q.cuda()
+        want = fc.lookup(0, q, k, thr, r)
+        size, served = binding.freeze_lookup_workspace_bytes(fc.ctx, 0, b, k, r), 0
+        while True:
+            ws = Guarded(size)
+            got = fc.alloc_outputs(b, k)
+            for t in got.values():
+                t.fill_(7)
+            try:
+                binding.freeze_lookup(fc.ctx, 0, q, k, thr, r, got["label"], got["hit"], got["votes"], got["idx"], got["dist"],
+                                      ws.payload)
+            except binding.FreezeError as e:
+                assert e.code == binding.FREEZE_EWORKSPACE
+                torch.cuda.synchronize()
+                assert all(bool((t == 7).all()) for t in got.values())    # a refused call writes nothing
+                break
+            _equal(got, want)
+            assert ws.intact()
+            served += 1
+            size -= max(256, size // 6)
+        assert served >= 1
+    finally:
+        fc.close()
+
+
+def test_cascade_and_thresholds_on_a_buffer_sized_for_the_full_batch():
+    wl = synth.scaled(synth.WORKLOADS["c4_cascade_noisy"], n=2600, d_div=8, batch=1100)
+    data = synth.make_workload(wl)
+    nl, k = len(wl.layers), wl.k
+    layers = list(range(nl))
+    fc = binding.FreezeCache(nl)
+    try:
+        for l, L in enumerate(data.layers):
+            fc.build_layer(l, L.entries.cuda(), L.labels.cuda(), L.spec.num_classes)
+        full, last = 1100, 700
+        ws = Guarded(binding.freeze_cascade_workspace_bytes(fc.ctx, layers, full, k))
+        assert binding.freeze_cascade_workspace_bytes(fc.ctx, layers, last, k) > ws.nbytes
+        model = torch.randint(0, 10, (full,), dtype=torch.int32).cuda()
+        for b in (full, last, 20):
+            qs = [q[full - b:].cuda().contiguous() for q in data.queries]
+            want = fc.lookup_cascade(layers, qs, k, [9] * nl)
+            got = {key: torch.empty_like(t) for key, t in want.items()}
+            binding.freeze_lookup_cascade(fc.ctx, layers, qs, k, [9] * nl, 0, got["label"], got["exit_layer"],
+                                          got["hits_per_layer"], ws.payload)
+            _equal(got, want)
+            thr = fc.compute_thresholds(layers, qs, k, model[:b])
+            out = torch.empty_like(thr)
+            binding.freeze_compute_thresholds(fc.ctx, layers, qs, k, 0, model[:b], out, ws.payload)
+            torch.cuda.synchronize()
+            assert torch.equal(out, thr) and ws.intact()
+    finally:
+        fc.close()
+
+
+def test_projection_on_a_buffer_sized_for_the_full_batch():
+    d, m, full = 1500, 1000, 600
+    g = torch.Generator().manual_seed(8)
+    x, w = torch.randn(full, d, generator=g), (torch.randn(m, d, generator=g) / d ** 0.5).to(torch.bfloat16)
+    bias = torch.randn(m, generator=g) * 0.1
+    ref = x.to(torch.bfloat16).double() @ w.double().t() + bias.double()
+    scale = x.to(torch.bfloat16).double().abs() @ w.double().abs().t() + bias.double().abs()
+    fc = binding.FreezeCache(1)
+    try:
+        fc.build_projection(0, w.cuda(), bias.cuda())
+        ws = Guarded(binding.freeze_project_workspace_bytes(fc.ctx, 0, full))
+        assert binding.freeze_project_workspace_bytes(fc.ctx, 0, 256) > ws.nbytes
+        for b in (full, 400, 256, 17, 1):
+            out = torch.empty(b, m, device="cuda")
+            binding.freeze_project(fc.ctx, 0, x[:b].cuda(), False, out, ws.payload)
+            torch.cuda.synchronize()
+            # fp32 accumulation of exact products in blocks: (log2(d) + 16) * 2^-24 of the magnitude sum
+            assert ((out.cpu().double() - ref[:b]).abs() <= 4e-6 * scale[:b]).all() and ws.intact()
     finally:
         fc.close()
