@@ -243,15 +243,23 @@ __global__ __launch_bounds__(512) void dist_block_kernel(BlockArgs p)
         int elane = lane;
         asm volatile("" : "+v"(elane));   // opaque: the addresses are formed here, not kept across the loop
         // (the compiler does not see that max3 reads matrix results: the no-ops are the distance the hardware
-        // wants, and the operands keep every maximum behind them)
+        // wants.  They take the first half of the accumulators through their operands and lie between two
+        // statements that take the second half: every matrix instruction of the tile comes before them and every
+        // maximum after, by the values alone, wherever the compiler moves either.)
+        auto second_half = [&]() {
+            asm volatile(""
+                         : "+v"(acc[4][0]), "+v"(acc[4][1]), "+v"(acc[4][2]), "+v"(acc[4][3]),
+                           "+v"(acc[5][0]), "+v"(acc[5][1]), "+v"(acc[5][2]), "+v"(acc[5][3]),
+                           "+v"(acc[6][0]), "+v"(acc[6][1]), "+v"(acc[6][2]), "+v"(acc[6][3]),
+                           "+v"(acc[7][0]), "+v"(acc[7][1]), "+v"(acc[7][2]), "+v"(acc[7][3]));
+        };
+        second_half();
         asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7"
-                     : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[0][2]), "+v"(acc[0][3]), "+v"(acc[1][0]), "+v"(acc[1][1]),
-                       "+v"(acc[1][2]), "+v"(acc[1][3]), "+v"(acc[2][0]), "+v"(acc[2][1]), "+v"(acc[2][2]), "+v"(acc[2][3]),
+                     : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[0][2]), "+v"(acc[0][3]),
+                       "+v"(acc[1][0]), "+v"(acc[1][1]), "+v"(acc[1][2]), "+v"(acc[1][3]),
+                       "+v"(acc[2][0]), "+v"(acc[2][1]), "+v"(acc[2][2]), "+v"(acc[2][3]),
                        "+v"(acc[3][0]), "+v"(acc[3][1]), "+v"(acc[3][2]), "+v"(acc[3][3]));
-        asm volatile(""
-                     : "+v"(acc[4][0]), "+v"(acc[4][1]), "+v"(acc[4][2]), "+v"(acc[4][3]), "+v"(acc[5][0]), "+v"(acc[5][1]),
-                       "+v"(acc[5][2]), "+v"(acc[5][3]), "+v"(acc[6][0]), "+v"(acc[6][1]), "+v"(acc[6][2]), "+v"(acc[6][3]),
-                       "+v"(acc[7][0]), "+v"(acc[7][1]), "+v"(acc[7][2]), "+v"(acc[7][3]));
+        second_half();
         const int64_t nb = (int64_t)p.n_tiles * (kTileN / 8);
         float *dst = p.bkey + ((int64_t)cur.mt * 256 + wm * 128 + (elane & 15)) * nb + cur.nt * (kTileN / 8) + wn * 8 + (elane >> 4) * 2;
 #pragma unroll
