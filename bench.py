@@ -26,6 +26,10 @@ if ROOT not in sys.path:
 
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA, published
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E, published
+# distance kernel of the workloads (of a cascade's first layer), as kernel traces of these runs show it
+DIST_KERNEL = {"c1_tiny": "dist_stream_kernel", "c2_batched": "dist_topr_kernel", "c3_wide": "dist_topr_kernel",
+               "c4_cascade": "dist_topr_kernel", "c4_cascade_noisy": "dist_topr_kernel",
+               "c5_latency_b1": "dist_skinny_kernel", "c5_latency_b8": "dist_skinny_kernel"}
 
 
 def measured_traffic(kernel: str, workload: str):
@@ -227,7 +231,7 @@ def run_workload(torch, np, binding, synth, dev, name, steps, warmup, cache_copi
     dist_ms = sum(first) / max(len(first), 1)
     flops = 2.0 * b * spec.n * spec.d
     cache_bytes = float(spec.n) * spec.d * 2
-    skinny = (not cascade) and b <= 16 and spec.d <= 1024
+    skinny = DIST_KERNEL[wl.name] == "dist_skinny_kernel"
     if not skinny:
         achieved = flops / (dist_ms * 1e-3) / 1e12
         roofline = dict(bound="mfma", achieved=round(achieved, 2), peak=PEAK_BF16_TFLOPS, unit="TFLOP/s",
@@ -238,9 +242,7 @@ def run_workload(torch, np, binding, synth, dev, name, steps, warmup, cache_copi
         achieved = cache_bytes / (dist_ms * 1e-3) / 1e9
         roofline = dict(bound="hbm", achieved=round(achieved, 1), peak=PEAK_HBM_GBS, unit="GB/s",
                         frac=round(achieved / PEAK_HBM_GBS, 4), traffic=None)
-    # (a small cache is streamed against small query tiles: the library's rule is on 256-row tiles x k-steps)
-    streamed = not cascade and not skinny and (b <= 128 or (b <= 256 and 2 * -(-spec.n // 256) * -(-spec.d // 64) * 2 < 4096))
-    roofline["kernel"] = "dist_skinny_kernel" if skinny else ("dist_stream_kernel" if streamed else "dist_topr_kernel")
+    roofline["kernel"] = DIST_KERNEL[wl.name]
     roofline["kernel_ms"] = round(dist_ms, 4)
     # (a cascade's profile averages the kernel over its four layers: no per-layer traffic figure)
     roofline["traffic"] = None if cascade else measured_traffic(roofline["kernel"], wl.name)
