@@ -2201,8 +2201,8 @@ hipError_t launch_block_finish(const FinishArgs &a, const float *bkey, const flo
 
 hipError_t launch_finish(const FinishArgs &a, hipStream_t s)
 {
-    const int total = a.part_count ? a.part_stride : a.alloc_splits * a.r;
-    if (total > kMaxMergeEntries || a.r > kMaxRescore || a.k > kMaxK || a.k > a.r) return hipErrorInvalidValue;
+    const int total = a.alloc_splits * a.r;   // (candidate lists with a count are keys_finish_kernel's)
+    if (a.part_count || total > kMaxMergeEntries || a.r > kMaxRescore || a.k > kMaxK || a.k > a.r) return hipErrorInvalidValue;
     if (!a.flag_count || !a.flag_list || !a.flag_list2) return hipErrorInvalidValue;
     FinishKernelArgs fa{a, 2};
     while (fa.sort_cap < total) fa.sort_cap <<= 1;

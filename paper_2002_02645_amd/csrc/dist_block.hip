@@ -307,15 +307,15 @@ DistPlan plan_block(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad)
     const int64_t cache_bytes = (int64_t)pl.n_tiles * kTileN * d_pad * 2;
     int64_t g = (cache_bytes > ((int64_t)256 << 20) ? 2 << 20 : 1 << 20) / tile_bytes;
     g = g < 1 ? 1 : g;
-    pl.bal_f = (int)(g < pl.m_tiles ? g : pl.m_tiles);
+    pl.group = (int)(g < pl.m_tiles ? g : pl.m_tiles);
     return pl;
 }
 
 hipError_t launch_dist_block(const DistPlan &pl, const DistArgs &a, hipStream_t s)
 {
-    if (pl.variant != 5 || !a.keys || a.d_pad < 64 || a.d_pad % kPadD != 0 || a.b < 1 || a.b > pl.b_pad || pl.bal_f < 1 || pl.grid_units < 1)
+    if (pl.variant != 5 || !a.keys || a.d_pad < 64 || a.d_pad % kPadD != 0 || a.b < 1 || a.b > pl.b_pad || pl.group < 1 || pl.grid_units < 1)
         return hipErrorInvalidValue;
-    BlockArgs k{a.q_bf, a.c_bf, a.norm, a.keys, a.count, a.b, pl.n_tiles, a.d_pad / kKB, pl.bal_f};
+    BlockArgs k{a.q_bf, a.c_bf, a.norm, a.keys, a.count, a.b, pl.n_tiles, a.d_pad / kKB, pl.group};
     hipLaunchKernelGGL(dist_block_kernel, dim3((unsigned)pl.grid_units), dim3(512), 0, s, k);
     return hipGetLastError();
 }

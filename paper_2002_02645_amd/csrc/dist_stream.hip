@@ -1,5 +1,6 @@
-// Distance pass for serving batches (at most 128 queries, any activation length) and for small
-// caches: every ranking key is written out, the selection is left to separate kernels.
+// Distance pass for serving batches (at most 128 queries, any activation length), for up to 1,024 queries on
+// small caches, and for projections of up to 512 inputs: every ranking key is written out (or every output), the
+// selection is left to keys_finish_kernel.
 //
 // With 128 queries or fewer the pass is bound by reading the cache once from HBM: a tile of 256
 // entries x 32 elements is 16 KiB, 0.6 us of a CU's share of the memory rate, and 128 x 256 x 32
@@ -24,7 +25,7 @@
 // What it takes (whole look-ups, batched kernel -> this one): 50,000 x 16,384, one query 461 -> 304 us
 // (this kernel 260 us = 6.3 TB/s, where a pure read reaches 7.1); 50,000 x 8,192, 32 queries 296 -> 203 us
 // (145 us = 5.7 TB/s); 20,000 x 16,384, 64 / 128 queries 250 -> 179 / 255 -> 213 us; 300,000 x 512, 64
-// queries 172 -> 115 us.  At 160 queries a 256-row tile is as fast, so 128 is the last size served here.
+// queries 172 -> 115 us.  At 160 queries a 256-row tile is as fast on a large cache, so 128 is the last size served there.
 //
 // Paper: Sec. 3 (k nearest neighbours of the layer output), Sec. 5 "Cache lookup performance".
 #include "freeze_internal.h"

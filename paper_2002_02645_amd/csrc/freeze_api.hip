@@ -108,7 +108,7 @@ int default_rescore(int k) { return k == 1 ? 8 : (k <= 10 ? 16 : (k <= 24 ? 32 :
 struct LookupShape {
     int r;
     bool skinny;   // small-batch bandwidth-bound kernel instead of the tiled matrix-core kernel
-    bool keys;     // tiled kernel writes every key; selection by the threshold / filter kernels
+    bool keys;     // every key is written out; selection and everything after it by keys_finish_kernel
     bool blocks;   // tiled kernel writes block minima; selection and re-scoring by block_finish_kernel
     bool cascade;  // sized for a look-up whose live count may sit on the device
     DistPlan plan;
@@ -146,10 +146,10 @@ bool block_route(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, i
     return 20.0 + matrix / 12.0 + (double)b * 8.0 * (k + 2 > 8 ? k + 2 : 8) * row / per_us < lists;
 }
 
-// The streaming kernel serves batches of at most this many queries (50,000 x 2,048: 128 queries 135 -> 113 us,
+// The streaming kernel serves single-layer batches of at most this many queries on any cache (50,000 x 2,048: 128 queries 135 -> 113 us,
 // but 160 queries as two tiles of 128 would read the cache twice; the 256-row tile takes 137 us), and
-// batches up to 256 on caches so small that 256-row tiles would leave most CUs idle (256 x 2,000 x 512:
-// 52 -> 36 us, 256 x 3,000 x 4,096: 127 -> 81 us).
+// larger ones (up to 1,024) that materialise their keys where a 256-row query tile has fewer than 8 k-steps per CU, so
+// that most CUs would have nothing to do (256 x 2,000 x 512: 52 -> 36 us, 256 x 3,000 x 4,096: 127 -> 81 us).
 constexpr int kStreamRows = 128;
 
 // Which decomposition of the work a look-up is planned with; the result does not depend on it.

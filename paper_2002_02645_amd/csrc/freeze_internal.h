@@ -160,6 +160,7 @@ struct DistPlan {
     int64_t st_len;
     int st_wgs;
     bool st_cut;
+    int group;      // block minima (variant 5): query tiles that share a cache tile in a row
 };
 
 // d_pad decides stream-K for the keys-out variant (pass 0 to leave it off).
@@ -168,7 +169,7 @@ DistPlan plan_dist(int64_t b, int64_t n, int r, int num_cus, bool keys_out, int6
 void plan_stream_k(DistPlan &pl, int num_cus, int64_t d_pad, double least_idle);
 // Streaming kernel; whole: never cut a tile (needs no accumulator slots).
 DistPlan plan_stream(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad, bool whole);
-// Block minima; bal_f = query tiles per group, grid_units = workgroups.
+// Block minima; grid_units = workgroups.
 DistPlan plan_block(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad);
 size_t dist_partial_bytes(const DistPlan &plan);   // accumulator slots of cut tiles (0 when none are cut)
 
@@ -305,12 +306,10 @@ hipError_t launch_cascade_scatter(const int32_t *labels, const uint8_t *hit, con
 
 // k-means cache build (the assignment step is the look-up itself)
 // sizes [k], offsets [k + 1] and members [n] int32 are scratch
+// (members: the points grouped by the centre they are assigned to, each group ascending)
 hipError_t launch_kmeans_update(const float *points, const int32_t *assign, int64_t n, int64_t d, int64_t k,
                                 const float *old_centers, float *new_centers, int32_t *sizes, int32_t *offsets,
                                 int32_t *members, hipStream_t s);
-// members = the ids 0 .. n-1 grouped by key (in [0, k)), each group ascending
-hipError_t launch_kmeans_group(const int32_t *key, int64_t n, int64_t k, int32_t *sizes, int32_t *offsets, int32_t *members,
-                               hipStream_t s);
 hipError_t launch_kmeans_majority(const int32_t *assign, const int32_t *labels, int64_t n, int num_classes, int64_t k,
                                   int32_t *majority, float *fraction, int64_t *sizes, hipStream_t s);
 hipError_t launch_copy_rows_f32(const float *src, int64_t src_stride, float *dst, int64_t rows, int64_t d, hipStream_t s);

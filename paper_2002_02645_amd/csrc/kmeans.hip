@@ -150,8 +150,9 @@ __global__ __launch_bounds__(64) void kmeans_update4_kernel(const float *points,
     *reinterpret_cast<f32x4 *>(new_centers + (int64_t)c * d + dim) = o;
 }
 
-hipError_t launch_kmeans_group(const int32_t *key, int64_t n, int64_t k, int32_t *sizes, int32_t *offsets, int32_t *members,
-                               hipStream_t s)
+// members = the ids 0 .. n-1 grouped by key (in [0, k)), each group ascending
+static hipError_t launch_kmeans_group(const int32_t *key, int64_t n, int64_t k, int32_t *sizes, int32_t *offsets,
+                                      int32_t *members, hipStream_t s)
 {
     hipError_t e = launch_fill_i32(sizes, 0, k, s);
     if (e != hipSuccess) return e;
