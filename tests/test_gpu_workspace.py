@@ -160,3 +160,32 @@ def test_projection_on_a_buffer_sized_for_the_full_batch():
             assert ((out.cpu().double() - ref[:b]).abs() <= 4e-6 * scale[:b]).all() and ws.intact()
     finally:
         fc.close()
+
+
+def test_kmeans_build_on_smaller_buffers():
+    n, d, kc, iters = 3000, 520, 300, 2
+    g = torch.Generator().manual_seed(12)
+    pts, lab = torch.randn(n, d, generator=g).cuda(), torch.randint(0, 7, (n,), generator=g, dtype=torch.int32).cuda()
+    init = pts[:kc].clone()
+    fc = binding.FreezeCache(1)
+    try:
+        want = fc.build_kmeans_layer(0, pts, lab, 7, init, iters)
+        storage = torch.empty(binding.freeze_kmeans_storage_bytes(kc, d), dtype=torch.uint8, device="cuda")
+        size, served = binding.freeze_kmeans_workspace_bytes(fc.ctx, n, d, kc), 0
+        while True:
+            ws = Guarded(size)
+            try:
+                binding.freeze_kmeans_build(fc.ctx, 0, pts, lab, 7, init, iters, storage, ws.payload)
+            except binding.FreezeError as e:
+                assert e.code == binding.FREEZE_EWORKSPACE
+                break
+            got = dict(centers=torch.empty(kc, d, device="cuda"), majority=torch.empty(kc, dtype=torch.int32, device="cuda"),
+                       fraction=torch.empty(kc, device="cuda"))
+            binding.freeze_kmeans_read(fc.ctx, 0, got["centers"], got["majority"], got["fraction"])
+            _equal(got, want)
+            assert ws.intact()
+            served += 1
+            size -= max(256, size // 32)
+        assert served >= 2
+    finally:
+        fc.close()
