@@ -26,7 +26,9 @@ def _inputs(n, d, b, k, dtype, seed, relu=True):
     (2049, 100, 300, 1, torch.bfloat16),     # k = 1; d a multiple of 4 only; a tile with one entry
     (8200, 517, 300, 20, torch.float32),     # R = 32, odd d
     (20000, 260, 400, 40, torch.bfloat16),   # R = 64: every wave gives its 16th smallest
-    (3000, 1000, 260, 64, torch.bfloat16),   # k = 64
+    (3000, 1000, 260, 64, torch.bfloat16),   # (the streaming kernel; k = 64 below)
+    (3000, 300, 260, 64, torch.float32),     # k = 64: the first round takes all that may be taken
+    (3000, 128, 1100, 64, torch.bfloat16),   # ... two waves per query
     (66000, 64, 1100, 10, torch.bfloat16),   # two waves per query; more blocks than the registers hold
     (9000, 1030, 1030, 7, torch.bfloat16),   # five query tiles, two per group
 ])

@@ -81,14 +81,14 @@ def test_config1_confidence_full_batch():
 
 
 @pytest.mark.parametrize("n,d,b,k,r,dtype", [
-    (777, 100, 37, 7, 0, torch.float32),       # fused kernel, ragged everything
-    (5000, 1024, 600, 10, 0, torch.bfloat16),  # several query tiles and splits
+    (777, 100, 37, 7, 0, torch.float32),       # streaming kernel, ragged everything
+    (5000, 1024, 600, 10, 0, torch.bfloat16),  # ... ten query tiles
     (20000, 512, 8, 20, 0, torch.bfloat16),    # small-batch kernel
-    (3000, 2048, 100, 10, 0, torch.bfloat16),  # keys-out kernel
+    (3000, 2048, 100, 10, 0, torch.bfloat16),  # long rows
     (1500, 192, 9, 33, 0, torch.bfloat16),     # k > 24
     (300, 64, 1, 1, 0, torch.float32),         # k = 1: confidence = 1 / distance
     (1200, 4096, 300, 10, 0, torch.bfloat16),  # long activations: the two-step re-scoring in front of the rule
-    (900, 4104, 40, 20, 0, torch.float32),     # ... width 32, keys-out kernel, fp32 cache
+    (900, 4104, 40, 20, 0, torch.float32),     # ... width 32, few queries (one step), fp32 cache
 ])
 def test_confidence_shapes_random_labels(n, d, b, k, r, dtype):
     wl = synth.scaled(synth.WORKLOADS["c2_batched"], n=n, batch=b)

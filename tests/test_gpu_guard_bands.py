@@ -1,8 +1,9 @@
 """Out-of-bounds writes: every output and the workspace sit between two 4 KiB guard bands filled
 with a poison byte, the workspace is exactly as large as the library says it needs, and after
 the call the bands must be untouched (and the outputs must still match a run with ordinary
-buffers).  Shapes are ragged on purpose and cover the fused kernel, the keys-out kernel with and
-without stream-K, the small-batch kernel, the cascade, the compaction and the row gather."""
+buffers).  Shapes are ragged on purpose and cover block minima, the streaming kernel with whole and cut
+tiles, the small-batch kernel, the cascade, the compaction and the row gather (test_gpu_lists.py has the
+fused kernel's lists and the 256-query keys-out kernel)."""
 import ctypes
 
 import numpy as np
@@ -49,10 +50,10 @@ def _make(n, d, b, k, r, dtype, seed):
 
 
 @pytest.mark.parametrize("n,d,b,k,r,dtype", [
-    (2999, 250, 301, 7, 0, torch.bfloat16),      # fused kernel, two query tiles, nothing a multiple of a tile
-    (3001, 333, 301, 20, 0, torch.float32),      # ... the 32-slot variant, fp32 cache
-    (2500, 4160, 37, 10, 64, torch.float32),     # keys-out kernel, R = 64
-    (50000, 2048, 64, 10, 0, torch.bfloat16),    # keys-out kernel under stream-K
+    (2999, 250, 301, 7, 0, torch.bfloat16),      # block minima, two query tiles, nothing a multiple of a tile
+    (3001, 333, 301, 20, 0, torch.float32),      # ... R = 32, fp32 cache
+    (2500, 4160, 37, 10, 64, torch.float32),     # streaming kernel, R = 64
+    (50000, 2048, 64, 10, 0, torch.bfloat16),    # ... tiles cut along the depth
     (20001, 500, 7, 20, 0, torch.bfloat16),      # small-batch kernel
     (4000, 64, 50, 10, 10, torch.bfloat16),      # no spare candidates: the wider re-scoring and the exact scan run
     (300, 40, 1, 1, 0, torch.float32),           # one query, one neighbour

@@ -13,6 +13,7 @@ from tests import parity
 from tests import test_gpu_guard_bands as guard_bands
 from tests import test_gpu_kmeans as kmeans
 from tests.test_gpu_parity import TIGHT, _host_entries, check_case
+from tests.test_gpu_sweep import _cases as sweep_cases
 
 pytestmark = pytest.mark.gpu
 
@@ -77,6 +78,45 @@ def test_lists(n, d, b, k, r, dtype):
     finally:
         fc.close()
     e_h, l_h, q_h = _host_entries(L.entries), L.labels.numpy(), q.numpy()
+    ref = parity.oracle_reference(q_h, e_h, l_h, 10, k, thr)
+    parity.assert_lookup_matches(got, ref, q_h, e_h, l_h, 10, k, thr, rel=TIGHT, dist_rel=TIGHT)
+
+
+@pytest.mark.parametrize("kind,n,d,b,k,r,bf16,relu,seed", [c for c in sweep_cases() if c[0] in ("tiled", "wide", "balanced")])
+def test_random_shape_on_the_smallest_workspace(kind, n, d, b, k, r, bf16, relu, seed):
+    L, q = _layer(n, d, b, k, torch.bfloat16 if bf16 else torch.float32, seed, relu)
+    thr = max(1, k - 2)
+    fc = binding.FreezeCache(1)
+    try:
+        fc.build_layer(0, L.entries.cuda(), L.labels.cuda(), 10)
+        got = _lookup_on_the_smallest_workspace(fc, q.cuda(), k, thr, r)
+    finally:
+        fc.close()
+    e_h, l_h, q_h = _host_entries(L.entries), L.labels.numpy(), q.numpy()
+    ref = parity.oracle_reference(q_h, e_h, l_h, 10, k, thr)
+    parity.assert_lookup_matches(got, ref, q_h, e_h, l_h, 10, k, thr, rel=TIGHT, dist_rel=TIGHT)
+
+
+@pytest.mark.parametrize("n,d,k,offset,dtype", [
+    (3000, 4096, 10, 0.0, torch.bfloat16),   # lists of 16: twelve candidates first, four more when unconfirmed
+    (3000, 4096, 10, 3.0, torch.float32),
+    (2500, 4104, 20, 1.0, torch.bfloat16),   # lists of 32: 24 first, then 8
+])
+def test_two_steps_on_lists(n, d, k, offset, dtype):
+    """One dense Gaussian cloud, so that the first step does not confirm every query (test_gpu_parity.py has the same
+    inputs on materialised keys)."""
+    g = torch.Generator().manual_seed(4242 + n + d + k)
+    ent = (torch.randn(n, d, generator=g) + offset).to(dtype)
+    lab = torch.randint(0, 10, (n,), generator=g, dtype=torch.int32)
+    q = torch.randn(300, d, generator=g) * 0.7 + offset
+    thr = max(1, k - 3)
+    fc = binding.FreezeCache(1)
+    try:
+        fc.build_layer(0, ent.cuda(), lab.cuda(), 10)
+        got = _lookup_on_the_smallest_workspace(fc, q.cuda(), k, thr, 0)
+    finally:
+        fc.close()
+    e_h, l_h, q_h = _host_entries(ent), lab.numpy(), q.numpy()
     ref = parity.oracle_reference(q_h, e_h, l_h, 10, k, thr)
     parity.assert_lookup_matches(got, ref, q_h, e_h, l_h, 10, k, thr, rel=TIGHT, dist_rel=TIGHT)
 

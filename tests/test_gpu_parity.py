@@ -67,9 +67,9 @@ def test_hand_example_on_gpu():
 @pytest.mark.parametrize("n,d,b,k,r,dtype", [
     (777, 100, 37, 7, 0, torch.float32),      # nothing a multiple of a tile; d not a multiple of 8
     (777, 100, 37, 7, 0, torch.bfloat16),
-    (5000, 1024, 600, 10, 0, torch.bfloat16),  # 3 query tiles (ragged), 20 cache tiles, several splits
-    (3000, 256, 300, 10, 32, torch.bfloat16),  # R = 32 kernel variant
-    (3000, 320, 130, 20, 64, torch.float32),   # R = 64 kernel variant (128-query tiles), k = 20
+    (5000, 1024, 600, 10, 0, torch.bfloat16),  # small cache, ten query tiles of the streaming kernel (ragged)
+    (3000, 256, 300, 10, 32, torch.bfloat16),  # block minima, R = 32
+    (3000, 320, 130, 20, 64, torch.float32),   # streaming kernel, R = 64, k = 20
     (40, 64, 5, 40, 0, torch.bfloat16),        # k = N
     (300, 64, 1, 1, 0, torch.float32),         # batch 1, k = 1
     (1500, 192, 9, 33, 0, torch.bfloat16),     # k > 24 -> default R = 64
@@ -80,32 +80,32 @@ def test_hand_example_on_gpu():
     (3000, 100, 2, 5, 0, torch.float32),       # small-batch kernel, d not a multiple of 8
     (2000, 128, 5, 10, 0, torch.bfloat16),     # small-batch kernel, fewer workgroups than blocks to take
     (70000, 256, 16, 10, 0, torch.bfloat16),   # small-batch kernel, one tile per workgroup
-    (3000, 1100, 3, 5, 0, torch.bfloat16),     # d too long for the small-batch kernel -> tiled kernel
-    (3000, 2048, 100, 10, 0, torch.bfloat16),  # one query tile, long activation -> keys-out kernel + selection
-    (2500, 4160, 200, 10, 64, torch.float32),  # keys-out, R = 64, fp32 cache, ragged everything
-    (1000, 640, 20, 5, 0, torch.bfloat16),     # keys-out with few cache tiles
-    (50000, 2048, 64, 10, 0, torch.bfloat16),  # keys-out, 196 cache tiles on 256 CUs: stream-K over (tile, k-step)
-    (36000, 2080, 100, 10, 64, torch.float32), # stream-K, ragged d, workgroup ranges that span three tiles' parts
-    (600, 16384, 40, 10, 0, torch.bfloat16),   # long activation, few queries: 1024-thread finishing blocks
-    (600, 16392, 300, 10, 0, torch.float32),   # fused kernel, fp32 cache, long activation, d not a multiple of 64
-    (5000, 128, 50, 48, 0, torch.bfloat16),    # a large k on the tiled kernel (R = 64)
+    (3000, 1100, 3, 5, 0, torch.bfloat16),     # d too long for the small-batch kernel -> streaming kernel
+    (3000, 2048, 100, 10, 0, torch.bfloat16),  # long activation: every key is written out, by the streaming kernel
+    (2500, 4160, 200, 10, 64, torch.float32),  # ... R = 64, fp32 cache, ragged everything
+    (1000, 640, 20, 5, 0, torch.bfloat16),     # ... few cache tiles
+    (50000, 2048, 64, 10, 0, torch.bfloat16),  # ... 196 cache tiles cut along the depth
+    (36000, 2080, 100, 10, 64, torch.float32), # ... ragged d, R = 64
+    (600, 16384, 40, 10, 0, torch.bfloat16),   # long activation, few queries: re-scored by the whole finishing workgroup
+    (600, 16392, 300, 10, 0, torch.float32),   # ... fp32 cache, d not a multiple of 64
+    (5000, 128, 50, 48, 0, torch.bfloat16),    # a large k on the streaming kernel (R = 64)
     (5000, 128, 4, 48, 0, torch.float32),      # ... and on the small-batch kernel
     (5000, 128, 50, 64, 0, torch.bfloat16),    # k = R = 64: no spare candidate, the bf16 ranking alone gets the 64th wrong for some queries
     (5000, 128, 4, 64, 0, torch.float32),      # ... and on the small-batch kernel
     (1585, 6, 2140, 34, 63, torch.bfloat16),   # low-dimensional dense data: many entries within the bf16 rounding of the 34th neighbour
     (4000, 64, 300, 10, 0, torch.bfloat16),    # (see test_clusters_far_from_the_origin for this shape on offset data)
     (64, 128, 20, 64, 0, torch.bfloat16),      # k = n = the re-scoring width: every entry is a candidate
-    (50000, 64, 10000, 10, 0, torch.bfloat16), # 40 x 196 tiles on 256 CUs: balanced decomposition, workgroups that serve two query tiles
-    (33000, 96, 7000, 5, 0, torch.float32),    # balanced decomposition, ragged last query tile
-    (4000, 512, 300, 5, 12, torch.bfloat16),   # R = 12: lists shorter than the kernel variant's 16 slots
-    (4000, 512, 300, 9, 24, torch.float32),    # R = 24 on the 32-slot variant
+    (50000, 64, 10000, 10, 0, torch.bfloat16), # block minima: 40 x 196 tiles on 256 CUs
+    (33000, 96, 7000, 5, 0, torch.float32),    # ... ragged last query tile, fp32 cache
+    (4000, 512, 300, 5, 12, torch.bfloat16),   # R = 12, no power of two
+    (4000, 512, 300, 9, 24, torch.float32),    # R = 24
     (1, 1, 3, 1, 0, torch.float32),            # a cache of one scalar entry
     (5, 3, 2, 2, 0, torch.bfloat16),           # a handful of short entries, small-batch kernel
-    (7, 5, 40, 3, 0, torch.float32),           # ... and the tiled kernel (more queries than entries)
+    (7, 5, 40, 3, 0, torch.float32),           # ... and the streaming kernel (more queries than entries)
     (257, 33, 257, 4, 0, torch.bfloat16),      # one entry and one query past a tile
-    (20000, 2048, 1800, 10, 0, torch.bfloat16),  # 8 x 79 tiles in 32 splits of 2 or 3 tiles, long rows
-    (9000, 2112, 4000, 20, 0, torch.float32),    # 16 query tiles on the R = 32 variant, ragged d, fp32 cache
-    (9000, 2048, 2000, 10, 64, torch.bfloat16),  # 16 query tiles on the R = 64 variant (128-query tiles)
+    (20000, 2048, 1800, 10, 0, torch.bfloat16),  # lists: 8 x 79 tiles in 32 splits of 2 or 3 tiles, long rows
+    (9000, 2112, 4000, 20, 0, torch.float32),    # lists: 16 query tiles on the R = 32 variant, ragged d, fp32 cache
+    (9000, 2048, 2000, 10, 64, torch.bfloat16),  # block minima, R = 64
     (2000000, 64, 300, 48, 0, torch.bfloat16),   # two million entries, the largest k
     (3000, 64, 100000, 10, 0, torch.bfloat16),   # a hundred thousand queries (391 query tiles)
     (1500000, 96, 16, 20, 0, torch.bfloat16),    # small-batch kernel at its largest batch, 1.5 million entries
@@ -127,12 +127,12 @@ def _verdicts(fc):
 
 
 @pytest.mark.parametrize("b,store_bf16,n,d,k", [
-    (300, True, 4000, 64, 10),      # fused kernel; most queries need the wider re-scoring or the exact scan
+    (300, True, 4000, 64, 10),      # block minima; most queries need further blocks or the exact scan
     (300, False, 4000, 64, 10),     # ... with the cache stored in fp32
     (6, True, 4000, 64, 10),        # small-batch kernel: few flagged queries, each scanned by many workgroups
     (3000, True, 20000, 64, 10),    # more flagged queries than the exact scan has workgroups: several per workgroup
-    (40, True, 3000, 2048, 10),     # keys-out kernel, long rows: the scan's whole-block re-scoring
-    (25, False, 2500, 4104, 5),     # ... fp32 cache, ragged depth
+    (40, True, 3000, 2048, 10),     # materialised keys, long rows
+    (25, False, 2500, 4104, 5),     # ... fp32 cache, ragged depth: the scan's whole-block re-scoring
     (200, True, 5000, 96, 64),      # k = 64: the scan's lists at their longest
 ])
 def test_clusters_far_from_the_origin(b, store_bf16, n, d, k):
@@ -208,9 +208,9 @@ def test_cascade_on_clusters_far_from_the_origin():
 
 
 @pytest.mark.parametrize("n,d,b,k,dtype", [
-    (3000, 256, 300, 10, torch.bfloat16),    # fused kernel
+    (3000, 256, 300, 10, torch.bfloat16),    # block minima
     (20000, 512, 8, 20, torch.bfloat16),     # small-batch kernel (the queries are converted inside the streaming kernel)
-    (2500, 4160, 100, 10, torch.float32),    # keys-out kernel, fp32 cache, ragged depth
+    (2500, 4160, 100, 10, torch.float32),    # streaming kernel, fp32 cache, ragged depth
 ])
 def test_forced_centring_keeps_results_exact(n, d, b, k, dtype):
     # centring changes which copy the matrix cores rank with, never the answer
@@ -237,7 +237,7 @@ def test_forced_centring_keeps_results_exact(n, d, b, k, dtype):
     (3000, 4096, 300, 10, 0.0, torch.bfloat16),   # width 16: twelve candidates first, four more when unconfirmed
     (3000, 4096, 300, 10, 3.0, torch.float32),    # ... fp32 cache, a mean the automatic rule leaves alone
     (2500, 4104, 280, 20, 1.0, torch.bfloat16),   # width 32: 24 first, then 8; ragged depth
-    (3000, 4096, 60, 10, 2.0, torch.bfloat16),    # one query tile: the keys-out selection in front of the same finish
+    (3000, 4096, 60, 10, 2.0, torch.bfloat16),    # at most 64 queries: one step
 ])
 def test_two_step_rescoring_on_dense_data(n, d, b, k, offset, dtype):
     """Long activations are re-scored in two steps (three quarters of the width, the rest only when

@@ -26,10 +26,10 @@ def _abs_scale(x, w):
 
 @pytest.mark.parametrize("b,d,m,wdtype,relu", [
     (300, 520, 1024, torch.float32, False),   # two tiles of inputs (ragged), four of outputs, ragged depth
-    (70, 2048, 100, torch.bfloat16, True),    # fewer outputs than a tile: goes through the padded buffer
+    (70, 2048, 100, torch.bfloat16, True),    # fewer outputs than a tile
     (1, 64, 1, torch.float32, False),
     (600, 96, 300, torch.float32, True),
-    (200, 32768, 1024, torch.bfloat16, False),  # four (input tile, output tile) units of great depth: stream-K
+    (200, 32768, 1024, torch.bfloat16, False),  # great depth: tiles cut over many workgroups
     (520, 22000, 512, torch.float32, True),     # stream-K over several input tiles, ragged depth
 ])
 def test_projection_against_oracle(b, d, m, wdtype, relu):

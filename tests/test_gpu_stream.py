@@ -1,4 +1,4 @@
-"""The streaming distance kernel (batches of at most 128 queries, small caches): every query tile,
+"""The streaming distance kernel (batches of at most 128 queries, up to 1,024 on small caches): every query tile,
 tiles cut by the ends of ranges and whole ones, first and last sizes of its range, against the CPU
 oracle; the later layers of a small cascade, whose live count is on the device; and the entry point
 with the fixed workspace, which has to fall back to ranges of whole tiles."""
@@ -42,11 +42,11 @@ def test_stream_shapes(n, d, b, k, dtype):
 
 
 @pytest.mark.parametrize("n,d,b,k,dtype", [
-    (2900, 4100, 257, 10, torch.bfloat16),   # keys-out kernel, two query tiles cut along the depth
+    (2900, 4100, 257, 10, torch.bfloat16),   # three query tiles cut along the depth
     (2900, 4100, 600, 20, torch.float32),
-    (1500, 2048, 1024, 10, torch.bfloat16),  # four query tiles, the last batch size of this route
-    (1500, 2048, 1025, 10, torch.bfloat16),  # ... and the first beyond it
-    (5000, 1024, 640, 5, torch.bfloat16),    # whole tiles (32 k-steps), in place of block minima
+    (1500, 2048, 1024, 10, torch.bfloat16),  # (block minima)
+    (1500, 2048, 1025, 10, torch.bfloat16),  # (block minima)
+    (5000, 1024, 640, 5, torch.bfloat16),    # ten query tiles, whole (32 k-steps), in place of block minima
 ])
 def test_keys_out_for_several_query_tiles(n, d, b, k, dtype):
     L, q = _inputs(n, d, b, k, dtype, 900 + n + b)

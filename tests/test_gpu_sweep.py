@@ -1,5 +1,5 @@
-"""GPU parity on seeded random shapes: every path (tiled kernels with 4 and 8 waves, balanced
-decomposition, keys-out with stream-K, small-batch kernel) against the CPU oracle, with the default
+"""GPU parity on seeded random shapes (block minima, streaming kernel, small-batch kernel; test_gpu_lists.py
+runs the first on per-query lists too) against the CPU oracle, with the default
 re-scoring width or any width from k to 64 (a narrow one makes the certificate send queries to the
 wider re-scoring or to the exact scan).  The shapes are drawn once from a fixed seed."""
 import random

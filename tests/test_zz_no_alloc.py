@@ -36,9 +36,9 @@ def _both(fc, q, k, thr, r):
 
 
 @pytest.mark.parametrize("n,d,b1,b2,k,r,dtype", [
-    (3000, 256, 300, 41, 10, 0, torch.bfloat16),     # fused kernel, two query tiles, then one ragged tile (keys-out)
+    (3000, 256, 300, 41, 10, 0, torch.bfloat16),     # block minima, two query tiles, then the streaming kernel
     (20000, 512, 8, 3, 20, 0, torch.bfloat16),       # small-batch kernel twice
-    (2000, 512, 256, 100, 5, 0, torch.float32),      # keys-out kernel, fp32 cache
+    (2000, 512, 256, 100, 5, 0, torch.float32),      # streaming kernel, fp32 cache
 ])
 def test_static_scratch_matches_workspace_variant(n, d, b1, b2, k, r, dtype):
     wl = synth.scaled(synth.WORKLOADS["c2_batched"], n=n, batch=b1)
