@@ -907,7 +907,8 @@ struct FinishKernelArgs {
 // and when this exceeds dk no excluded entry can be among the k nearest: the result is the exact
 // one.  z = kCertZ; the estimate needs kCertMinSamples samples from as many distinct distances
 // (duplicated rows repeat one sample).  Otherwise the verdict is "unconfirmed" and the caller
-// widens the candidate set or hands the query to the exact scan.
+// widens the candidate set or hands the query to the exact scan.  Two calls with the same verdict_s want a
+// barrier between them.
 // floor_ulps: the margin is at least this many fp32 ulps of the quantities involved (ties; rounding that the
 // samples do not show).
 __device__ __forceinline__ bool certificate(const uint64_t *ent, const float *dist_s, int m, float dk, uint32_t excl_bits,
@@ -1633,6 +1634,7 @@ __global__ __launch_bounds__(kThrThreads) void keys_finish_kernel(KeysFinishArgs
         // (50,000 x 8,192, 32 queries, 21 copies of every entry: 2,484 us by the exact scan, 275 so.)
         const uint64_t *src = list;
         int keep = real;
+        __syncthreads();   // (everyone has read the verdict that this one replaces)
         const bool enough = certificate(list, dist_s, r, dsel_s[a.k - 1], excl0, distinct_s, tid, &verdict_s);
         if (!enough && real < kTier1 && real < a.n) {   // uniform
             uint64_t *wide = list + kThrList / 2;   // (the candidates at hand stay in the first 2,048 places)
