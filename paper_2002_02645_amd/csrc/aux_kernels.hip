@@ -1617,7 +1617,7 @@ __global__ __launch_bounds__(kThrThreads) void keys_finish_kernel(KeysFinishArgs
             const uint32_t nxt = (uint32_t)(list[m] >> 32);
             excl = nxt < excl ? nxt : excl;
         }
-        return certificate(list, dist_s, m, dsel_s[a.k - 1], excl, distinct_s, tid, &verdict_s);
+        return __builtin_amdgcn_readfirstlane((int)certificate(list, dist_s, m, dsel_s[a.k - 1], excl, distinct_s, tid, &verdict_s)) != 0;
     };
     bool ok = confirm(m_first);
     if (!ok && m_first < r) {   // uniform
@@ -1626,7 +1626,7 @@ __global__ __launch_bounds__(kThrThreads) void keys_finish_kernel(KeysFinishArgs
         __syncthreads();
         ok = confirm(r);
     }
-    if (!ok) {   // uniform
+    if (__builtin_expect(!ok, 0)) {   // uniform (and out of the way of the instruction fetch)
         // Unconfirmed: the wider re-scoring, or the exact scan, redoes this query.  The candidates at hand do when
         // their largest key as the bound would have confirmed the result.  Else (duplicates, neighbours closer than
         // the key's error) the wider re-scoring gets at least the kTier1 entries with the smallest keys: T2 = the largest
@@ -1753,10 +1753,15 @@ hipError_t launch_keys_finish(const FinishArgs &a, const float *keys, const uint
 //     error per block.  What they do not show is the rounding of the matrix cores' additions, at most one ulp of a
 //     partial sum per k-step: the margin's floor covers that.  Entries outside the blocks taken have a key
 //     at or above the next minimum.  A query that fails takes R blocks, then all that were gathered (up to
-//     64), then goes on the exact scan's list.
+//     64), then up to 256.
+//  5. The 256 are selected anew.  The first kMeetQueries queries that get here leave that to the follow-up kernel,
+//     where sixteen workgroups share each: that is all of them on most inputs, and a single workgroup would be the
+//     last to finish by far.  With more (duplicates, neighbours closer than the key's error) the chip is busy
+//     anyway, and each goes on here.
 // Bound by the rows it reads, 8 per block: 4,096 queries x 12 blocks x 8 rows of 1 KB are 0.4 GB, beyond L2 for
 // a cache of 50,000 x 512 (51 MB); 112 us with the minima's 103 MB, 80 us on a cache of 5,000 rows.
 // ---------------------------------------------------------------------------------------
+constexpr int kMeetQueries = 32;
 struct BlockFinishArgs {
     FinishArgs a;
     const float *bkey;   // [b, nb] smallest coarse key of every block
@@ -1784,25 +1789,280 @@ __device__ __forceinline__ f32x2 through_bf16(float x, float y)
     return f32x2{__uint_as_float(u << 16), __uint_as_float(u & 0xffff0000u)};
 }
 
+// the query's elements i .. i + 7 (zeros past d, where the cache's rows are zero too)
+__device__ __forceinline__ void load_query8(const float *qrow, int64_t i, int64_t d, float (&x)[8])
+{
+    if ((d % 8) == 0 || ((d % 4) == 0 && i + 8 <= d)) {   // 16-byte aligned
+        const f32x4 q0 = *reinterpret_cast<const f32x4 *>(qrow + i), q1 = *reinterpret_cast<const f32x4 *>(qrow + i + 4);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = e < 4 ? q0[e & 3] : q1[e & 3];
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = i + e < d ? qrow[i + e] : 0.f;
+    }
+}
+
+// Exact distances of the eight entries of the block that starts at entry e0 (uniform), by one wave: the packed
+// (distance, index) of row lane >> 3 in every lane, the marker for padding rows.  Same order of additions as in
+// rescore_wave, for rows of any length.
+__device__ __forceinline__ uint64_t rescore_block8(const FinishArgs &a, const float *qrow, int e0, int lane)
+{
+    const bool whole = (a.d % 8) == 0;
+    // the row's place in the cache (uniform); rows past it (padding) are read as the last row and dropped below
+    auto row_of = [&](int j) {
+        const int e = e0 + (j & 3) + (j >> 2) * 16;
+        return (int64_t)(e < a.n ? e : a.n - 1) * a.d_pad;
+    };
+    float acc[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+    if (whole) {   // uniform
+        for (int64_t i = (int64_t)lane * 8; i < a.d; i += 512) {
+            float qv[8];
+            load_query8(qrow, i, a.d, qv);
+            if (a.c_f32) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const f32x4 c0 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row_of(j) + i);
+                    const f32x4 c1 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row_of(j) + i + 4);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float df = qv[e] - (e < 4 ? c0[e & 3] : c1[e & 3]);
+                        acc[j] = __builtin_fmaf(df, df, acc[j]);
+                    }
+                }
+            } else {
+                uint4 cb[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) cb[j] = *reinterpret_cast<const uint4 *>(a.c_rows + row_of(j) + i);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const uint32_t wv[4] = {cb[j].x, cb[j].y, cb[j].z, cb[j].w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float d0 = qv[2 * e] - __uint_as_float(wv[e] << 16);
+                        acc[j] = __builtin_fmaf(d0, d0, acc[j]);
+                        const float d1 = qv[2 * e + 1] - __uint_as_float(wv[e] & 0xffff0000u);
+                        acc[j] = __builtin_fmaf(d1, d1, acc[j]);
+                    }
+                }
+            }
+        }
+    } else if (a.c_f32) {
+        // Rows of another length: rescore_wave's order, chain l of 64 takes elements l, l + 64, .., so that a
+        // distance does not depend on the kernel that formed it.  A chain per lane; four steps' loads of all
+        // eight rows in flight (whole look-ups, 20,011 x 517, 1,537 queries, k = 20: 242 us with eight elements per lane, 189 so).
+        auto steps = [&](int64_t i, auto count) {
+            constexpr int U = decltype(count)::value;
+            float qv[U], cv[8][U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                qv[u] = qrow[i + u * 64];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) cv[j][u] = a.c_f32[row_of(j) + i + u * 64];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float df = qv[u] - cv[j][u];
+                    acc[j] = __builtin_fmaf(df, df, acc[j]);
+                }
+        };
+        int64_t i = lane;
+        for (; i + 3 * 64 < a.d; i += 4 * 64) steps(i, std::integral_constant<int, 4>{});
+        for (; i < a.d; i += 64) steps(i, std::integral_constant<int, 1>{});
+    }
+    float s1;
+    if (whole || a.c_f32) {   // uniform
+        // transposed reduction: after the steps over lane bits 5, 4 and 3 a lane holds the partial sum of
+        // row 4 b5 + 2 b4 + b3, the rest is a butterfly
+        float s4[4], s2[2];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool hi = lane & 32;
+            s4[j] = (hi ? acc[4 + j] : acc[j]) + __shfl_xor(hi ? acc[j] : acc[4 + j], 32, 64);
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const bool hi = lane & 16;
+            s2[j] = (hi ? s4[2 + j] : s4[j]) + __shfl_xor(hi ? s4[j] : s4[2 + j], 16, 64);
+        }
+        {
+            const bool hi = lane & 8;
+            s1 = (hi ? s2[1] : s2[0]) + __shfl_xor(hi ? s2[0] : s2[1], 8, 64);
+        }
+#pragma unroll
+        for (int off = 4; off >= 1; off >>= 1) s1 += __shfl_xor(s1, off, 64);
+    } else {
+        // The same order on bf16 rows: half a wave per row, chains 2 p and 2 p + 1 in lane p of the half, so that a
+        // lane's load is 4 bytes (50,000 x 517, 4,096 queries: 363 us with eight elements per lane, 708 with a chain per lane
+        // and 2-byte loads, 350 so).  Lane bit 5 and jp name the row; elements past d are zeros on both sides and
+        // leave a chain as it is.
+        const int p = lane & 31, hf = lane >> 5;
+        const uint32_t *row[4];
+#pragma unroll
+        for (int jp = 0; jp < 4; ++jp) {
+            const int e = e0 + jp + hf * 16;
+            row[jp] = reinterpret_cast<const uint32_t *>(a.c_rows + (int64_t)(e < a.n ? e : a.n - 1) * a.d_pad) + p;
+        }
+        float ch[4][2];   // [jp][chain of the lane]
+#pragma unroll
+        for (int jp = 0; jp < 4; ++jp) ch[jp][0] = ch[jp][1] = 0.f;
+        auto steps = [&](int64_t i0, auto count) {   // elements [i0, i0 + 64 U), i0 + 64 U <= d_pad
+            constexpr int U = decltype(count)::value;
+            float qv[U][2];
+            uint32_t cv[4][U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t i = i0 + u * 64 + 2 * p;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) qv[u][h] = i + h < a.d ? qrow[i + h] : 0.f;
+#pragma unroll
+                for (int jp = 0; jp < 4; ++jp) cv[jp][u] = row[jp][(i0 >> 1) + u * 32];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int jp = 0; jp < 4; ++jp) {
+                    const float d0 = qv[u][0] - __uint_as_float(cv[jp][u] << 16);
+                    ch[jp][0] = __builtin_fmaf(d0, d0, ch[jp][0]);
+                    const float d1 = qv[u][1] - __uint_as_float(cv[jp][u] & 0xffff0000u);
+                    ch[jp][1] = __builtin_fmaf(d1, d1, ch[jp][1]);
+                }
+        };
+        int64_t i0 = 0;
+        for (; i0 + 4 * 64 <= a.d_pad; i0 += 4 * 64) steps(i0, std::integral_constant<int, 4>{});
+        for (; i0 < a.d_pad; i0 += 64) steps(i0, std::integral_constant<int, 1>{});
+        // the butterfly over chains 32, 16, 8, 4, 2 and 1 apart: lanes 16, 8, 4, 2 and 1 apart, then the
+        // lane's two chains; transposed over lane bits 4 and 3 (jp) and 2 (the chain)
+        float t4[2][2], t2[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const bool hi = lane & 16;
+                t4[j][h] = (hi ? ch[2 + j][h] : ch[j][h]) + __shfl_xor(hi ? ch[j][h] : ch[2 + j][h], 16, 64);
+            }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const bool hi = lane & 8;
+            t2[h] = (hi ? t4[1][h] : t4[0][h]) + __shfl_xor(hi ? t4[0][h] : t4[1][h], 8, 64);
+        }
+        {
+            const bool hi = lane & 4;
+            s1 = (hi ? t2[1] : t2[0]) + __shfl_xor(hi ? t2[0] : t2[1], 4, 64);
+        }
+        s1 += __shfl_xor(s1, 2, 64);
+        s1 += __shfl_xor(s1, 1, 64);
+        s1 += __shfl_xor(s1, 4, 64);
+    }
+    // lane >> 3 = 4 b5 + 2 b4 + b3: the row
+    const int e = e0 + ((lane >> 3) & 3) + (lane >> 5) * 16;
+    return e < a.n ? ((uint64_t)ordered_bits(s1) << 32) | (uint32_t)e : kSentinel;
+}
+
+// The smallest of the eight rows' values of rescore_block8.
+__device__ __forceinline__ uint64_t block_nearest(uint64_t x)
+{
+#pragma unroll
+    for (int off = 32; off >= 8; off >>= 1) {
+        const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)x, off, 64);
+        const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(x >> 32), off, 64);
+        const uint64_t y = ((uint64_t)hi << 32) | lo;
+        x = y < x ? y : x;
+    }
+    return x;
+}
+
+// Dot products of the bf16 copies of the query and of entries idx[b0 .. b0 + 3] (of m), as the coarse keys are made of,
+// relative to mu where that is given, by one wave: that of entry b0 + (lane >> 4) in every lane.
+__device__ __forceinline__ float coarse_dot4(const FinishArgs &a, const float *mu, const float *qrow, const int32_t *idx, int b0, int m, int lane)
+{
+    int64_t row[4];
+    float dot[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        row[j] = (int64_t)__builtin_amdgcn_readfirstlane(idx[b0 + j < m ? b0 + j : m - 1]) * a.d_pad;
+        dot[j] = 0.f;
+    }
+    for (int64_t i = (int64_t)lane * 8; i < a.d; i += 512) {
+        float qv[8], mv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        load_query8(qrow, i, a.d, qv);
+        if (mu) {
+            const f32x4 m0 = *reinterpret_cast<const f32x4 *>(mu + i), m1 = *reinterpret_cast<const f32x4 *>(mu + i + 4);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) mv[e] = e < 4 ? m0[e & 3] : m1[e & 3];
+        }
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+            const f32x2 v = through_bf16(qv[e] - mv[e], qv[e + 1] - mv[e + 1]);
+            qv[e] = v[0];
+            qv[e + 1] = v[1];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            float cv[8];
+            if (a.c_f32) {
+                const f32x4 c0 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row[j] + i);
+                const f32x4 c1 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row[j] + i + 4);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) cv[e] = e < 4 ? c0[e & 3] : c1[e & 3];
+            } else {
+                const uint4 cb = *reinterpret_cast<const uint4 *>(a.c_rows + row[j] + i);
+                const uint32_t wv[4] = {cb.x, cb.y, cb.z, cb.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    cv[2 * e] = __uint_as_float(wv[e] << 16);
+                    cv[2 * e + 1] = __uint_as_float(wv[e] & 0xffff0000u);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 8; e += 2) {
+                const f32x2 v = through_bf16(cv[e] - mv[e], cv[e + 1] - mv[e + 1]);
+                dot[j] = __builtin_fmaf(qv[e], v[0], dot[j]);
+                dot[j] = __builtin_fmaf(qv[e + 1], v[1], dot[j]);
+            }
+        }
+    }
+    // the four sums, transposed: lane bits 5 and 4 name the row
+    float s2[2], s1;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const bool hi = lane & 32;
+        s2[j] = (hi ? dot[2 + j] : dot[j]) + __shfl_xor(hi ? dot[j] : dot[2 + j], 32, 64);
+    }
+    {
+        const bool hi = lane & 16;
+        s1 = (hi ? s2[1] : s2[0]) + __shfl_xor(hi ? s2[0] : s2[1], 16, 64);
+    }
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) s1 += __shfl_xor(s1, off, 64);
+    return s1;
+}
+
 template <int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void block_finish_kernel(BlockFinishArgs ba)
 {
     const FinishArgs &a = ba.a;
     constexpr int NW = NT / 64;
-    constexpr int RMAX = kMaxRescore;                 // blocks taken at most
+    constexpr int RMAX = kMaxRescore;                 // blocks taken before the 256 at most
     constexpr int kBlkList = 4 * NT;                  // gathered minima at most
     __shared__ uint64_t list[kBlkList];
-    __shared__ uint64_t ent[RMAX * 8], ent2[RMAX * 8 < 128 ? 128 : RMAX * 8];
-    __shared__ uint64_t samp_s[RMAX];
-    __shared__ float sdist_s[RMAX];
-    __shared__ int32_t sidx_s[RMAX];
+    __shared__ uint64_t ent[RMAX * 16];               // entries of the blocks; group minima
+    uint64_t *ent2 = ent + RMAX * 8;
+    static_assert(RMAX * 16 >= kBlkList && kBlkList >= 2 * kTier1, "step 5");
+    __shared__ uint64_t samp_s[kTier1];
+    __shared__ float sdist_s[kTier1];
+    __shared__ int32_t sidx_s[kTier1];
+    __shared__ uint64_t best_s[kMaxK];
     __shared__ uint32_t wave_s[4];
     __shared__ int32_t lab_s[kMaxK], cnt_s[kMaxK];
     __shared__ float dsel_s[kMaxK];
     __shared__ double conf_s[kMaxK];
     __shared__ int32_t nearest_s;
     __shared__ uint64_t kth_s;
-    __shared__ int list_n, near_n, distinct_s, verdict_s;
+    __shared__ int list_n, near_n, distinct_s, verdict_s, flagged_s;
     const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (a.count && q >= *a.count) return;   // uniform
@@ -1912,185 +2172,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
     }
 
     const float *qrow = a.queries + (int64_t)(a.sel ? a.sel[q] : q) * a.d;
-    // the query's elements i .. i + 7 (zeros past d, where the cache's rows are zero too)
-    const bool whole = (a.d % 8) == 0, quads = (a.d % 4) == 0;
-    auto load_q = [&](int64_t i, float (&x)[8]) {
-        if (whole || (quads && i + 8 <= a.d)) {
-            const f32x4 q0 = *reinterpret_cast<const f32x4 *>(qrow + i), q1 = *reinterpret_cast<const f32x4 *>(qrow + i + 4);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] = e < 4 ? q0[e & 3] : q1[e & 3];
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] = i + e < a.d ? qrow[i + e] : 0.f;
-        }
-    };
     bool ok = false;
     // first ba.first blocks, unconfirmed queries R, then all that were gathered
     int done = 0, nblk = ba.first < cnt ? ba.first : cnt;
     while (true) {
         // ---- 2. exact re-scoring of blocks [done, nblk): packed (distance, index) of their entries ----
         for (int b = done + w; b < nblk; b += NW) {
-            const int e0 = block_first_entry(__builtin_amdgcn_readfirstlane((int)(uint32_t)list[b]));
-            // the row's place in the cache (uniform); rows past it (padding) are read as the last row and dropped below
-            auto row_of = [&](int j) {
-                const int e = e0 + (j & 3) + (j >> 2) * 16;
-                return (int64_t)(e < a.n ? e : a.n - 1) * a.d_pad;
-            };
-            float acc[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-            if (whole) {   // uniform
-                for (int64_t i = (int64_t)lane * 8; i < a.d; i += 512) {
-                    float qv[8];
-                    load_q(i, qv);
-                    if (a.c_f32) {
-    #pragma unroll
-                        for (int j = 0; j < 8; ++j) {
-                            const f32x4 c0 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row_of(j) + i);
-                            const f32x4 c1 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row_of(j) + i + 4);
-    #pragma unroll
-                            for (int e = 0; e < 8; ++e) {
-                                const float df = qv[e] - (e < 4 ? c0[e & 3] : c1[e & 3]);
-                                acc[j] = __builtin_fmaf(df, df, acc[j]);
-                            }
-                        }
-                    } else {
-                        uint4 cb[8];
-    #pragma unroll
-                        for (int j = 0; j < 8; ++j) cb[j] = *reinterpret_cast<const uint4 *>(a.c_rows + row_of(j) + i);
-    #pragma unroll
-                        for (int j = 0; j < 8; ++j) {
-                            const uint32_t wv[4] = {cb[j].x, cb[j].y, cb[j].z, cb[j].w};
-    #pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                const float d0 = qv[2 * e] - __uint_as_float(wv[e] << 16);
-                                acc[j] = __builtin_fmaf(d0, d0, acc[j]);
-                                const float d1 = qv[2 * e + 1] - __uint_as_float(wv[e] & 0xffff0000u);
-                                acc[j] = __builtin_fmaf(d1, d1, acc[j]);
-                            }
-                        }
-                    }
-                }
-            } else if (a.c_f32) {
-                // Rows of another length: rescore_wave's order, chain l of 64 takes elements l, l + 64, .., so that a
-                // distance does not depend on the kernel that formed it.  A chain per lane; four steps' loads of all
-                // eight rows in flight (whole look-ups, 20,011 x 517, 1,537 queries, k = 20: 242 us with eight elements per lane, 189 so).
-                auto steps = [&](int64_t i, auto count) {
-                    constexpr int U = decltype(count)::value;
-                    float qv[U], cv[8][U];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        qv[u] = qrow[i + u * 64];
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) cv[j][u] = a.c_f32[row_of(j) + i + u * 64];
-                    }
-#pragma unroll
-                    for (int u = 0; u < U; ++u)
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) {
-                            const float df = qv[u] - cv[j][u];
-                            acc[j] = __builtin_fmaf(df, df, acc[j]);
-                        }
-                };
-                int64_t i = lane;
-                for (; i + 3 * 64 < a.d; i += 4 * 64) steps(i, std::integral_constant<int, 4>{});
-                for (; i < a.d; i += 64) steps(i, std::integral_constant<int, 1>{});
-            }
-            float s1;
-            if (whole || a.c_f32) {   // uniform
-                // transposed reduction: after the steps over lane bits 5, 4 and 3 a lane holds the partial sum of
-                // row 4 b5 + 2 b4 + b3, the rest is a butterfly
-                float s4[4], s2[2];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const bool hi = lane & 32;
-                    s4[j] = (hi ? acc[4 + j] : acc[j]) + __shfl_xor(hi ? acc[j] : acc[4 + j], 32, 64);
-                }
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const bool hi = lane & 16;
-                    s2[j] = (hi ? s4[2 + j] : s4[j]) + __shfl_xor(hi ? s4[j] : s4[2 + j], 16, 64);
-                }
-                {
-                    const bool hi = lane & 8;
-                    s1 = (hi ? s2[1] : s2[0]) + __shfl_xor(hi ? s2[0] : s2[1], 8, 64);
-                }
-#pragma unroll
-                for (int off = 4; off >= 1; off >>= 1) s1 += __shfl_xor(s1, off, 64);
-            } else {
-                // The same order on bf16 rows: half a wave per row, chains 2 p and 2 p + 1 in lane p of the half, so that a
-                // lane's load is 4 bytes (50,000 x 517, 4,096 queries: 363 us with eight elements per lane, 708 with a chain per lane
-                // and 2-byte loads, 350 so).  Lane bit 5 and jp
-                // name the row; elements past d are zeros on both sides and leave a chain as it is.
-                const int p = lane & 31, hf = lane >> 5;
-                const uint32_t *row[4];
-#pragma unroll
-                for (int jp = 0; jp < 4; ++jp) {
-                    const int e = e0 + jp + hf * 16;
-                    row[jp] = reinterpret_cast<const uint32_t *>(a.c_rows + (int64_t)(e < a.n ? e : a.n - 1) * a.d_pad) + p;
-                }
-                float ch[4][2];   // [jp][chain of the lane]
-#pragma unroll
-                for (int jp = 0; jp < 4; ++jp) ch[jp][0] = ch[jp][1] = 0.f;
-                auto steps = [&](int64_t i0, auto count) {   // elements [i0, i0 + 64 U), i0 + 64 U <= d_pad
-                    constexpr int U = decltype(count)::value;
-                    float qv[U][2];
-                    uint32_t cv[4][U];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const int64_t i = i0 + u * 64 + 2 * p;
-#pragma unroll
-                        for (int h = 0; h < 2; ++h) qv[u][h] = i + h < a.d ? qrow[i + h] : 0.f;
-#pragma unroll
-                        for (int jp = 0; jp < 4; ++jp) cv[jp][u] = row[jp][(i0 >> 1) + u * 32];
-                    }
-#pragma unroll
-                    for (int u = 0; u < U; ++u)
-#pragma unroll
-                        for (int jp = 0; jp < 4; ++jp) {
-                            const float d0 = qv[u][0] - __uint_as_float(cv[jp][u] << 16);
-                            ch[jp][0] = __builtin_fmaf(d0, d0, ch[jp][0]);
-                            const float d1 = qv[u][1] - __uint_as_float(cv[jp][u] & 0xffff0000u);
-                            ch[jp][1] = __builtin_fmaf(d1, d1, ch[jp][1]);
-                        }
-                };
-                int64_t i0 = 0;
-                for (; i0 + 4 * 64 <= a.d_pad; i0 += 4 * 64) steps(i0, std::integral_constant<int, 4>{});
-                for (; i0 < a.d_pad; i0 += 64) steps(i0, std::integral_constant<int, 1>{});
-                // the butterfly over chains 32, 16, 8, 4, 2 and 1 apart: lanes 16, 8, 4, 2 and 1 apart, then the
-                // lane's two chains; transposed over lane bits 4 and 3 (jp) and 2 (the chain)
-                float t4[2][2], t2[2];
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const bool hi = lane & 16;
-                        t4[j][h] = (hi ? ch[2 + j][h] : ch[j][h]) + __shfl_xor(hi ? ch[j][h] : ch[2 + j][h], 16, 64);
-                    }
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const bool hi = lane & 8;
-                    t2[h] = (hi ? t4[1][h] : t4[0][h]) + __shfl_xor(hi ? t4[0][h] : t4[1][h], 8, 64);
-                }
-                {
-                    const bool hi = lane & 4;
-                    s1 = (hi ? t2[1] : t2[0]) + __shfl_xor(hi ? t2[0] : t2[1], 4, 64);
-                }
-                s1 += __shfl_xor(s1, 2, 64);
-                s1 += __shfl_xor(s1, 1, 64);
-                s1 += __shfl_xor(s1, 4, 64);
-            }
-            // lane >> 3 = 4 b5 + 2 b4 + b3: the row; the block's nearest entry is the certificate's sample
-            const int e = e0 + ((lane >> 3) & 3) + (lane >> 5) * 16;
-            uint64_t x = e < a.n ? ((uint64_t)ordered_bits(s1) << 32) | (uint32_t)e : kSentinel;
+            uint64_t x = rescore_block8(a, qrow, block_first_entry(__builtin_amdgcn_readfirstlane((int)(uint32_t)list[b])), lane);
             if ((lane & 7) == 0) ent[b * 8 + (lane >> 3)] = x;
-#pragma unroll
-            for (int off = 32; off >= 8; off >>= 1) {
-                const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)x, off, 64);
-                const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(x >> 32), off, 64);
-                const uint64_t y = ((uint64_t)hi << 32) | lo;
-                x = y < x ? y : x;
-            }
+            x = block_nearest(x);   // the certificate's sample
             if (lane == 0) {
                 // (a block that was taken holds a real entry; the marker only with non-finite inputs)
                 sidx_s[b] = (uint32_t)x < (uint32_t)a.n ? (int32_t)(uint32_t)x : 0;
@@ -2146,70 +2236,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
             a.out_nbr_dist[(int64_t)q * a.k + tid] = dm;
             lab_s[tid] = a.labels[im];
             dsel_s[tid] = dm;
+            best_s[tid] = x;
             if (tid == 0) nearest_s = im;
         }
 
         // ---- 4. the certificate ----
         for (int b0 = done + w * 4; b0 < nblk; b0 += 4 * NW) {
-            int64_t row[4];
-            float dot[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                row[j] = (int64_t)__builtin_amdgcn_readfirstlane(sidx_s[b0 + j < nblk ? b0 + j : nblk - 1]) * a.d_pad;
-                dot[j] = 0.f;
-            }
-            for (int64_t i = (int64_t)lane * 8; i < a.d; i += 512) {
-                float qv[8], mv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                load_q(i, qv);
-                if (ba.mu) {
-                    const f32x4 m0 = *reinterpret_cast<const f32x4 *>(ba.mu + i), m1 = *reinterpret_cast<const f32x4 *>(ba.mu + i + 4);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) mv[e] = e < 4 ? m0[e & 3] : m1[e & 3];
-                }
-#pragma unroll
-                for (int e = 0; e < 8; e += 2) {
-                    const f32x2 v = through_bf16(qv[e] - mv[e], qv[e + 1] - mv[e + 1]);
-                    qv[e] = v[0];
-                    qv[e + 1] = v[1];
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    float cv[8];
-                    if (a.c_f32) {
-                        const f32x4 c0 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row[j] + i);
-                        const f32x4 c1 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row[j] + i + 4);
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) cv[e] = e < 4 ? c0[e & 3] : c1[e & 3];
-                    } else {
-                        const uint4 cb = *reinterpret_cast<const uint4 *>(a.c_rows + row[j] + i);
-                        const uint32_t wv[4] = {cb.x, cb.y, cb.z, cb.w};
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            cv[2 * e] = __uint_as_float(wv[e] << 16);
-                            cv[2 * e + 1] = __uint_as_float(wv[e] & 0xffff0000u);
-                        }
-                    }
-#pragma unroll
-                    for (int e = 0; e < 8; e += 2) {
-                        const f32x2 v = through_bf16(cv[e] - mv[e], cv[e + 1] - mv[e + 1]);
-                        dot[j] = __builtin_fmaf(qv[e], v[0], dot[j]);
-                        dot[j] = __builtin_fmaf(qv[e + 1], v[1], dot[j]);
-                    }
-                }
-            }
-            // the four sums, transposed: lane bits 5 and 4 name the row
-            float s2[2], s1;
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const bool hi = lane & 32;
-                s2[j] = (hi ? dot[2 + j] : dot[j]) + __shfl_xor(hi ? dot[j] : dot[2 + j], 32, 64);
-            }
-            {
-                const bool hi = lane & 16;
-                s1 = (hi ? s2[1] : s2[0]) + __shfl_xor(hi ? s2[0] : s2[1], 16, 64);
-            }
-#pragma unroll
-            for (int off = 8; off >= 1; off >>= 1) s1 += __shfl_xor(s1, off, 64);
+            const float s1 = coarse_dot4(a, ba.mu, qrow, sidx_s, b0, nblk, lane);
             const int bj = b0 + (lane >> 4);
             if ((lane & 15) == 0 && bj < nblk) samp_s[bj] = (uint64_t)ordered_bits(__builtin_fmaf(-2.f, s1, ba.norm[sidx_s[bj]])) << 32;
         }
@@ -2233,25 +2266,134 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
         nblk = nblk < r && r < most ? r : most;
         __syncthreads();
     }
-    if (tid == 0) {
-        if (!ok) a.flag_list2[atomicAdd(a.flag_count + 1, 1)] = q;
-        if (a.stats) atomicAdd(a.stats + (ok ? (nblk > r ? 1 : 0) : 2), 1ull);
+    if (__builtin_expect(!ok, 0)) {   // uniform (and out of the way of the instruction fetch)
+        if (tid == 0) flagged_s = atomicAdd(a.flag_count, 1);
+        __syncthreads();
+        const int flagged = __builtin_amdgcn_readfirstlane(flagged_s);
+        if (flagged < kMeetQueries) {
+            if (tid == 0) a.flag_list[flagged] = q;   // (and counted in the statistics there)
+        } else {
+            // ---- 5. the 256 blocks with the smallest minima; the first nblk of them are done ----
+            // T = the kTier1-th smallest of kBlkList group minima: at least that many blocks (or all) are <= T
+            auto minimum = [&](int64_t blk) { return ((uint64_t)ordered_bits(bq[blk]) << 32) | (uint32_t)blk; };
+            for (int g = tid; g < kBlkList; g += NT) {
+                uint64_t m = kSentinel;
+                for (int64_t blk = g; blk < ba.nb; blk += kBlkList) {
+                    const uint64_t x = minimum(blk);
+                    m = x < m ? x : m;
+                }
+                ent[g] = m;
+            }
+            if (tid == 0) list_n = 0;
+            __syncthreads();
+            bitonic_sort_lds(ent, kBlkList, tid, NT);
+            const uint64_t t = ent[kTier1 - 1];
+            const uint32_t tk = (uint32_t)(t >> 32);
+            for (int64_t blk = tid; blk < ba.nb; blk += NT) {
+                const uint64_t x = minimum(blk);
+                if (x <= t && (uint32_t)(x >> 32) < kInf) {
+                    const int pos = atomicAdd(&list_n, 1);
+                    if (pos < kBlkList) list[pos] = x;
+                }
+            }
+            __syncthreads();
+            const int got = __builtin_amdgcn_readfirstlane(list_n);
+            if (got <= kBlkList && (tk < kInf || got == ba.real_blocks)) {   // uniform; else the exact scan
+                int n2 = 64;
+                while (n2 < got) n2 <<= 1;
+                for (int i = got + tid; i < n2; i += NT) list[i] = kSentinel;
+                __syncthreads();
+                bitonic_sort_lds(list, n2, tid, NT);
+                const int all = got < kTier1 ? got : kTier1;
+                constexpr int CH = 16, STEP = 64;   // blocks between two merges, and between two certificates
+                for (int from = nblk;;) {
+                    const int end = from + STEP < all ? from + STEP : all;
+                    for (int c0 = from; c0 < end; c0 += CH) {
+                        if (tid == 0) near_n = 0;
+                        __syncthreads();
+                        const uint64_t tau = best_s[a.k - 1];
+                        for (int b = c0 + w; b < c0 + CH && b < end; b += NW) {
+                            const uint64_t x =
+                                rescore_block8(a, qrow, block_first_entry(__builtin_amdgcn_readfirstlane((int)(uint32_t)list[b])), lane);
+                            if ((lane & 7) == 0 && x < tau) ent[atomicAdd(&near_n, 1)] = x;   // <= 8 CH
+                            const uint64_t near = block_nearest(x);
+                            if (lane == 0) {
+                                sidx_s[b] = (uint32_t)near < (uint32_t)a.n ? (int32_t)(uint32_t)near : 0;
+                                sdist_s[b] = from_ordered_bits((uint32_t)(near >> 32));
+                            }
+                        }
+                        __syncthreads();
+                        const int c = __builtin_amdgcn_readfirstlane(near_n);
+                        if (c > 0) {   // uniform
+                            int m2 = 2;
+                            while (m2 < c + a.k) m2 <<= 1;   // <= 256
+                            for (int i = c + tid; i < m2; i += NT) ent[i] = i < c + a.k ? best_s[i - c] : kSentinel;
+                            __syncthreads();
+                            bitonic_sort_lds(ent, m2, tid, NT);
+                            if (tid < a.k) best_s[tid] = ent[tid];
+                        }
+                        __syncthreads();
+                    }
+                    for (int b = from + w * 4; b < end; b += 4 * NW) {
+                        const float dot = coarse_dot4(a, ba.mu, qrow, sidx_s, b, end, lane);
+                        const int bj = b + (lane >> 4);
+                        if ((lane & 15) == 0 && bj < end)
+                            samp_s[bj] = (uint64_t)ordered_bits(__builtin_fmaf(-2.f, dot, ba.norm[sidx_s[bj]])) << 32;
+                    }
+                    if (tid == 0) distinct_s = 0;
+                    __syncthreads();
+                    if (tid < a.k) {
+                        const uint64_t x = best_s[tid];
+                        const int32_t im = x == kSentinel ? 0 : (int32_t)(uint32_t)x;
+                        const float dm = from_ordered_bits((uint32_t)(x >> 32));
+                        a.out_nbr_idx[(int64_t)q * a.k + tid] = im;
+                        a.out_nbr_dist[(int64_t)q * a.k + tid] = dm;
+                        lab_s[tid] = a.labels[im];
+                        dsel_s[tid] = dm;
+                        if (tid == 0) nearest_s = im;
+                    }
+                    for (int i = tid; i < end; i += NT) {
+                        int twin = 0;
+                        for (int j = 0; j < i; ++j) twin |= (sdist_s[j] == sdist_s[i]);
+                        if (!twin) atomicAdd(&distinct_s, 1);
+                    }
+                    __syncthreads();
+                    const uint32_t out = tk >= kInf ? 0xffffffffu : tk, nxt = got > end ? (uint32_t)(list[end] >> 32) : 0xffffffffu;
+                    ok = __builtin_amdgcn_readfirstlane((int)certificate(samp_s, sdist_s, end, dsel_s[a.k - 1], nxt < out ? nxt : out,
+                                                                         distinct_s, tid, &verdict_s, 4.0 + 2.0 * ba.nk)) != 0;
+                    if (ok || end >= all) break;   // uniform
+                    from = end;
+                    __syncthreads();
+                }
+            }
+            if (tid == 0) {
+                if (!ok) a.flag_list2[atomicAdd(a.flag_count + 1, 1)] = q;
+                if (a.stats) atomicAdd(a.stats + (ok ? 1 : 2), 1ull);
+            }
+        }
+    } else if (tid == 0 && a.stats) {
+        atomicAdd(a.stats + (nblk > r ? 1 : 0), 1ull);
     }
     decide_and_write(a, q, tid, lab_s, dsel_s, cnt_s, conf_s, nearest_s);
 }
 
+static int64_t real_blocks_of(int64_t n, int64_t n_pad)   // blocks that hold an entry
+{
+    int64_t real = (n_pad / kTileN - 1) * (kTileN / 8);
+    for (int blk = 0; blk < kTileN / 8; ++blk) real += n_pad - kTileN + block_first_entry(blk) < n;
+    return real;
+}
+
 hipError_t launch_block_finish(const FinishArgs &a, const float *bkey, const float *norm, const float *mu, int64_t n_pad, hipStream_t s)
 {
-    if (a.r < 1 || a.r > kMaxRescore || a.k > kMaxK || a.k > a.r || a.b < 1 || !a.flag_count || !a.flag_list2 || n_pad % kTileN != 0)
+    if (a.r < 1 || a.r > kMaxRescore || a.k > kMaxK || a.k > a.r || a.b < 1 || !a.flag_count || !a.flag_list || !a.flag_list2 || n_pad % kTileN != 0)
         return hipErrorInvalidValue;
     // two blocks more than neighbours confirm most queries (4,096 x 50,000 x 512, k = 10: 112 us with 12 blocks at
     // first, 115 with 11 or 14, 123 with 16); the certificate wants eight samples at least
     int first = a.k + 2 > kCertMinSamples ? a.k + 2 : kCertMinSamples;
     first = first < a.r ? first : a.r;
     const int gather = 2 * a.r < kMaxRescore ? 2 * a.r : kMaxRescore;
-    int64_t real_blocks = (n_pad / kTileN - 1) * (kTileN / 8);
-    for (int blk = 0; blk < kTileN / 8; ++blk) real_blocks += n_pad - kTileN + block_first_entry(blk) < a.n;
-    BlockFinishArgs ba{a, bkey, norm, mu, n_pad / 8, real_blocks, (int)(a.d_pad / kKB), first, gather};
+    BlockFinishArgs ba{a, bkey, norm, mu, n_pad / 8, real_blocks_of(a.n, n_pad), (int)(a.d_pad / kKB), first, gather};
     // Two waves per query where the batch fills the chip with them, four where it does not (50,000 x 512: 1,500
     // queries 52 against 57 us, 600 queries 37 against 28 us; one wave per query is slower than two at both).
     if (a.b >= 1024)
@@ -2283,8 +2425,8 @@ hipError_t launch_finish(const FinishArgs &a, hipStream_t s)
 // an empty launch costs 4.6 us and the gap before it, so the two rounds share one (256 x 2,000 x 512: whole
 // look-up 26.0 -> 24.4 us).
 //
-// Round 1, the wider re-scoring (list 0): up to kTier1 of the candidates gathered by the distance pass
-// are re-scored and the certificate is taken again.  Workgroups take items off a queue: a query, or, with
+// Round 1, the wider re-scoring (list 0): up to kTier1 of the candidates gathered by the distance pass, or of
+// the blocks with the smallest minima, are re-scored and the certificate is taken again.  Workgroups take items off a queue: a query, or, with
 // few flagged queries, a sixteenth of a query's candidates; the last of its sixteen to finish (a ticket
 // per query) decides.  (One request of a 65,536-value layer, 32 MB of rows, kept a single workgroup busy
 // for 630 us; shared it takes 70.  20 queries
@@ -2307,7 +2449,14 @@ struct ScanArgs {
     uint64_t *part_x;    // [items, k] the k nearest of each (query, range), packed (ordered distance, index)
     int max_splits;
     int64_t part_bytes;  // size of part_x
+    // block-minima route (else null / unused): the smallest coarse key of every block, as in BlockFinishArgs
+    const float *bkey, *norm, *mu;
+    int64_t nb, real_blocks;
+    int nk;
+    uint64_t *meet;      // [kMeetQueries, kWiderParts, kMeetEntries] what the workgroups that share a query pass on
 };
+constexpr int kMeetSamples = kTier1 / kWiderParts, kMeetEntries = kMaxK + kMeetSamples;
+constexpr int kWiderList = 1024;   // block minima gathered for the wider re-scoring at most
 
 __global__ __launch_bounds__(256) void follow_up_kernel(ScanArgs sa)
 {
@@ -2326,9 +2475,11 @@ __global__ __launch_bounds__(256) void follow_up_kernel(ScanArgs sa)
     __shared__ int surv_s, last_s, job_s, real_s, distinct_s, verdict_s;
     __shared__ uint32_t excl_s;
 
-    const int n_wider = a.flag_count[0];
+    const int flagged = a.flag_count[0];
     int nf = a.flag_count[1];
-    if (n_wider <= 0 && nf <= 0) return;   // the usual case
+    if (flagged <= 0 && nf <= 0) return;   // the usual case
+    // (of block minima only the first kMeetQueries flagged queries are left to this kernel)
+    const int n_wider = sa.bkey && flagged > kMeetQueries ? kMeetQueries : flagged;
     const int tid = threadIdx.x;
     const int grid = (int)gridDim.x, k = a.k;
 
@@ -2336,7 +2487,8 @@ __global__ __launch_bounds__(256) void follow_up_kernel(ScanArgs sa)
     if (n_wider > 0) {   // uniform
         const int nq = a.count ? *a.count : a.b;
         // few flagged queries: kWiderParts workgroups share each, the distances meet in round 2's scratch
-        const bool split = n_wider * kWiderParts <= grid && (int64_t)n_wider * kTier1 * 4 <= sa.part_bytes;
+        const bool split = n_wider * kWiderParts <= grid &&
+                           (sa.bkey || (int64_t)n_wider * kTier1 * 4 <= sa.part_bytes);
         const int items = split ? n_wider * kWiderParts : n_wider;
         bool held = false;   // an item taken off the queue is finished, but not yet counted
         while (true) {
@@ -2353,68 +2505,203 @@ __global__ __launch_bounds__(256) void follow_up_kernel(ScanArgs sa)
             held = true;
             const int j = split ? job / kWiderParts : job;
             const int q = __builtin_amdgcn_readfirstlane(a.flag_list[j]);
-            const int total = gather_entries(a, q, nq, ent, &real_s, &excl_s, tid, 256);
-            int sort_n = 2;
-            while (sort_n < total) sort_n <<= 1;
-            bitonic_sort_lds(ent, sort_n, tid, 256);
-            const int real = __builtin_amdgcn_readfirstlane(real_s);
-            const int most = real < kTier1 ? real : kTier1;   // (real entries sort in front of the markers)
             const float *qrow = a.queries + (int64_t)(a.sel ? a.sel[q] : q) * a.d;
-            const bool whole_block = a.d >= 4096 && a.d % 8 == 0;
-            // a candidate list (keys-out routes) holds every entry up to its largest pair
-            const uint32_t excl0 = a.part_count ? (real >= a.n || real < 1 ? 0xffffffffu : (uint32_t)(ent[real - 1] >> 32)) : excl_s;
-            if (tid < most) idx_s[tid] = (int32_t)(uint32_t)ent[tid];   // < n: counted as real
-            __syncthreads();
-            auto rescore = [&](int m0, int m) {   // candidates [m0, m)
-                if (whole_block) {
-                    for (int c0 = m0; c0 < m; c0 += 16)
-                        rescore_block_all<256, 16>(a, qrow, idx_s + c0, dist_s + c0, red, m - c0 < 16 ? m - c0 : 16, tid);
-                } else {
-                    rescore_wave<4>(a, qrow, idx_s + m0, dist_s + m0, m - m0, tid >> 6, tid & 63);
+            bool mine = true, ok = false;   // mine: this workgroup decides the query
+            if (sa.bkey) {   // uniform
+                // Selection: the 1,024 groups j mod 1,024 of the block minima; T = the kTier1-th smallest group
+                // minimum, so that at least kTier1 blocks (or all) have a minimum <= T.  Blocks of +inf hold padding, or
+                // entries whose key overflowed, and are not taken.
+                const float *bq = sa.bkey + (size_t)q * sa.nb;
+                constexpr uint32_t kInf = 0xff800000u;
+                auto minimum = [&](int64_t blk) { return ((uint64_t)ordered_bits(bq[blk]) << 32) | (uint32_t)blk; };
+                for (int g = tid; g < 1024; g += 256) {
+                    uint64_t m = kSentinel;
+                    for (int64_t blk = g; blk < sa.nb; blk += 1024) {
+                        const uint64_t x = minimum(blk);
+                        m = x < m ? x : m;
+                    }
+                    ent[g] = m;
+                }
+                if (tid == 0) surv_s = 0;
+                __syncthreads();
+                bitonic_sort_lds(ent, 1024, tid, 256);
+                const uint64_t t = ent[kTier1 - 1];
+                const uint32_t tk = (uint32_t)(t >> 32);
+                uint64_t *blocks = ent + 1024;         // [kWiderList] what is gathered, in order
+                uint64_t *samples = ent + 1024 + kWiderList;   // [kTier1] coarse keys (upper halves) of the blocks' nearest entries
+                for (int64_t blk = tid; blk < sa.nb; blk += 256) {
+                    const uint64_t x = minimum(blk);
+                    if (x <= t && (uint32_t)(x >> 32) < kInf) {
+                        const int pos = atomicAdd(&surv_s, 1);
+                        if (pos < kWiderList) blocks[pos] = x;
+                    }
+                }
+                __syncthreads();
+                const int cnt = __builtin_amdgcn_readfirstlane(surv_s);
+                // more than fit, or entries whose key overflowed are left out: the exact scan
+                const bool sound = cnt <= kWiderList && (tk < kInf || cnt == sa.real_blocks);
+                const int nblk = !sound ? 0 : (cnt < kTier1 ? cnt : kTier1);
+                if (sound) {   // uniform
+                    int n2 = 64;
+                    while (n2 < cnt) n2 <<= 1;
+                    for (int i = cnt + tid; i < n2; i += 256) blocks[i] = kSentinel;
+                    __syncthreads();
+                    bitonic_sort_lds(blocks, n2, tid, 256);
+                }
+                // exact re-scoring, sixteen blocks at a time: their nearest entries as samples, the k nearest of all
+                const int w = tid >> 6, lane = tid & 63, part = split ? job % kWiderParts : 0;
+                const int p0 = part * kMeetSamples, p1 = split && p0 + kMeetSamples < nblk ? p0 + kMeetSamples : nblk;
+                if (tid < kMaxK) best_s[tid] = kSentinel;
+                for (int b0 = p0; b0 < p1; b0 += kMeetSamples) {
+                    if (tid == 0) surv_s = 0;
+                    __syncthreads();
+                    const int b1 = b0 + kMeetSamples < p1 ? b0 + kMeetSamples : p1;
+                    const uint64_t tau = best_s[k - 1];
+                    for (int b = b0 + w; b < b1; b += 4) {
+                        const uint64_t x =
+                            rescore_block8(a, qrow, block_first_entry(__builtin_amdgcn_readfirstlane((int)(uint32_t)blocks[b])), lane);
+                        if ((lane & 7) == 0 && x < tau) ent[atomicAdd(&surv_s, 1)] = x;   // <= 128
+                        const uint64_t near = block_nearest(x);
+                        if (lane == 0) {
+                            idx_s[b] = (uint32_t)near < (uint32_t)a.n ? (int32_t)(uint32_t)near : 0;
+                            dist_s[b] = from_ordered_bits((uint32_t)(near >> 32));
+                        }
+                    }
+                    __syncthreads();
+                    const int c = __builtin_amdgcn_readfirstlane(surv_s);
+                    if (c > 0) {   // uniform
+                        int n2 = 2;
+                        while (n2 < c + k) n2 <<= 1;   // <= 256
+                        for (int i = c + tid; i < n2; i += 256) ent[i] = i < c + k ? best_s[i - c] : kSentinel;
+                        __syncthreads();
+                        bitonic_sort_lds(ent, n2, tid, 256);
+                        if (tid < k) best_s[tid] = ent[tid];
+                    }
                     __syncthreads();
                 }
-            };
-            auto confirm = [&](int m) {
-                if (tid == 0) distinct_s = 0;
-                __syncthreads();
-                rank_and_emit(a, q, m, tid, 256, dist_s, idx_s, lab_s, dsel_s, &nearest_s, &distinct_s);
-                __syncthreads();
-                uint32_t excl = excl0;
-                if (real > m) {
-                    const uint32_t nxt = (uint32_t)(ent[m] >> 32);
-                    excl = nxt < excl ? nxt : excl;
-                }
-                return __builtin_amdgcn_readfirstlane(
-                           (int)certificate(ent, dist_s, m, dsel_s[k - 1], excl, distinct_s, tid, &verdict_s)) != 0;
-            };
-            bool mine = true, ok = false;   // mine: this workgroup decides the query
-            if (split) {
-                constexpr int per = kTier1 / kWiderParts;
-                float *meet = reinterpret_cast<float *>(sa.part_x) + (size_t)j * kTier1;
-                const int m0 = (job % kWiderParts) * per, m = m0 + per < most ? m0 + per : most;
-                if (m0 < m) rescore(m0, m);
-                // device-coherent stores, complete before the ticket is taken, and device-coherent loads: no fence,
-                // which would write back the whole L2 (a fence per wave took 100 us in place of 45 on 20 queries)
-                if (tid >= m0 && tid < m) __hip_atomic_store(meet + tid, dist_s[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                __syncthreads();
-                if (tid == 0) {
-                    last_s = (atomicAdd(&sa.tickets[j], 1) == kWiderParts - 1);
-                    if (last_s) atomicExch(&sa.tickets[j], 0);   // round 2 finds it zero
+                for (int b0 = p0 + w * 4; b0 < p1; b0 += 16) {
+                    const float dot = coarse_dot4(a, sa.mu, qrow, idx_s, b0, p1, lane);
+                    const int bj = b0 + (lane >> 4);
+                    if ((lane & 15) == 0 && bj < p1)
+                        samples[bj] = (uint64_t)ordered_bits(__builtin_fmaf(-2.f, dot, sa.norm[idx_s[bj]])) << 32;
                 }
                 __syncthreads();
-                mine = __builtin_amdgcn_readfirstlane(last_s) != 0;
-                if (mine) {
-                    if (tid < most) dist_s[tid] = __hip_atomic_load(meet + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    ok = confirm(most);
+                if (split) {
+                    uint64_t *meet = sa.meet + (size_t)j * kWiderParts * kMeetEntries, *own = meet + part * kMeetEntries;
+                    if (tid < k) __hip_atomic_store(own + tid, best_s[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (p0 + tid < p1 && tid < kMeetSamples)
+                        __hip_atomic_store(own + kMaxK + tid, samples[p0 + tid] | __float_as_uint(dist_s[p0 + tid]), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    __syncthreads();
+                    if (tid == 0) {
+                        last_s = (atomicAdd(&sa.tickets[j], 1) == kWiderParts - 1);
+                        if (last_s) atomicExch(&sa.tickets[j], 0);   // round 2 finds it zero
+                    }
+                    __syncthreads();
+                    mine = __builtin_amdgcn_readfirstlane(last_s) != 0;
+                    if (mine) {
+                        for (int i = tid; i < 1024; i += 256)
+                            ent[i] = i < kWiderParts * k ? __hip_atomic_load(meet + i / k * kMeetEntries + i % k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                                         : kSentinel;
+                        if (tid < nblk) {
+                            const uint64_t sv = __hip_atomic_load(meet + tid / kMeetSamples * kMeetEntries + kMaxK + tid % kMeetSamples,
+                                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            samples[tid] = sv & 0xffffffff00000000ull;
+                            dist_s[tid] = __uint_as_float((uint32_t)sv);
+                        }
+                        __syncthreads();
+                        bitonic_sort_lds(ent, 1024, tid, 256);
+                        if (tid < k) best_s[tid] = ent[tid];
+                        __syncthreads();
+                    }
+                }
+                if (mine) {   // uniform
+                    if (tid == 0) distinct_s = 0;
+                    __syncthreads();
+                    if (tid < k) {
+                        const uint64_t x = best_s[tid];   // (a marker only where nothing sound was selected: the exact scan follows)
+                        const int32_t im = x == kSentinel ? 0 : (int32_t)(uint32_t)x;
+                        const float dm = from_ordered_bits((uint32_t)(x >> 32));
+                        a.out_nbr_idx[(int64_t)q * k + tid] = im;
+                        a.out_nbr_dist[(int64_t)q * k + tid] = dm;
+                        lab_s[tid] = a.labels[im];
+                        dsel_s[tid] = dm;
+                        if (tid == 0) nearest_s = im;
+                    }
+                    if (tid < nblk) {
+                        int twin = 0;
+                        for (int i = 0; i < tid; ++i) twin |= (dist_s[i] == dist_s[tid]);
+                        if (!twin) atomicAdd(&distinct_s, 1);
+                    }
+                    __syncthreads();
+                    const uint32_t out = tk >= kInf ? 0xffffffffu : tk;
+                    const uint32_t nxt = cnt > nblk && sound ? (uint32_t)(blocks[nblk] >> 32) : 0xffffffffu;
+                    ok = sound && __builtin_amdgcn_readfirstlane((int)certificate(samples, dist_s, nblk, dsel_s[k - 1], nxt < out ? nxt : out,
+                                                                                  distinct_s, tid, &verdict_s, 4.0 + 2.0 * sa.nk)) != 0;
                 }
             } else {
-                // many flagged queries: a workgroup each; of long rows twice as many at a time, until the
-                // certificate, whose bound grows with the first key left out, confirms the result
-                for (int m0 = 0, m = whole_block ? 64 : most; !ok && m0 < most; m0 = m, m *= 2) {
-                    m = m < most ? m : most;
-                    rescore(m0, m);
-                    ok = confirm(m);
+                const int total = gather_entries(a, q, nq, ent, &real_s, &excl_s, tid, 256);
+                int sort_n = 2;
+                while (sort_n < total) sort_n <<= 1;
+                bitonic_sort_lds(ent, sort_n, tid, 256);
+                const int real = __builtin_amdgcn_readfirstlane(real_s);
+                const int most = real < kTier1 ? real : kTier1;   // (real entries sort in front of the markers)
+                const bool whole_block = a.d >= 4096 && a.d % 8 == 0;
+                // a candidate list (keys-out routes) holds every entry up to its largest pair
+                const uint32_t excl0 = a.part_count ? (real >= a.n || real < 1 ? 0xffffffffu : (uint32_t)(ent[real - 1] >> 32)) : excl_s;
+                if (tid < most) idx_s[tid] = (int32_t)(uint32_t)ent[tid];   // < n: counted as real
+                __syncthreads();
+                auto rescore = [&](int m0, int m) {   // candidates [m0, m)
+                    if (whole_block) {
+                        for (int c0 = m0; c0 < m; c0 += 16)
+                            rescore_block_all<256, 16>(a, qrow, idx_s + c0, dist_s + c0, red, m - c0 < 16 ? m - c0 : 16, tid);
+                    } else {
+                        rescore_wave<4>(a, qrow, idx_s + m0, dist_s + m0, m - m0, tid >> 6, tid & 63);
+                        __syncthreads();
+                    }
+                };
+                auto confirm = [&](int m) {
+                    if (tid == 0) distinct_s = 0;
+                    __syncthreads();
+                    rank_and_emit(a, q, m, tid, 256, dist_s, idx_s, lab_s, dsel_s, &nearest_s, &distinct_s);
+                    __syncthreads();
+                    uint32_t excl = excl0;
+                    if (real > m) {
+                        const uint32_t nxt = (uint32_t)(ent[m] >> 32);
+                        excl = nxt < excl ? nxt : excl;
+                    }
+                    return __builtin_amdgcn_readfirstlane(
+                               (int)certificate(ent, dist_s, m, dsel_s[k - 1], excl, distinct_s, tid, &verdict_s)) != 0;
+                };
+                if (split) {
+                    constexpr int per = kTier1 / kWiderParts;
+                    float *meet = reinterpret_cast<float *>(sa.part_x) + (size_t)j * kTier1;
+                    const int m0 = (job % kWiderParts) * per, m = m0 + per < most ? m0 + per : most;
+                    if (m0 < m) rescore(m0, m);
+                    // device-coherent stores, complete before the ticket is taken, and device-coherent loads: no fence,
+                    // which would write back the whole L2 (a fence per wave took 100 us in place of 45 on 20 queries)
+                    if (tid >= m0 && tid < m) __hip_atomic_store(meet + tid, dist_s[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    __syncthreads();
+                    if (tid == 0) {
+                        last_s = (atomicAdd(&sa.tickets[j], 1) == kWiderParts - 1);
+                        if (last_s) atomicExch(&sa.tickets[j], 0);   // round 2 finds it zero
+                    }
+                    __syncthreads();
+                    mine = __builtin_amdgcn_readfirstlane(last_s) != 0;
+                    if (mine) {
+                        if (tid < most) dist_s[tid] = __hip_atomic_load(meet + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        ok = confirm(most);
+                    }
+                } else {
+                    // many flagged queries: a workgroup each; of long rows twice as many at a time, until the
+                    // certificate, whose bound grows with the first key left out, confirms the result
+                    for (int m0 = 0, m = whole_block ? 64 : most; !ok && m0 < most; m0 = m, m *= 2) {
+                        m = m < most ? m : most;
+                        rescore(m0, m);
+                        ok = confirm(m);
+                    }
                 }
             }
             if (mine) {
@@ -2556,16 +2843,30 @@ size_t scan_scratch_entries(int64_t b, int k, int num_cus)
     return (size_t)items * (size_t)k;
 }
 
-hipError_t launch_follow_up(const FinishArgs &a, int32_t *tickets, uint64_t *part_x, int num_cus, hipStream_t s)
+size_t follow_up_meet_entries() { return (size_t)kMeetQueries * kWiderParts * kMeetEntries; }
+
+hipError_t launch_follow_up(const FinishArgs &a, int32_t *tickets, uint64_t *part_x, int num_cus, const BlockMinima *blocks, hipStream_t s)
 {
     if (!a.flag_count || !a.flag_list || !a.flag_list2 || !tickets || !part_x || a.k < 1 || a.k > kMaxK) return hipErrorInvalidValue;
-    const int total = a.part_count ? a.part_stride : a.alloc_splits * a.r;   // (0: nothing goes on list 0)
+    const int total = a.part_count ? a.part_stride : a.alloc_splits * a.r;   // (0: block minima, or nothing goes on list 0)
     if (total > kMaxMergeEntries) return hipErrorInvalidValue;
     const int grid = scan_grid(num_cus, a.b);
     ScanArgs sa{a, tickets, part_x, scan_max_splits(a.k) < grid ? scan_max_splits(a.k) : grid,
                 (int64_t)(scan_scratch_entries(a.b, a.k, num_cus) * 8)};
     int cap = 512;
-    while (cap < sa.max_splits * a.k || cap < total) cap <<= 1;
+    if (blocks) {
+        if (!blocks->bkey || !blocks->norm || !blocks->meet || total != 0) return hipErrorInvalidValue;
+        sa.bkey = blocks->bkey;
+        sa.norm = blocks->norm;
+        sa.mu = blocks->mu;
+        sa.nb = blocks->n_pad / 8;
+        sa.real_blocks = real_blocks_of(a.n, blocks->n_pad);
+        sa.nk = (int)(a.d_pad / kKB);
+        sa.meet = blocks->meet;
+        static_assert(1024 + kWiderList + kTier1 <= 4096, "group minima, blocks, samples");
+        cap = 4096;
+    }
+    while (cap < sa.max_splits * a.k || cap < total) cap <<= 1;   // (a power of two: the sorts pad to one)
     hipLaunchKernelGGL(follow_up_kernel, dim3((unsigned)grid), dim3(256), (size_t)cap * sizeof(uint64_t), s, sa);
     return hipGetLastError();
 }

@@ -227,7 +227,7 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
             out->ws_bytes += keys_finish_workspace_bytes(out->plan.b_pad, L.n_pad, r, kAlign) +
                              align_up(dist_partial_bytes(out->plan));
         else if (out->blocks)
-            out->ws_bytes += align_up((size_t)out->plan.b_pad * (L.n_pad / 8) * 4);
+            out->ws_bytes += align_up((size_t)out->plan.b_pad * (L.n_pad / 8) * 4) + align_up(follow_up_meet_entries() * 8);
         else
             out->ws_bytes += align_up((size_t)out->plan.b_pad * lists_per_query(out->plan, cascade) * r * 8);
         out->ws_bytes += scan_bytes;
@@ -346,7 +346,7 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
     FinishArgs fa{};
     marks.mark(1);
     const float *keys = nullptr;
-    const float *bkey = nullptr;
+    BlockMinima minima{nullptr, L.norm, L.mu, L.n_pad, nullptr};
     const uint64_t *keys_bmin = nullptr;
     uint64_t *keys_cand = nullptr;
     int32_t *keys_cand_count = nullptr;
@@ -402,7 +402,8 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
         } else if (sh.blocks) {
             da.keys = ws.take<float>((size_t)sh.plan.b_pad * (L.n_pad / 8));
             if (launch_dist_topr(sh.plan, da, s) != hipSuccess) return FREEZE_EHIP;
-            bkey = da.keys;
+            minima.bkey = da.keys;
+            minima.meet = ws.take<uint64_t>(follow_up_meet_entries());
         } else {
             // the workspace was sized by sh.cascade; the balanced decomposition only goes with it off
             const int alloc = lists_per_query(sh.plan, sh.cascade);
@@ -454,14 +455,14 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
         if (launch_skinny_finish(fa, skinny_bmin, skinny_wgmin, L.n_pad / 32, sh.plan.n_splits,
                                  (int)(L.n_pad / kTileN), skinny_cand, skinny_samp, tickets + kSkinnyRows, s) != hipSuccess)
             return FREEZE_EHIP;
-    } else if (bkey) {
-        if (launch_block_finish(fa, bkey, L.norm, L.mu, L.n_pad, s) != hipSuccess) return FREEZE_EHIP;
+    } else if (minima.bkey) {
+        if (launch_block_finish(fa, minima.bkey, L.norm, L.mu, L.n_pad, s) != hipSuccess) return FREEZE_EHIP;
     } else if ((keys ? launch_keys_finish(fa, keys, keys_bmin, L.n_pad, keys_cand, keys_cand_count, s) : launch_finish(fa, s)) !=
                hipSuccess) {
         return FREEZE_EHIP;
     }
     // the queries whose result the certificate did not confirm (usually none) are redone exactly
-    if (launch_follow_up(fa, tickets, scan_lists, ctx->num_cus, s) != hipSuccess) return FREEZE_EHIP;
+    if (launch_follow_up(fa, tickets, scan_lists, ctx->num_cus, minima.bkey ? &minima : nullptr, s) != hipSuccess) return FREEZE_EHIP;
     marks.mark(3);
     marks.done();
     return FREEZE_OK;

@@ -262,7 +262,8 @@ struct FinishArgs {
     // Queries whose result the certificate could not confirm, by their (compact) positions: list 0
     // (flag_list, counted in flag_count[0]) is redone by the wider re-scoring, list 1 (flag_list2,
     // flag_count[1]) by the exact scan.  flag_count[2] and [3] count the queries of list 0 taken and done.
-    // The first kernel of the look-up clears all four.
+    // The first kernel of the look-up clears all four.  (Block minima: list 0 holds the first 32 of them only, the
+    // finishing kernel goes on with the others itself.)
     int32_t *flag_count;    // [kFlagCounts]
     int32_t *flag_list;     // [b]
     int32_t *flag_list2;    // [b]
@@ -285,9 +286,16 @@ hipError_t launch_block_finish(const FinishArgs &a, const float *bkey, const flo
 // Follow-up for the flagged queries, both lists: the wider re-scoring of list 0, then the exact scan of
 // list 1 (brute-force fp32 distances to every entry, the k nearest, the label and hit decision, written
 // over the outputs of those queries).
-// tickets [b] int32 (zero on entry, zero again afterwards), part_x scan_scratch_entries(b, k, num_cus) u64.
+// tickets [b] int32 (zero on entry, zero again afterwards), part_x scan_scratch_entries(b, k, num_cus) u64;
+// blocks: where the wider re-scoring selects from (block-minima route), or null (a.part holds the candidates).
+struct BlockMinima {
+    const float *bkey, *norm, *mu;   // as for launch_block_finish
+    int64_t n_pad;
+    uint64_t *meet;                  // follow_up_meet_entries() u64 of scratch
+};
 size_t scan_scratch_entries(int64_t b, int k, int num_cus);
-hipError_t launch_follow_up(const FinishArgs &a, int32_t *tickets, uint64_t *part_x, int num_cus, hipStream_t s);
+size_t follow_up_meet_entries();
+hipError_t launch_follow_up(const FinishArgs &a, int32_t *tickets, uint64_t *part_x, int num_cus, const BlockMinima *blocks, hipStream_t s);
 // Small-batch path: from the block minima [b, nb] and the per-group minima to the outputs (takes
 // a.r blocks).  cand and samp are scratch (skinny_finish_workspace_bytes covers both); tickets
 // [16] int32 must be zero on entry and are left zero.

@@ -61,3 +61,45 @@ def _check(kind, n, d, b, k, dtype, most_scanned):
 ])
 def test_materialised_keys(kind, n, d, b, k, dtype, most_scanned):
     _check(kind, n, d, b, k, dtype, most_scanned)
+
+
+@pytest.mark.parametrize("kind,n,d,b,k,dtype,most_scanned", [
+    ("copies", 10000, 512, 300, 10, torch.bfloat16, 0.0),
+    ("copies", 10000, 517, 1100, 10, torch.float32, 0.0),     # more flagged queries than workgroups
+    ("copies", 20000, 1030, 300, 20, torch.bfloat16, 0.0),    # R = 32, odd rows
+    ("neighbours", 10000, 256, 300, 5, torch.bfloat16, 0.0),
+    ("neighbours", 4000, 100, 260, 1, torch.float32, 0.0),
+    ("copies", 300000, 64, 140, 10, torch.bfloat16, 0.05),    # more minima than the group minima's first round
+    (0.02, 5000, 256, 600, 10, torch.bfloat16, 0.1),
+    (0.05, 3000, 512, 300, 40, torch.float32, 0.1),           # R = 64
+])
+def test_block_minima(kind, n, d, b, k, dtype, most_scanned):
+    _check(kind, n, d, b, k, dtype, most_scanned)
+
+
+def test_few_flagged_queries_share_workgroups():
+    """Block minima with seven queries among entries present 21 times, the others among ordinary ones: sixteen workgroups
+    share the wider re-scoring of each of the seven."""
+    n, d, b, k = 6000, 256, 300, 10
+    ent, lab, q = _data("copies", n, d, b, torch.float32, 5)
+    g = torch.Generator().manual_seed(6)
+    ent = torch.cat([3.0 * ent, torch.randn(n, d, generator=g)]).to(torch.bfloat16)
+    lab = torch.cat([lab, lab])
+    q = 3.0 * q
+    q[7:] = 0.7 * torch.randn(b - 7, d, generator=g)
+    c = torch.zeros(3, dtype=torch.int64, device="cuda")
+    fc = binding.FreezeCache(1)
+    try:
+        binding.freeze_lookup_stats_attach(fc.ctx, c)
+        binding.freeze_set_centring(fc.ctx, 0)
+        fc.build_layer(0, ent.cuda(), lab.cuda(), 10)
+        out = fc.lookup(0, q.cuda(), k, 8)
+        torch.cuda.synchronize()
+        got = {key: v.cpu().numpy() for key, v in out.items()}
+    finally:
+        fc.close()
+    e_h, l_h, q_h = _host_entries(ent), lab.numpy(), q.numpy()
+    ref = parity.oracle_reference(q_h, e_h, l_h, 10, k, 8)
+    parity.assert_lookup_matches(got, ref, q_h, e_h, l_h, 10, k, 8, rel=TIGHT, dist_rel=TIGHT)
+    c = c.tolist()
+    assert sum(c) == b and 7 <= c[1] <= 20 and c[2] == 0, c
