@@ -682,16 +682,22 @@ __device__ __forceinline__ void rescore_block_all(const FinishArgs &a, const flo
             if (g < r) {   // uniform
                 if (a.c_f32) {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const float *c = a.c_f32 + (int64_t)idx_s[(g + j < r) ? g + j : r - 1] * a.d_pad + i;
-                        const f32x4 c0v = *reinterpret_cast<const f32x4 *>(c);
-                        const f32x4 c1v = *reinterpret_cast<const f32x4 *>(c + 4);
-                        const float cv[8] = {c0v[0], c0v[1], c0v[2], c0v[3], c1v[0], c1v[1], c1v[2], c1v[3]};
+                    for (int j0 = 0; j0 < 8; j0 += 4) {
+                        f32x4 cv[4][2];
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            const float df = qv[e] - cv[e];
-                            acc[g + j] = __builtin_fmaf(df, df, acc[g + j]);
+                        for (int j = 0; j < 4; ++j) {
+                            const float *c = a.c_f32 + (int64_t)idx_s[(g + j0 + j < r) ? g + j0 + j : r - 1] * a.d_pad + i;
+                            cv[j][0] = *reinterpret_cast<const f32x4 *>(c);
+                            cv[j][1] = *reinterpret_cast<const f32x4 *>(c + 4);
                         }
+                        __builtin_amdgcn_sched_barrier(0);   // four rows' loads leave before the first is used
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) {
+                                const float df = qv[e] - cv[j][e >> 2][e & 3];
+                                acc[g + j0 + j] = __builtin_fmaf(df, df, acc[g + j0 + j]);
+                            }
                     }
                 } else {
                     uint4 cb[8];
