@@ -553,19 +553,81 @@ __device__ __forceinline__ void rescore_wave(const FinishArgs &a, const float *q
                 }
             }
         } else {
-            for (int64_t i = lane; i < a.d; i += 64) {
-                const float qv = qrow[i];
+            // Rows of another length: chain l of 64 takes elements l, l + 64, ..  fp32: a chain per lane, a few steps'
+            // loads of all rows before the first is used (20,000 x 4,101, 1,100 queries: whole look-ups 694 -> 414 us).
+            constexpr int U = G <= 4 ? 4 : (G <= 8 ? 2 : 1);
+            if (a.c_f32) {   // uniform
+                auto steps = [&](int64_t i, auto count) {
+                    constexpr int N = decltype(count)::value;
+                    float qv[N], cv[G][N];
 #pragma unroll
-                for (int j = 0; j < G; ++j) {
-                    float cv;
-                    if (a.c_f32) {
-                        cv = a.c_f32[cand[j] * a.d_pad + i];
-                    } else {
-                        cv = bf16_to_f32(a.c_rows[cand[j] * a.d_pad + i]);
+                    for (int u = 0; u < N; ++u) {
+                        qv[u] = qrow[i + u * 64];
+#pragma unroll
+                        for (int j = 0; j < G; ++j) cv[j][u] = a.c_f32[cand[j] * a.d_pad + i + u * 64];
                     }
-                    const float df = qv - cv;
-                    acc[j] = __builtin_fmaf(df, df, acc[j]);
+#pragma unroll
+                    for (int u = 0; u < N; ++u)
+#pragma unroll
+                        for (int j = 0; j < G; ++j) {
+                            const float df = qv[u] - cv[j][u];
+                            acc[j] = __builtin_fmaf(df, df, acc[j]);
+                        }
+                };
+                int64_t i = lane;
+                for (; i + (U - 1) * 64 < a.d; i += U * 64) steps(i, std::integral_constant<int, U>{});
+                for (; i < a.d; i += 64) steps(i, std::integral_constant<int, 1>{});
+            } else {
+                // bf16: half a wave per row, chains 2 p and 2 p + 1 in lane p of the half, so that a lane's load is 4 bytes
+                // (39 x 27,486, 11,169 queries: 5,298 us with a chain per lane and 2-byte loads).  Elements past d are zeros on
+                // both sides and leave a chain as it is.
+                constexpr int P = (G + 1) / 2;   // pairs of rows
+                const int p = lane & 31, hf = lane >> 5;
+                const uint32_t *row[P];
+                float ch[P][2];
+#pragma unroll
+                for (int j = 0; j < P; ++j) {
+                    const int64_t lo = cand[2 * j], hi = cand[2 * j + 1 < G ? 2 * j + 1 : 2 * j];
+                    row[j] = reinterpret_cast<const uint32_t *>(a.c_rows + (hf ? hi : lo) * a.d_pad) + p;
+                    ch[j][0] = ch[j][1] = 0.f;
                 }
+                auto steps = [&](int64_t i0, auto count) {   // elements [i0, i0 + 64 N), i0 + 64 N <= d_pad
+                    constexpr int N = decltype(count)::value;
+                    float qv[N][2];
+                    uint32_t cv[P][N];
+#pragma unroll
+                    for (int u = 0; u < N; ++u) {
+                        const int64_t i = i0 + u * 64 + 2 * p;
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) qv[u][h] = i + h < a.d ? qrow[i + h] : 0.f;
+#pragma unroll
+                        for (int j = 0; j < P; ++j) cv[j][u] = row[j][(i0 >> 1) + u * 32];
+                    }
+#pragma unroll
+                    for (int u = 0; u < N; ++u)
+#pragma unroll
+                        for (int j = 0; j < P; ++j) {
+                            const float d0 = qv[u][0] - __uint_as_float(cv[j][u] << 16);
+                            ch[j][0] = __builtin_fmaf(d0, d0, ch[j][0]);
+                            const float d1 = qv[u][1] - __uint_as_float(cv[j][u] & 0xffff0000u);
+                            ch[j][1] = __builtin_fmaf(d1, d1, ch[j][1]);
+                        }
+                };
+                int64_t i0 = 0;
+                for (; i0 + U * 64 <= a.d_pad; i0 += U * 64) steps(i0, std::integral_constant<int, U>{});
+                for (; i0 < a.d_pad; i0 += 64) steps(i0, std::integral_constant<int, 1>{});
+                // the butterfly below, over chains 32, 16, 8, 4, 2 and 1 apart: lanes 16, 8, 4, 2 and 1 apart within the
+                // half, then the lane's two chains
+#pragma unroll
+                for (int j = 0; j < P; ++j) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int off = 16; off >= 1; off >>= 1) ch[j][h] += __shfl_xor(ch[j][h], off, 64);
+                    const int c = c0 + 2 * j + hf;
+                    if (p == 0 && 2 * j + hf < G && c < r) dist_s[c] = ch[j][0] + ch[j][1];
+                }
+                continue;
             }
         }
 #pragma unroll
@@ -2663,7 +2725,9 @@ __global__ __launch_bounds__(256) void follow_up_kernel(ScanArgs sa)
                         for (int c0 = m0; c0 < m; c0 += 16)
                             rescore_block_all<256, 16>(a, qrow, idx_s + c0, dist_s + c0, red, m - c0 < 16 ? m - c0 : 16, tid);
                     } else {
-                        rescore_wave<4>(a, qrow, idx_s + m0, dist_s + m0, m - m0, tid >> 6, tid & 63);
+                        // (sixteen rows in flight per wave where there are enough: 4,538 x 29,747 fp32, 47 queries 901 us, 1,474 with four)
+                        if (m - m0 > 32) rescore_wave<16>(a, qrow, idx_s + m0, dist_s + m0, m - m0, tid >> 6, tid & 63);
+                        else rescore_wave<4>(a, qrow, idx_s + m0, dist_s + m0, m - m0, tid >> 6, tid & 63);
                         __syncthreads();
                     }
                 };

@@ -230,3 +230,47 @@ def test_rescoring_by_groups_of_waves(n, d, b, k, r, dtype):
 ])
 def test_kmeans_in_grouped_order(n, d, kc):
     kmeans.test_kmeans_build_and_lookup_against_oracle(n, d, kc, 7, 2, False)
+
+
+def _distance_in_order(q, row):
+    """sum (q_i - c_i)^2 in fp32 as the library adds it up for rows whose length is no multiple of eight: chain l of 64 takes
+    elements l, l + 64, .. with fused multiply-adds, then the chains 32, 16, 8, 4, 2 and 1 apart are added.  q, row [m, d]."""
+    m, d = q.shape
+    pad = -d % 64
+    diff = np.pad(q - row, ((0, 0), (0, pad))).reshape(m, -1, 64)        # fp32; padding adds zeros
+    acc = np.zeros((m, 64), dtype=np.float32)
+    for s in range(diff.shape[1]):
+        x = diff[:, s].astype(np.float64)
+        acc = (x * x + acc.astype(np.float64)).astype(np.float32)        # the product is exact in fp64
+    lane = np.arange(64)
+    for off in (32, 16, 8, 4, 2, 1):
+        acc = acc + acc[:, lane ^ off]
+    return acc[:, 0]
+
+
+@pytest.mark.parametrize("n,d,b,k,dtype", [
+    (3000, 517, 300, 10, torch.bfloat16),     # block minima
+    (3000, 517, 300, 10, torch.float32),
+    (3000, 517, 100, 20, torch.bfloat16),     # keys: one or two rows per wave
+    (3000, 517, 100, 40, torch.float32),      # ... four
+    (3000, 517, 100, 1, torch.bfloat16),      # fewer rows than waves
+    (3000, 517, 9, 10, torch.bfloat16),       # small-batch kernel
+    (1500, 4101, 1030, 10, torch.bfloat16),   # lists: four rows per wave
+    (1500, 4101, 1030, 20, torch.float32),    # ... eight
+    (1500, 4101, 1030, 40, torch.bfloat16),   # ... sixteen
+    (700, 62, 300, 5, torch.float32),         # shorter than a wave
+])
+def test_order_of_additions(n, d, b, k, dtype):
+    """Distances bit for bit, whichever kernel formed them."""
+    L, q = _layer(n, d, b, k, dtype, 3 + n + d + b)
+    fc = binding.FreezeCache(1)
+    try:
+        fc.build_layer(0, L.entries.cuda(), L.labels.cuda(), 10)
+        out = fc.lookup(0, q.cuda(), k, max(1, k - 2))
+        torch.cuda.synchronize()
+        idx, dist = out["idx"].cpu().numpy(), out["dist"].cpu().numpy()
+    finally:
+        fc.close()
+    ent, q = L.entries.float().numpy(), q.numpy()
+    for j in (0, k // 2, k - 1):
+        assert np.array_equal(_distance_in_order(q, ent[idx[:, j]]), dist[:, j]), j
