@@ -274,3 +274,25 @@ def test_order_of_additions(n, d, b, k, dtype):
     ent, q = L.entries.float().numpy(), q.numpy()
     for j in (0, k // 2, k - 1):
         assert np.array_equal(_distance_in_order(q, ent[idx[:, j]]), dist[:, j]), j
+
+
+@pytest.mark.parametrize("n,d,b,k", [(20000, 2, 1, 1), (20000, 2, 3, 2), (20000, 2, 1, 3), (20000, 3, 2, 30), (500, 1, 5, 2)])
+def test_merge_of_the_exact_scan(n, d, b, k):
+    """Dense points on a line or plane, which the coarse key cannot rank: every query is scanned, and the lists of up to 512
+    workgroups meet, few enough in all to be sorted at once or not."""
+    g = torch.Generator().manual_seed(n + d + k)
+    ent, q = torch.rand(n, d, generator=g), torch.rand(b, d, generator=g)
+    lab = torch.randint(0, 10, (n,), generator=g, dtype=torch.int32)
+    fc = binding.FreezeCache(1)
+    try:
+        c = torch.zeros(3, dtype=torch.int64, device="cuda")
+        binding.freeze_lookup_stats_attach(fc.ctx, c)
+        fc.build_layer(0, ent.cuda(), lab.cuda(), 10)
+        out = fc.lookup(0, q.cuda(), k, 1)
+        torch.cuda.synchronize()
+        got = {key: v.cpu().numpy() for key, v in out.items()}
+    finally:
+        fc.close()
+    ref = parity.oracle_reference(q.numpy(), ent.numpy(), lab.numpy(), 10, k, 1)
+    parity.assert_lookup_matches(got, ref, q.numpy(), ent.numpy(), lab.numpy(), 10, k, 1, rel=TIGHT, dist_rel=TIGHT)
+    assert n < 1000 or c.tolist()[2] > 0
