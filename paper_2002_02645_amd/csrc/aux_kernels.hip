@@ -2242,7 +2242,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
     const float *qrow = a.queries + (int64_t)(a.sel ? a.sel[q] : q) * a.d;
     bool ok = false;
     // first ba.first blocks, unconfirmed queries R, then all that were gathered
-    int done = 0, nblk = ba.first < cnt ? ba.first : cnt;
+    // (where every block with an entry was gathered, and they are few, all at once: no certificate is needed then)
+    int done = 0, nblk = cnt <= (t1 >= kInf ? 2 * ba.first : ba.first) ? cnt : ba.first;
+    nblk = nblk < RMAX ? nblk : RMAX;
     while (true) {
         // ---- 2. exact re-scoring of blocks [done, nblk): packed (distance, index) of their entries ----
         for (int b = done + w; b < nblk; b += NW) {
@@ -2309,6 +2311,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
         }
 
         // ---- 4. the certificate ----
+        ok = t1 >= kInf && nblk >= cnt;   // nothing is left out
+        if (ok) {   // uniform
+            __syncthreads();
+            break;
+        }
         for (int b0 = done + w * 4; b0 < nblk; b0 += 4 * NW) {
             const float s1 = coarse_dot4(a, ba.mu, qrow, sidx_s, b0, nblk, lane);
             const int bj = b0 + (lane >> 4);
@@ -2320,7 +2327,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
             if (!twin) atomicAdd(&distinct_s, 1);
         }
         __syncthreads();
-        // what was not gathered has a key above T (nothing is left out when T is infinite: see above)
+        // what was not gathered has a key above T (nothing when T is infinite: see above)
         uint32_t excl = t1 >= kInf ? 0xffffffffu : t1;
         if (cnt > nblk) {
             const uint32_t nxt = (uint32_t)(list[nblk] >> 32);

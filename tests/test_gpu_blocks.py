@@ -22,6 +22,8 @@ def _inputs(n, d, b, k, dtype, seed, relu=True):
 
 @pytest.mark.parametrize("n,d,b,k,dtype", [
     (300, 64, 257, 5, torch.bfloat16),       # two k-steps a tile: fewer than the ring's stages; 38 blocks with an entry
+    (51, 48, 300, 1, torch.float32),         # a few blocks in all: taken at once
+    (97, 60, 600, 5, torch.bfloat16),
     (256, 20, 513, 10, torch.float32),       # one cache tile, a third query tile with one row, d not a multiple of 8
     (2049, 100, 300, 1, torch.bfloat16),     # k = 1; d a multiple of 4 only; a tile with one entry
     (8200, 517, 300, 20, torch.float32),     # R = 32, odd d
