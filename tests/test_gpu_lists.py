@@ -276,7 +276,7 @@ def test_order_of_additions(n, d, b, k, dtype):
         assert np.array_equal(_distance_in_order(q, ent[idx[:, j]]), dist[:, j]), j
 
 
-@pytest.mark.parametrize("n,d,b,k", [(20000, 2, 1, 1), (20000, 2, 3, 2), (20000, 2, 1, 3), (20000, 3, 2, 30), (500, 1, 5, 2)])
+@pytest.mark.parametrize("n,d,b,k", [(20000, 2, 1, 1), (20000, 2, 3, 2), (20000, 2, 1, 3), (500, 1, 5, 2)])
 def test_merge_of_the_exact_scan(n, d, b, k):
     """Dense points on a line or plane, which the coarse key cannot rank: every query is scanned, and the lists of up to 512
     workgroups meet, few enough in all to be sorted at once or not."""
