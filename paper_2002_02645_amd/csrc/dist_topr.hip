@@ -811,8 +811,8 @@ DistPlan plan_dist(int64_t b, int64_t n, int r, int num_cus, bool keys_out, int6
 // is long enough to be worth cutting.  Writing, reading and adding up the slots takes about 50 us whatever the
 // depth, so for a look-up it pays only where whole tiles would leave the average CU idle for more k-steps
 // (0.55 us each) than that: 96 pay (1,000 x 10,000 x 8,192: 281 us whole, 256 cut), 60 do not (256 x 50,000 x
-// 8,192: 269 whole, 302 cut).  A projection is cut wherever whole tiles fill badly: shorter chains of additions
-// are part of its precision.
+// 8,192: 269 whole, 302 cut).  A projection of 16 k-steps per CU or more is cut wherever whole tiles fill badly: shorter
+// chains of additions are part of its precision.
 void plan_stream_k(DistPlan &pl, int num_cus, int64_t d_pad, double least_idle)
 {
     pl.sk_wgs = pl.sk_len = pl.sk_slots = 0;

@@ -673,7 +673,10 @@ DistPlan projection_plan(const freeze_ctx *ctx, const LayerCache &P, int64_t b, 
     pl.grid_units = pl.m_tiles * pl.n_tiles;
     pl.num_cus = ctx->num_cus;
     pl.b_pad = (int64_t)pl.m_tiles * 256;
-    if (!whole) plan_stream_k(pl, ctx->num_cus, P.d_pad, 0.0);
+    // With fewer than 16 k-steps per CU in all the slots cost more than short idle stretches, as for a look-up (13,948 x
+    // 2,295 -> 4: 56 us whole, 49 cut, but the slots push the inputs out of the memory-side cache: whole passes 92, 99).
+    const int64_t k_steps = (int64_t)pl.m_tiles * pl.n_tiles * (P.d_pad / kKB);
+    if (!whole) plan_stream_k(pl, ctx->num_cus, P.d_pad, k_steps < 16 * (int64_t)ctx->num_cus ? 90.0 : 0.0);
     if (b <= 512 && pl.sk_wgs == 0) return plan_stream(b, P.n, 1, ctx->num_cus, P.d_pad, whole);
     return pl;
 }
