@@ -935,7 +935,7 @@ __device__ __forceinline__ int gather_entries(const FinishArgs &a, int q, int nq
     }
     if (mine) atomicAdd(real_s, mine);
     __syncthreads();
-    if (!a.part_count) {
+    if (!a.part_count && *real_s < a.n) {   // uniform (else nothing is left out)
         // Per-split lists: a split that filled its list kept its r smallest keys, so every entry
         // of its range that it dropped has a key >= the list's largest.  The smallest of these
         // bounds every entry outside the gathered lists.  (Slots rotate with the thread

@@ -296,3 +296,29 @@ def test_merge_of_the_exact_scan(n, d, b, k):
     ref = parity.oracle_reference(q.numpy(), ent.numpy(), lab.numpy(), 10, k, 1)
     parity.assert_lookup_matches(got, ref, q.numpy(), ent.numpy(), lab.numpy(), 10, k, 1, rel=TIGHT, dist_rel=TIGHT)
     assert n < 1000 or c.tolist()[2] > 0
+
+
+@pytest.mark.parametrize("n,d,b,k,dtype", [
+    (1, 3100, 1030, 1, torch.bfloat16),
+    (7, 3333, 1100, 3, torch.float32),
+    (30, 4104, 1030, 20, torch.bfloat16),
+])
+def test_lists_that_hold_the_whole_cache(n, d, b, k, dtype):
+    """Nothing is left out of the lists of a cache that small: no query needs more than the first re-scoring of all entries."""
+    g = torch.Generator().manual_seed(n + d)
+    ent, q = torch.randn(n, d, generator=g).to(dtype), torch.randn(b, d, generator=g)
+    lab = torch.randint(0, 10, (n,), generator=g, dtype=torch.int32)
+    fc = binding.FreezeCache(1)
+    try:
+        c = torch.zeros(3, dtype=torch.int64, device="cuda")
+        binding.freeze_lookup_stats_attach(fc.ctx, c)
+        fc.build_layer(0, ent.cuda(), lab.cuda(), 10)
+        out = fc.lookup(0, q.cuda(), k, 1)
+        torch.cuda.synchronize()
+        got = {key: v.cpu().numpy() for key, v in out.items()}
+    finally:
+        fc.close()
+    e_h, l_h, q_h = _host_entries(ent), lab.numpy(), q.numpy()
+    ref = parity.oracle_reference(q_h, e_h, l_h, 10, k, 1)
+    parity.assert_lookup_matches(got, ref, q_h, e_h, l_h, 10, k, 1, rel=TIGHT, dist_rel=TIGHT)
+    assert c.tolist()[2] == 0

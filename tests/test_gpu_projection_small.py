@@ -18,6 +18,8 @@ pytestmark = pytest.mark.gpu
     (129, 2048, 250, torch.bfloat16, True),
     (512, 1030, 510, torch.float32, False),   # the last batch size of this route
     (513, 1030, 510, torch.float32, False),   # ... and the first beyond it
+    (700, 8200, 700, torch.bfloat16, True),   # fewer than 16 k-steps per CU, deep enough to be cut
+    (1000, 2295, 4, torch.float32, False),    # ... and not
 ])
 def test_small_projection(b, d, m, wdtype, relu):
     g = torch.Generator().manual_seed(77 + b + d + m)
