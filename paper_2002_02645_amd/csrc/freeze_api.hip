@@ -249,11 +249,12 @@ bool fit_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, int
 // last, partial one.
 bool asked_bytes(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, int rescore_r, bool cascade, size_t *bytes)
 {
-    LookupShape best, plain;
-    if (!lookup_shape(ctx, L, b, k, rescore_r, cascade, &best) ||
-        !lookup_shape(ctx, L, b, k, rescore_r, cascade, &plain, Decomp::plain))
-        return false;
-    *bytes = best.ws_bytes > plain.ws_bytes ? best.ws_bytes : plain.ws_bytes;
+    LookupShape sh;
+    if (!lookup_shape(ctx, L, b, k, rescore_r, cascade, &sh)) return false;
+    *bytes = sh.ws_bytes;
+    if (!sh.keys && !sh.blocks) return true;   // (lists and the small-batch kernel are what they are)
+    if (!lookup_shape(ctx, L, b, k, rescore_r, cascade, &sh, Decomp::plain)) return false;
+    if (sh.ws_bytes > *bytes) *bytes = sh.ws_bytes;
     return true;
 }
 
@@ -536,7 +537,8 @@ int lookup_checked(freeze_ctx *ctx, int layer, const float *queries, int64_t b, 
     if (!queries || !out_labels || !out_hit || !out_votes || !out_nbr_idx || !out_nbr_dist || !workspace)
         return FREEZE_EINVAL;
     if ((reinterpret_cast<uintptr_t>(queries) % 16) != 0) return FREEZE_EINVAL;
-    if ((reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0 || !fit_shape(ctx, *L, b, k, rescore_r, false, workspace_bytes, &sh))
+    if ((reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0 ||
+        (workspace_bytes < sh.ws_bytes && !fit_shape(ctx, *L, b, k, rescore_r, false, workspace_bytes, &sh)))
         return FREEZE_EWORKSPACE;
     return enqueue_lookup(ctx, *L, sh, queries, nullptr, nullptr, b, k, rule, out_labels, out_hit, out_votes,
                           out_nbr_idx, out_nbr_dist, workspace, static_cast<hipStream_t>(stream));
@@ -562,10 +564,10 @@ int cascade_checked(freeze_ctx *ctx, int num_layers, const int *layers, const fl
     // the count known on the host (any route, any decomposition); the later layers are sized for
     // b and read the live count on the device.
     const size_t room = cl.room(workspace_bytes);
-    LookupShape sh;
+    std::vector<LookupShape> shapes((size_t)num_layers);
     if ((reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0) return FREEZE_EWORKSPACE;
     for (int l = 0; l < num_layers; ++l)
-        if (!fit_shape(ctx, ctx->layers[layers[l]], b, k, rescore_r, l != 0, room, &sh)) return FREEZE_EWORKSPACE;
+        if (!fit_shape(ctx, ctx->layers[layers[l]], b, k, rescore_r, l != 0, room, &shapes[(size_t)l])) return FREEZE_EWORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
 
     Carver ws(workspace);
@@ -594,7 +596,7 @@ int cascade_checked(freeze_ctx *ctx, int num_layers, const int *layers, const fl
     const int32_t *count = nullptr;
     for (int l = 0; l < num_layers; ++l) {
         const LayerCache &L = ctx->layers[layers[l]];
-        fit_shape(ctx, L, b, k, rescore_r, l != 0, room, &sh);
+        const LookupShape &sh = shapes[(size_t)l];
         HitRule rule = rules[(size_t)l];
         rule.out_conf = t_conf;
         int rc = enqueue_lookup(ctx, L, sh, queries_per_layer[l], sel, count, b, k, rule, t_labels, t_hit, t_votes,
