@@ -32,6 +32,7 @@
 #include "select_common.h"
 
 #include <algorithm>
+#include <cmath>
 
 namespace fz {
 
@@ -408,8 +409,8 @@ hipError_t launch_cfg(const DistPlan &pl, const DistArgs &a, hipStream_t s)
 
 }  // namespace
 
-// Query tile and ranges of the streaming kernel.  whole: never cut a tile (no slots in the workspace).
-DistPlan plan_stream(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad, bool whole)
+// Query tile and ranges of the streaming kernel.
+DistPlan plan_stream(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad, StreamCut cut)
 {
     DistPlan pl{};
     pl.variant = 4;
@@ -437,7 +438,24 @@ DistPlan plan_stream(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad, bo
     if (len < least) len = least;
     // whole tiles where a tile is short (a second launch costs more than the idle workgroups) or where a
     // range holds so many that cutting one gains little
-    if (whole || nk <= 32 || len >= 16 * (int64_t)nk) len = (len + nk - 1) / nk * nk;
+    bool whole = cut == StreamCut::none || nk <= 32 || len >= 16 * (int64_t)nk;
+    if (cut == StreamCut::where_faster && !whole) {
+        // Whole tiles go in rounds of wgs tiles, nk k-steps each, of which the last may leave most of the chip idle; a
+        // cut evens the ranges out and costs the slots and stream_fixup_kernel. A round's k-step takes 0.45 us by its
+        // latency for each workgroup of the fullest CU, or 2.6 ns for each tile (16 KiB at 6.3 TB/s) where
+        // memory is what bounds it; the fix-up 6 us and 0.1 us for each 128-query tile among the first wgs. Fitted to
+        // the times of both at 260 random shapes (257 .. 374,631 rows, 1,025 .. 65,536 columns, up to 200 queries):
+        // always cut 39.6 ms in sum, by this line 38.04, the faster of the two at each shape 38.00.
+        //   99,862 x 1,585, 74 queries: cut 183 us, whole 103. 374,631 x 3,582, 92 queries: 717, 577.
+        //   78,855 x 16,887, 15 queries: cut 460 us, whole 517. 9,050 x 33,202, 12 queries: 166, 395.
+        const double tiles = (double)pl.m_tiles * pl.n_tiles, rounds = std::ceil(tiles / wgs);
+        const double last = tiles - (rounds - 1) * wgs;
+        auto round_us = [&](double t) { return nk * std::max(std::ceil(t / num_cus) * 0.45, t * 0.0026); };
+        const double t_whole = (rounds - 1) * round_us(wgs) + round_us(last);
+        const double t_cut = std::max(tiles * nk * 0.0026, (double)len * 0.45) + 6.0 + 0.1 * std::min(tiles, (double)wgs) * bm / 128;
+        whole = t_whole <= t_cut;
+    }
+    if (whole) len = (len + nk - 1) / nk * nk;
     pl.st_len = len;
     pl.st_wgs = (int)((all + len - 1) / len);
     pl.st_cut = len % nk != 0;

@@ -217,7 +217,7 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
         }
         const int64_t k_steps = (L.n_pad / kTileN) * (L.d_pad / kKB);   // per query tile
         if (out->keys && how != Decomp::plain && (b <= kStreamRows || 2 * k_steps < 16 * (int64_t)ctx->num_cus))
-            out->plan = plan_stream(b, L.n, r, ctx->num_cus, L.d_pad, how == Decomp::small);
+            out->plan = plan_stream(b, L.n, r, ctx->num_cus, L.d_pad, how == Decomp::small ? StreamCut::none : StreamCut::where_faster);
         else if (out->blocks)
             out->plan = plan_block(b, L.n, r, ctx->num_cus, L.d_pad);
         else
@@ -662,7 +662,7 @@ const LayerCache *get_projection(const freeze_ctx *ctx, int slot, int *err)
 // of 256 inputs, tile of 256 outputs), whole depth or stream-K.  whole: no cut tiles (no accumulator slots).
 DistPlan projection_plan(const freeze_ctx *ctx, const LayerCache &P, int64_t b, bool whole)
 {
-    if (b <= 256) return plan_stream(b > 0 ? b : 1, P.n, 1, ctx->num_cus, P.d_pad, whole);
+    if (b <= 256) return plan_stream(b > 0 ? b : 1, P.n, 1, ctx->num_cus, P.d_pad, whole ? StreamCut::none : StreamCut::always);
     DistPlan pl{};
     pl.variant = 3;
     pl.bm = 256;
@@ -679,7 +679,7 @@ DistPlan projection_plan(const freeze_ctx *ctx, const LayerCache &P, int64_t b, 
     // 2,295 -> 4: 56 us whole, 49 cut, but the slots push the inputs out of the memory-side cache: whole passes 92, 99).
     const int64_t k_steps = (int64_t)pl.m_tiles * pl.n_tiles * (P.d_pad / kKB);
     if (!whole) plan_stream_k(pl, ctx->num_cus, P.d_pad, k_steps < 16 * (int64_t)ctx->num_cus ? 90.0 : 0.0);
-    if (b <= 512 && pl.sk_wgs == 0) return plan_stream(b, P.n, 1, ctx->num_cus, P.d_pad, whole);
+    if (b <= 512 && pl.sk_wgs == 0) return plan_stream(b, P.n, 1, ctx->num_cus, P.d_pad, whole ? StreamCut::none : StreamCut::always);
     return pl;
 }
 

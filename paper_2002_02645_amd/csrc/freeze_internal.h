@@ -167,8 +167,14 @@ struct DistPlan {
 DistPlan plan_dist(int64_t b, int64_t n, int r, int num_cus, bool keys_out, int64_t d_pad = 0);
 // Sets the sk_* fields of a keys-out plan; least_idle: k-steps the average CU must be idle under whole tiles.
 void plan_stream_k(DistPlan &pl, int num_cus, int64_t d_pad, double least_idle);
-// Streaming kernel; whole: never cut a tile (needs no accumulator slots).
-DistPlan plan_stream(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad, bool whole);
+// Whether the streaming kernel cuts tiles along the depth.
+enum class StreamCut {
+    none,           // whole tiles only: needs no accumulator slots
+    where_faster,   // look-ups: the order of the coarse sums is free, so time decides
+    always          // projections: wherever ranges come out shorter than a tile, whose shorter chains of additions
+                    // are part of the precision of the result
+};
+DistPlan plan_stream(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad, StreamCut cut);
 // Block minima; grid_units = workgroups.
 DistPlan plan_block(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad);
 size_t dist_partial_bytes(const DistPlan &plan);   // accumulator slots of cut tiles (0 when none are cut)

@@ -31,6 +31,10 @@ def _inputs(n, d, b, k, dtype, seed):
     (16640, 2048, 64, 10, torch.bfloat16),
     (16500, 2100, 65, 10, torch.bfloat16),   # 128-query tile
     (16500, 2100, 128, 30, torch.bfloat16),  # k = 30: R = 64
+    (27000, 1200, 12, 5, torch.float32),     # tiles long enough to be cut (38 k-steps), whole because that is faster,
+    (27000, 1200, 28, 10, torch.bfloat16),   # at every size of the query tile
+    (27000, 1100, 70, 10, torch.bfloat16),
+    (33393, 1100, 120, 10, torch.bfloat16),
     (70000, 500, 33, 10, torch.bfloat16),    # short activation: whole tiles
     (140000, 64, 100, 10, torch.float32),    # the shortest tile: two k-steps, fewer than the ring's stages
     (2000, 512, 256, 5, torch.float32),      # small cache, several query tiles
