@@ -515,7 +515,7 @@ __device__ __forceinline__ void rescore_wave(const FinishArgs &a, const float *q
 #pragma unroll
         for (int j = 0; j < G; ++j) {
             acc[j] = 0.f;
-            cand[j] = __builtin_amdgcn_readfirstlane(idx_s[(c0 + j < r) ? c0 + j : r - 1]);   // (uniform: the wave's rows)
+            cand[j] = idx_s[(c0 + j < r) ? c0 + j : r - 1];
         }
         if (vec) {
             for (int64_t i = (int64_t)lane * 8; i < a.d; i += 64 * 8) {
@@ -556,6 +556,8 @@ __device__ __forceinline__ void rescore_wave(const FinishArgs &a, const float *q
             // Rows of another length: chain l of 64 takes elements l, l + 64, ..  fp32: a chain per lane, a few steps'
             // loads of all rows before the first is used (20,000 x 4,101, 1,100 queries: whole look-ups 694 -> 414 us).
             constexpr int U = G <= 4 ? 4 : 2;
+#pragma unroll
+            for (int j = 0; j < G; ++j) cand[j] = __builtin_amdgcn_readfirstlane((int32_t)cand[j]);   // (uniform: the wave's rows)
             if (a.c_f32) {   // uniform
                 auto steps = [&](int64_t i, auto count) {
                     constexpr int N = decltype(count)::value;
