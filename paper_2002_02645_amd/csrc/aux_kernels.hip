@@ -1845,7 +1845,8 @@ hipError_t launch_keys_finish(const FinishArgs &a, const float *keys, const uint
 //     last to finish by far.  With more (duplicates, neighbours closer than the key's error) the chip is busy
 //     anyway, and each goes on here.
 // Bound by the rows it reads, 8 per block: 4,096 queries x 12 blocks x 8 rows of 1 KB are 0.4 GB, beyond L2 for
-// a cache of 50,000 x 512 (51 MB); 112 us with the minima's 103 MB, 80 us on a cache of 5,000 rows.
+// a cache of 50,000 x 512 (51 MB). With the minima's 103 MB 112 us where the first blocks confirm every query, 150 - 155 us on
+// data where some go on to more blocks; 86 us on a cache of 5,000 rows.
 // ---------------------------------------------------------------------------------------
 constexpr int kMeetQueries = 32;
 struct BlockFinishArgs {
@@ -2483,13 +2484,13 @@ hipError_t launch_block_finish(const FinishArgs &a, const float *bkey, const flo
     if (a.r < 1 || a.r > kMaxRescore || a.k > kMaxK || a.k > a.r || a.b < 1 || !a.flag_count || !a.flag_list || !a.flag_list2 || n_pad % kTileN != 0)
         return hipErrorInvalidValue;
     // two blocks more than neighbours confirm most queries (4,096 x 50,000 x 512, k = 10: 112 us with 12 blocks at
-    // first, 115 with 11 or 14, 123 with 16); the certificate wants eight samples at least
+    // first, 118 with 11, 119 with 14, 129 with 16); the certificate wants eight samples at least
     int first = a.k + 2 > kCertMinSamples ? a.k + 2 : kCertMinSamples;
     first = first < a.r ? first : a.r;
     const int gather = 2 * a.r < kMaxRescore ? 2 * a.r : kMaxRescore;
     BlockFinishArgs ba{a, bkey, norm, mu, n_pad / 8, real_blocks_of(a.n, n_pad), (int)(a.d_pad / kKB), first, gather};
     // Two waves per query where the batch fills the chip with them, four where it does not (50,000 x 512: 1,500
-    // queries 52 against 57 us, 600 queries 37 against 28 us; one wave per query is slower than two at both).
+    // queries 54 against 59 us, 600 queries 42 against 34 us; one wave per query is slower than two at both).
     if (a.b >= 1024)
         hipLaunchKernelGGL(block_finish_kernel<128>, dim3((unsigned)a.b), dim3(128), 0, s, ba);
     else

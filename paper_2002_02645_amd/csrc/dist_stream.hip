@@ -10,8 +10,8 @@
 // rows, and the kernel is built like the small-batch one: a stream with many bytes in flight.
 //
 //   - Work: the flattened space (query tile, cache tile, k-step of 32 elements) is cut into equal
-//     ranges, one per workgroup, two workgroups per CU (one's end of a tile overlaps the other's
-//     stream).  A tile that lies in one range is finished in place; a tile cut by a range's end
+//     ranges, one per workgroup, at most two workgroups per CU (one's end of a tile overlaps the other's
+//     stream); look-ups take ranges of whole tiles where that is faster (plan_stream).  A tile that lies in one range is finished in place; a tile cut by a range's end
 //     leaves its accumulators, BM x 256 fp32 (16 - 128 KiB), in a slot per piece, and
 //     stream_fixup_kernel adds the pieces up in a fixed order.
 //   - A k-step's stage in LDS is 16 KiB of cache and BM x 64 bytes of queries, both exact copies of
@@ -22,10 +22,11 @@
 //     four consecutive entries of one query, so keys leave as 16-byte stores straight from the
 //     accumulators, and the minimum of a block of 32 entries is an in-lane minimum and two shuffles.
 //
-// What it takes (whole look-ups, batched kernel -> this one): 50,000 x 16,384, one query 461 -> 304 us
-// (this kernel 260 us = 6.3 TB/s, where a pure read reaches 7.1); 50,000 x 8,192, 32 queries 296 -> 203 us
-// (145 us = 5.7 TB/s); 20,000 x 16,384, 64 / 128 queries 250 -> 179 / 255 -> 213 us; 300,000 x 512, 64
-// queries 172 -> 115 us.  At 160 queries a 256-row tile is as fast on a large cache, so 128 is the last size served there.
+// What it takes (whole look-ups, batched kernel -> this one with ranges cut evenly -> with whole tiles):
+// 50,000 x 16,384, one query 460 -> 294 -> 264 us (this kernel 257 us = 6.4 TB/s cut, 231 us whole, where a pure read
+// reaches 7.1 TB/s; on another card 299 -> 306); 50,000 x 8,192, 32 queries 296 -> 182 -> 153 us (148 us = 5.5 TB/s
+// cut, 119 us whole).  Cut: 20,000 x 16,384, 64 / 128 queries 250 -> 179 / 255 -> 213 us.  Short tiles, never cut: 300,000 x
+// 512, 64 queries 172 -> 115 us.  At 160 queries a 256-row tile is as fast on a large cache, so 128 is the last size served there.
 //
 // Paper: Sec. 3 (k nearest neighbours of the layer output), Sec. 5 "Cache lookup performance".
 #include "freeze_internal.h"

@@ -124,7 +124,9 @@ int lists_per_query(const DistPlan &pl, bool device_count)
 
 // Whether a batch goes through block minima instead of per-query lists: where what the lists cost
 // is more than what re-scoring whole blocks of eight costs.  Both are times in microseconds, fitted to
-// measurements of both routes over 2,000 .. 300,000 entries, 256 .. 3,072 values, 300 .. 10,000 queries:
+// measurements of both routes over 2,000 .. 300,000 entries, 256 .. 3,072 values, 300 .. 10,000 queries.  Used beyond
+// them too: of 344 random shapes it sends to blocks (4 .. 200,000 entries, 1 .. 3,072 values, 129 .. 20,000 queries) lists are
+// more than 3 % faster at three, 122 x 2,194 with 1,700 queries by most (158 us with blocks, 114):
 //   lists   filling every workgroup's empty lists, 110 at 16 slots, 180 at 32, 500 at 64, and 10 per
 //           256 x 256 tile of a workgroup;
 //   blocks  8 (k + 2) rows per query, 64 at least, at 5.3 TB/s (8 when the cache is small enough for the L2s), 20, and a
