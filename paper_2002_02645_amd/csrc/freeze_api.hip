@@ -628,16 +628,34 @@ bool centres_shape(int64_t kc, int64_t d, LayerCache *out)
     out->entries_dtype = FREEZE_F32;
     return true;
 }
-// workspace: two centre buffers, dummy labels, the look-up's outputs for n points and its workspace
-bool kmeans_layout(const freeze_ctx *ctx, int64_t n, int64_t d, int64_t kc, CallLayout *out)
+// Workspace of a k-means build.  `rows`: the assignment by the product of the points with split centres (rows.on), for
+// which `rows_bytes` are needed; else, and in a buffer that holds less, by look-ups of the points: two centre buffers, dummy
+// labels, the look-up's outputs for n points and its workspace.  Asked for: what either takes, so that a buffer
+// sized for a build serves the builds that are smaller.
+struct KmeansLayout {
+    CallLayout lookup;
+    RowsPlan rows;
+    size_t rows_bytes, bytes;
+};
+bool kmeans_layout(const freeze_ctx *ctx, int64_t n, int64_t d, int64_t kc, KmeansLayout *out)
 {
     LayerCache centres;
     if (!ctx || n < 1 || n > (int64_t)1 << 30 || kc < 1 || kc > n || !centres_shape(kc, d, &centres)) return false;
-    if (!asked_bytes(ctx, centres, n, 1, 0, false, &out->lookup_ws)) return false;
-    out->rest = 2 * align_up((size_t)kc * d * 4) + align_up((size_t)kc * 4) + 3 * align_up((size_t)n * 4) +
-                 align_up((size_t)n) + 2 * align_up((size_t)n * 4) +
-                 align_up((size_t)kc * 4) + align_up((size_t)(kc + 1) * 4) + align_up((size_t)n * 4);   // grouping by centre
-    out->bytes = out->lookup_ws + out->rest;
+    CallLayout &cl = out->lookup;
+    if (!asked_bytes(ctx, centres, n, 1, 0, false, &cl.lookup_ws)) return false;
+    // centres, dummy labels, assignment, grouping by centre
+    const size_t both = 2 * align_up((size_t)kc * d * 4) + align_up((size_t)kc * 4) + 2 * align_up((size_t)n * 4) +
+                        2 * align_up((size_t)kc * 4) + align_up((size_t)(kc + 1) * 4);
+    cl.rest = both + align_up((size_t)n) + 3 * align_up((size_t)n * 4);
+    cl.bytes = cl.lookup_ws + cl.rest;
+    out->bytes = cl.bytes;
+    out->rows = plan_rows(n, d, kc, ctx->num_cus);
+    out->rows_bytes = 0;
+    if (out->rows.on) {
+        out->rows_bytes = both + 2 * align_up((size_t)centres.n_pad * centres.d_pad * 2) + align_up((size_t)centres.n_pad * 4) +
+                          align_up(out->rows.part * 4) + align_up(out->rows.sq * 4);
+        if (out->rows_bytes > out->bytes) out->bytes = out->rows_bytes;
+    }
     return true;
 }
 
@@ -948,7 +966,7 @@ size_t freeze_kmeans_storage_bytes(int64_t num_centers, int64_t d)
 
 size_t freeze_kmeans_workspace_bytes(const freeze_ctx *ctx, int64_t n, int64_t d, int64_t num_centers)
 {
-    CallLayout kl;
+    KmeansLayout kl;
     return kmeans_layout(ctx, n, d, num_centers, &kl) ? kl.bytes : 0;
 }
 
@@ -960,36 +978,49 @@ int freeze_kmeans_build(freeze_ctx *ctx, int layer, const float *points, int64_t
         num_classes < 1 || num_classes > 8192)
         return FREEZE_EINVAL;
     if (layer < 0 || layer >= (int)ctx->layers.size()) return FREEZE_ELAYER;
-    CallLayout kl;
+    KmeansLayout kl;
     if (!kmeans_layout(ctx, n, d, num_centers, &kl)) return FREEZE_EINVAL;
     if ((reinterpret_cast<uintptr_t>(points) % 16) != 0) return FREEZE_EINVAL;
     const size_t st_bytes = freeze_kmeans_storage_bytes(num_centers, d);
     if (storage_bytes < st_bytes || (reinterpret_cast<uintptr_t>(storage) % kAlign) != 0) return FREEZE_EWORKSPACE;
-    // the points do not change from round to round: their bf16 copy is made once (the shape of
-    // the look-up, and with it the layout of its workspace, is the same in every round)
+    // (the shape of the look-up, and with it the layout of its workspace, is the same in every round)
     const int64_t kc = num_centers;
-    const size_t room = kl.room(workspace_bytes);
+    const bool by_rows = kl.rows.on && workspace_bytes >= kl.rows_bytes;
+    const size_t room = kl.lookup.room(workspace_bytes);
     LayerCache centres;
     LookupShape sh;
     centres_shape(kc, d, &centres);
-    if ((reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0 || !fit_shape(ctx, centres, n, 1, 0, false, room, &sh))
+    if ((reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0 || (!by_rows && !fit_shape(ctx, centres, n, 1, 0, false, room, &sh)))
         return FREEZE_EWORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
 
     Carver ws(workspace);
-    unsigned char *lookup_ws = ws.take<unsigned char>(room);
     float *cen[2] = {ws.take<float>((size_t)kc * d), ws.take<float>((size_t)kc * d)};
     int32_t *zero_labels = ws.take<int32_t>((size_t)kc);
-    int32_t *t_labels = ws.take<int32_t>((size_t)n);
-    int32_t *t_votes = ws.take<int32_t>((size_t)n);
     int32_t *assign = ws.take<int32_t>((size_t)n);
-    uint8_t *t_hit = ws.take<uint8_t>((size_t)n);
-    float *t_dist = ws.take<float>((size_t)n);
-    float *t_conf = ws.take<float>((size_t)n);
-    (void)t_conf;
     int32_t *grp_sizes = ws.take<int32_t>((size_t)kc);
     int32_t *grp_offsets = ws.take<int32_t>((size_t)kc + 1);
+    int32_t *grp_rank = ws.take<int32_t>((size_t)kc);
     int32_t *grp_members = ws.take<int32_t>((size_t)n);
+    // one of the two
+    unsigned char *lookup_ws = nullptr;
+    int32_t *t_labels = nullptr, *t_votes = nullptr;
+    uint8_t *t_hit = nullptr;
+    float *t_dist = nullptr, *c_norm = nullptr, *part = nullptr, *sq = nullptr;
+    uint16_t *c_hi = nullptr, *c_lo = nullptr;
+    if (by_rows) {
+        c_hi = ws.take<uint16_t>((size_t)centres.n_pad * centres.d_pad);
+        c_lo = ws.take<uint16_t>((size_t)centres.n_pad * centres.d_pad);
+        c_norm = ws.take<float>((size_t)centres.n_pad);
+        part = ws.take<float>(kl.rows.part);
+        sq = ws.take<float>(kl.rows.sq);
+    } else {
+        t_labels = ws.take<int32_t>((size_t)n);
+        t_votes = ws.take<int32_t>((size_t)n);
+        t_hit = ws.take<uint8_t>((size_t)n);
+        t_dist = ws.take<float>((size_t)n);
+        lookup_ws = ws.take<unsigned char>(room);
+    }
 
     CacheLayout cl;
     cache_layout(kc, d, FREEZE_F32, &cl);
@@ -997,24 +1028,33 @@ int freeze_kmeans_build(freeze_ctx *ctx, int layer, const float *points, int64_t
 
     if (launch_copy_rows_f32(init_centers, d, cen[0], kc, d, s) != hipSuccess) return FREEZE_EHIP;
     if (launch_fill_i32(zero_labels, 0, kc, s) != hipSuccess) return FREEZE_EHIP;
-    // rounds of (centres -> cache, every point looked up with k = 1, centres <- means); a last
-    // assignment to the final centres gives the majority labels and their shares
+    // rounds of (every point to its nearest centre, centres <- means); a last assignment to the final centres gives the
+    // majority labels and their shares
     const HitRule rule{0, 1, 0.f, nullptr};
-    // The points' candidates are re-scored against fp32 centres.  Where those exceed an XCD's L2 (4 MB) the
+    // Look-ups re-score the points' candidates against fp32 centres.  Where those exceed an XCD's L2 (4 MB) the
     // points are taken, from the second round on, in the order of the centre they were assigned to in the
     // round before, in which the update has grouped them anyway: neighbours share candidates (50,000 x 8,192,
     // 200 centres: 895 -> 840 us a round).
     const bool grouped = (double)kc * (double)d * 4.0 > 4e6;
     for (int it = 0; it <= iters; ++it) {
         const float *cur = cen[it & 1];
-        int rc = cache_build_impl(ctx, layer, cur, FREEZE_F32, kc, d, zero_labels, num_classes, storage, cl.bytes, stream, false);
-        if (rc != FREEZE_OK) return rc;
-        const LayerCache &L = ctx->layers[layer];
-        rc = enqueue_lookup(ctx, L, sh, points, nullptr, nullptr, n, 1, rule, t_labels, t_hit, t_votes, assign, t_dist,
-                            lookup_ws, s, it > 0, grouped && it > 0 ? grp_members : nullptr);
-        if (rc != FREEZE_OK) return rc;
+        // the centres as a cache: for the look-ups, and in the end for the caller's
+        if (!by_rows || it == iters) {
+            const int rc = cache_build_impl(ctx, layer, cur, FREEZE_F32, kc, d, zero_labels, num_classes, storage, cl.bytes, stream, false);
+            if (rc != FREEZE_OK) return rc;
+        }
+        if (by_rows) {
+            if (launch_rows_split(cur, kc, centres.n_pad, d, centres.d_pad, c_hi, c_lo, c_norm, s) != hipSuccess ||
+                launch_kmeans_assign(kl.rows, points, n, d, centres.d_pad, cur, kc, c_hi, c_lo, c_norm, part, sq, assign, s) != hipSuccess)
+                return FREEZE_EHIP;
+        } else {
+            // the points do not change from round to round: their bf16 copy is made once
+            const int rc = enqueue_lookup(ctx, ctx->layers[layer], sh, points, nullptr, nullptr, n, 1, rule, t_labels, t_hit, t_votes, assign,
+                                          t_dist, lookup_ws, s, it > 0, grouped && it > 0 ? grp_members : nullptr);
+            if (rc != FREEZE_OK) return rc;
+        }
         if (it < iters &&
-            launch_kmeans_update(points, assign, n, d, kc, cur, cen[(it + 1) & 1], grp_sizes, grp_offsets, grp_members, s) !=
+            launch_kmeans_update(points, assign, n, d, kc, cur, cen[(it + 1) & 1], grp_sizes, grp_offsets, grp_rank, grp_members, s) !=
                 hipSuccess)
             return FREEZE_EHIP;
     }

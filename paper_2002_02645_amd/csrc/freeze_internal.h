@@ -319,11 +319,28 @@ hipError_t launch_cascade_scatter(const int32_t *labels, const uint8_t *hit, con
                                   int32_t *out_exit, hipStream_t s);
 
 // k-means cache build (the assignment step is the look-up itself)
-// sizes [k], offsets [k + 1] and members [n] int32 are scratch
+// sizes [k], offsets [k + 1], rank [k] and members [n] int32 are scratch
 // (members: the points grouped by the centre they are assigned to, each group ascending)
 hipError_t launch_kmeans_update(const float *points, const int32_t *assign, int64_t n, int64_t d, int64_t k,
                                 const float *old_centers, float *new_centers, int32_t *sizes, int32_t *offsets,
-                                int32_t *members, hipStream_t s);
+                                int32_t *rank, int32_t *members, hipStream_t s);
+// The assignment step by the product of the fp32 points with centres split into two bf16 values each.
+constexpr int kRowsTile = 256;      // points per tile
+constexpr int kRowsMaxTiles = 2;    // tiles of at most kTileN centres
+struct RowsPlan {
+    bool on;            // false: the look-up assigns the points
+    int ncb, nc;        // blocks of 16 centres and centres per tile
+    int n_tiles, m_tiles, nk, slots, wgs;
+    int64_t len;        // k-steps per workgroup of the flattened (point tile, centre tile, k-step) space
+    size_t part, sq;    // floats of the sums and of the points' sums of squares
+};
+RowsPlan plan_rows(int64_t n, int64_t d, int64_t kc, int num_cus);
+// hi, lo [n_pad * d_pad] and norm [n_pad] of the centres (n_pad: kc rounded up to kTileN)
+hipError_t launch_rows_split(const float *rows, int64_t kc, int64_t n_pad, int64_t d, int64_t d_pad, uint16_t *hi, uint16_t *lo,
+                             float *norm, hipStream_t s);
+hipError_t launch_kmeans_assign(const RowsPlan &pl, const float *points, int64_t n, int64_t d, int64_t d_pad, const float *centers,
+                                int64_t kc, const uint16_t *hi, const uint16_t *lo, const float *norm, float *part, float *sq,
+                                int32_t *assign, hipStream_t s);
 hipError_t launch_kmeans_majority(const int32_t *assign, const int32_t *labels, int64_t n, int num_classes, int64_t k,
                                   int32_t *majority, float *fraction, int64_t *sizes, hipStream_t s);
 hipError_t launch_copy_rows_f32(const float *src, int64_t src_stride, float *dst, int64_t rows, int64_t d, hipStream_t s);

@@ -15,8 +15,7 @@ namespace fz {
 // assignment list and writes its members' ids in order (ballot / popcount compaction; the list is
 // n ints and stays in L2).  Then one workgroup per (centre, 256 dimensions) adds up its members'
 // rows in that order in fp64 and rounds the mean once to fp32, so the result does not depend on
-// scheduling; every point row is read exactly once, in 1 KiB pieces, eight rows in flight per
-// thread.  A cluster without points keeps its centre.
+// scheduling; every point row is read exactly once, in 1 KiB pieces.  A cluster without points keeps its centre.
 // Histogram of the keys, up to kCountBins of them in LDS first (one global atomic per point and a few
 // hundred addresses: 48 us for 50,000 points).
 constexpr int kCountBins = 4096;
@@ -40,9 +39,11 @@ __global__ __launch_bounds__(256) void kmeans_count_kernel(const int32_t *assign
         if (hist[c]) atomicAdd(&sizes[c], hist[c]);
 }
 
-// offsets[c] = sizes[0] + .. + sizes[c-1], offsets[k] = total; one workgroup
-__global__ __launch_bounds__(1024) void kmeans_offsets_kernel(const int32_t *sizes, int64_t k, int32_t *offsets)
+// offsets[c] = sizes[0] + .. + sizes[c-1], offsets[k] = total; one workgroup.  rank: the centres, the largest cluster
+// first (up to 1,024 centres, else in order: it only spreads the update's work).
+__global__ __launch_bounds__(1024) void kmeans_offsets_kernel(const int32_t *sizes, int64_t k, int32_t *offsets, int32_t *rank)
 {
+    __shared__ int size_s[1024];
     __shared__ int wave_tot[16];
     __shared__ int base_s;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -67,99 +68,146 @@ __global__ __launch_bounds__(1024) void kmeans_offsets_kernel(const int32_t *siz
         __syncthreads();
     }
     if (tid == 0) offsets[k] = base_s;
+    if (k <= 1024) {
+        const int mine = tid < k ? sizes[tid] : 0;
+        size_s[tid] = mine;
+        __syncthreads();
+        int larger = 0;
+#pragma unroll 16
+        for (int j = 0; j < (int)k; ++j) larger += (size_s[j] > mine) | ((size_s[j] == mine) & (j < tid));
+        if (tid < k) rank[larger] = tid;
+    } else {
+        for (int64_t c = tid; c < k; c += 1024) rank[c] = (int32_t)c;
+    }
 }
 
-// members[offsets[c] ..) = the ids of the points assigned to centre c = blockIdx.x, ascending
+// members[offsets[c] ..) = the ids of the points assigned to centre c = blockIdx.x, ascending.  Sixteen blocks of 1,024 points per
+// step: bound by the latency of the list's reads and the barriers (50,000 points: one block a step 32 us,
+// sixteen 22).
 __global__ __launch_bounds__(1024) void kmeans_members_kernel(const int32_t *assign, int64_t n, const int32_t *offsets,
                                                               int32_t *members)
 {
-    __shared__ int wave_tot[16];
+    constexpr int U = 16;
+    __shared__ __attribute__((aligned(16))) int wave_tot[2][U * 16];
     const int c = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     int base = offsets[c];
     if (offsets[c + 1] == base) return;   // uniform: an empty cluster
-    for (int64_t start = 0; start < n; start += 1024) {
-        const int64_t i = start + tid;
-        const bool mine = i < n && assign[i] == c;
-        const uint64_t bal = __ballot(mine);
-        if (lane == 0) wave_tot[w] = __builtin_popcountll(bal);
-        __syncthreads();
-        int before = 0, all = 0;
-        for (int j = 0; j < 16; ++j) {
-            before += j < w ? wave_tot[j] : 0;
-            all += wave_tot[j];
+    int par = 0;
+    for (int64_t start = 0; start < n; start += U * 1024, par ^= 1) {
+        bool mine[U];
+        uint64_t bal[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = start + u * 1024 + tid;
+            mine[u] = i < n && assign[i] == c;
         }
-        if (mine) members[base + before + __builtin_popcountll(bal & ((1ull << lane) - 1ull))] = (int32_t)i;
-        base += all;
-        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            bal[u] = __ballot(mine[u]);
+            if (lane == 0) wave_tot[par][u * 16 + w] = __builtin_popcountll(bal[u]);
+        }
+        __syncthreads();   // (two buffers: the next step's counts are written while slower waves still read these)
+        // the 256 counts are in point order: lane l scans counts 4 l .. 4 l + 3
+        const int4 c4 = reinterpret_cast<const int4 *>(wave_tot[par])[lane];
+        const int sum = c4.x + c4.y + c4.z + c4.w;
+        int incl = sum;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += o;
+        }
+        // points before this wave's count of 1,024-point block u, which is count u * 16 + w: element w & 3 of lane (u * 16 + w) / 4
+        const int mod = w & 3;
+        const int before = incl - sum + (mod > 0 ? c4.x : 0) + (mod > 1 ? c4.y : 0) + (mod > 2 ? c4.z : 0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int at = __builtin_amdgcn_readlane(before, u * 4 + (w >> 2));
+            if (mine[u])
+                members[base + at + __builtin_popcountll(bal[u] & ((1ull << lane) - 1ull))] = (int32_t)(start + u * 1024 + tid);
+        }
+        base += __builtin_amdgcn_readlane(incl, 63);
     }
 }
 
-__global__ __launch_bounds__(256) void kmeans_update_kernel(const float *points, const int32_t *offsets, const int32_t *members,
-                                                            int64_t d, const float *old_centers, float *new_centers)
-{
-    const int c = blockIdx.x;
-    const int64_t dim = (int64_t)blockIdx.y * 256 + threadIdx.x;
-    if (dim >= d) return;
-    const int m0 = offsets[c], m1 = offsets[c + 1];
-    double acc = 0.0;
-    int j = m0;
-    for (; j + 8 <= m1; j += 8) {
-        float v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = points[(int64_t)members[j + e] * d + dim];   // eight rows in flight
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc += (double)v[e];                                 // ... added in point order
-    }
-    for (; j < m1; ++j) acc += (double)points[(int64_t)members[j] * d + dim];
-    new_centers[(int64_t)c * d + dim] = m1 > m0 ? (float)(acc / (double)(m1 - m0)) : old_centers[(int64_t)c * d + dim];
-}
-
-// The same for rows of whole 16-byte pieces: one wave per (centre, 256 dimensions), four dimensions per lane, so
-// that a wave reads 1 KiB of a row at a time, sixteen rows in flight.
+// A workgroup per (centre, 256 dimensions) reads 64 rows' pieces of 1 KiB into registers, hands them on through LDS, and
+// while the next 64 are on their way every thread adds up the 64 values of its dimension in order.  Clusters are uneven
+// (50,000 x 8,192, 200 centres: the largest 1,862 points, half of them under 124), and a sum in point order cannot be
+// shared out, so the largest decide when the kernel ends: with a wave per cluster and sixteen rows in flight their chains
+// of loads took most of its 350 us.  Largest clusters first (rank): 290 us, 1.64 GB at 5.7 TB/s.
+// VEC: rows start on 16-byte boundaries (d a multiple of 4).
 typedef __attribute__((ext_vector_type(4))) float f32x4;
-__global__ __launch_bounds__(64) void kmeans_update4_kernel(const float *points, const int32_t *offsets, const int32_t *members,
-                                                            int64_t d, const float *old_centers, float *new_centers)
+template <bool VEC>
+__global__ __launch_bounds__(256) void kmeans_update_kernel(const float *points, const int32_t *offsets, const int32_t *members,
+                                                            const int32_t *rank, int64_t d, const float *old_centers, float *new_centers)
 {
-    constexpr int U = 16;
-    const int c = blockIdx.x;
-    const int64_t dim = (int64_t)blockIdx.y * 256 + threadIdx.x * 4;
-    if (dim >= d) return;
+    constexpr int U = 16;                     // rows per wave and batch
+    __shared__ __attribute__((aligned(16))) float rows_s[4 * U][256];
+    const uint32_t chunks = (uint32_t)((d + 255) / 256);
+    const int c = rank[blockIdx.x / chunks];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t dim0 = (int64_t)(blockIdx.x % chunks) * 256;
     const int m0 = offsets[c], m1 = offsets[c + 1];
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    int j = m0;
-    for (; j + U <= m1; j += U) {
-        f32x4 v[U];
+    // the lane's four dimensions of a piece: consecutive, or 64 apart; past the row's end any will do
+    int at[4];
 #pragma unroll
-        for (int e = 0; e < U; ++e) v[e] = *reinterpret_cast<const f32x4 *>(points + (int64_t)members[j + e] * d + dim);
-#pragma unroll
-        for (int e = 0; e < U; ++e)
-#pragma unroll
-            for (int x = 0; x < 4; ++x) acc[x] += (double)v[e][x];   // in point order
+    for (int h = 0; h < 4; ++h) {
+        const int x = VEC ? lane * 4 + h : lane + 64 * h;
+        at[h] = dim0 + x < d ? x : 0;
     }
-    for (; j < m1; ++j) {
-        const f32x4 v = *reinterpret_cast<const f32x4 *>(points + (int64_t)members[j] * d + dim);
+    f32x4 v[U];
+    auto load = [&](int j0) {                 // rows j0 + w U ..; past the end the last row again
 #pragma unroll
-        for (int x = 0; x < 4; ++x) acc[x] += (double)v[x];
-    }
-    f32x4 o = *reinterpret_cast<const f32x4 *>(old_centers + (int64_t)c * d + dim);
-    if (m1 > m0) {
+        for (int e = 0; e < U; ++e) {
+            const int j = j0 + w * U + e;
+            const float *src = points + (int64_t)members[j < m1 ? j : m1 - 1] * d + dim0;
+            if constexpr (VEC) {
+                v[e] = *reinterpret_cast<const f32x4 *>(src + at[0]);
+            } else {
 #pragma unroll
-        for (int x = 0; x < 4; ++x) o[x] = (float)(acc[x] / (double)(m1 - m0));
+                for (int h = 0; h < 4; ++h) v[e][h] = src[at[h]];
+            }
+        }
+    };
+    double acc = 0.0;
+    if (m1 > m0) load(m0);
+    for (int j0 = m0; j0 < m1; j0 += 4 * U) {
+        __syncthreads();                      // the batch before has been added
+#pragma unroll
+        for (int e = 0; e < U; ++e) {
+            if constexpr (VEC) {
+                *reinterpret_cast<f32x4 *>(&rows_s[w * U + e][lane * 4]) = v[e];
+            } else {
+#pragma unroll
+                for (int h = 0; h < 4; ++h) rows_s[w * U + e][lane + 64 * h] = v[e][h];
+            }
+        }
+        __syncthreads();
+        if (j0 + 4 * U < m1) load(j0 + 4 * U);
+        const int cnt = m1 - j0 < 4 * U ? m1 - j0 : 4 * U;
+        if (cnt == 4 * U) {
+#pragma unroll 16
+            for (int e = 0; e < 4 * U; ++e) acc += (double)rows_s[e][tid];   // in point order
+        } else {
+            for (int e = 0; e < cnt; ++e) acc += (double)rows_s[e][tid];
+        }
     }
-    *reinterpret_cast<f32x4 *>(new_centers + (int64_t)c * d + dim) = o;
+    const int64_t dim = dim0 + tid;
+    if (dim < d) new_centers[(int64_t)c * d + dim] = m1 > m0 ? (float)(acc / (double)(m1 - m0)) : old_centers[(int64_t)c * d + dim];
 }
 
 // members = the ids 0 .. n-1 grouped by key (in [0, k)), each group ascending
 static hipError_t launch_kmeans_group(const int32_t *key, int64_t n, int64_t k, int32_t *sizes, int32_t *offsets,
-                                      int32_t *members, hipStream_t s)
+                                      int32_t *rank, int32_t *members, hipStream_t s)
 {
     hipError_t e = launch_fill_i32(sizes, 0, k, s);
     if (e != hipSuccess) return e;
     const int64_t blocks = (n + 2047) / 2048 < 256 ? (n + 2047) / 2048 : 256;
     hipLaunchKernelGGL(kmeans_count_kernel, dim3((unsigned)blocks), dim3(256), 0, s, key, n, k, sizes);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(kmeans_offsets_kernel, dim3(1), dim3(1024), 0, s, sizes, k, offsets);
+    hipLaunchKernelGGL(kmeans_offsets_kernel, dim3(1), dim3(1024), 0, s, sizes, k, offsets, rank);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(kmeans_members_kernel, dim3((unsigned)k), dim3(1024), 0, s, key, n, offsets, members);
     return hipGetLastError();
@@ -167,17 +215,16 @@ static hipError_t launch_kmeans_group(const int32_t *key, int64_t n, int64_t k, 
 
 hipError_t launch_kmeans_update(const float *points, const int32_t *assign, int64_t n, int64_t d, int64_t k,
                                 const float *old_centers, float *new_centers, int32_t *sizes, int32_t *offsets,
-                                int32_t *members, hipStream_t s)
+                                int32_t *rank, int32_t *members, hipStream_t s)
 {
-    hipError_t e = launch_kmeans_group(assign, n, k, sizes, offsets, members, s);
+    hipError_t e = launch_kmeans_group(assign, n, k, sizes, offsets, rank, members, s);
     if (e != hipSuccess) return e;
     // (points, centres: 16-byte aligned by contract and by the workspace's layout)
+    const dim3 grid((unsigned)(k * ((d + 255) / 256)));
     if (d % 4 == 0)
-        hipLaunchKernelGGL(kmeans_update4_kernel, dim3((unsigned)k, (unsigned)((d + 255) / 256)), dim3(64), 0, s, points,
-                           offsets, members, d, old_centers, new_centers);
+        hipLaunchKernelGGL(kmeans_update_kernel<true>, grid, dim3(256), 0, s, points, offsets, members, rank, d, old_centers, new_centers);
     else
-        hipLaunchKernelGGL(kmeans_update_kernel, dim3((unsigned)k, (unsigned)((d + 255) / 256)), dim3(256), 0, s, points,
-                           offsets, members, d, old_centers, new_centers);
+        hipLaunchKernelGGL(kmeans_update_kernel<false>, grid, dim3(256), 0, s, points, offsets, members, rank, d, old_centers, new_centers);
     return hipGetLastError();
 }
 
@@ -186,60 +233,62 @@ hipError_t launch_kmeans_update(const float *points, const int32_t *assign, int6
 // no dependence on the order of the atomic additions).  An empty cluster gets label 0, share 0.
 constexpr int kKmeansMaxClasses = 8192;
 
-__global__ __launch_bounds__(256) void kmeans_majority_kernel(const int32_t *assign, const int32_t *labels, int64_t n,
-                                                              int num_classes, int32_t *majority, float *fraction,
-                                                              int64_t *sizes)
+__global__ __launch_bounds__(1024) void kmeans_majority_kernel(const int32_t *assign, const int32_t *labels, int64_t n,
+                                                               int num_classes, int32_t *majority, float *fraction,
+                                                               int64_t *sizes)
 {
     __shared__ int hist[kKmeansMaxClasses];
-    __shared__ int best_s[256], bestl_s[256], size_s;
-    const int c = blockIdx.x, tid = threadIdx.x;
-    for (int l = tid; l < num_classes; l += 256) hist[l] = 0;
+    __shared__ int best_s[16], bestl_s[16], size_s;
+    const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    for (int l = tid; l < num_classes; l += 1024) hist[l] = 0;
     if (tid == 0) size_s = 0;
     __syncthreads();
     int mine = 0;
+    auto count = [&](int64_t i, int32_t a) {
+        if (a != c) return;
+        const int l = labels[i];
+        if ((unsigned)l < (unsigned)num_classes) atomicAdd(&hist[l], 1);   // labels outside the contract are not counted
+        ++mine;
+    };
     int64_t i = tid;
-    for (; i + 7 * 256 < n; i += 8 * 256) {   // eight loads in flight; most points belong to other clusters
+    for (; i + 7 * 1024 < n; i += 8 * 1024) {   // eight loads in flight; most points belong to other clusters
         int32_t as[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) as[u] = assign[i + u * 256];
+        for (int u = 0; u < 8; ++u) as[u] = assign[i + u * 1024];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            if (as[u] == c) {
-                const int l = labels[i + u * 256];
-                if ((unsigned)l < (unsigned)num_classes) atomicAdd(&hist[l], 1);   // labels outside the contract are not counted
-                ++mine;
-            }
-        }
+        for (int u = 0; u < 8; ++u) count(i + u * 1024, as[u]);
     }
-    for (; i < n; i += 256) {
-        if (assign[i] == c) {
-            const int l = labels[i];
-            if ((unsigned)l < (unsigned)num_classes) atomicAdd(&hist[l], 1);   // labels outside the contract are not counted
-            ++mine;
-        }
-    }
-    atomicAdd(&size_s, mine);
+    for (; i < n; i += 1024) count(i, assign[i]);
+    if (mine) atomicAdd(&size_s, mine);
     __syncthreads();
     int best = -1, bestl = 0;
-    for (int l = tid; l < num_classes; l += 256) {   // ascending l per thread: the first maximum is the smallest label
+    for (int l = tid; l < num_classes; l += 1024) {   // ascending l per thread: the first maximum is the smallest label
         if (hist[l] > best) {
             best = hist[l];
             bestl = l;
         }
     }
-    best_s[tid] = best;
-    bestl_s[tid] = bestl;
+    auto better = [&](int b, int bl) {
+        if (b > best || (b == best && bl < bestl)) {
+            best = b;
+            bestl = bl;
+        }
+    };
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        const int b = __shfl_xor(best, off, 64), bl = __shfl_xor(bestl, off, 64);
+        better(b, bl);
+    }
+    if (lane == 0) {
+        best_s[w] = best;
+        bestl_s[w] = bestl;
+    }
     __syncthreads();
     if (tid == 0) {
-        int b = -1, bl = 0;
-        for (int t = 0; t < 256; ++t)
-            if (best_s[t] > b || (best_s[t] == b && bestl_s[t] < bl)) {
-                b = best_s[t];
-                bl = bestl_s[t];
-            }
+        for (int t = 1; t < 16; ++t) better(best_s[t], bestl_s[t]);
         const int size = size_s;
-        majority[c] = size ? bl : 0;
-        fraction[c] = size ? (float)((double)b / (double)size) : 0.f;
+        majority[c] = size ? bestl : 0;
+        fraction[c] = size ? (float)((double)best / (double)size) : 0.f;
         if (sizes) sizes[c] = size;
     }
 }
@@ -248,7 +297,7 @@ hipError_t launch_kmeans_majority(const int32_t *assign, const int32_t *labels, 
                                   int32_t *majority, float *fraction, int64_t *sizes, hipStream_t s)
 {
     if (num_classes < 1 || num_classes > kKmeansMaxClasses) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(kmeans_majority_kernel, dim3((unsigned)k), dim3(256), 0, s, assign, labels, n, num_classes,
+    hipLaunchKernelGGL(kmeans_majority_kernel, dim3((unsigned)k), dim3(1024), 0, s, assign, labels, n, num_classes,
                        majority, fraction, sizes);
     return hipGetLastError();
 }

@@ -1,0 +1,640 @@
+// Matrix product of many fp32 rows with a few hundred prepared ones, the fp32 rows converted on their way into the
+// matrix cores (gfx950 / CDNA4).  It serves the assignment step of the k-means build.
+//
+// The assignment needs, for every point, the nearest of a few hundred centres.  Through the look-up that was a bf16
+// copy of the points (read and written once per build), a bf16 pass with candidate lists and eight exactly re-scored
+// fp32 centres per point: 50,000 x 8,192, 200 centres 250 + 820 us a round, the latter for 13 GB of centre rows
+// out of the L2s, and 430 us for the copy.  Here a value x is taken as hi + lo, two bf16 values, and
+//     q.c = hi.hi + hi.lo + lo.hi   (lo.lo, at most 2^-16 of the product, is left out)
+// so that the keys are good to 2^-15 of |q||c|, mostly far better, instead of 2^-7 and nearly every point's nearest
+// centre is known from them alone (kmeans_pick_kernel, which re-scores what the bound of its comment leaves open).
+// Three matrix instructions per block instead of one: 0.51 TFLOP in that case, 400 to 470 us (1.1 to 1.25 PFLOP/s; the matrix
+// pipes are busy 60 % of the time at 2.0 GHz, and it is the power limit that sets the clock), and 45 us for the choice.  The
+// whole build, two rounds, 4,630 -> 2,090 us; 50,000 x 512 1,677 -> 503, 50,000 x 8,191 6,850 -> 2,470, 50,000 x 8,192 with 400
+// centres 5,620 -> 3,570, 3,000 x 300 with 20 centres 234 -> 157.
+//
+//   - 512 threads, 4 x 2 waves, a wave 64 rows x half the columns; a k-step is 32 elements.  The fp32 rows are copied
+//     as they are (LDS-direct loads, ring of three stages: the stage after the next is on its way for one and a
+//     half k-steps before it is needed), and a wave converts its 64 rows' fragments of the next k-step between the matrix
+//     instructions of this one.  Converting before the LDS would need the loads in registers; a prepared copy
+//     would need the memory traffic this kernel is there to save.
+//   - The prepared rows (hi and lo, tiled like a cache) come out of L2 one k-step ahead, two stages.
+//   - LDS: 3 x 32 KiB + 2 x 2 KiB per 16 columns, one workgroup per CU.  A k-step of 13 column blocks reads 164 KiB of
+//     fragments (about half the time of its matrix instructions) and writes 58.
+//   - Work: the flattened (row tile, column tile, k-step) space in even ranges, one per CU (196 row tiles would leave
+//     60 CUs idle); a range leaves the sums of each tile it touches in a slot, and the reader of the sums adds the
+//     slots of a tile in order.  Many tiles per CU: whole tiles, one slot.
+//
+// Paper: Sec. 4 "k-means".
+#include "freeze_internal.h"
+#include "select_common.h"
+
+#include <type_traits>
+
+namespace fz {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(8))) float f32x8;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((address_space(3))) void *lds_void_ptr;
+
+namespace {
+
+constexpr int kAStage = kRowsTile * kKB * 4;    // 32 KiB: one k-step of the fp32 rows
+constexpr int kAStages = 3;
+
+// LDS-direct 4-byte load: as load16_global_to_lds, 4 bytes per lane
+__device__ __forceinline__ void load4_global_to_lds(uint64_t sbase, uint32_t voff, uint32_t lds_byte_addr)
+{
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_byte_addr), "v"(voff), "s"(sbase)
+                 : "memory", "m0");
+}
+
+struct RowsGemmArgs {
+    const float *x;               // [n, d]
+    const uint16_t *hi, *lo;      // prepared rows, tiled (tiles of kTileN rows, d_pad elements)
+    float *part;                  // [tile][slot][kRowsTile][16 NCB]
+    float *sq;                    // [row tile][slot][kRowsTile] sums of squares of the fp32 rows, or null
+    int64_t n, d, d_pad;
+    int64_t len;                  // k-steps of a range
+    int nk, n_tiles, m_tiles, slots;
+};
+
+__device__ __forceinline__ int a_swizzle(int row)
+{
+    const int u = (row >> 1) & 7;
+    return u ^ (((u + 2) & 4) >> 1);
+}
+
+// VEC: rows start on 16-byte boundaries (d a multiple of 4)
+// NCB: blocks of 16 columns of a tile; the second wave of a row of waves has one less where the number is odd
+template <int NCB, bool VEC>
+__global__ __launch_bounds__(512) void rows_gemm_kernel(RowsGemmArgs p)
+{
+    constexpr int TNB = (NCB + 1) / 2;                  // column blocks of a wave
+    constexpr int NC = 16 * NCB;                        // columns of a tile
+    constexpr int B_IMG = NC * 64;                      // one k-step of hi (or lo)
+    constexpr int B_STAGE = 2 * B_IMG;
+    constexpr int NBI = B_STAGE / 1024;                 // load instructions of a stage
+    constexpr int NI_B = (NBI + 7) / 8;                 // per wave (the last wave's surplus repeats a load)
+    constexpr int NI_A = VEC ? 4 : 16;
+    constexpr int NL = NI_B + NI_A;
+    constexpr int kB = kAStages * kAStage;              // byte offset of the prepared rows' stages
+    static_assert(kB + 2 * B_STAGE <= 163840, "LDS budget");
+    static_assert(2 * NI_A + NI_B <= 63, "vmcnt range");
+    __shared__ __attribute__((aligned(16))) unsigned char smem[kB + 2 * B_STAGE];
+    const f32x4 *smem_a = reinterpret_cast<const f32x4 *>(smem);
+    const bf16x8 *smem_b = reinterpret_cast<const bf16x8 *>(smem + kB);
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = w >> 1, wn = (w ^ (w >> 2)) & 1;     // (waves w and w + 4 share a SIMD: one of each kind)
+    const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_void_ptr)smem;
+    const int nk = p.nk;
+
+    const int64_t total = (int64_t)p.m_tiles * p.n_tiles * nk;
+    const int64_t g_begin = (int64_t)blockIdx.x * p.len;
+    const int64_t g_end = g_begin + p.len < total ? g_begin + p.len : total;
+    if (g_begin >= g_end) return;   // uniform
+
+    // fp32 rows: lane's place in a load instruction.  The LDS image of a row is its eight 16-byte chunks, chunk c at
+    // position c ^ a_swizzle(row): a fragment read takes one chunk of each of 16 rows for every two lanes groups, and the
+    // 16 lanes a cycle serves (rows 0-3 and 12-15 of one group with rows 4-11 of the next) meet 16 different positions.
+    const uint32_t d4 = (uint32_t)p.d * 4;
+    const uint32_t a_row = VEC ? w * 32 + (lane >> 3) : w * 32 + (lane >> 5);   // + i * (8 or 2)
+    const uint32_t a_row_off = a_row * d4;
+    // fragment addresses, in 16-byte units
+    const int rA = wm * 64 + (lane & 15);               // + 16 i: leaves the swizzle as it is
+    const int swA = a_swizzle(rA);
+    const int rdA0 = rA * 8 + ((2 * (lane >> 4)) ^ swA), rdA1 = rA * 8 + ((2 * (lane >> 4) + 1) ^ swA);
+    const int rB = wn * TNB * 16 + (lane & 15);
+    const int rdB = rB * 4 + ((lane >> 4) ^ tiled_chunk_swizzle(rB));
+
+    for (int64_t g = g_begin; g < g_end;) {
+        const int64_t tile = g / nk;
+        const int ka = (int)(g - tile * nk);
+        const int kb = g_end - tile * nk < nk ? (int)(g_end - tile * nk) : nk;
+        const int nt = (int)(tile % p.n_tiles);
+        const int64_t mt = tile / p.n_tiles;
+        // slot: how many ranges before this one touch the tile
+        const int slot = (int)(blockIdx.x - (tile * nk) / p.len);
+        // the last row tile reaches back: every load is of a row that exists
+        const int64_t row0 = (mt + 1) * kRowsTile <= p.n ? mt * kRowsTile : p.n - kRowsTile;
+        const uint64_t gA = uniform_u64((uint64_t)(uintptr_t)(p.x + row0 * p.d));
+
+        // load l of k-step kt's prepared rows
+        auto issue_b = [&](int buf, int kt, int l) {
+            int id = l * 8 + w;
+            id = id < NBI ? id : NBI - 1;
+            const int rb = nt * NCB + id % NCB;   // block of 16 prepared rows
+            const uint64_t src = (uint64_t)(uintptr_t)(id < NCB ? p.hi : p.lo) +
+                                 ((uint64_t)(rb >> 4) * (p.d_pad / kKB) + kt) * (kTileN * 64) + (rb & 15) * 1024;
+            load16_global_to_lds(uniform_u64(src), lane * 16, smem_base + kB + buf * B_STAGE + id * 1024);
+        };
+        // load i of k-step kt's fp32 rows; elements past the row's end are met by zeros in the prepared rows: any
+        // element of the row will do for them
+        auto issue_a = [&](int stage, int kt, int i) {
+            const uint32_t ko = (uint32_t)kt * 128;
+            if constexpr (VEC) {
+                const uint32_t c = (lane & 7) ^ a_swizzle(i * 8 + (lane >> 3));
+                const uint32_t at = ko + c * 16;
+                load16_global_to_lds_nt(gA + (uint64_t)(i * 8) * d4, a_row_off + (at < d4 ? at : 0u), smem_base + stage * kAStage + w * 4096 + i * 1024);
+            } else {
+                const uint32_t at = ko + (((lane & 31) ^ (a_swizzle(i * 2) << 2)) << 2);
+                load4_global_to_lds(gA + (uint64_t)(i * 2) * d4, a_row_off + (at < d4 ? at : 0u), smem_base + stage * kAStage + w * 4096 + i * 256);
+            }
+        };
+
+        bf16x8 ah[2][4], al[2][4], bh[2], bl[2];
+        float sq[4] = {0.f, 0.f, 0.f, 0.f};
+        f32x4 raw[2];
+        auto read_a = [&](int stage, int i) {
+            raw[0] = smem_a[stage * (kAStage / 16) + rdA0 + i * 128];
+            raw[1] = smem_a[stage * (kAStage / 16) + rdA1 + i * 128];
+        };
+        auto convert = [&](int set, int i) {
+            f32x8 x;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                x[e] = raw[0][e];
+                x[4 + e] = raw[1][e];
+            }
+            const u32x4 h = __builtin_bit_cast(u32x4, __builtin_convertvector(x, bf16x8));   // round to nearest even
+            f32x8 r;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                r[2 * e] = x[2 * e] - __uint_as_float(h[e] << 16);
+                r[2 * e + 1] = x[2 * e + 1] - __uint_as_float(h[e] & 0xffff0000u);
+            }
+            u32x4 hv = h, lv = __builtin_bit_cast(u32x4, __builtin_convertvector(r, bf16x8));
+            // here, among the matrix instructions, and not where the values are first used
+            asm volatile("" : "+v"(hv), "+v"(lv));
+            ah[set][i] = __builtin_bit_cast(bf16x8, hv);
+            al[set][i] = __builtin_bit_cast(bf16x8, lv);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) sq[i] = __builtin_fmaf(x[e], x[e], sq[i]);
+        };
+        auto read_b = [&](int set, int buf, int j) {
+            const int at = (NCB % 2 && j == TNB - 1) ? j - wn : j;   // (the second wave has no such block)
+            bh[set] = smem_b[buf * (B_STAGE / 16) + rdB + at * 64];
+            bl[set] = smem_b[buf * (B_STAGE / 16) + B_IMG / 16 + rdB + at * 64];
+        };
+
+        f32x4 acc[4][TNB];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < TNB; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
+
+        const int klast = kb - 1;
+        auto at_most = [&](int kt) { return kt < klast ? kt : klast; };
+        __syncthreads();   // the LDS is free (a range's previous tile)
+#pragma unroll
+        for (int i = 0; i < NI_A; ++i) issue_a(0, ka, i);
+#pragma unroll
+        for (int i = 0; i < NI_A; ++i) issue_a(1, at_most(ka + 1), i);
+#pragma unroll
+        for (int l = 0; l < NI_B; ++l) issue_b(0, ka, l);
+#pragma unroll
+        for (int i = 0; i < NI_A; ++i) issue_a(2, at_most(ka + 2), i);
+        wait_global_loads_le<2 * NI_A + NI_B>();
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            read_a(0, i);
+            convert(0, i);
+        }
+        wait_global_loads_le<NI_A>();
+        __syncthreads();
+        int st = 0;   // stage of the fp32 rows of k-step kt
+        read_b(0, 0, 0);
+        // At the top of k-step kt: its A fragments are in register set `cur`, its first B fragments on their way to
+        // registers; its prepared rows and the fp32 rows of kt + 1 are in LDS, the fp32 rows of kt + 2 in flight.  The
+        // step's barrier comes before its last group of matrix instructions, which need nothing newer: it publishes
+        // the prepared rows of kt + 1 and the fp32 rows of kt + 2 and frees the stages of kt's prepared rows and of the fp32
+        // rows of kt + 1, which have been converted.
+        auto k_step = [&](int kt, auto tag) {
+            constexpr int cur = decltype(tag)::value;
+            constexpr int S0 = cur * TNB;   // B fragments alternate between two register sets, on from step to step
+            const int nst = st + 1 == kAStages ? 0 : st + 1;
+            const int b_kt = at_most(kt + 1), a_kt = at_most(kt + 3);
+#pragma unroll
+            for (int j = 0; j < TNB; ++j) {
+                constexpr int GA = TNB - 1;   // groups that convert A blocks and issue loads
+                auto group_of = [](int i) { return GA >= 4 ? i : i * GA / 4; };
+                auto mfma = [&](bf16x8(&b)[2], bf16x8(&x)[2][4]) {
+                    if (NCB % 2 && j == TNB - 1 && wn) return;   // uniform
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[(S0 + j) & 1], x[cur][i], acc[i][j], 0, 0, 0);
+                };
+                if (j == TNB - 1) {
+                    wait_global_loads_le<NI_A>();
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    __syncthreads();
+                    read_b((S0 + TNB) & 1, cur ^ 1, 0);
+                } else {
+                    read_b((S0 + j + 1) & 1, cur, j + 1);
+                    if (GA >= 4 && j < 4) read_a(nst, j);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                mfma(bh, ah);
+                mfma(bl, ah);
+                if (j < GA) {
+#pragma unroll
+                    for (int l = j * NL / GA; l < (j + 1) * NL / GA; ++l) {
+                        if (l < NI_B) issue_b(cur ^ 1, b_kt, l);
+                        else issue_a(st, a_kt, l - NI_B);
+                    }
+                }
+                mfma(bh, al);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (j >= GA || group_of(i) != j) continue;
+                    if (GA < 4) read_a(nst, i);
+                    convert(cur ^ 1, i);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            st = nst;
+        };
+        int kt = ka;
+        while (true) {
+            k_step(kt, std::integral_constant<int, 0>{});
+            if (++kt >= kb) break;
+            k_step(kt, std::integral_constant<int, 1>{});
+            if (++kt >= kb) break;
+        }
+        wait_global_loads_le<0>();   // the refills past the last k-step
+        // Sums out: the matrix instruction takes the prepared rows as its rows, so a lane holds four consecutive
+        // columns of one fp32 row.
+        float *dst = p.part + ((tile * p.slots + slot) * kRowsTile + wm * 64 + (lane & 15)) * NC + wn * TNB * 16 + (lane >> 4) * 4;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < TNB; ++j)
+                if (wn * TNB + j < NCB) *reinterpret_cast<f32x4 *>(dst + i * 16 * NC + j * 16) = acc[i][j];
+        if (p.sq && nt == 0 && wn == 0) {
+            // (the fragments converted past the last k-step are of that step again: sums of squares only grow by them)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float v = sq[i];
+                v += __shfl_xor(v, 16, 64);
+                v += __shfl_xor(v, 32, 64);
+                if (lane < 16) p.sq[(mt * p.slots + slot) * kRowsTile + wm * 64 + i * 16 + lane] = v;
+            }
+        }
+        g = tile * nk + kb;
+    }
+}
+
+// hi, lo [tile of kTileN rows][k-block][row][32] and norm of the fp32 rows [kc, d]: x = hi + lo up to 2^-17 |x|.  Rows past
+// kc are zeros with norm +inf.
+__global__ __launch_bounds__(512) void rows_split_kernel(const float *rows, int64_t kc, int64_t d, int64_t d_pad, uint16_t *hi, uint16_t *lo, float *norm)
+{
+    __shared__ double wave_sum[8];
+    const int64_t r = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int64_t base = (r / kTileN) * (int64_t)kTileN * d_pad;
+    double s = 0.0;
+    for (int64_t j = tid; j < d_pad / 8; j += 512) {
+        __attribute__((aligned(16))) uint16_t h[8], l[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int64_t at = j * 8 + e;
+            const float x = r < kc && at < d ? rows[r * d + at] : 0.f;
+            h[e] = bf16_rne(x);
+            l[e] = bf16_rne(x - __uint_as_float((uint32_t)h[e] << 16));
+            s += (double)x * (double)x;
+        }
+        const int64_t o = base + tiled_chunk_offset((int)(r % kTileN), j, kTileN) * 8;
+        *reinterpret_cast<uint4 *>(hi + o) = *reinterpret_cast<const uint4 *>(h);
+        *reinterpret_cast<uint4 *>(lo + o) = *reinterpret_cast<const uint4 *>(l);
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (lane == 0) wave_sum[w] = s;
+    __syncthreads();
+    if (tid == 0) {
+        double t = 0.0;
+        for (int i = 0; i < 8; ++i) t += wave_sum[i];
+        norm[r] = r < kc ? (float)t : __builtin_inff();
+    }
+}
+
+struct PickArgs {
+    const float *x, *centers;   // [n, d], [kc, d]
+    const float *part, *sq, *norm;
+    int32_t *assign;
+    int64_t n, d, kc;
+    uint32_t len;               // (the flattened space has fewer than 2^31 k-steps)
+    int nk, n_tiles, slots, nc;
+    float eps;                  // bound of a key's error, in units of 2 |q||c|
+};
+
+constexpr int kPickPoints = 4;   // points per wave
+
+// Nearest centre of every point, kPickPoints points per wave.  key(c) = |c|^2 - 2 q.c is off by at most
+//     e(c) = 2 eps |q||c| + 2^-22 (|c|^2 + |q|^2):
+// eps covers lo.lo (2^-16 of the sum of |q_i c_i| at most, which is at most |q||c|) and what hi + lo leaves of the values (2^-17
+// of each), both always,
+// and the rounding of the 3 nk additions of a sum (each at most an ulp of a partial sum: as independent errors they
+// come to sqrt(3 nk) 2^-24, and eight times that is allowed); the second term covers the rounding of |c|^2 and of the
+// last subtraction, and of an fp32 distance.  Centres with key - e above the smallest key + e are not the nearest.  If more
+// than one is left, the workgroup re-scores them exactly; equal distances go to the lower index.  Keys that are no
+// numbers (overflow) leave all centres in.
+// fp32 distances of point row q to the m centres cand_s, by 256 threads, in the order of additions that the look-ups'
+// re-scoring has for rows of this length (rescore_block_all<256, .> and rescore_wave): whoever assigns a point, nearly equal
+// distances compare alike.
+__device__ inline void exact_distances(const float *q, const float *centers, int64_t d, const int32_t *cand_s, int m, float *dist_s, float *red_s, int tid)
+{
+    const int lane = tid & 63, w = tid >> 6;
+    auto wave_sum = [](float v) {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+        return v;
+    };
+    auto eight = [](const f32x4 (&x)[2], const f32x4 (&c)[2], float acc) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float df = x[e >> 2][e & 3] - c[e >> 2][e & 3];
+            acc = __builtin_fmaf(df, df, acc);
+        }
+        return acc;
+    };
+    // chain of pieces of eight elements at first, first + step, .., four pieces' loads in flight
+    auto chain = [&](const float *r, int64_t first, int64_t step) {
+        float acc = 0.f;
+        int64_t i = first;
+        for (; i + 3 * step < d; i += 4 * step) {
+            f32x4 x[4][2], c[4][2];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    x[u][h] = *reinterpret_cast<const f32x4 *>(q + i + u * step + 4 * h);
+                    c[u][h] = *reinterpret_cast<const f32x4 *>(r + i + u * step + 4 * h);
+                }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) acc = eight(x[u], c[u], acc);
+        }
+        for (; i < d; i += step) {
+            const f32x4 x[2] = {*reinterpret_cast<const f32x4 *>(q + i), *reinterpret_cast<const f32x4 *>(q + i + 4)};
+            const f32x4 c[2] = {*reinterpret_cast<const f32x4 *>(r + i), *reinterpret_cast<const f32x4 *>(r + i + 4)};
+            acc = eight(x, c, acc);
+        }
+        return acc;
+    };
+    if (d >= 4096 && d % 8 == 0) {   // (rows start on 16-byte boundaries)
+        for (int j = 0; j < m; ++j) {
+            const float v = wave_sum(chain(centers + cand_s[j] * d, (int64_t)tid * 8, 256 * 8));
+            if (lane == 0) red_s[w] = v;
+            __syncthreads();
+            if (tid == 0) dist_s[j] = (red_s[0] + red_s[1]) + (red_s[2] + red_s[3]);
+            __syncthreads();
+        }
+        return;
+    }
+    for (int j = w; j < m; j += 4) {
+        const float *r = centers + cand_s[j] * d;
+        float acc = 0.f;
+        if (d % 8 == 0) {
+            acc = chain(r, (int64_t)lane * 8, 64 * 8);
+        } else {
+            int64_t i = lane;
+            for (; i + 3 * 64 < d; i += 4 * 64) {
+                float x[4], c[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    x[u] = q[i + u * 64];
+                    c[u] = r[i + u * 64];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const float df = x[u] - c[u];
+                    acc = __builtin_fmaf(df, df, acc);
+                }
+            }
+            for (; i < d; i += 64) {
+                const float df = q[i] - r[i];
+                acc = __builtin_fmaf(df, df, acc);
+            }
+        }
+        acc = wave_sum(acc);
+        if (lane == 0) dist_s[j] = acc;
+    }
+    __syncthreads();
+}
+
+template <int MT>   // centre tiles
+__global__ __launch_bounds__(256) void kmeans_pick_kernel(PickArgs p)
+{
+    constexpr int U = kPickPoints;
+    const int lane = threadIdx.x & 63;
+    const int64_t i0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * U;   // (U divides kRowsTile: one row tile)
+    // (a wave past the end goes through the motions on the last point: the workgroup's barriers need it)
+    const int live = i0 >= p.n ? 0 : (p.n - i0 < U ? (int)(p.n - i0) : U);
+    const int64_t at0 = live ? i0 : p.n - 1;
+    const int64_t m_tile = at0 / kRowsTile;
+    const int64_t row0 = (m_tile + 1) * kRowsTile <= p.n ? m_tile * kRowsTile : p.n - kRowsTile;
+    const int row = (int)(at0 - row0);
+    auto slots_of = [&](int64_t tile) {
+        const uint32_t at = (uint32_t)tile * (uint32_t)p.nk;
+        return p.slots == 1 ? 1 : (int)((at + p.nk - 1) / p.len - at / p.len) + 1;
+    };
+    float q2[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) q2[u] = 0.f;
+    {
+        const int ns = slots_of(m_tile * p.n_tiles);
+        for (int s = 0; s < ns; ++s)
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                q2[u] += p.sq[(m_tile * p.slots + s) * kRowsTile + row + (u < live ? u : 0)];
+    }
+    // columns of a lane: 4 lane .. + 3 of every column tile (a tile has at most 256)
+    float lower[U][MT][4], upper[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) upper[u] = __builtin_inff();
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+        if (t >= p.n_tiles || 4 * lane >= p.nc) continue;
+        const int64_t tile = m_tile * p.n_tiles + t;
+        const int ns = slots_of(tile);
+        const float *src = p.part + (tile * p.slots * kRowsTile + row) * p.nc + 4 * lane;
+        f32x4 dot[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) dot[u] = *reinterpret_cast<const f32x4 *>(src + (u < live ? u : 0) * p.nc);
+        for (int s = 1; s < ns; ++s)
+#pragma unroll
+            for (int u = 0; u < U; ++u) dot[u] += *reinterpret_cast<const f32x4 *>(src + ((int64_t)s * kRowsTile + (u < live ? u : 0)) * p.nc);
+        // (the norms' buffer has whole tiles of kTileN entries, +inf past the last centre)
+        const f32x4 c2 = *reinterpret_cast<const f32x4 *>(p.norm + t * p.nc + 4 * lane);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float c1 = __builtin_sqrtf(c2[e]);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float key = __builtin_fmaf(-2.f, dot[u][e], c2[e]);
+                const float err = 2.f * p.eps * __builtin_sqrtf(q2[u]) * c1 + 2.4e-7f * (c2[e] + q2[u]) + 1e-36f * (float)p.d;
+                lower[u][t][e] = key - err;
+                if ((int64_t)t * p.nc + 4 * lane + e < p.kc) upper[u] = __builtin_fminf(upper[u], key + err);
+            }
+        }
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+        for (int u = 0; u < U; ++u) upper[u] = __builtin_fminf(upper[u], __shfl_xor(upper[u], off, 64));
+    // masks[point][lane]: the lane's centres that are left (bit 4 t + e: column 4 lane + e of tile t), where more than one is
+    __shared__ uint32_t masks[4 * U][64];
+    __shared__ int open_s[4 * U];
+    __shared__ int32_t cand_s[MT * 256];
+    __shared__ float dist_s[MT * 256];
+    __shared__ float red_s[4];
+    __shared__ int count_s;
+    const int w = threadIdx.x >> 6;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        uint32_t mine = 0;
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (t < p.n_tiles && 4 * lane < p.nc && (int64_t)t * p.nc + 4 * lane + e < p.kc && !(lower[u][t][e] > upper[u])) mine |= 1u << (t * 4 + e);
+        const uint64_t any = __ballot(mine != 0);
+        const uint32_t only = (uint32_t)__builtin_amdgcn_readlane((int)mine, any ? __builtin_ctzll(any) : 0);
+        const bool one = any && (any & (any - 1)) == 0 && (only & (only - 1)) == 0;
+        masks[w * U + u][lane] = mine;
+        if (lane == 0) {
+            open_s[w * U + u] = u < live && !one;
+            const int bit = __builtin_ctz(only | 0x80000000u);
+            if (u < live && one) p.assign[i0 + u] = (int32_t)((bit >> 2) * p.nc + 4 * __builtin_ctzll(any) + (bit & 3));
+        }
+    }
+    __syncthreads();
+    for (int o = 0; o < 4 * U; ++o) {
+        if (!open_s[o]) continue;   // uniform
+        const int64_t i = (int64_t)blockIdx.x * 4 * U + o;
+        if (w == 0) {   // the centres that are left, ascending
+            const uint32_t mine = masks[o][lane];
+            int base = 0;
+            for (int t = 0; t < p.n_tiles; ++t) {
+                const uint32_t bits = mine >> (t * 4) & 15u;
+                const int own = __builtin_popcount(bits);
+                int at = own;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const int v = __shfl_up(at, off, 64);
+                    if (lane >= off) at += v;
+                }
+                const int all = __shfl(at, 63, 64);
+                at += base - own;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (bits >> e & 1u) cand_s[at++] = t * p.nc + 4 * lane + e;
+                base += all;
+            }
+            if (lane == 0) count_s = base;
+        }
+        __syncthreads();
+        const int m = count_s;
+        exact_distances(p.x + i * p.d, p.centers, p.d, cand_s, m, dist_s, red_s, (int)threadIdx.x);
+        if (w == 0) {   // the nearest, equal distances the lower index (which comes first)
+            uint64_t best = kSentinel;
+            for (int j = lane; j < m; j += 64) {
+                const uint64_t v = ((uint64_t)ordered_bits(dist_s[j]) << 32) | (uint32_t)j;
+                best = v < best ? v : best;
+            }
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+                const uint64_t v = ((uint64_t)(uint32_t)__shfl_xor((int)(uint32_t)(best >> 32), off, 64) << 32) | (uint32_t)__shfl_xor((int)(uint32_t)best, off, 64);
+                best = v < best ? v : best;
+            }
+            const uint32_t j = (uint32_t)best;
+            if (lane == 0) p.assign[i] = cand_s[j < (uint32_t)m ? j : 0];
+        }
+        __syncthreads();   // cand_s and dist_s are free
+    }
+}
+
+template <int NCB>
+hipError_t launch_gemm(const RowsPlan &pl, const RowsGemmArgs &a, hipStream_t s)
+{
+    if (a.d % 4 == 0)
+        hipLaunchKernelGGL((rows_gemm_kernel<NCB, true>), dim3((unsigned)pl.wgs), dim3(512), 0, s, a);
+    else
+        hipLaunchKernelGGL((rows_gemm_kernel<NCB, false>), dim3((unsigned)pl.wgs), dim3(512), 0, s, a);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+RowsPlan plan_rows(int64_t n, int64_t d, int64_t kc, int num_cus)
+{
+    RowsPlan pl{};
+    // a tile's rows reach 4 GiB at most; the last row tile reaches back over the one before it
+    if (n < kRowsTile || d < 1 || d > (int64_t)1 << 20 || kc < 1 || kc > kRowsMaxTiles * kTileN) return pl;
+    pl.n_tiles = (int)((kc + kTileN - 1) / kTileN);
+    const int per = (int)((kc + pl.n_tiles - 1) / pl.n_tiles);
+    for (int b : {4, 6, 8, 10, 12, 13, 14, 16}) {
+        pl.ncb = b;
+        if (16 * b >= per) break;
+    }
+    pl.nc = 16 * pl.ncb;
+    pl.m_tiles = (int)((n + kRowsTile - 1) / kRowsTile);
+    pl.nk = (int)((d + kKB - 1) / kKB);
+    const int64_t tiles = (int64_t)pl.m_tiles * pl.n_tiles, total = tiles * pl.nk;
+    if (tiles >= 8 * (int64_t)num_cus) {
+        pl.len = (tiles + num_cus - 1) / num_cus * pl.nk;   // whole tiles: an idle eighth at most
+    } else {
+        pl.len = (total + num_cus - 1) / num_cus;
+        const int64_t least = pl.nk < 8 ? pl.nk : 8;        // a slot is written and read for it
+        if (pl.len < least) pl.len = least;
+    }
+    pl.wgs = (int)((total + pl.len - 1) / pl.len);
+    pl.slots = pl.len % pl.nk == 0 ? 1 : (int)((pl.nk + pl.len - 2) / pl.len) + 1;
+    pl.part = (size_t)tiles * pl.slots * kRowsTile * pl.nc;
+    pl.sq = (size_t)pl.m_tiles * pl.slots * kRowsTile;
+    pl.on = pl.part * 4 <= (size_t)1 << 30 && total < (int64_t)1 << 31;
+    return pl;
+}
+
+hipError_t launch_rows_split(const float *rows, int64_t kc, int64_t n_pad, int64_t d, int64_t d_pad, uint16_t *hi, uint16_t *lo, float *norm, hipStream_t s)
+{
+    hipLaunchKernelGGL(rows_split_kernel, dim3((unsigned)n_pad), dim3(512), 0, s, rows, kc, d, d_pad, hi, lo, norm);
+    return hipGetLastError();
+}
+
+hipError_t launch_kmeans_assign(const RowsPlan &pl, const float *points, int64_t n, int64_t d, int64_t d_pad, const float *centers, int64_t kc,
+                                const uint16_t *hi, const uint16_t *lo, const float *norm, float *part, float *sq, int32_t *assign, hipStream_t s)
+{
+    if (!pl.on || n < kRowsTile || pl.m_tiles != (n + kRowsTile - 1) / kRowsTile || d_pad < (int64_t)pl.nk * kKB || kc > (int64_t)pl.n_tiles * pl.nc ||
+        (int64_t)pl.n_tiles * pl.nc > (kc + kTileN - 1) / kTileN * kTileN || (reinterpret_cast<uintptr_t>(points) % 16) != 0)
+        return hipErrorInvalidValue;
+    RowsGemmArgs a{points, hi, lo, part, sq, n, d, d_pad, pl.len, pl.nk, pl.n_tiles, pl.m_tiles, pl.slots};
+    hipError_t e;
+    switch (pl.ncb) {
+    case 4: e = launch_gemm<4>(pl, a, s); break;
+    case 6: e = launch_gemm<6>(pl, a, s); break;
+    case 8: e = launch_gemm<8>(pl, a, s); break;
+    case 10: e = launch_gemm<10>(pl, a, s); break;
+    case 12: e = launch_gemm<12>(pl, a, s); break;
+    case 13: e = launch_gemm<13>(pl, a, s); break;
+    case 14: e = launch_gemm<14>(pl, a, s); break;
+    case 16: e = launch_gemm<16>(pl, a, s); break;
+    default: return hipErrorInvalidValue;
+    }
+    if (e != hipSuccess) return e;
+    const float eps = 3.1e-5f + 5.96e-8f * (16.f + 8.f * __builtin_sqrtf(3.f * (float)pl.nk));
+    PickArgs k{points, centers, part, sq, norm, assign, n, d, kc, (uint32_t)pl.len, pl.nk, pl.n_tiles, pl.slots, pl.nc, eps};
+    const dim3 grid((unsigned)((n + 4 * kPickPoints - 1) / (4 * kPickPoints)));
+    if (pl.n_tiles == 1) hipLaunchKernelGGL(kmeans_pick_kernel<1>, grid, dim3(256), 0, s, k);
+    else hipLaunchKernelGGL(kmeans_pick_kernel<kRowsMaxTiles>, grid, dim3(256), 0, s, k);
+    return hipGetLastError();
+}
+
+}  // namespace fz

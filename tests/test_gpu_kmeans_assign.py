@@ -1,0 +1,113 @@
+"""The k-means build's assignment by the product with split centres: the edges of its tiles (points, centres, depth), rows of
+any length, ranges that cut tiles and ranges of whole ones, ties, and values that are no numbers.  The assignment shows in the
+centres after one round, which are compared with means over the nearest centres by float64 distances."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2002_02645_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+def _nearest64(pts, cen):
+    """Index of the nearest centre (equal distances: the lower), and the smallest relative gap to the second, float64."""
+    p, c = torch.from_numpy(pts).double(), torch.from_numpy(cen).double()
+    best, gap = [], np.inf
+    for lo in range(0, p.shape[0], max(1, (1 << 24) // c.numel())):
+        x = p[lo:lo + max(1, (1 << 24) // c.numel())]
+        dist = ((x[:, None, :] - c[None]) ** 2).sum(2).numpy()
+        best.append(dist.argmin(1))
+        if c.shape[0] > 1:
+            two = np.partition(dist, 1, axis=1)
+            gap = min(gap, ((two[:, 1] - two[:, 0]) / np.maximum(two[:, 1], 1e-30)).min())
+    return np.concatenate(best), gap
+
+
+def _means(pts, assign, cen):
+    out = cen.copy()
+    for c in range(cen.shape[0]):
+        rows = pts[assign == c].astype(np.float64)
+        if rows.shape[0]:
+            out[c] = (np.add.accumulate(rows, axis=0)[-1] / rows.shape[0]).astype(np.float32)
+    return out
+
+
+def _build(pts, cen, iters=1):
+    fc = binding.FreezeCache(1)
+    try:
+        lab = torch.zeros(pts.shape[0], dtype=torch.int32, device="cuda")
+        got = fc.build_kmeans_layer(0, torch.from_numpy(pts).cuda(), lab, 3, torch.from_numpy(cen).cuda(), iters)
+        torch.cuda.synchronize()
+        return {k: v.cpu().numpy() for k, v in got.items()}
+    finally:
+        fc.close()
+
+
+@pytest.mark.parametrize("n,d,kc", [
+    (256, 32, 1),         # one tile of points, one k-step, one centre
+    (257, 33, 16),        # the second tile reaches back over 255 rows of the first
+    (300, 4, 64), (511, 100, 65), (1021, 31, 97),
+    (2051, 36, 200),      # 13 column blocks: the waves of a pair differ
+    (700, 520, 256),      # the widest tile
+    (900, 68, 257), (1500, 98, 512),       # two tiles of centres
+    (1300, 60, 513),      # more centres than the product takes
+    (601, 4104, 13),      # re-scored by the whole workgroup, ranges that cut tiles in several places
+    (600, 4099, 33),      # ... by waves, rows on any boundary
+    (255, 64, 9),         # fewer points than a tile
+])
+def test_assignment_on_random_points(n, d, kc):
+    rng = np.random.default_rng(n * 7 + d + kc)
+    centre = 2.0 * rng.standard_normal((5, d))
+    pts = (centre[rng.integers(0, 5, n)] + rng.standard_normal((n, d))).astype(np.float32)
+    cen = pts[rng.permutation(n)[:kc]].copy() if kc <= n else pts[:kc].copy()
+    want, gap = _nearest64(pts, cen)
+    # an fp32 distance is good to (log2 d + 16) 2^-24 < 2e-6; no point of these inputs is that close to two centres
+    assert gap > 4e-6
+    got = _build(pts, cen)
+    np.testing.assert_allclose(got["centers"], _means(pts, want, cen), rtol=1e-6, atol=1e-7)
+    assert (got["fraction"][np.bincount(_nearest64(pts, got["centers"])[0], minlength=kc) == 0] == 0).all()
+
+
+@pytest.mark.parametrize("n,d,kc", [
+    (3000, 6, 40),
+    (530000, 8, 5),       # so many tiles that ranges are whole ones
+    (1200, 7, 300),
+])
+def test_assignment_with_ties(n, d, kc):
+    # whole numbers that bf16 does not hold: every distance is exact, many are equal, and some centres are there twice
+    rng = np.random.default_rng(n)
+    pts = rng.integers(-2, 3, (n, d)).astype(np.float32) * 257.0
+    cen = pts[:kc].copy()
+    cen[kc // 2] = cen[kc // 3]
+    want, _ = _nearest64(pts, cen)
+    got = _build(pts, cen)
+    np.testing.assert_allclose(got["centers"], _means(pts, want, cen), rtol=1e-6, atol=1e-4)
+    assert np.array_equal(got["centers"][kc // 2], cen[kc // 2])      # its twin has the lower index and every point
+
+
+def test_identical_points():
+    # every centre is left for every point: all of them re-scored, all equal, the first one takes them
+    pts = np.full((400, 40), 1.0039, dtype=np.float32)
+    got = _build(pts, pts[:30].copy())
+    assert np.array_equal(got["centers"], pts[:30]) and got["fraction"][0] == 1.0 and (got["fraction"][1:] == 0).all()
+
+
+def test_points_that_are_no_numbers():
+    # outside the contract, but nothing is read or written out of bounds and the other points are assigned as ever
+    rng = np.random.default_rng(3)
+    n, d, kc = 777, 45, 20
+    pts = rng.standard_normal((n, d)).astype(np.float32)
+    cen = pts[:kc].copy()
+    want, gap = _nearest64(pts, cen)
+    assert gap > 4e-6
+    bad = [100, 300, 776]
+    broken = pts.copy()
+    broken[100, 7], broken[300, :], broken[776, 44] = np.nan, np.inf, -np.inf
+    got = _build(broken, cen)["centers"]
+    keep = np.ones(n, bool)
+    keep[bad] = False
+    exp = _means(pts[keep], want[keep], cen)
+    hit = ~np.isfinite(got).all(axis=1)                               # centres that took one of the three
+    assert hit.sum() <= 3
+    np.testing.assert_allclose(got[~hit], exp[~hit], rtol=1e-6, atol=1e-7)
