@@ -1039,6 +1039,21 @@ __device__ __forceinline__ bool certificate(const uint64_t *ent, const float *di
     return *verdict_s != 0;
 }
 
+// Candidates re-scored in a first step; the others of the r only for the queries that these do not confirm.  Long
+// rows only: they are what the finishing kernels wait for.
+//   - three quarters of a width that leaves room (16 with k <= 10, 32 with k <= 20, 64 with k <= 40): 92 % of the queries of
+//     10,000 x 50,000 x 8,192, k = 10, are spared the last four rows (0.42 -> 0.36 ms for the batch).  `quarter` false: not
+//     this one (few queries: fetching the last quarter at once costs less than a second round of latency);
+//   - of a wider width than k has by default the default: 256 queries x 50,000 x 65,536, k = 10, width 64, 1,830 -> 1,621 us the
+//     whole look-up.
+__host__ __device__ inline int first_width(const FinishArgs &a, bool quarter)
+{
+    if (a.d < 4096 || a.d % 8 != 0) return a.r;
+    const int own = a.k <= 10 ? 16 : (a.k <= 24 ? 32 : 64);
+    if (a.r > own) return own;
+    return quarter && a.r == own && a.k <= own / 2 + own / 8 ? own - own / 4 : a.r;
+}
+
 // 256-thread blocks are held to four waves per SIMD, i.e. at most 128 registers: the compiler
 // would take 169 and leave two blocks per CU, too few to cover one block's merge and final
 // phases with the other blocks' re-scoring loads (0.55 -> 0.45 ms on 10,000 queries x 8,192).
@@ -1079,12 +1094,9 @@ __global__ __launch_bounds__(NT, NT == 256 ? 4 : 1) void finish_kernel(FinishKer
     if (tid == 0) distinct_s = 0;
     bitonic_sort_lds(ent, sort_n, tid, NT);
     const float *qrow = a.queries + (int64_t)(a.sel ? a.sel[q] : q) * a.d;
-    // Long activations, a width of 16 (or 32) that leaves room: the last quarter of the candidates
-    // is re-scored only when the certificate over the first twelve (24), which then counts the
-    // others among the excluded entries, does not confirm the result; most queries are spared a
-    // quarter of the rows (C2: 92 % of the queries, 0.42 -> 0.36 ms for the batch).
-    const bool two_steps = (r == 16 || r == 32) && a.k <= r / 2 + r / 8 && a.d >= 4096 && a.d % 8 == 0;
-    const int m_first = two_steps ? r - r / 4 : r;
+    // the others are re-scored only when the certificate over the first ones, which then counts them among the
+    // excluded entries, does not confirm the result (first_width)
+    const int m_first = first_width(a, true);
 
     for (int c = tid; c < r; c += NT) {
         // With finite inputs every one of the first r entries is a real cache row.  Non-finite
@@ -1098,14 +1110,14 @@ __global__ __launch_bounds__(NT, NT == 256 ? 4 : 1) void finish_kernel(FinishKer
     // 2. exact fp32 re-scoring: each wave takes a group of candidates and needs no block barrier
     if (a.d >= 4096 && a.d % 8 == 0) {
         // long activations: the whole block per candidate, the query row read once
-        if (r <= 16) {
+        if (m_first <= 16) {
             rescore_block_all<NT, 16, true>(a, qrow, idx_s, dist_s, red, m_first, tid);
-        } else if (r <= 32) {
+        } else if (m_first <= 32) {
             rescore_block_all<NT, 32, true>(a, qrow, idx_s, dist_s, red, m_first, tid);
         } else {
             // (two passes of 32: 64 accumulators per thread spill, and the pass is 8 % slower for it)
             rescore_block_all<NT, 32>(a, qrow, idx_s, dist_s, red, 32, tid);
-            rescore_block_all<NT, 32>(a, qrow, idx_s + 32, dist_s + 32, red, r - 32, tid);
+            rescore_block_all<NT, 32>(a, qrow, idx_s + 32, dist_s + 32, red, m_first - 32, tid);
         }
     } else if (tid < 256) {   // short activations: four waves, one group of candidates each
         if (r <= 16)
@@ -1122,13 +1134,14 @@ __global__ __launch_bounds__(NT, NT == 256 ? 4 : 1) void finish_kernel(FinishKer
     const int wider = real < kTier1 ? real : kTier1;
     // the certificate: is any entry that was not re-scored possibly nearer than the k-th?
     bool ok = false;
-    if (two_steps) {
+    if (m_first < r) {
         rank_and_emit(a, q, m_first, tid, NT, dist_s, idx_s, lab_s, dsel_s, &nearest_s, &distinct_s);
         __syncthreads();
         const uint32_t nxt = (uint32_t)(ent[m_first] >> 32);   // (real >= r > m_first with finite inputs; else the marker)
         ok = certificate(ent, dist_s, m_first, dsel_s[a.k - 1], nxt < excl_s ? nxt : excl_s, distinct_s, tid, &verdict_s);
         if (!ok) {   // uniform
-            rescore_block_all<NT, 16, true>(a, qrow, idx_s + m_first, dist_s + m_first, red, r - m_first, tid);
+            for (int c0 = m_first; c0 < r; c0 += 16)
+                rescore_block_all<NT, 16, true>(a, qrow, idx_s + c0, dist_s + c0, red, r - c0 < 16 ? r - c0 : 16, tid);
             if (tid == 0) distinct_s = 0;
             __syncthreads();
         }
@@ -1458,7 +1471,7 @@ struct KeysFinishArgs {
     int r_sel;              // blocks the threshold lets in at least (<= kMaxRescore)
     uint64_t *cand;         // [b, a.part_stride] candidates left for the wider re-scoring of an unconfirmed query
     int32_t *cand_count;    // [b]
-    int two_steps;          // re-score the last quarter only when the first three do not confirm the result
+    int m_first;            // candidates re-scored at first (first_width)
 };
 
 // dist_s[0 .. m) for rows of d values (a multiple of 8), 1,024 threads: group g of four waves takes
@@ -1689,7 +1702,7 @@ __global__ __launch_bounds__(kThrThreads) void keys_finish_kernel(KeysFinishArgs
         }
         __syncthreads();
     };
-    const int m_first = ka.two_steps ? r - r / 4 : r;
+    const int m_first = ka.m_first;
     rescore(0, m_first);
 
     // ---- 3. final order, certificate, vote ----
@@ -1815,9 +1828,7 @@ hipError_t launch_keys_finish(const FinishArgs &a, const float *keys, const uint
     const int64_t nb = n_pad / 32, per_group = (nb + kThrGroups - 1) / kThrGroups;
     int r_sel = 2 * a.r < kMaxRescore ? 2 * a.r : kMaxRescore;
     while (r_sel > a.r && per_group * r_sel > kThrList) --r_sel;   // the gathered minima fit the list
-    // few queries: fetching the last quarter at once costs less than a second round of latency
-    const int two = (a.r == 16 || a.r == 32) && a.k <= a.r / 2 + a.r / 8 && a.d >= 4096 && a.d % 8 == 0 && a.b > 64;
-    KeysFinishArgs ka{a, bmin, keys, nb, n_pad, r_sel, cand, cand_count, two};
+    KeysFinishArgs ka{a, bmin, keys, nb, n_pad, r_sel, cand, cand_count, first_width(a, a.b > 64)};
     hipLaunchKernelGGL(keys_finish_kernel, dim3((unsigned)a.b), dim3(kThrThreads), 0, s, ka);
     return hipGetLastError();
 }
