@@ -1834,35 +1834,37 @@ hipError_t launch_keys_finish(const FinishArgs &a, const float *keys, const uint
 }
 
 // ---------------------------------------------------------------------------------------
-// Finishing kernel of the block-minima route (batches on short activations), one workgroup of 128 or
+// Finishing kernel of the block-minima route, one workgroup of 128 or
 // 256 threads per query, from the smallest coarse key of every block of eight entries:
 //  1. Selection.  Every wave takes the (2 R / waves)-th smallest of its 64 lanes' minima; T = the largest of
 //     these.  At least 2 R block minima are <= T, usually a few more: those are gathered and sorted.  The
 //     first m of them hold the m best entries by the coarse key: each holds one that is no worse than any
 //     entry outside them.
-//  2. Exact re-scoring of the entries of the first k + 2 blocks, a block per wave at a time: eight rows in flight per lane, and
-//     one transposed reduction for the eight sums (ten shuffles instead of 48).  Same order of additions as in
-//     rescore_wave, for rows of any length, hence the same distances bit for bit.
+//  2. Exact re-scoring, of the first k + 2 blocks at first: of each the entry that has the smallest key, where the
+//     matrix kernel has left that (NEXT), and all eight where the bound of the others' keys lies under the smallest key that is
+//     left out (two of the nearest in one block; no lead, i.e. equal keys).  Without it, all eight of every block.  Eight rows
+//     in flight per lane, and one transposed reduction for the eight sums (ten shuffles instead of 48).  Same order of
+//     additions as in the other kernels, for rows of any length, hence the same distances bit for bit.
 //  3. The k nearest by (distance, index).
-//  4. The certificate.  Which entry of a block had the smallest key is not known; the coarse key of
+//  4. The certificate.  Its samples are the blocks' smallest keys and the distances of the entries that have them (NEXT).
+//     Without NEXT it is not known which that is: the coarse key of
 //     the block's nearest entry is formed again from the same bf16 values (the query's and the row's,
-//     relative to the cache's mean where the matrix cores' copy is), which gives a sample of the key's
-//     error per block.  What they do not show is the rounding of the matrix cores' additions, at most one ulp of a
-//     partial sum per k-step: the margin's floor covers that.  Entries outside the blocks taken have a key
-//     at or above the next minimum.  A query that fails takes R blocks, then all that were gathered (up to
-//     64), then up to 256.
-//  5. The 256 are selected anew.  The first kMeetQueries queries that get here leave that to the follow-up kernel,
-//     where sixteen workgroups share each: that is all of them on most inputs, and a single workgroup would be the
-//     last to finish by far.  With more (duplicates, neighbours closer than the key's error) the chip is busy
+//     relative to the cache's mean where the matrix cores' copy is), and what this sample does not show, the rounding of the
+//     matrix cores' additions, at most one ulp of a partial sum per k-step, the margin's floor covers.
+//     Entries outside the blocks taken have a key at or above the next minimum, and so have those that were passed over in
+//     them.  A query that fails takes R blocks, then all that were gathered (up to 64), then up to 256.
+//  5. The 256 are selected anew and re-scored whole.  The first kMeetQueries queries that get here leave that to the
+//     follow-up kernel, where sixteen workgroups share each: that is all of them on most inputs, and a single workgroup would
+//     be the last to finish by far.  With more (duplicates, neighbours closer than the key's error) the chip is busy
 //     anyway, and each goes on here.
-// Bound by the rows it reads, 8 per block: 4,096 queries x 12 blocks x 8 rows of 1 KB are 0.4 GB, beyond L2 for
-// a cache of 50,000 x 512 (51 MB). With the minima's 103 MB 112 us where the first blocks confirm every query, 150 - 155 us on
-// data where some go on to more blocks; 86 us on a cache of 5,000 rows.
+// Bound by its chain of dependent steps and the minima it reads (103 MB at 4,096 queries x 50,000): 70 - 76 us for 4,096
+// queries x 50,000 x 512, k = 10, with NEXT; 137 - 155 with eight rows per block, 0.4 GB and more beyond L2 (51 MB of cache).
 // ---------------------------------------------------------------------------------------
 constexpr int kMeetQueries = 32;
 struct BlockFinishArgs {
     FinishArgs a;
     const float *bkey;   // [b, nb] smallest coarse key of every block
+    const uint16_t *bnext;   // [b, nb] which entry has it, and a bound of the others (block_others)
     const float *norm;   // [n_pad]
     const float *mu;     // [d_pad] centring vector or null
     int64_t nb;
@@ -1900,56 +1902,108 @@ __device__ __forceinline__ void load_query8(const float *qrow, int64_t i, int64_
     }
 }
 
-// Exact distances of the eight entries of the block that starts at entry e0 (uniform), by one wave: the packed
-// (distance, index) of row lane >> 3 in every lane, the marker for padding rows.  Same order of additions as in
-// rescore_wave, for rows of any length.
-__device__ __forceinline__ uint64_t rescore_block8(const FinishArgs &a, const float *qrow, int e0, int lane)
+// The eight entries of the block that starts at entry e0 (uniform).
+struct BlockRows {
+    int e0;
+    __device__ __forceinline__ int operator()(int j) const { return e0 + (j & 3) + (j >> 2) * 16; }
+    __device__ __forceinline__ int uniform(int j) const { return (*this)(j); }
+};
+
+// Eight entries anywhere: of(j), the same in every lane, and first[j] = of(j) in scalar registers.
+template <class F>
+struct ListRows {
+    const F &of;
+    int first[8];
+    __device__ __forceinline__ int operator()(int j) const { return of(j); }
+    __device__ __forceinline__ int uniform(int j) const { return first[j]; }
+};
+
+// Exact distances of the eight entries rows(0 .. 7), by one wave: the packed (distance, index) of row lane >> 3 in every
+// lane, the marker where that is no entry.  Same order of additions as in the other kernels for rows of any length:
+// rescore_block_all<256, .>'s four waves' chains, one after the other, from 4,096 on, rescore_wave's else.
+template <class Rows>
+__device__ __forceinline__ uint64_t rescore_rows8(const FinishArgs &a, const float *qrow, const Rows &rows, int lane)
 {
     const bool whole = (a.d % 8) == 0;
     // the row's place in the cache (uniform); rows past it (padding) are read as the last row and dropped below
     auto row_of = [&](int j) {
-        const int e = e0 + (j & 3) + (j >> 2) * 16;
-        return (int64_t)(e < a.n ? e : a.n - 1) * a.d_pad;
+        const int e = rows.uniform(j);
+        return (int64_t)((uint32_t)e < (uint32_t)a.n ? e : a.n - 1) * a.d_pad;
     };
     float acc[8];
+    // transposed reduction: after the steps over lane bits 5, 4 and 3 a lane holds the partial sum of
+    // row 4 b5 + 2 b4 + b3, the rest is a butterfly
+    auto reduce = [&]() {
+        float s4[4], s2[2], s1;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+        for (int j = 0; j < 4; ++j) {
+            const bool hi = lane & 32;
+            s4[j] = (hi ? acc[4 + j] : acc[j]) + __shfl_xor(hi ? acc[j] : acc[4 + j], 32, 64);
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const bool hi = lane & 16;
+            s2[j] = (hi ? s4[2 + j] : s4[j]) + __shfl_xor(hi ? s4[j] : s4[2 + j], 16, 64);
+        }
+        {
+            const bool hi = lane & 8;
+            s1 = (hi ? s2[1] : s2[0]) + __shfl_xor(hi ? s2[0] : s2[1], 8, 64);
+        }
+#pragma unroll
+        for (int off = 4; off >= 1; off >>= 1) s1 += __shfl_xor(s1, off, 64);
+        return s1;
+    };
+    float s1;
     if (whole) {   // uniform
-        for (int64_t i = (int64_t)lane * 8; i < a.d; i += 512) {
-            float qv[8];
-            load_query8(qrow, i, a.d, qv);
-            if (a.c_f32) {
+        const int chains = a.d >= 4096 ? 4 : 1;
+        float pair = 0.f;
+        s1 = 0.f;
+        for (int c = 0; c < chains; ++c) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const f32x4 c0 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row_of(j) + i);
-                    const f32x4 c1 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row_of(j) + i + 4);
+            for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+            for (int64_t i = (int64_t)(c * 64 + lane) * 8; i < a.d; i += 512 * chains) {
+                float qv[8];
+                load_query8(qrow, i, a.d, qv);
+                if (a.c_f32) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const float df = qv[e] - (e < 4 ? c0[e & 3] : c1[e & 3]);
-                        acc[j] = __builtin_fmaf(df, df, acc[j]);
+                    for (int j = 0; j < 8; ++j) {
+                        const f32x4 c0 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row_of(j) + i);
+                        const f32x4 c1 = *reinterpret_cast<const f32x4 *>(a.c_f32 + row_of(j) + i + 4);
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const float df = qv[e] - (e < 4 ? c0[e & 3] : c1[e & 3]);
+                            acc[j] = __builtin_fmaf(df, df, acc[j]);
+                        }
                     }
-                }
-            } else {
-                uint4 cb[8];
+                } else {
+                    uint4 cb[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) cb[j] = *reinterpret_cast<const uint4 *>(a.c_rows + row_of(j) + i);
+                    for (int j = 0; j < 8; ++j) cb[j] = *reinterpret_cast<const uint4 *>(a.c_rows + row_of(j) + i);
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const uint32_t wv[4] = {cb[j].x, cb[j].y, cb[j].z, cb[j].w};
+                    for (int j = 0; j < 8; ++j) {
+                        const uint32_t wv[4] = {cb[j].x, cb[j].y, cb[j].z, cb[j].w};
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float d0 = qv[2 * e] - __uint_as_float(wv[e] << 16);
-                        acc[j] = __builtin_fmaf(d0, d0, acc[j]);
-                        const float d1 = qv[2 * e + 1] - __uint_as_float(wv[e] & 0xffff0000u);
-                        acc[j] = __builtin_fmaf(d1, d1, acc[j]);
+                        for (int e = 0; e < 4; ++e) {
+                            const float d0 = qv[2 * e] - __uint_as_float(wv[e] << 16);
+                            acc[j] = __builtin_fmaf(d0, d0, acc[j]);
+                            const float d1 = qv[2 * e + 1] - __uint_as_float(wv[e] & 0xffff0000u);
+                            acc[j] = __builtin_fmaf(d1, d1, acc[j]);
+                        }
                     }
                 }
             }
+            // one chain: its sum; four: (0 + 1) + (2 + 3)
+            const float sum = reduce();
+            if (c & 1) s1 += pair + sum;
+            else pair = sum;
         }
+        if (chains == 1) s1 = pair;
     } else if (a.c_f32) {
         // Rows of another length: rescore_wave's order, chain l of 64 takes elements l, l + 64, .., so that a
         // distance does not depend on the kernel that formed it.  A chain per lane; four steps' loads of all
         // eight rows in flight (whole look-ups, 20,011 x 517, 1,537 queries, k = 20: 242 us with eight elements per lane, 189 so).
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[j] = 0.f;
         auto steps = [&](int64_t i, auto count) {
             constexpr int U = decltype(count)::value;
             float qv[U], cv[8][U];
@@ -1970,28 +2024,7 @@ __device__ __forceinline__ uint64_t rescore_block8(const FinishArgs &a, const fl
         int64_t i = lane;
         for (; i + 3 * 64 < a.d; i += 4 * 64) steps(i, std::integral_constant<int, 4>{});
         for (; i < a.d; i += 64) steps(i, std::integral_constant<int, 1>{});
-    }
-    float s1;
-    if (whole || a.c_f32) {   // uniform
-        // transposed reduction: after the steps over lane bits 5, 4 and 3 a lane holds the partial sum of
-        // row 4 b5 + 2 b4 + b3, the rest is a butterfly
-        float s4[4], s2[2];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const bool hi = lane & 32;
-            s4[j] = (hi ? acc[4 + j] : acc[j]) + __shfl_xor(hi ? acc[j] : acc[4 + j], 32, 64);
-        }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const bool hi = lane & 16;
-            s2[j] = (hi ? s4[2 + j] : s4[j]) + __shfl_xor(hi ? s4[j] : s4[2 + j], 16, 64);
-        }
-        {
-            const bool hi = lane & 8;
-            s1 = (hi ? s2[1] : s2[0]) + __shfl_xor(hi ? s2[0] : s2[1], 8, 64);
-        }
-#pragma unroll
-        for (int off = 4; off >= 1; off >>= 1) s1 += __shfl_xor(s1, off, 64);
+        s1 = reduce();
     } else {
         // The same order on bf16 rows: half a wave per row, chains 2 p and 2 p + 1 in lane p of the half, so that a
         // lane's load is 4 bytes (50,000 x 517, 4,096 queries: 363 us with eight elements per lane, 708 with a chain per lane
@@ -2001,8 +2034,8 @@ __device__ __forceinline__ uint64_t rescore_block8(const FinishArgs &a, const fl
         const uint32_t *row[4];
 #pragma unroll
         for (int jp = 0; jp < 4; ++jp) {
-            const int e = e0 + jp + hf * 16;
-            row[jp] = reinterpret_cast<const uint32_t *>(a.c_rows + (int64_t)(e < a.n ? e : a.n - 1) * a.d_pad) + p;
+            const int e = rows(jp + hf * 4);
+            row[jp] = reinterpret_cast<const uint32_t *>(a.c_rows + (int64_t)((uint32_t)e < (uint32_t)a.n ? e : a.n - 1) * a.d_pad) + p;
         }
         float ch[4][2];   // [jp][chain of the lane]
 #pragma unroll
@@ -2056,11 +2089,11 @@ __device__ __forceinline__ uint64_t rescore_block8(const FinishArgs &a, const fl
         s1 += __shfl_xor(s1, 4, 64);
     }
     // lane >> 3 = 4 b5 + 2 b4 + b3: the row
-    const int e = e0 + ((lane >> 3) & 3) + (lane >> 5) * 16;
-    return e < a.n ? ((uint64_t)ordered_bits(s1) << 32) | (uint32_t)e : kSentinel;
+    const int e = rows(lane >> 3);
+    return (uint32_t)e < (uint32_t)a.n ? ((uint64_t)ordered_bits(s1) << 32) | (uint32_t)e : kSentinel;
 }
 
-// The smallest of the eight rows' values of rescore_block8.
+// The smallest of the eight rows' values of rescore_rows8.
 __device__ __forceinline__ uint64_t block_nearest(uint64_t x)
 {
 #pragma unroll
@@ -2139,7 +2172,8 @@ __device__ __forceinline__ float coarse_dot4(const FinishArgs &a, const float *m
     return s1;
 }
 
-template <int NT>
+// NEXT: of a block it is known which entry has the smallest key, and a bound of the others'; else all eight are re-scored.
+template <int NT, bool NEXT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void block_finish_kernel(BlockFinishArgs ba)
 {
     const FinishArgs &a = ba.a;
@@ -2160,7 +2194,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
     __shared__ double conf_s[kMaxK];
     __shared__ int32_t nearest_s;
     __shared__ uint64_t kth_s;
-    __shared__ int list_n, near_n, distinct_s, verdict_s, flagged_s;
+    __shared__ int list_n, near_n, open_n, distinct_s, verdict_s, flagged_s;
+    __shared__ float others_s[RMAX];                  // bound of the keys of a block's other entries; +inf: re-scored too
+    __shared__ uint8_t at_s[RMAX];                    // which of a block's entries has the smallest key
+    __shared__ uint16_t work_s[RMAX * 9];             // slots to re-score
     const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (a.count && q >= *a.count) return;   // uniform
@@ -2270,6 +2307,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
     }
 
     const float *qrow = a.queries + (int64_t)(a.sel ? a.sel[q] : q) * a.d;
+    // slot 8 b + e: entry e of block b of the list
+    auto entry_of = [&](int slot) { return block_first_entry((int)(uint32_t)list[slot >> 3]) + (slot & 3) + (slot >> 2 & 1) * 16; };
+    if (!NEXT) {
+        if (tid < RMAX) others_s[tid] = __builtin_nanf("");
+    } else if (tid < RMAX && tid < cnt) {
+        const uint32_t next = ba.bnext[(size_t)q * ba.nb + (uint32_t)list[tid]];
+        others_s[tid] = block_others(from_ordered_bits((uint32_t)(list[tid] >> 32)), next);
+        at_s[tid] = (uint8_t)(next & 7u);
+    }
     bool ok = false;
     // first ba.first blocks, unconfirmed queries R, then all that were gathered
     // (where every block with an entry was gathered and they are hardly more, all at once: no certificate is needed
@@ -2277,20 +2323,56 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
     int done = 0, nblk = cnt <= (t1 >= kInf ? ba.first + ba.first / 4 : ba.first) ? cnt : ba.first;
     nblk = nblk < RMAX ? nblk : RMAX;
     while (true) {
-        // ---- 2. exact re-scoring of blocks [done, nblk): packed (distance, index) of their entries ----
-        for (int b = done + w; b < nblk; b += NW) {
-            uint64_t x = rescore_block8(a, qrow, block_first_entry(__builtin_amdgcn_readfirstlane((int)(uint32_t)list[b])), lane);
-            if ((lane & 7) == 0) ent[b * 8 + (lane >> 3)] = x;
-            x = block_nearest(x);   // the certificate's sample
-            if (lane == 0) {
-                // (a block that was taken holds a real entry; the marker only with non-finite inputs)
-                sidx_s[b] = (uint32_t)x < (uint32_t)a.n ? (int32_t)(uint32_t)x : 0;
-                sdist_s[b] = from_ordered_bits((uint32_t)(x >> 32));
+        // what is outside these blocks has a key above T, or at or above the next minimum (nothing is where T is infinite
+        // and all blocks are taken)
+        uint32_t excl = t1 >= kInf ? 0xffffffffu : t1;
+        if (cnt > nblk) {
+            const uint32_t nxt = (uint32_t)(list[nblk] >> 32);
+            excl = nxt < excl ? nxt : excl;
+        }
+        const float exclf = excl >= kInf ? inf : from_ordered_bits(excl);
+        if (tid == 0) open_n = 0;
+        for (int i = done * 8 + tid; i < nblk * 8; i += NT) ent[i] = kSentinel;
+        __syncthreads();
+        // ---- 2. exact re-scoring: of blocks [done, nblk) the entry with the smallest key; of blocks whose other entries
+        // may come before what is left out, all of them ----
+        if (tid < nblk) {
+            if (NEXT && tid >= done) {
+                work_s[tid - done] = (uint16_t)(tid * 8 + at_s[tid]);
+                sidx_s[tid] = entry_of(tid * 8 + at_s[tid]);
             }
+            if (!(others_s[tid] >= exclf)) {   // (also no number)
+                const int at = (NEXT ? nblk - done : 0) + 8 * atomicAdd(&open_n, 1);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) work_s[at + e] = (uint16_t)(tid * 8 + e);
+                others_s[tid] = inf;   // done with
+            }
+        }
+        __syncthreads();
+        const int work = __builtin_amdgcn_readfirstlane((NEXT ? nblk - done : 0) + 8 * open_n);
+        for (int c0 = 8 * w; c0 < work; c0 += 8 * NW) {
+            auto slot = [&](int j) { return (int)work_s[c0 + j < work ? c0 + j : work - 1]; };
+            auto entry = [&](int j) { return entry_of(slot(j)); };
+            ListRows<decltype(entry)> rows{entry, {}};
+#pragma unroll
+            for (int j = 0; j < 8; ++j) rows.first[j] = __builtin_amdgcn_readfirstlane(entry(j));
+            const uint64_t x = rescore_rows8(a, qrow, rows, lane);
+            if ((lane & 7) == 0) ent[slot(lane >> 3)] = x;
         }
         if (tid == 0) {
             distinct_s = 0;
             near_n = 0;
+        }
+        __syncthreads();
+        if (tid >= done && tid < nblk) {   // the certificate's samples
+            uint64_t x = ent[tid * 8 + (NEXT ? at_s[tid] : 0)];
+            if (!NEXT) {   // the nearest entry; its key is formed again below
+#pragma unroll
+                for (int e = 1; e < 8; ++e) x = ent[tid * 8 + e] < x ? ent[tid * 8 + e] : x;
+                // (a block that was taken holds a real entry; the marker only with non-finite inputs)
+                sidx_s[tid] = (uint32_t)x < (uint32_t)a.n ? (int32_t)(uint32_t)x : 0;
+            }
+            sdist_s[tid] = from_ordered_bits((uint32_t)(x >> 32));
         }
         __syncthreads();
 
@@ -2347,10 +2429,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
             __syncthreads();
             break;
         }
-        for (int b0 = done + w * 4; b0 < nblk; b0 += 4 * NW) {
-            const float s1 = coarse_dot4(a, ba.mu, qrow, sidx_s, b0, nblk, lane);
-            const int bj = b0 + (lane >> 4);
-            if ((lane & 15) == 0 && bj < nblk) samp_s[bj] = (uint64_t)ordered_bits(__builtin_fmaf(-2.f, s1, ba.norm[sidx_s[bj]])) << 32;
+        if constexpr (!NEXT) {
+            for (int b0 = done + w * 4; b0 < nblk; b0 += 4 * NW) {
+                const float s1 = coarse_dot4(a, ba.mu, qrow, sidx_s, b0, nblk, lane);
+                const int bj = b0 + (lane >> 4);
+                if ((lane & 15) == 0 && bj < nblk) samp_s[bj] = (uint64_t)ordered_bits(__builtin_fmaf(-2.f, s1, ba.norm[sidx_s[bj]])) << 32;
+            }
         }
         if (tid < nblk) {
             int twin = 0;
@@ -2358,14 +2442,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
             if (!twin) atomicAdd(&distinct_s, 1);
         }
         __syncthreads();
-        // what was not gathered has a key above T (nothing when T is infinite: see above)
-        uint32_t excl = t1 >= kInf ? 0xffffffffu : t1;
-        if (cnt > nblk) {
-            const uint32_t nxt = (uint32_t)(list[nblk] >> 32);
-            excl = nxt < excl ? nxt : excl;
-        }
         ok = __builtin_amdgcn_readfirstlane(
-                 (int)certificate(samp_s, sdist_s, nblk, dsel_s[a.k - 1], excl, distinct_s, tid, &verdict_s, 4.0 + 2.0 * ba.nk)) != 0;
+                 (int)certificate(NEXT ? list : samp_s, sdist_s, nblk, dsel_s[a.k - 1], excl, distinct_s, tid, &verdict_s,
+                                  NEXT ? 4.0 : 4.0 + 2.0 * ba.nk)) != 0;
         const int most = cnt < RMAX ? cnt : RMAX;
         if (ok || nblk >= most) break;   // uniform
         done = nblk;
@@ -2379,7 +2458,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
         if (flagged < kMeetQueries) {
             if (tid == 0) a.flag_list[flagged] = q;   // (and counted in the statistics there)
         } else {
-            // ---- 5. the 256 blocks with the smallest minima; the first nblk of them are done ----
+            // ---- 5. the 256 blocks with the smallest minima, all their entries ----
             // T = the kTier1-th smallest of kBlkList group minima: at least that many blocks (or all) are <= T
             auto minimum = [&](int64_t blk) { return ((uint64_t)ordered_bits(bq[blk]) << 32) | (uint32_t)blk; };
             for (int g = tid; g < kBlkList; g += NT) {
@@ -2412,7 +2491,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
                 bitonic_sort_lds(list, n2, tid, NT);
                 const int all = got < kTier1 ? got : kTier1;
                 constexpr int CH = 16, STEP = 64;   // blocks between two merges, and between two certificates
-                for (int from = nblk;;) {
+                if (tid < kMaxK) best_s[tid] = kSentinel;
+                for (int from = 0;;) {
                     const int end = from + STEP < all ? from + STEP : all;
                     for (int c0 = from; c0 < end; c0 += CH) {
                         if (tid == 0) near_n = 0;
@@ -2420,7 +2500,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
                         const uint64_t tau = best_s[a.k - 1];
                         for (int b = c0 + w; b < c0 + CH && b < end; b += NW) {
                             const uint64_t x =
-                                rescore_block8(a, qrow, block_first_entry(__builtin_amdgcn_readfirstlane((int)(uint32_t)list[b])), lane);
+                                rescore_rows8(a, qrow, BlockRows{block_first_entry(__builtin_amdgcn_readfirstlane((int)(uint32_t)list[b]))}, lane);
                             if ((lane & 7) == 0 && x < tau) ent[atomicAdd(&near_n, 1)] = x;   // <= 8 CH
                             const uint64_t near = block_nearest(x);
                             if (lane == 0) {
@@ -2490,22 +2570,27 @@ static int64_t real_blocks_of(int64_t n, int64_t n_pad)   // blocks that hold an
     return real;
 }
 
-hipError_t launch_block_finish(const FinishArgs &a, const float *bkey, const float *norm, const float *mu, int64_t n_pad, hipStream_t s)
+hipError_t launch_block_finish(const FinishArgs &a, const BlockMinima &m, hipStream_t s)
 {
-    if (a.r < 1 || a.r > kMaxRescore || a.k > kMaxK || a.k > a.r || a.b < 1 || !a.flag_count || !a.flag_list || !a.flag_list2 || n_pad % kTileN != 0)
+    const int64_t n_pad = m.n_pad;
+    if (!m.bkey || a.r < 1 || a.r > kMaxRescore || a.k > kMaxK || a.k > a.r || a.b < 1 || !a.flag_count || !a.flag_list || !a.flag_list2 || n_pad % kTileN != 0)
         return hipErrorInvalidValue;
-    // two blocks more than neighbours confirm most queries (4,096 x 50,000 x 512, k = 10: 112 us with 12 blocks at
+    // two blocks more than neighbours confirm most queries (4,096 x 50,000 x 512, k = 10, whole blocks: 112 us with 12 at
     // first, 118 with 11, 119 with 14, 129 with 16); the certificate wants eight samples at least
     int first = a.k + 2 > kCertMinSamples ? a.k + 2 : kCertMinSamples;
     first = first < a.r ? first : a.r;
     const int gather = 2 * a.r < kMaxRescore ? 2 * a.r : kMaxRescore;
-    BlockFinishArgs ba{a, bkey, norm, mu, n_pad / 8, real_blocks_of(a.n, n_pad), (int)(a.d_pad / kKB), first, gather};
+    BlockFinishArgs ba{a, m.bkey, m.bnext, m.norm, m.mu, n_pad / 8, real_blocks_of(a.n, n_pad), (int)(a.d_pad / kKB), first, gather};
     // Two waves per query where the batch fills the chip with them, four where it does not (50,000 x 512: 1,500
     // queries 54 against 59 us, 600 queries 42 against 34 us; one wave per query is slower than two at both).
-    if (a.b >= 1024)
-        hipLaunchKernelGGL(block_finish_kernel<128>, dim3((unsigned)a.b), dim3(128), 0, s, ba);
+    if (a.b >= 1024 && m.bnext)
+        hipLaunchKernelGGL((block_finish_kernel<128, true>), dim3((unsigned)a.b), dim3(128), 0, s, ba);
+    else if (a.b >= 1024)
+        hipLaunchKernelGGL((block_finish_kernel<128, false>), dim3((unsigned)a.b), dim3(128), 0, s, ba);
+    else if (m.bnext)
+        hipLaunchKernelGGL((block_finish_kernel<256, true>), dim3((unsigned)a.b), dim3(256), 0, s, ba);
     else
-        hipLaunchKernelGGL(block_finish_kernel<256>, dim3((unsigned)a.b), dim3(256), 0, s, ba);
+        hipLaunchKernelGGL((block_finish_kernel<256, false>), dim3((unsigned)a.b), dim3(256), 0, s, ba);
     return hipGetLastError();
 }
 
@@ -2664,7 +2749,7 @@ __global__ __launch_bounds__(256) void follow_up_kernel(ScanArgs sa)
                     const uint64_t tau = best_s[k - 1];
                     for (int b = b0 + w; b < b1; b += 4) {
                         const uint64_t x =
-                            rescore_block8(a, qrow, block_first_entry(__builtin_amdgcn_readfirstlane((int)(uint32_t)blocks[b])), lane);
+                            rescore_rows8(a, qrow, BlockRows{block_first_entry(__builtin_amdgcn_readfirstlane((int)(uint32_t)blocks[b]))}, lane);
                         if ((lane & 7) == 0 && x < tau) ent[atomicAdd(&surv_s, 1)] = x;   // <= 128
                         const uint64_t near = block_nearest(x);
                         if (lane == 0) {

@@ -1,4 +1,4 @@
-// Distance pass for batches on short activations: block minima instead of candidate lists.
+// Distance pass for batches: block minima instead of candidate lists.
 //
 // The fused kernel folds every 256 x 256 tile of keys into per-query lists in LDS.  That takes 12 us a
 // tile once the lists have settled and 60 us for a workgroup's first one, whatever the activation's
@@ -7,8 +7,10 @@
 // of the block (4 bytes per 8 entries and query), and nothing in the kernel depends on the data: four
 // max3 per block in registers, one 8-byte store per two blocks, no LDS, no barrier.  block_finish_kernel
 // then finds the R blocks with the smallest minima, which hold the R best entries by the coarse key
-// and more, and re-scores their 8 R entries exactly: cheap as long as rows are short, which is what
-// limits this route (block_route in the API file).
+// and more, and re-scores their 8 R entries exactly.  That is cheap for short rows and few queries.  Elsewhere
+// (block_next_pays in the API file) a block leaves 16 bits more: which entry has the smallest key, and by how
+// much it leads (block_next), and one row per block is re-scored.  That takes some 25 instructions per block in place of
+// five, 2.4 us a tile (4,096 x 50,000 x 512: 189 -> 209 - 220 us here, 141 -> 73 in the finishing kernel).
 //
 //   - The accumulators start at -|c|^2 / 2 (the first matrix instruction of a tile takes the norms as its
 //     third operand), so a finished accumulator is q.c - |c|^2 / 2 = -key / 2: no arithmetic on the way out
@@ -23,8 +25,8 @@
 //     query tiles, cache tile, query tile of the group): a workgroup uses a cache tile for all query tiles
 //     of a group in a row, and a group's queries (1 or 2 MB) stay in the XCD's L2.
 //
-// 4,096 x 50,000 x 512, k = 10: this kernel 180 us = 1.17 PFLOP/s and 103 MB of minima (399 us with lists), the
-// whole look-up 510 -> 324 us; 300 queries 170 -> 64 us; 1,500 queries, k = 40 726 -> 222 us.
+// 4,096 x 50,000 x 512, k = 10: whole look-ups 510 us with lists, 330 with minima alone, 261 with the further bits;
+// 300 queries 170, 64, 59 us; 20,011 x 517 fp32, 1,537 queries, k = 20 323, 185, 98.
 //
 // Paper: Sec. 3 (k nearest neighbours), Sec. 4 "Computational Complexity".
 #include "freeze_internal.h"
@@ -46,7 +48,6 @@ constexpr int kStageBytes = 2 * kStageHalf;     // queries, then entries
 constexpr int NS = 4;                           // stages
 constexpr int LPS = 4, LB = 2;                  // loads per wave and stage; issued in the half-step that frees the stage
 constexpr int AM = 8, AH = 4, BNB = 4;          // 16-query blocks per wave (and half), 16-entry blocks per wave
-constexpr int STORES = AM;                      // per wave and tile
 constexpr int kNorms = NS * kStageBytes;        // byte offset of the norm buffers: per tile parity and wave, 64 floats
 constexpr int kLds = kNorms + 2 * 8 * 256;
 static_assert(kLds <= 163840, "LDS budget");
@@ -56,20 +57,54 @@ struct BlockArgs {
     const uint16_t *c_bf;
     const float *norm;
     float *bkey;            // [b_pad, n_pad / 8] smallest key of every block
+    uint32_t *bnext;        // [b_pad, n_pad / 16] of every block: where it lies, and a bound of the others (block_next in select_common.h)
     const int32_t *count;   // device: live queries, or null (= b)
     int b, n_tiles, nk, group;   // nk k-steps per tile (even); group: query tiles that share a cache tile in a row
 };
 
-template <class T>
-__device__ __forceinline__ T max3(T a, T b, T c)
+// (one instruction each, without the compiler's quieting of signalling NaNs, which no arithmetic leaves)
+#define FZ_OP3(name, op)                                                             \
+    __device__ __forceinline__ float name(float a, float b, float c)                 \
+    {                                                                                \
+        float r;                                                                     \
+        asm(op " %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));                \
+        return r;                                                                    \
+    }
+FZ_OP3(max3, "v_max3_f32")
+FZ_OP3(med3, "v_med3_f32")
+#undef FZ_OP3
+#define FZ_OP2(name, op)                                                             \
+    __device__ __forceinline__ float name(float a, float b)                          \
+    {                                                                                \
+        float r;                                                                     \
+        asm(op " %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));                            \
+        return r;                                                                    \
+    }
+FZ_OP2(max2, "v_max_f32")
+FZ_OP2(min2, "v_min_f32")
+#undef FZ_OP2
+
+// The largest of the eight values of a block and, in 16 bits, its place and its lead over the second largest.
+template <bool NEXT>
+__device__ __forceinline__ float block_top(const f32x4 &a, const f32x4 &b, uint32_t &next)
 {
-    T r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
+    const float m0 = max3(a[0], a[1], a[2]), m1 = max3(a[3], b[0], b[1]), m2 = max2(b[2], b[3]);
+    if constexpr (!NEXT) return max3(m0, m1, m2);
+    const float s0 = med3(a[0], a[1], a[2]), s1 = med3(a[3], b[0], b[1]), s2 = min2(b[2], b[3]);
+    const float top = max3(m0, m1, m2);
+    const float second = max2(med3(m0, m1, m2), max3(s0, s1, s2));
+    uint32_t at = 0;
+#pragma unroll
+    for (int e = 1; e < 8; ++e) at = (e < 4 ? a[e & 3] : b[e & 3]) == top ? e : at;
+    next = block_next(top - second, at);
+    return top;
 }
 
+// NEXT: 16 more bits per block (block_next)
+template <bool NEXT>
 __global__ __launch_bounds__(512) void dist_block_kernel(BlockArgs p)
 {
+    constexpr int STORES = NEXT ? 2 * AM : AM;      // per wave and tile
     __shared__ __attribute__((aligned(16))) unsigned char smem[kLds];
     const bf16x8 *smem16 = reinterpret_cast<const bf16x8 *>(smem);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -174,7 +209,9 @@ __global__ __launch_bounds__(512) void dist_block_kernel(BlockArgs p)
     // The k-step of the batched kernel's 8-wave loop: half the wave's query blocks against all its entry
     // blocks, then, past the step's only barrier, the other half.  The second half's A fragments are read
     // during the first half; the next stage's first fragments and the refill of the stage just freed leave
-    // between the second half's matrix instructions, the rest of the refill between the next step's first ones.
+    // between the second half's matrix instructions, the rest of the refill between the next step's first ones.  Matrix
+    // instructions in a row share their first operand: a register-only loop of 4 x 8 blocks sustains 2,140 TFLOP/s so and 2,020
+    // where they share the second (one wave per SIMD, power limit).
     auto k_step = [&](auto set_tag, auto first_tag) {
         constexpr int set = decltype(set_tag)::value;
         constexpr bool first = decltype(first_tag)::value;   // the tile's first k-step: the accumulators start at the norms
@@ -184,13 +221,15 @@ __global__ __launch_bounds__(512) void dist_block_kernel(BlockArgs p)
         for (int i = 0; i < AH; ++i) read_a(1, st, i);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < AH; ++i) {
+        for (int j = 0; j < BNB; ++j) {
 #pragma unroll
-            for (int j = 0; j < BNB; ++j)
+            for (int t = 0; t < AH; ++t) {
+                const int i = j & 1 ? AH - 1 - t : t;
                 acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[set][j], af[0][i], first ? nrm[j] : acc[i][j], 0, 0, 0);
+            }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int l = LB + i * (LPS - LB) / AH; l < LB + (i + 1) * (LPS - LB) / AH; ++l) issue_one(pst, l);
+            for (int l = LB + j * (LPS - LB) / BNB; l < LB + (j + 1) * (LPS - LB) / BNB; ++l) issue_one(pst, l);
             __builtin_amdgcn_sched_barrier(0);
         }
         advance();
@@ -203,12 +242,14 @@ __global__ __launch_bounds__(512) void dist_block_kernel(BlockArgs p)
         __syncthreads();                                // ... everyone's; and stage st is free
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < AH; ++i) {
+        for (int j = 0; j < BNB; ++j) {
 #pragma unroll
-            for (int j = 0; j < BNB; ++j)
+            for (int t = 0; t < AH; ++t) {
+                const int i = j & 1 ? AH - 1 - t : t;
                 acc[AH + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[set][j], af[1][i], first ? nrm[j] : acc[AH + i][j], 0, 0, 0);
+            }
 #pragma unroll
-            for (int rr = i * 8 / 3; rr < (i + 1) * 8 / 3 && rr < AH + BNB && i < 3; ++rr) {
+            for (int rr = j * 8 / 3; rr < (j + 1) * 8 / 3 && rr < AH + BNB && j < 3; ++rr) {
                 if (rr < AH)
                     read_a(0, nst, rr);
                 else
@@ -216,7 +257,7 @@ __global__ __launch_bounds__(512) void dist_block_kernel(BlockArgs p)
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int l = i * LB / AH; l < (i + 1) * LB / AH; ++l) issue_one(st, l);
+            for (int l = j * LB / BNB; l < (j + 1) * LB / BNB; ++l) issue_one(st, l);
             __builtin_amdgcn_sched_barrier(0);
         }
         st = nst;
@@ -236,10 +277,7 @@ __global__ __launch_bounds__(512) void dist_block_kernel(BlockArgs p)
             k_step(S1{}, std::false_type{});
         }
         // ---- the tile is finished: the block minima ----
-        if (t + 1 < t1) {
-            if (p.nk <= 6) wait_global_loads_le<0>();   // a short tile: the norms may still be on their way
-            read_norms(par ^ 1);
-        }
+        if (p.nk <= 6) wait_global_loads_le<0>();   // a short tile: the next one's norms may still be on their way
         int elane = lane;
         asm volatile("" : "+v"(elane));   // opaque: the addresses are formed here, not kept across the loop
         // (the compiler does not see that max3 reads matrix results: the no-ops are the distance the hardware
@@ -261,20 +299,21 @@ __global__ __launch_bounds__(512) void dist_block_kernel(BlockArgs p)
                        "+v"(acc[3][0]), "+v"(acc[3][1]), "+v"(acc[3][2]), "+v"(acc[3][3]));
         second_half();
         const int64_t nb = (int64_t)p.n_tiles * (kTileN / 8);
-        float *dst = p.bkey + ((int64_t)cur.mt * 256 + wm * 128 + (elane & 15)) * nb + cur.nt * (kTileN / 8) + wn * 8 + (elane >> 4) * 2;
+        const int64_t at = ((int64_t)cur.mt * 256 + wm * 128 + (elane & 15)) * nb + cur.nt * (kTileN / 8) + wn * 8 + (elane >> 4) * 2;
+        float *dst = p.bkey + at;
+        uint32_t *dst_next = p.bnext + (at >> 1);
 #pragma unroll
         for (int i = 0; i < AM; ++i) {
             f32x2 v;
+            uint32_t nx[2];
 #pragma unroll
-            for (int j2 = 0; j2 < 2; ++j2) {
-                const f32x4 a = acc[i][2 * j2], b = acc[i][2 * j2 + 1];
-                const float m = max3(max3(a[0], a[1], a[2]), max3(a[3], b[0], b[1]), __builtin_fmaxf(b[2], b[3]));
-                v[j2] = -2.f * m;
-            }
+            for (int j2 = 0; j2 < 2; ++j2) v[j2] = -2.f * block_top<NEXT>(acc[i][2 * j2], acc[i][2 * j2 + 1], nx[j2]);
             // (rows past the batch are written too: the buffer has whole tiles of rows)
             asm volatile("global_store_dwordx2 %0, %1, off" ::"v"(dst + i * 16 * nb), "v"(v) : "memory");
+            if constexpr (NEXT) asm volatile("global_store_dword %0, %1, off" ::"v"(dst_next + i * 8 * nb), "v"(nx[0] | nx[1] << 16) : "memory");
             __builtin_amdgcn_sched_barrier(0);
         }
+        if (t + 1 < t1) read_norms(par ^ 1);
         stores_at = 1;
         cur = nxt;
         par ^= 1;
@@ -284,10 +323,11 @@ __global__ __launch_bounds__(512) void dist_block_kernel(BlockArgs p)
 
 }  // namespace
 
-DistPlan plan_block(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad)
+DistPlan plan_block(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad, bool next)
 {
     DistPlan pl{};
     pl.variant = 5;
+    pl.next = next;
     pl.bm = 256;
     pl.r = r;
     pl.m_tiles = (int)((b + 255) / 256);
@@ -313,10 +353,11 @@ DistPlan plan_block(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad)
 
 hipError_t launch_dist_block(const DistPlan &pl, const DistArgs &a, hipStream_t s)
 {
-    if (pl.variant != 5 || !a.keys || a.d_pad < 64 || a.d_pad % kPadD != 0 || a.b < 1 || a.b > pl.b_pad || pl.group < 1 || pl.grid_units < 1)
+    if (pl.variant != 5 || !a.keys || (pl.next && !a.bnext) || a.d_pad < 64 || a.d_pad % kPadD != 0 || a.b < 1 || a.b > pl.b_pad || pl.group < 1 || pl.grid_units < 1)
         return hipErrorInvalidValue;
-    BlockArgs k{a.q_bf, a.c_bf, a.norm, a.keys, a.count, a.b, pl.n_tiles, a.d_pad / kKB, pl.group};
-    hipLaunchKernelGGL(dist_block_kernel, dim3((unsigned)pl.grid_units), dim3(512), 0, s, k);
+    BlockArgs k{a.q_bf, a.c_bf, a.norm, a.keys, a.bnext, a.count, a.b, pl.n_tiles, a.d_pad / kKB, pl.group};
+    if (pl.next) hipLaunchKernelGGL(dist_block_kernel<true>, dim3((unsigned)pl.grid_units), dim3(512), 0, s, k);
+    else hipLaunchKernelGGL(dist_block_kernel<false>, dim3((unsigned)pl.grid_units), dim3(512), 0, s, k);
     return hipGetLastError();
 }
 

@@ -122,30 +122,46 @@ int lists_per_query(const DistPlan &pl, bool device_count)
     return pl.bal_f > 0 ? pl.bal_lists : pl.n_splits;
 }
 
-// Whether a batch goes through block minima instead of per-query lists: where what the lists cost
-// is more than what re-scoring whole blocks of eight costs.  Both are times in microseconds, fitted to
-// measurements of both routes over 2,000 .. 300,000 entries, 256 .. 3,072 values, 300 .. 10,000 queries.  Used beyond
-// them too: of 344 random shapes it sends to blocks (4 .. 200,000 entries, 1 .. 3,072 values, 129 .. 20,000 queries) lists are
-// more than 3 % faster at three, 122 x 2,194 with 1,700 queries by most (158 us with blocks, 114):
-//   lists   filling every workgroup's empty lists, 110 at 16 slots, 180 at 32, 500 at 64, and 10 per
-//           256 x 256 tile of a workgroup;
-//   blocks  8 (k + 2) rows per query, 64 at least, at 5.3 TB/s (8 when the cache is small enough for the L2s), 20, and a
-//           twelfth of the matrix work (the 8-wave loop against the 4-wave one of the lists at R <= 16).
-// 4,096 x 50,000, k = 10: 512 values 474 us with lists, 296 with blocks; 1,024: 583, 502; 1,536: 724, 722;
-// 2,048: 834, 914.  300 queries x 50,000 x 3,072: 271, 208.
-bool block_route(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, int r)
+// Whether a block leaves where its smallest key lies and a bound of the other seven, so that one row of it is
+// re-scored in place of eight: 2.4 us per tile of a workgroup, and a quarter more to write, against the rows (4,096 x 50,000 x
+// 512, k = 10: 31 us more in the matrix kernel, 75 less in the finishing one; 600 x 1,000,000 x 512: 100 more, 10 less).
+bool block_next_pays(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k)
 {
-    // 1 GiB of minima at most (2 with the padding of the last query tile); longer rows than measured lose more to the re-scoring (259 x 13,556 x 8,192, k = 20:
-    // 345 us with lists, 415 with blocks)
-    if (b * L.n_pad > (int64_t)1 << 31 || L.d_pad > 3072) return false;
-    // (600 x 250,000 x 3,000: 1,011 us with lists, 1,091 with blocks)
-    if (L.d_pad > 2048 && L.n_pad * L.d_pad * 2 > (int64_t)512 << 20) return false;
     const double tiles = (double)((b + 255) / 256) * (double)(L.n_pad / kTileN);
-    const double lists = (r <= 16 ? 110.0 : (r <= 32 ? 180.0 : 500.0)) + 10.0 * (1.0 + (double)(int64_t)(tiles / ctx->num_cus));
     const double row = (double)L.d_pad * (L.entries_dtype == FREEZE_F32 ? 4.0 : 2.0);
     const double per_us = (double)L.n * row <= 16e6 ? 8e6 : 5.3e6;
+    const double rows = (double)b * 7.0 * (k + 2 > 8 ? k + 2 : 8) * row / per_us;
+    return 2.4 * (1.0 + (double)(int64_t)(tiles / ctx->num_cus)) < rows;
+}
+
+// Whether a batch goes through block minima instead of per-query lists: where what the lists cost
+// is more than what the minima and the slower matrix loop cost.  Both are times in microseconds:
+//   lists   filling every workgroup's empty lists, 110 at 16 slots, 180 at 32, 500 at 64, and 10 per
+//           256 x 256 tile of a workgroup;
+//   blocks  20, a twelfth of the matrix work (the 8-wave loop against the 4-wave one of the lists at R <= 16; half
+//           that at more slots, whose lists have an 8-wave loop too), the minima out and in again, and what the finishing kernel
+//           loses on long rows (it takes eight rows per wave and reads the query's for each of these): 30 us per GB at 8,192
+//           values; or, where it is not known which row of a block may do (`next` false), eight rows per block.
+// 1,537 queries x 20,011 x 4,104, k = 20: 620 us with lists, 451 with blocks; 2,000 x 30,000 x 8,192, k = 10 945, 884, k = 30
+// 1,609, 1,026; 8,000 x 20,000 x 4,096 1,290, 1,149; 2,500 x 3,000 x 12,000, k = 25 855, 704; 4,456 x 2,666 x 36,968 2,440,
+// 2,920 (beyond the limit on rows); 10,000 x 50,000 x 8,192 6,370, 7,080.
+bool block_route(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, int r, bool next)
+{
+    // 1.5 GiB of minima at most (3 with the padding of the last query tile); longer rows than measured
+    if (b * L.n_pad > (int64_t)1 << 31 || L.d_pad > 16384) return false;
+    // (600 x 250,000 x 3,000: 1,011 us with lists, 1,091 with blocks)
+    if (L.d_pad > 2048 && L.n_pad * L.d_pad * 2 > (int64_t)512 << 20 && b <= 1280) return false;
+    const double tiles = (double)((b + 255) / 256) * (double)(L.n_pad / kTileN);
+    const double lists = (r <= 16 ? 110.0 : (r <= 32 ? 180.0 : 500.0)) + 10.0 * (1.0 + (double)(int64_t)(tiles / ctx->num_cus));
     const double matrix = tiles * 256.0 * 256.0 * 2.0 * (double)L.d_pad / 1.4e9;
-    return 20.0 + matrix / 12.0 + (double)b * 8.0 * (k + 2 > 8 ? k + 2 : 8) * row / per_us < lists;
+    const double minima = (double)b * (double)L.n_pad / 8.0 * 10.0 / 6e6;
+    const double row = (double)L.d_pad * (L.entries_dtype == FREEZE_F32 ? 4.0 : 2.0);
+    // (all eight rows of a block where one is not known to do: longer ones lose too much)
+    if (!next && L.d_pad > 3072) return false;
+    const double per_us = (double)L.n * row <= 16e6 ? 8e6 : 5.3e6;
+    const double rows = next ? (L.d_pad > 4096 ? (double)b * (k + 2) * row * (double)L.d_pad / 3e14 : 0.0)
+                             : (double)b * 8.0 * (k + 2 > 8 ? k + 2 : 8) * row / per_us;
+    return 20.0 + matrix / (r <= 16 ? 12.0 : 24.0) + minima + rows < lists;
 }
 
 // The streaming kernel serves single-layer batches of at most this many queries on any cache (50,000 x 2,048: 128 queries 135 -> 113 us,
@@ -157,6 +173,7 @@ constexpr int kStreamRows = 128;
 // Which decomposition of the work a look-up is planned with; the result does not depend on it.
 enum class Decomp {
     best,    // the fastest
+    lean,    // the fastest, but block minima without the further bits: where the workspace does not hold those
     small,   // whole tiles only, no accumulator slots, no block minima: where the workspace does not hold the fastest
     plain    // the 256-query kernel alone, as `small` (only its size is asked for: see asked_bytes)
 };
@@ -179,6 +196,8 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
     out->skinny = !cascade && skinny_supported(b, L.n_pad, L.d_pad, r, ctx->num_cus);
     out->keys = false;
     out->blocks = false;
+    const bool fast = how == Decomp::best || how == Decomp::lean;
+    const bool next = how == Decomp::best && block_next_pays(ctx, L, b, k);   // block minima with the further bits
     if (out->skinny) {
         DistPlan pl{};
         pl.variant = -1;
@@ -197,11 +216,11 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
         // moderate size: every workgroup of the fused kernel gets a few tiles only and spends most of
         // its time filling its empty candidate lists key by key, so the keys go out here too
         // (measured cross-over: about 2^26 keys; 256 x 2,000: 129 -> 69 us, 200 x 50,000 x 512: 209 -> 80 us).
-        out->keys = b <= (cascade ? kStreamRows : 256) && !(cascade && how != Decomp::best) && (b * 20 <= L.d_pad || b * L.n_pad <= ((int64_t)1 << 26)) &&
+        out->keys = b <= (cascade ? kStreamRows : 256) && !(cascade && !fast) && (b * 20 <= L.d_pad || b * L.n_pad <= ((int64_t)1 << 26)) &&
                     keys_finish_supported(L.n_pad, r);
         // (batches of 129 to 256 queries on large caches: the keys' traffic costs more than the blocks' rows;
         // 160 x 300,000 x 512: 183 against 136 us)
-        if ((!out->keys || (b > kStreamRows && b * L.n_pad > (int64_t)1 << 25)) && how == Decomp::best && block_route(ctx, L, b, k, r)) {
+        if ((!out->keys || (b > kStreamRows && b * L.n_pad > (int64_t)1 << 25)) && fast && block_route(ctx, L, b, k, r, next)) {
             out->keys = false;
             out->blocks = true;
         }
@@ -209,27 +228,34 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
         // see few tiles, and whole tiles fill the chip badly, where the keys-out kernel cuts them along the
         // depth (300 / 600 / 1,000 x 10,000 x 16,384: 471 -> 233, 516 -> 358, 587 -> 406 us; 1,000 x 50,000 x 8,192: 839 ->
         // 770).  At 1,537 queries its finishing kernel, a workgroup of 1,024 threads per query, has caught up
-        // (20,011 x 4,104: 464 -> 476).  Block minima give way where their whole tiles leave half the chip idle
-        // (300 x 5,000 x 2,048: 94 -> 65 us; 1,000 x 2,000 x 2,048 goes the other way: 110, 136).
+        // (20,011 x 4,104: 464 -> 476).  Block minima give way where their whole tiles leave half the chip idle: up to 640
+        // queries from 1,024 values on (300 x 5,000 x 2,048: 94 -> 65 us; 1,000 x 2,000 x 2,048 goes the other way: 110, 136), more
+        // from 4,096 on (700 x 2,600: 4,096 values 124, 126; 8,192 209 -> 148; 1,000 x 2,600 x 8,192 217 -> 166); and on very long rows
+        // (1,000 x 10,000 x 16,384 454 -> 419; 12,000 values 362, 393), unless the streaming kernel would have to write them
+        // (900 x 1,000 x 8,192: 213, 259).
         const int64_t tiles = ((b + 255) / 256) * (L.n_pad / kTileN);
-        if (!cascade && how == Decomp::best && b > 256 && b <= 1024 && b * L.n_pad <= ((int64_t)1 << 26) && keys_finish_supported(L.n_pad, r) &&
-            (!out->blocks || (2 * tiles <= ctx->num_cus && L.d_pad >= 1024 && b <= 640))) {
+        const int64_t k_steps = (L.n_pad / kTileN) * (L.d_pad / kKB);   // per query tile
+        const bool streamed = b <= kStreamRows || 2 * k_steps < 16 * (int64_t)ctx->num_cus;
+        const bool idle = 2 * tiles <= ctx->num_cus;
+        if (!cascade && fast && b > 256 && b <= 1024 && b * L.n_pad <= ((int64_t)1 << 26) && keys_finish_supported(L.n_pad, r) &&
+            (!out->blocks || (idle && L.d_pad >= 1024 && b <= 640) || (!streamed && ((idle && L.d_pad > 4096) || L.d_pad > 12288)))) {
             out->keys = true;
             out->blocks = false;
         }
-        const int64_t k_steps = (L.n_pad / kTileN) * (L.d_pad / kKB);   // per query tile
-        if (out->keys && how != Decomp::plain && (b <= kStreamRows || 2 * k_steps < 16 * (int64_t)ctx->num_cus))
+        if (out->keys && how != Decomp::plain && streamed)
             out->plan = plan_stream(b, L.n, r, ctx->num_cus, L.d_pad, how == Decomp::small ? StreamCut::none : StreamCut::where_faster);
         else if (out->blocks)
-            out->plan = plan_block(b, L.n, r, ctx->num_cus, L.d_pad);
+            out->plan = plan_block(b, L.n, r, ctx->num_cus, L.d_pad, next);
         else
-            out->plan = plan_dist(b, L.n, r, ctx->num_cus, out->keys, how == Decomp::best ? L.d_pad : 0);   // depth 0: no cut tiles, no slots
+            out->plan = plan_dist(b, L.n, r, ctx->num_cus, out->keys, fast ? L.d_pad : 0);   // depth 0: no cut tiles, no slots
         out->ws_bytes = align_up((size_t)out->plan.b_pad * L.d_pad * 2);
         if (out->keys)
             out->ws_bytes += keys_finish_workspace_bytes(out->plan.b_pad, L.n_pad, r, kAlign) +
                              align_up(dist_partial_bytes(out->plan));
         else if (out->blocks)
-            out->ws_bytes += align_up((size_t)out->plan.b_pad * (L.n_pad / 8) * 4) + align_up(follow_up_meet_entries() * 8);
+            out->ws_bytes += align_up((size_t)out->plan.b_pad * (L.n_pad / 8) * 4) +
+                             (out->plan.next ? align_up((size_t)out->plan.b_pad * (L.n_pad / 16) * 4) : 0) +
+                             align_up(follow_up_meet_entries() * 8);
         else
             out->ws_bytes += align_up((size_t)out->plan.b_pad * lists_per_query(out->plan, cascade) * r * 8);
         out->ws_bytes += scan_bytes;
@@ -242,6 +268,7 @@ bool fit_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, int
                LookupShape *out)
 {
     return (lookup_shape(ctx, L, b, k, rescore_r, cascade, out) && out->ws_bytes <= room) ||
+           (lookup_shape(ctx, L, b, k, rescore_r, cascade, out, Decomp::lean) && out->ws_bytes <= room) ||
            (lookup_shape(ctx, L, b, k, rescore_r, cascade, out, Decomp::small) && out->ws_bytes <= room);
 }
 
@@ -349,7 +376,7 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
     FinishArgs fa{};
     marks.mark(1);
     const float *keys = nullptr;
-    BlockMinima minima{nullptr, L.norm, L.mu, L.n_pad, nullptr};
+    BlockMinima minima{nullptr, nullptr, L.norm, L.mu, L.n_pad, nullptr};
     const uint64_t *keys_bmin = nullptr;
     uint64_t *keys_cand = nullptr;
     int32_t *keys_cand_count = nullptr;
@@ -404,8 +431,10 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
             fa.n_splits = 1;
         } else if (sh.blocks) {
             da.keys = ws.take<float>((size_t)sh.plan.b_pad * (L.n_pad / 8));
+            da.bnext = sh.plan.next ? ws.take<uint32_t>((size_t)sh.plan.b_pad * (L.n_pad / 16)) : nullptr;
             if (launch_dist_topr(sh.plan, da, s) != hipSuccess) return FREEZE_EHIP;
             minima.bkey = da.keys;
+            minima.bnext = reinterpret_cast<const uint16_t *>(da.bnext);
             minima.meet = ws.take<uint64_t>(follow_up_meet_entries());
         } else {
             // the workspace was sized by sh.cascade; the balanced decomposition only goes with it off
@@ -459,7 +488,7 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
                                  (int)(L.n_pad / kTileN), skinny_cand, skinny_samp, tickets + kSkinnyRows, s) != hipSuccess)
             return FREEZE_EHIP;
     } else if (minima.bkey) {
-        if (launch_block_finish(fa, minima.bkey, L.norm, L.mu, L.n_pad, s) != hipSuccess) return FREEZE_EHIP;
+        if (launch_block_finish(fa, minima, s) != hipSuccess) return FREEZE_EHIP;
     } else if ((keys ? launch_keys_finish(fa, keys, keys_bmin, L.n_pad, keys_cand, keys_cand_count, s) : launch_finish(fa, s)) !=
                hipSuccess) {
         return FREEZE_EHIP;

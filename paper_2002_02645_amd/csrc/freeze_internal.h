@@ -161,6 +161,7 @@ struct DistPlan {
     int st_wgs;
     bool st_cut;
     int group;      // block minima (variant 5): query tiles that share a cache tile in a row
+    bool next;      // ... and 16 more bits per block
 };
 
 // d_pad decides stream-K for the keys-out variant (pass 0 to leave it off).
@@ -176,7 +177,7 @@ enum class StreamCut {
 };
 DistPlan plan_stream(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad, StreamCut cut);
 // Block minima; grid_units = workgroups.
-DistPlan plan_block(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad);
+DistPlan plan_block(int64_t b, int64_t n, int r, int num_cus, int64_t d_pad, bool next);
 size_t dist_partial_bytes(const DistPlan &plan);   // accumulator slots of cut tiles (0 when none are cut)
 
 struct DistArgs {
@@ -186,6 +187,7 @@ struct DistArgs {
     uint64_t *part;         // [b_pad, alloc_splits, r] packed (ordered key, index) (fused variants)
     float *keys;            // [b_pad, n_pad] every key (keys-out variant)
     uint64_t *bmin;         // [b_pad, n_pad / 32] block minima (keys-out variant)
+    uint32_t *bnext;        // [b_pad, n_pad / 16] (block minima) two blocks' 16 bits beside their minima
     float *partial;         // dist_partial_bytes(plan) bytes of scratch (keys-out variant under stream-K)
     bool projection;        // keys-out variant as a projection: keys = acc + norm[col] (norm holds the bias), no bmin
     bool relu;              // ... through max(., 0)
@@ -286,19 +288,20 @@ int keys_finish_cand(int r);
 size_t keys_finish_workspace_bytes(int64_t rows, int64_t n_pad, int r, size_t align);
 hipError_t launch_keys_finish(const FinishArgs &a, const float *keys, const uint64_t *bmin, int64_t n_pad, uint64_t *cand,
                               int32_t *cand_count, hipStream_t s);
-// Block-minima route: from the smallest key of every block of eight entries [b, n_pad / 8] to the outputs.
-hipError_t launch_block_finish(const FinishArgs &a, const float *bkey, const float *norm, const float *mu, int64_t n_pad,
-                               hipStream_t s);
+// Block-minima route: from the smallest key of every block of eight entries [b, n_pad / 8] (and bnext) to the outputs.
+struct BlockMinima {
+    const float *bkey;
+    const uint16_t *bnext;           // which entry of a block has the smallest key, and a bound of the others' keys; or null
+    const float *norm, *mu;
+    int64_t n_pad;
+    uint64_t *meet;                  // follow_up_meet_entries() u64 of scratch
+};
+hipError_t launch_block_finish(const FinishArgs &a, const BlockMinima &m, hipStream_t s);
 // Follow-up for the flagged queries, both lists: the wider re-scoring of list 0, then the exact scan of
 // list 1 (brute-force fp32 distances to every entry, the k nearest, the label and hit decision, written
 // over the outputs of those queries).
 // tickets [b] int32 (zero on entry, zero again afterwards), part_x scan_scratch_entries(b, k, num_cus) u64;
 // blocks: where the wider re-scoring selects from (block-minima route), or null (a.part holds the candidates).
-struct BlockMinima {
-    const float *bkey, *norm, *mu;   // as for launch_block_finish
-    int64_t n_pad;
-    uint64_t *meet;                  // follow_up_meet_entries() u64 of scratch
-};
 size_t scan_scratch_entries(int64_t b, int k, int num_cus);
 size_t follow_up_meet_entries();
 hipError_t launch_follow_up(const FinishArgs &a, int32_t *tickets, uint64_t *part_x, int num_cus, const BlockMinima *blocks, hipStream_t s);

@@ -16,6 +16,18 @@ __device__ __forceinline__ float from_ordered_bits(uint32_t u)
     return __uint_as_float((u & 0x80000000u) ? (u & 0x7fffffffu) : ~u);
 }
 
+// What a block of eight entries leaves beside its smallest key (block-minima route), in 16 bits: the place of
+// the entry that has it (lowest three bits) and the lead of that key over the block's second smallest, halved, cut off to a
+// float of eight exponent and four mantissa bits: never more than the lead is.  Equal keys: no lead.
+__device__ __forceinline__ uint32_t block_next(float half_lead, uint32_t at) { return (__float_as_uint(half_lead) >> 16 & 0xfff8u) | at; }
+// A lower bound of the keys of a block's other entries from its smallest key.  (The lead is the rounded difference of two
+// sums, and twice it is added with another rounding: an ulp of either.)  No number: no bound.
+__device__ __forceinline__ float block_others(float key, uint32_t next)
+{
+    const float lead = 2.f * __uint_as_float((next & 0xfff8u) << 16);
+    return key + lead - 2.4e-7f * (__builtin_fabsf(key) + lead);
+}
+
 constexpr int kThrThreads = 1024;
 constexpr int kThrGroups = 256;
 constexpr int kThrList = 8192;    // capacity of the gathered list; callers check V * R <= kThrList
