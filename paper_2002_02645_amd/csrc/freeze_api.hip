@@ -705,6 +705,18 @@ const LayerCache *get_projection(const freeze_ctx *ctx, int slot, int *err)
     *err = FREEZE_OK;
     return &ctx->layers[slot];
 }
+// The projection straight from the fp32 rows; off: by a bf16 copy of them (projection_plan): for few k-steps in all, where
+// the sums of cut tiles cost more than the copy (512 x 4,096 -> 256: 26 us so, 25 by the copy; 257 x 512 -> 1,024 22, 14; 2,500 x
+// 517 -> 1,001 43, 40), unless there are many tiles (10,000 x 512 -> 128: 20, 38).
+RowsPlan projection_rows(const freeze_ctx *ctx, const LayerCache &P, int64_t b)
+{
+    if (b <= 256) return RowsPlan{};
+    RowsPlan pl = plan_projection(b, P.d, P.n, ctx->num_cus);
+    const int64_t tiles = (int64_t)pl.m_tiles * pl.n_tiles;
+    if (tiles * pl.nk < 4 * (int64_t)ctx->num_cus && (tiles < 20 || P.d % 4 != 0)) pl.on = false;
+    return pl;
+}
+
 // Up to 256 inputs, and up to 512 where their 256 x 256 tiles would go without stream-K: the streaming kernel, which
 // cuts the few output tiles along the depth for small input tiles too (8,192 -> 1,024 outputs: 1 input 155 -> 20 us,
 // 128 inputs 155 -> 39 us; 384 x 16,384, where stream-K applies: 124 us against 133).  Else a workgroup per (tile
@@ -1151,7 +1163,9 @@ size_t freeze_project_workspace_bytes(const freeze_ctx *ctx, int slot, int64_t b
     const int64_t b1 = b > 0 ? b : 1, b_pad = (b1 + 255) / 256 * 256;
     const size_t plain = align_up((size_t)b_pad * P->d_pad * 2) + align_up((size_t)b1 * P->n_pad * 4);
     const size_t best = projection_bytes(*P, b, projection_plan(ctx, *P, b, false));
-    return best > plain ? best : plain;
+    const RowsPlan rows = projection_rows(ctx, *P, b);
+    const size_t asked = best > plain ? best : plain, part = rows.on ? align_up(rows.part * 4) : 0;
+    return asked > part ? asked : part;
 }
 
 int freeze_project(freeze_ctx *ctx, int slot, const float *x, int64_t b, int relu, float *out, void *workspace,
@@ -1165,11 +1179,17 @@ int freeze_project(freeze_ctx *ctx, int slot, const float *x, int64_t b, int rel
     if (!x || !out || !workspace || (reinterpret_cast<uintptr_t>(x) % 16) != 0 ||
         (reinterpret_cast<uintptr_t>(out) % 16) != 0)
         return FREEZE_EINVAL;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const RowsPlan rows = projection_rows(ctx, *P, b);
+    if (rows.on && rows.part * 4 <= workspace_bytes && (reinterpret_cast<uintptr_t>(workspace) % kAlign) == 0)
+        return launch_project(rows, x, b, P->d, P->d_pad, P->c_bf, P->n, P->n_pad, P->bias, relu != 0, static_cast<float *>(workspace), out, s) ==
+                       hipSuccess
+                   ? FREEZE_OK
+                   : FREEZE_EHIP;
     DistPlan pl = projection_plan(ctx, *P, b, false);
     if (projection_bytes(*P, b, pl) > workspace_bytes) pl = projection_plan(ctx, *P, b, true);
     if (projection_bytes(*P, b, pl) > workspace_bytes || (reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0)
         return FREEZE_EWORKSPACE;
-    hipStream_t s = static_cast<hipStream_t>(stream);
     Carver ws(workspace);
     uint16_t *x_bf = ws.take<uint16_t>((size_t)pl.b_pad * P->d_pad);
     const bool streamed = pl.variant == 4;

@@ -1,6 +1,7 @@
 // Matrix product of many fp32 rows with a few hundred prepared ones, the fp32 rows converted on their way into the
-// matrix cores (gfx950 / CDNA4).  It serves the assignment step of the k-means build.
+// matrix cores (gfx950 / CDNA4).  It serves the assignment step of the k-means build and the projection.
 //
+// k-means.
 // The assignment needs, for every point, the nearest of a few hundred centres.  Through the look-up that was a bf16
 // copy of the points (read and written once per build), a bf16 pass with candidate lists and eight exactly re-scored
 // fp32 centres per point: 50,000 x 8,192, 200 centres 250 + 820 us a round, the latter for 13 GB of centre rows
@@ -25,7 +26,15 @@
 //     60 CUs idle); a range leaves the sums of each tile it touches in a slot, and the reader of the sums adds the
 //     slots of a tile in order.  Many tiles per CU: whole tiles, one slot.
 //
-// Paper: Sec. 4 "k-means".
+// Projection: one bf16 value per element on both sides, as the layer is defined.  A bf16 copy of the inputs first cost 82 us
+// at 10,000 x 8,192 -> 1,024 (and the product 148, the sums of cut tiles 36).
+//   - Ranges of the (row tile, k-step) space, each for a group of workgroups of one XCD, one per column tile: they take the
+//     same fp32 rows at about the same time, out of HBM once and out of the XCD's L2 for the others.
+//   - Bound by what reaches the CUs out of L2, 48 KiB per k-step and workgroup, at 10 TB/s: 195 us there for 168 GFLOP (0.86
+//     PFLOP/s).  Whole calls 265 -> 209 us; 10,000 x 32,768 -> 256 604 -> 319; 10,000 x 1,000 -> 1,500 75 -> 41; 300 x 30,000 ->
+//     300 176 -> 35; 1,500 x 8,192 -> 1,024 87 -> 46.
+//
+// Paper: Sec. 4 "k-means"; Sec. 3 (one-layer dimensionality reduction).
 #include "freeze_internal.h"
 #include "select_common.h"
 
@@ -41,8 +50,6 @@ typedef __attribute__((address_space(3))) void *lds_void_ptr;
 
 namespace {
 
-constexpr int kAStage = kRowsTile * kKB * 4;    // 32 KiB: one k-step of the fp32 rows
-constexpr int kAStages = 3;
 
 // LDS-direct 4-byte load: as load16_global_to_lds, 4 bytes per lane
 __device__ __forceinline__ void load4_global_to_lds(uint64_t sbase, uint32_t voff, uint32_t lds_byte_addr)
@@ -53,13 +60,39 @@ __device__ __forceinline__ void load4_global_to_lds(uint64_t sbase, uint32_t vof
 
 struct RowsGemmArgs {
     const float *x;               // [n, d]
-    const uint16_t *hi, *lo;      // prepared rows, tiled (tiles of kTileN rows, d_pad elements)
+    const uint16_t *hi, *lo;      // prepared rows, tiled (tiles of kTileN rows, d_pad elements); lo: split ones only
     float *part;                  // [tile][slot][kRowsTile][16 NCB]
-    float *sq;                    // [row tile][slot][kRowsTile] sums of squares of the fp32 rows, or null
+    float *sq;                    // [row tile][slot][kRowsTile] sums of squares of the fp32 rows (split ones)
     int64_t n, d, d_pad;
     int64_t len;                  // k-steps of a range
     int nk, n_tiles, m_tiles, slots;
+    // projection
+    int rows;                     // per tile
+    int groups;                   // per XCD: n_tiles workgroups of one XCD share the fp32 rows of a range
+    const float *bias;            // [n_tiles 16 NCB at least]
+    float *out;                   // [n, m]
+    int64_t m;
+    int relu;
 };
+
+// four consecutive columns of one output row of the projection
+__device__ __forceinline__ void store_projected(const RowsGemmArgs &p, int64_t row, int64_t col, f32x4 v)
+{
+    const f32x4 b = *reinterpret_cast<const f32x4 *>(p.bias + col);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        v[e] += b[e];
+        if (p.relu) v[e] = __builtin_fmaxf(v[e], 0.f);
+    }
+    float *dst = p.out + row * p.m + col;
+    if (p.m % 4 == 0) {   // uniform; col is a multiple of 4, so no group of four crosses the end
+        if (col < p.m) *reinterpret_cast<f32x4 *>(dst) = v;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (col + e < p.m) dst[e] = v[e];
+    }
+}
 
 __device__ __forceinline__ int a_swizzle(int row)
 {
@@ -69,21 +102,37 @@ __device__ __forceinline__ int a_swizzle(int row)
 
 // VEC: rows start on 16-byte boundaries (d a multiple of 4)
 // NCB: blocks of 16 columns of a tile; the second wave of a row of waves has one less where the number is odd
-template <int NCB, bool VEC>
+// SPLIT: hi + lo on both sides (k-means); else one bf16 value on both sides, and the sums of a tile that no range's end
+// cuts go straight to the output (projection)
+// RB: blocks of 16 rows of a wave (SPLIT: 4)
+template <int NCB, bool VEC, bool SPLIT, int RB>
 __global__ __launch_bounds__(512) void rows_gemm_kernel(RowsGemmArgs p)
 {
     constexpr int TNB = (NCB + 1) / 2;                  // column blocks of a wave
     constexpr int NC = 16 * NCB;                        // columns of a tile
     constexpr int B_IMG = NC * 64;                      // one k-step of hi (or lo)
-    constexpr int B_STAGE = 2 * B_IMG;
+    constexpr int B_STAGE = SPLIT ? 2 * B_IMG : B_IMG;
+    // groups of matrix instructions that the prepared rows' fragments are read ahead: a group is 12 or 4 of them
+    constexpr int PD = SPLIT ? 1 : 2, RING = SPLIT ? 2 : 4;
+    static_assert((2 * TNB) % RING == 0 && TNB > PD, "fragments' register sets");
+    // A k-step of the projection has a third of the matrix work, and its prepared rows come from beyond L2 (the groups of an
+    // XCD are at different depths).  As many stages of both as fit, so that loads leave one k-step ahead with tiles of 256 rows,
+    // two with 192; plan_projection chooses.
+    constexpr int ROWS = 64 * RB;                       // rows of a tile
+    static_assert(!SPLIT || ROWS == kRowsTile, "");
+    constexpr int kAStages = RB == 4 ? 3 : 4, kAStage = ROWS * kKB * 4;   // one k-step of the fp32 rows
+    constexpr int NSB = SPLIT ? 2 : kAStages;
     constexpr int NBI = B_STAGE / 1024;                 // load instructions of a stage
     constexpr int NI_B = (NBI + 7) / 8;                 // per wave (the last wave's surplus repeats a load)
-    constexpr int NI_A = VEC ? 4 : 16;
+    constexpr int NI_A = VEC ? RB : 4 * RB;
+    constexpr int WR = ROWS / 8;                        // rows a wave loads
+    // loads younger than those a step waits for
+    constexpr int AHEAD = SPLIT ? NI_A : (NSB - 2) * (NI_A + NI_B);
     constexpr int NL = NI_B + NI_A;
     constexpr int kB = kAStages * kAStage;              // byte offset of the prepared rows' stages
-    static_assert(kB + 2 * B_STAGE <= 163840, "LDS budget");
-    static_assert(2 * NI_A + NI_B <= 63, "vmcnt range");
-    __shared__ __attribute__((aligned(16))) unsigned char smem[kB + 2 * B_STAGE];
+    static_assert(kB + NSB * B_STAGE <= 163840, "LDS budget");
+    static_assert((kAStages - 1) * NI_A + (NSB - 1) * NI_B <= 63, "vmcnt range");
+    __shared__ __attribute__((aligned(16))) unsigned char smem[kB + NSB * B_STAGE];
     const f32x4 *smem_a = reinterpret_cast<const f32x4 *>(smem);
     const bf16x8 *smem_b = reinterpret_cast<const bf16x8 *>(smem + kB);
 
@@ -93,8 +142,13 @@ __global__ __launch_bounds__(512) void rows_gemm_kernel(RowsGemmArgs p)
     const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_void_ptr)smem;
     const int nk = p.nk;
 
-    const int64_t total = (int64_t)p.m_tiles * p.n_tiles * nk;
-    const int64_t g_begin = (int64_t)blockIdx.x * p.len;
+    // ranges of the flattened (row tile, column tile, k-step) space; the projection: of (row tile, k-step), a range for
+    // the n_tiles workgroups of a group, one per column tile (block id modulo 8: the XCD)
+    const int across = SPLIT ? p.n_tiles : 1;
+    const int place = (int)blockIdx.x >> 3;
+    const int range = SPLIT ? (int)blockIdx.x : (int)(blockIdx.x & 7) * p.groups + place / p.n_tiles;
+    const int64_t total = (int64_t)p.m_tiles * across * nk;
+    const int64_t g_begin = (int64_t)range * p.len;
     const int64_t g_end = g_begin + p.len < total ? g_begin + p.len : total;
     if (g_begin >= g_end) return;   // uniform
 
@@ -102,10 +156,10 @@ __global__ __launch_bounds__(512) void rows_gemm_kernel(RowsGemmArgs p)
     // position c ^ a_swizzle(row): a fragment read takes one chunk of each of 16 rows for every two lanes groups, and the
     // 16 lanes a cycle serves (rows 0-3 and 12-15 of one group with rows 4-11 of the next) meet 16 different positions.
     const uint32_t d4 = (uint32_t)p.d * 4;
-    const uint32_t a_row = VEC ? w * 32 + (lane >> 3) : w * 32 + (lane >> 5);   // + i * (8 or 2)
+    const uint32_t a_row = VEC ? w * WR + (lane >> 3) : w * WR + (lane >> 5);   // + i * (8 or 2)
     const uint32_t a_row_off = a_row * d4;
     // fragment addresses, in 16-byte units
-    const int rA = wm * 64 + (lane & 15);               // + 16 i: leaves the swizzle as it is
+    const int rA = wm * 16 * RB + (lane & 15);          // + 16 i: leaves the swizzle as it is
     const int swA = a_swizzle(rA);
     const int rdA0 = rA * 8 + ((2 * (lane >> 4)) ^ swA), rdA1 = rA * 8 + ((2 * (lane >> 4) + 1) ^ swA);
     const int rB = wn * TNB * 16 + (lane & 15);
@@ -115,12 +169,12 @@ __global__ __launch_bounds__(512) void rows_gemm_kernel(RowsGemmArgs p)
         const int64_t tile = g / nk;
         const int ka = (int)(g - tile * nk);
         const int kb = g_end - tile * nk < nk ? (int)(g_end - tile * nk) : nk;
-        const int nt = (int)(tile % p.n_tiles);
-        const int64_t mt = tile / p.n_tiles;
+        const int nt = SPLIT ? (int)(tile % p.n_tiles) : place % p.n_tiles;
+        const int64_t mt = tile / across;
         // slot: how many ranges before this one touch the tile
-        const int slot = (int)(blockIdx.x - (tile * nk) / p.len);
+        const int slot = (int)(range - (tile * nk) / p.len);
         // the last row tile reaches back: every load is of a row that exists
-        const int64_t row0 = (mt + 1) * kRowsTile <= p.n ? mt * kRowsTile : p.n - kRowsTile;
+        const int64_t row0 = (mt + 1) * ROWS <= p.n ? mt * ROWS : p.n - ROWS;
         const uint64_t gA = uniform_u64((uint64_t)(uintptr_t)(p.x + row0 * p.d));
 
         // load l of k-step kt's prepared rows
@@ -129,7 +183,7 @@ __global__ __launch_bounds__(512) void rows_gemm_kernel(RowsGemmArgs p)
             id = id < NBI ? id : NBI - 1;
             const int rb = nt * NCB + id % NCB;   // block of 16 prepared rows
             const uint64_t src = (uint64_t)(uintptr_t)(id < NCB ? p.hi : p.lo) +
-                                 ((uint64_t)(rb >> 4) * (p.d_pad / kKB) + kt) * (kTileN * 64) + (rb & 15) * 1024;
+                                 ((uint64_t)(rb >> 4) * (p.d_pad / kKB) + kt) * (kTileN * 64) + (rb & 15) * 1024;   // (!SPLIT: id < NCB)
             load16_global_to_lds(uniform_u64(src), lane * 16, smem_base + kB + buf * B_STAGE + id * 1024);
         };
         // load i of k-step kt's fp32 rows; elements past the row's end are met by zeros in the prepared rows: any
@@ -137,29 +191,45 @@ __global__ __launch_bounds__(512) void rows_gemm_kernel(RowsGemmArgs p)
         auto issue_a = [&](int stage, int kt, int i) {
             const uint32_t ko = (uint32_t)kt * 128;
             if constexpr (VEC) {
-                const uint32_t c = (lane & 7) ^ a_swizzle(i * 8 + (lane >> 3));
+                const uint32_t c = (lane & 7) ^ a_swizzle(w * WR + i * 8 + (lane >> 3));
                 const uint32_t at = ko + c * 16;
-                load16_global_to_lds_nt(gA + (uint64_t)(i * 8) * d4, a_row_off + (at < d4 ? at : 0u), smem_base + stage * kAStage + w * 4096 + i * 1024);
+                const uint64_t base = gA + (uint64_t)(i * 8) * d4;
+                const uint32_t off = a_row_off + (at < d4 ? at : 0u), to = smem_base + stage * kAStage + w * (WR * 128) + i * 1024;
+                if constexpr (SPLIT) load16_global_to_lds_nt(base, off, to);
+                else load16_global_to_lds(base, off, to);   // (the group's other workgroups ask for it too: 3,000 x 8,192 -> 700 81 us, 72 so)
             } else {
-                const uint32_t at = ko + (((lane & 31) ^ (a_swizzle(i * 2) << 2)) << 2);
-                load4_global_to_lds(gA + (uint64_t)(i * 2) * d4, a_row_off + (at < d4 ? at : 0u), smem_base + stage * kAStage + w * 4096 + i * 256);
+                const uint32_t at = ko + (((lane & 31) ^ (a_swizzle(w * WR + i * 2) << 2)) << 2);
+                load4_global_to_lds(gA + (uint64_t)(i * 2) * d4, a_row_off + (at < d4 ? at : 0u), smem_base + stage * kAStage + w * (WR * 128) + i * 256);
             }
         };
 
-        bf16x8 ah[2][4], al[2][4], bh[2], bl[2];
+        bf16x8 ah[2][RB], al[SPLIT ? 2 : 1][RB], bh[RING], bl[SPLIT ? 2 : 1];
         float sq[4] = {0.f, 0.f, 0.f, 0.f};
+        const int tail = (int)(p.d - (int64_t)(nk - 1) * kKB);   // elements of a row's last k-step
         f32x4 raw[2];
         auto read_a = [&](int stage, int i) {
             raw[0] = smem_a[stage * (kAStage / 16) + rdA0 + i * 128];
             raw[1] = smem_a[stage * (kAStage / 16) + rdA1 + i * 128];
         };
-        auto convert = [&](int set, int i) {
+        auto convert = [&](int set, int i, bool cut) {
             f32x8 x;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 x[e] = raw[0][e];
                 x[4 + e] = raw[1][e];
             }
+            if constexpr (!SPLIT) {
+                if (cut) {   // uniform: what was read past the row's end is no zero, and may be no number
+                    int left = tail - (lane >> 4) * 8;
+                    asm volatile("" : "+v"(left));   // (formed here: eight masks kept over the loop would spill)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[e] = e < left ? x[e] : 0.f;
+                }
+                u32x4 v = __builtin_bit_cast(u32x4, __builtin_convertvector(x, bf16x8));   // round to nearest even
+                asm volatile("" : "+v"(v));   // (as below)
+                ah[set][i] = __builtin_bit_cast(bf16x8, v);
+                return;
+            } else {
             const u32x4 h = __builtin_bit_cast(u32x4, __builtin_convertvector(x, bf16x8));   // round to nearest even
             f32x8 r;
 #pragma unroll
@@ -174,16 +244,17 @@ __global__ __launch_bounds__(512) void rows_gemm_kernel(RowsGemmArgs p)
             al[set][i] = __builtin_bit_cast(bf16x8, lv);
 #pragma unroll
             for (int e = 0; e < 8; ++e) sq[i] = __builtin_fmaf(x[e], x[e], sq[i]);
+            }
         };
         auto read_b = [&](int set, int buf, int j) {
             const int at = (NCB % 2 && j == TNB - 1) ? j - wn : j;   // (the second wave has no such block)
             bh[set] = smem_b[buf * (B_STAGE / 16) + rdB + at * 64];
-            bl[set] = smem_b[buf * (B_STAGE / 16) + B_IMG / 16 + rdB + at * 64];
+            if constexpr (SPLIT) bl[set] = smem_b[buf * (B_STAGE / 16) + B_IMG / 16 + rdB + at * 64];
         };
 
-        f32x4 acc[4][TNB];
+        f32x4 acc[RB][TNB];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < RB; ++i)
 #pragma unroll
             for (int j = 0; j < TNB; ++j)
 #pragma unroll
@@ -197,65 +268,77 @@ __global__ __launch_bounds__(512) void rows_gemm_kernel(RowsGemmArgs p)
 #pragma unroll
         for (int i = 0; i < NI_A; ++i) issue_a(1, at_most(ka + 1), i);
 #pragma unroll
-        for (int l = 0; l < NI_B; ++l) issue_b(0, ka, l);
+        for (int l = 0; l < (SPLIT ? 1 : 2) * NI_B; ++l) issue_b(l / NI_B, at_most(ka + l / NI_B), l % NI_B);
 #pragma unroll
         for (int i = 0; i < NI_A; ++i) issue_a(2, at_most(ka + 2), i);
-        wait_global_loads_le<2 * NI_A + NI_B>();
+        if constexpr (kAStages == 4) {
+#pragma unroll
+            for (int l = 0; l < NI_B; ++l) issue_b(2, at_most(ka + 2), l);
+#pragma unroll
+            for (int i = 0; i < NI_A; ++i) issue_a(3, at_most(ka + 3), i);
+        }
+        wait_global_loads_le<(kAStages - 1) * NI_A + (NSB - 1) * NI_B>();
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < RB; ++i) {
             read_a(0, i);
-            convert(0, i);
+            convert(0, i, ka == nk - 1 && tail < kKB);
         }
-        wait_global_loads_le<NI_A>();
+        wait_global_loads_le<AHEAD>();
         __syncthreads();
         int st = 0;   // stage of the fp32 rows of k-step kt
-        read_b(0, 0, 0);
-        // At the top of k-step kt: its A fragments are in register set `cur`, its first B fragments on their way to
-        // registers; its prepared rows and the fp32 rows of kt + 1 are in LDS, the fp32 rows of kt + 2 in flight.  The
-        // step's barrier comes before its last group of matrix instructions, which need nothing newer: it publishes
+#pragma unroll
+        for (int j = 0; j < PD; ++j) read_b(j, 0, j);
+        // At the top of k-step kt: its A fragments are in register set `cur`, the B fragments of its first PD groups on their
+        // way to registers; its prepared rows and the fp32 rows of kt + 1 are in LDS, the fp32 rows of kt + 2 in flight.  The
+        // step's barrier comes before its last PD groups of matrix instructions, which need nothing newer: it publishes
         // the prepared rows of kt + 1 and the fp32 rows of kt + 2 and frees the stages of kt's prepared rows and of the fp32
-        // rows of kt + 1, which have been converted.
+        // rows of kt + 1, which have been converted.  (The projection's loads are further ahead: AHEAD.)
         auto k_step = [&](int kt, auto tag) {
             constexpr int cur = decltype(tag)::value;
-            constexpr int S0 = cur * TNB;   // B fragments alternate between two register sets, on from step to step
+            constexpr int S0 = cur * TNB;   // B fragments take RING register sets in turn, on from step to step
+            const bool cut = kt + 1 == nk - 1 && tail < kKB;
             const int nst = st + 1 == kAStages ? 0 : st + 1;
-            const int b_kt = at_most(kt + 1), a_kt = at_most(kt + 3);
+            const int b_kt = at_most(kt + NSB - 1), a_kt = at_most(kt + kAStages);
+            static_assert(SPLIT || NSB == kAStages, "one stage index for both");
+            const int b_st = SPLIT ? cur : st, b_next = SPLIT ? cur ^ 1 : nst, b_fill = SPLIT ? cur ^ 1 : (st == 0 ? NSB - 1 : st - 1);
 #pragma unroll
             for (int j = 0; j < TNB; ++j) {
-                constexpr int GA = TNB - 1;   // groups that convert A blocks and issue loads
-                auto group_of = [](int i) { return GA >= 4 ? i : i * GA / 4; };
-                auto mfma = [&](bf16x8(&b)[2], bf16x8(&x)[2][4]) {
+                constexpr int GA = TNB - PD;   // groups that convert A blocks and issue loads
+                auto group_of = [](int i) { return GA >= RB ? i : i * GA / RB; };
+                auto mfma = [&](const bf16x8 &b, bf16x8(&x)[RB]) {
                     if (NCB % 2 && j == TNB - 1 && wn) return;   // uniform
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[(S0 + j) & 1], x[cur][i], acc[i][j], 0, 0, 0);
+                    for (int i = 0; i < RB; ++i)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, x[i], acc[i][j], 0, 0, 0);
                 };
-                if (j == TNB - 1) {
-                    wait_global_loads_le<NI_A>();
+                if (j == TNB - PD) {
+                    wait_global_loads_le<AHEAD>();
                     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                     __syncthreads();
-                    read_b((S0 + TNB) & 1, cur ^ 1, 0);
+                }
+                if (j + PD < TNB) {
+                    read_b((S0 + j + PD) % RING, b_st, j + PD);
+                    if (GA >= RB && j < RB) read_a(nst, j);
                 } else {
-                    read_b((S0 + j + 1) & 1, cur, j + 1);
-                    if (GA >= 4 && j < 4) read_a(nst, j);
+                    read_b((S0 + j + PD) % RING, b_next, j + PD - TNB);
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                mfma(bh, ah);
-                mfma(bl, ah);
+                mfma(bh[(S0 + j) % RING], ah[cur]);
+                if constexpr (SPLIT) mfma(bl[(S0 + j) % RING], ah[cur]);
                 if (j < GA) {
 #pragma unroll
                     for (int l = j * NL / GA; l < (j + 1) * NL / GA; ++l) {
-                        if (l < NI_B) issue_b(cur ^ 1, b_kt, l);
+                        if (l < NI_B) issue_b(b_fill, b_kt, l);
                         else issue_a(st, a_kt, l - NI_B);
                     }
                 }
-                mfma(bh, al);
+                if constexpr (SPLIT) mfma(bh[(S0 + j) % RING], al[cur]);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int i = 0; i < RB; ++i) {
                     if (j >= GA || group_of(i) != j) continue;
-                    if (GA < 4) read_a(nst, i);
-                    convert(cur ^ 1, i);
+                    if (GA < RB) read_a(nst, i);
+                    convert(cur ^ 1, i, cut);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -271,13 +354,26 @@ __global__ __launch_bounds__(512) void rows_gemm_kernel(RowsGemmArgs p)
         wait_global_loads_le<0>();   // the refills past the last k-step
         // Sums out: the matrix instruction takes the prepared rows as its rows, so a lane holds four consecutive
         // columns of one fp32 row.
-        float *dst = p.part + ((tile * p.slots + slot) * kRowsTile + wm * 64 + (lane & 15)) * NC + wn * TNB * 16 + (lane >> 4) * 4;
+        if constexpr (!SPLIT) {
+            if (ka == 0 && kb == nk) {   // uniform: the whole tile.  (Rows that the last row tile reaches back over are the one's before it.)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < RB; ++i) {
+                    const int64_t row = row0 + wm * 16 * RB + i * 16 + (lane & 15);
+                    if (row < mt * ROWS) continue;
+#pragma unroll
+                    for (int j = 0; j < TNB; ++j) store_projected(p, row, nt * NC + (wn * TNB + j) * 16 + (lane >> 4) * 4, acc[i][j]);
+                }
+                g = tile * nk + kb;
+                continue;
+            }
+        }
+        float *dst = p.part + (((SPLIT ? tile : mt * p.n_tiles + nt) * p.slots + slot) * ROWS + wm * 16 * RB + (lane & 15)) * NC + wn * TNB * 16 + (lane >> 4) * 4;
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
 #pragma unroll
             for (int j = 0; j < TNB; ++j)
                 if (wn * TNB + j < NCB) *reinterpret_cast<f32x4 *>(dst + i * 16 * NC + j * 16) = acc[i][j];
-        if (p.sq && nt == 0 && wn == 0) {
+        if (SPLIT && nt == 0 && wn == 0) {
             // (the fragments converted past the last k-step are of that step again: sums of squares only grow by them)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -288,6 +384,37 @@ __global__ __launch_bounds__(512) void rows_gemm_kernel(RowsGemmArgs p)
             }
         }
         g = tile * nk + kb;
+    }
+}
+
+// The projection's output where ranges cut its tiles: the sums of a tile's slots, in order, kSumRows rows of a tile per
+// workgroup.
+constexpr int kSumRows = 4;
+__global__ __launch_bounds__(256) void project_sum_kernel(RowsGemmArgs p, int nc)
+{
+    const int rows = p.rows;   // of a tile
+    const int64_t tile = blockIdx.x / (rows / kSumRows), mt = tile / p.n_tiles;
+    const int64_t first = mt * p.nk / p.len, last = (mt * p.nk + p.nk - 1) / p.len;
+    if (first == last) return;   // uniform: written by its range
+    const int ns = (int)(last - first) + 1, nt = (int)(tile - mt * p.n_tiles);
+    const int64_t row0 = (mt + 1) * rows <= p.n ? mt * rows : p.n - rows;
+    const int r0 = (int)(blockIdx.x % (rows / kSumRows)) * kSumRows, q = nc / 4;
+    for (int i = threadIdx.x; i < kSumRows * q; i += 256) {
+        const int r = r0 + i / q, c = i % q * 4;
+        if (row0 + r < mt * rows || (int64_t)nt * nc + c >= p.m) continue;
+        const float *src = p.part + (tile * p.slots * rows + r) * nc + c;
+        const int64_t step = (int64_t)rows * nc;
+        f32x4 v = *reinterpret_cast<const f32x4 *>(src);
+        int s = 1;
+        for (; s + 3 < ns; s += 4) {   // four in flight
+            f32x4 t[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) t[u] = *reinterpret_cast<const f32x4 *>(src + (s + u) * step);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v += t[u];
+        }
+        for (; s < ns; ++s) v += *reinterpret_cast<const f32x4 *>(src + s * step);
+        store_projected(p, row0 + r, (int64_t)nt * nc + c, v);
     }
 }
 
@@ -561,13 +688,13 @@ __global__ __launch_bounds__(256) void kmeans_pick_kernel(PickArgs p)
     }
 }
 
-template <int NCB>
+template <int NCB, bool SPLIT, int RB = 4>
 hipError_t launch_gemm(const RowsPlan &pl, const RowsGemmArgs &a, hipStream_t s)
 {
     if (a.d % 4 == 0)
-        hipLaunchKernelGGL((rows_gemm_kernel<NCB, true>), dim3((unsigned)pl.wgs), dim3(512), 0, s, a);
+        hipLaunchKernelGGL((rows_gemm_kernel<NCB, true, SPLIT, RB>), dim3((unsigned)pl.wgs), dim3(512), 0, s, a);
     else
-        hipLaunchKernelGGL((rows_gemm_kernel<NCB, false>), dim3((unsigned)pl.wgs), dim3(512), 0, s, a);
+        hipLaunchKernelGGL((rows_gemm_kernel<NCB, false, SPLIT, RB>), dim3((unsigned)pl.wgs), dim3(512), 0, s, a);
     return hipGetLastError();
 }
 
@@ -615,17 +742,17 @@ hipError_t launch_kmeans_assign(const RowsPlan &pl, const float *points, int64_t
     if (!pl.on || n < kRowsTile || pl.m_tiles != (n + kRowsTile - 1) / kRowsTile || d_pad < (int64_t)pl.nk * kKB || kc > (int64_t)pl.n_tiles * pl.nc ||
         (int64_t)pl.n_tiles * pl.nc > (kc + kTileN - 1) / kTileN * kTileN || (reinterpret_cast<uintptr_t>(points) % 16) != 0)
         return hipErrorInvalidValue;
-    RowsGemmArgs a{points, hi, lo, part, sq, n, d, d_pad, pl.len, pl.nk, pl.n_tiles, pl.m_tiles, pl.slots};
+    RowsGemmArgs a{points, hi, lo, part, sq, n, d, d_pad, pl.len, pl.nk, pl.n_tiles, pl.m_tiles, pl.slots, kRowsTile, 0, nullptr, nullptr, 0, 0};
     hipError_t e;
     switch (pl.ncb) {
-    case 4: e = launch_gemm<4>(pl, a, s); break;
-    case 6: e = launch_gemm<6>(pl, a, s); break;
-    case 8: e = launch_gemm<8>(pl, a, s); break;
-    case 10: e = launch_gemm<10>(pl, a, s); break;
-    case 12: e = launch_gemm<12>(pl, a, s); break;
-    case 13: e = launch_gemm<13>(pl, a, s); break;
-    case 14: e = launch_gemm<14>(pl, a, s); break;
-    case 16: e = launch_gemm<16>(pl, a, s); break;
+    case 4: e = launch_gemm<4, true>(pl, a, s); break;
+    case 6: e = launch_gemm<6, true>(pl, a, s); break;
+    case 8: e = launch_gemm<8, true>(pl, a, s); break;
+    case 10: e = launch_gemm<10, true>(pl, a, s); break;
+    case 12: e = launch_gemm<12, true>(pl, a, s); break;
+    case 13: e = launch_gemm<13, true>(pl, a, s); break;
+    case 14: e = launch_gemm<14, true>(pl, a, s); break;
+    case 16: e = launch_gemm<16, true>(pl, a, s); break;
     default: return hipErrorInvalidValue;
     }
     if (e != hipSuccess) return e;
@@ -634,6 +761,64 @@ hipError_t launch_kmeans_assign(const RowsPlan &pl, const float *points, int64_t
     const dim3 grid((unsigned)((n + 4 * kPickPoints - 1) / (4 * kPickPoints)));
     if (pl.n_tiles == 1) hipLaunchKernelGGL(kmeans_pick_kernel<1>, grid, dim3(256), 0, s, k);
     else hipLaunchKernelGGL(kmeans_pick_kernel<kRowsMaxTiles>, grid, dim3(256), 0, s, k);
+    return hipGetLastError();
+}
+
+static RowsPlan plan_projection_rows(int64_t n, int64_t d, int64_t m, int num_cus, int rows)
+{
+    RowsPlan pl{};
+    pl.rows = rows;
+    const int per_xcd = num_cus / 8;
+    if (n < rows || d < 1 || d > (int64_t)1 << 20 || m < 1 || m > (int64_t)per_xcd * kTileN) return pl;
+    pl.n_tiles = (int)((m + kTileN - 1) / kTileN);
+    const int per = (int)((m + pl.n_tiles - 1) / pl.n_tiles);
+    pl.ncb = per <= 128 ? 8 : (per <= 192 ? 12 : 16);
+    pl.nc = 16 * pl.ncb;
+    pl.m_tiles = (int)((n + rows - 1) / rows);
+    pl.nk = (int)((d + kKB - 1) / kKB);
+    pl.groups = per_xcd / pl.n_tiles;
+    const int64_t total = (int64_t)pl.m_tiles * pl.nk, ranges = 8 * (int64_t)pl.groups;
+    if (pl.m_tiles >= 8 * ranges) {
+        pl.len = (pl.m_tiles + ranges - 1) / ranges * pl.nk;   // whole tiles: an idle eighth at most
+    } else {
+        pl.len = (total + ranges - 1) / ranges;
+        const int64_t least = pl.nk < 8 ? pl.nk : 8;           // a slot is written and read for it
+        if (pl.len < least) pl.len = least;
+    }
+    pl.wgs = 8 * pl.groups * pl.n_tiles;   // (ranges past the end return at once)
+    pl.slots = pl.len % pl.nk == 0 ? 1 : (int)((pl.nk + pl.len - 2) / pl.len) + 1;
+    pl.part = pl.slots == 1 ? 0 : (size_t)pl.m_tiles * pl.n_tiles * pl.slots * rows * pl.nc;
+    pl.on = pl.part * 4 <= (size_t)1 << 30;
+    return pl;
+}
+
+// Tiles of 256 rows take 1.22 us a k-step, of 192 rows 0.94 where the chip is busy (10,000 x 8,192 -> 1,024: what L2
+// hands to the CUs, 10 TB/s, bounds both: 210, 219 us) and about 0.8 in short ranges (1,500 x 8,192 -> 1,024, 24 and 32 k-steps: 55, 46;
+// 3,000 x 8,192 -> 700 67, 60; but 2,000 x 16,384 -> 256, 16 and 22 k-steps: 53, 58).
+RowsPlan plan_projection(int64_t n, int64_t d, int64_t m, int num_cus)
+{
+    const RowsPlan p4 = plan_projection_rows(n, d, m, num_cus, 256), p3 = plan_projection_rows(n, d, m, num_cus, 192);
+    if (!p4.on || !p3.on) return p4.on ? p4 : p3;
+    return p3.len * 100 >= p4.len * (p4.len >= 128 || p4.slots == 1 ? 130 : 136) ? p4 : p3;
+}
+
+hipError_t launch_project(const RowsPlan &pl, const float *x, int64_t n, int64_t d, int64_t d_pad, const uint16_t *w, int64_t m, int64_t m_pad,
+                          const float *bias, bool relu, float *part, float *out, hipStream_t s)
+{
+    if (!pl.on || (pl.rows != 192 && pl.rows != 256) || n < pl.rows || pl.m_tiles != (n + pl.rows - 1) / pl.rows || pl.nk != (d + kKB - 1) / kKB || d_pad < (int64_t)pl.nk * kKB ||
+        m > (int64_t)pl.n_tiles * pl.nc || (int64_t)pl.n_tiles * pl.nc > m_pad || (pl.part > 0 && !part) ||
+        ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(out)) % 16) != 0)
+        return hipErrorInvalidValue;
+    RowsGemmArgs a{x, w, nullptr, part, nullptr, n, d, d_pad, pl.len, pl.nk, pl.n_tiles, pl.m_tiles, pl.slots, pl.rows, pl.groups, bias, out, m, relu ? 1 : 0};
+    hipError_t e;
+    switch (pl.ncb) {
+    case 8: e = pl.rows == 192 ? launch_gemm<8, false, 3>(pl, a, s) : launch_gemm<8, false, 4>(pl, a, s); break;
+    case 12: e = pl.rows == 192 ? launch_gemm<12, false, 3>(pl, a, s) : launch_gemm<12, false, 4>(pl, a, s); break;
+    case 16: e = pl.rows == 192 ? launch_gemm<16, false, 3>(pl, a, s) : launch_gemm<16, false, 4>(pl, a, s); break;
+    default: return hipErrorInvalidValue;
+    }
+    if (e != hipSuccess || pl.slots == 1) return e;
+    hipLaunchKernelGGL(project_sum_kernel, dim3((unsigned)(pl.m_tiles * pl.n_tiles * (pl.rows / kSumRows))), dim3(256), 0, s, a, pl.nc);
     return hipGetLastError();
 }
 
