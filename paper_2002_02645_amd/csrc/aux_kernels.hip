@@ -733,7 +733,8 @@ __device__ __forceinline__ void rescore_short(const FinishArgs &a, const float *
 // BATCHED: fp32 rows four at a time, all their loads ahead of the first use.  1,066 queries x 38,673 x 22,128, width 32: whole
 // look-ups 2,227 us without, 2,087 with; width 64, i.e. two passes of 32, 3,000 x 286 x 44,976: 3,024 without, 4,294 with
 // (workgroups that drift apart share less of L2).
-template <int NT, int RG, bool BATCHED = false>
+// GS: rows whose loads are in flight at once; fewer than eight where fewer are asked for (RG = GS).
+template <int NT, int RG, bool BATCHED = false, int GS = 8>
 __device__ __forceinline__ void rescore_block_all(const FinishArgs &a, const float *qrow, const int32_t *idx_s,
                                                   float *dist_s, float (*red)[8], int r, int tid)
 {
@@ -745,7 +746,7 @@ __device__ __forceinline__ void rescore_block_all(const FinishArgs &a, const flo
         const f32x4 q1 = *reinterpret_cast<const f32x4 *>(qrow + i + 4);
         const float qv[8] = {q0[0], q0[1], q0[2], q0[3], q1[0], q1[1], q1[2], q1[3]};
 #pragma unroll
-        for (int g = 0; g < RG; g += 8) {
+        for (int g = 0; g < RG; g += GS) {
             if (g < r) {   // uniform
                 if (BATCHED && a.c_f32) {
 #pragma unroll
@@ -768,7 +769,7 @@ __device__ __forceinline__ void rescore_block_all(const FinishArgs &a, const flo
                     }
                 } else if (a.c_f32) {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
+                    for (int j = 0; j < GS; ++j) {
                         const float *c = a.c_f32 + (int64_t)idx_s[(g + j < r) ? g + j : r - 1] * a.d_pad + i;
                         const f32x4 c0v = *reinterpret_cast<const f32x4 *>(c);
                         const f32x4 c1v = *reinterpret_cast<const f32x4 *>(c + 4);
@@ -780,12 +781,12 @@ __device__ __forceinline__ void rescore_block_all(const FinishArgs &a, const flo
                         }
                     }
                 } else {
-                    uint4 cb[8];
+                    uint4 cb[GS];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j)
+                    for (int j = 0; j < GS; ++j)
                         cb[j] = *reinterpret_cast<const uint4 *>(a.c_rows + (int64_t)idx_s[(g + j < r) ? g + j : r - 1] * a.d_pad + i);
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
+                    for (int j = 0; j < GS; ++j) {
                         const uint32_t wv[4] = {cb[j].x, cb[j].y, cb[j].z, cb[j].w};
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
@@ -802,17 +803,17 @@ __device__ __forceinline__ void rescore_block_all(const FinishArgs &a, const flo
         }
     }
 #pragma unroll
-    for (int g = 0; g < RG; g += 8) {
+    for (int g = 0; g < RG; g += GS) {
         if (g < r) {   // uniform
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
+            for (int j = 0; j < GS; ++j) {
                 float v = acc[g + j];
 #pragma unroll
                 for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
                 if ((tid & 63) == 0) red[tid >> 6][j] = v;
             }
             __syncthreads();
-            if (tid < 8 && g + tid < r) {
+            if (tid < GS && g + tid < r) {
                 float t = 0.f;
 #pragma unroll
                 for (int wv = 0; wv < NT / 64; wv += 4)   // fixed order: groups of four waves
@@ -1472,6 +1473,9 @@ struct KeysFinishArgs {
     uint64_t *cand;         // [b, a.part_stride] candidates left for the wider re-scoring of an unconfirmed query
     int32_t *cand_count;    // [b]
     int m_first;            // candidates re-scored at first (first_width)
+    int parts;              // workgroups that share a query's first re-scoring
+    float *meet;            // [b, kMaxRescore] (parts > 1) their distances
+    int32_t *tickets;       // [b] (parts > 1) zero on entry; left zero
 };
 
 // dist_s[0 .. m) for rows of d values (a multiple of 8), 1,024 threads: group g of four waves takes
@@ -1544,7 +1548,7 @@ __global__ __launch_bounds__(kThrThreads) void keys_finish_kernel(KeysFinishArgs
     __shared__ uint64_t grp_s[kThrGroups];
     __shared__ int rank_s[kThrGroups];
     __shared__ uint64_t sel_s;
-    __shared__ int list_n, blk_n, cand_n, distinct_s, verdict_s;
+    __shared__ int list_n, blk_n, cand_n, distinct_s, verdict_s, last_s;
     __shared__ float red16[16][16];
     __shared__ float dist_s[kMaxRescore];
     __shared__ int32_t idx_s[kMaxRescore];
@@ -1679,14 +1683,20 @@ __global__ __launch_bounds__(kThrThreads) void keys_finish_kernel(KeysFinishArgs
     auto rescore = [&](int c0, int m) {
         if (a.d >= 16384 && a.d % 8 == 0) {
             float(*red)[8] = reinterpret_cast<float(*)[8]>(&red16[0][0]);
-            if (m <= 16) {
+            if (m <= 2) {
+                rescore_block_all<1024, 2, false, 2>(a, qrow, idx_s + c0, dist_s + c0, red, m, tid);
+            } else if (m <= 4) {
+                rescore_block_all<1024, 4, false, 4>(a, qrow, idx_s + c0, dist_s + c0, red, m, tid);
+            } else if (m <= 16) {
                 rescore_block_all<1024, 16>(a, qrow, idx_s + c0, dist_s + c0, red, m, tid);
             } else {
                 for (int c = 0; c < m; c += 32)
                     rescore_block_all<1024, 32>(a, qrow, idx_s + c0 + c, dist_s + c0 + c, red, m - c < 32 ? m - c : 32, tid);
             }
         } else if (a.d >= 4096 && a.d % 8 == 0) {
-            if (m <= 16)
+            if (m <= 4)
+                rescore_groups<1>(a, qrow, idx_s + c0, dist_s + c0, reinterpret_cast<float(*)[1]>(&red16[0][0]), m, tid);
+            else if (m <= 16)
                 rescore_groups<4>(a, qrow, idx_s + c0, dist_s + c0, reinterpret_cast<float(*)[4]>(&red16[0][0]), m, tid);
             else if (m <= 32)
                 rescore_groups<8>(a, qrow, idx_s + c0, dist_s + c0, reinterpret_cast<float(*)[8]>(&red16[0][0]), m, tid);
@@ -1703,7 +1713,25 @@ __global__ __launch_bounds__(kThrThreads) void keys_finish_kernel(KeysFinishArgs
         __syncthreads();
     };
     const int m_first = ka.m_first;
-    rescore(0, m_first);
+    if (ka.parts > 1) {   // uniform
+        const int per = (m_first + ka.parts - 1) / ka.parts, c0 = (int)blockIdx.y * per, m = m_first - c0 < per ? m_first - c0 : per;
+        if (m > 0) rescore(c0, m);   // uniform
+        // (device-coherent stores, complete before the ticket is taken, and device-coherent loads: as in follow_up_kernel)
+        float *meet = ka.meet + (size_t)q * kMaxRescore;
+        if (tid >= c0 && tid < c0 + m) __hip_atomic_store(meet + tid, dist_s[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) {
+            last_s = atomicAdd(&ka.tickets[q], 1) == ka.parts - 1;
+            if (last_s) atomicExch(&ka.tickets[q], 0);   // the exact scan's tickets are these
+        }
+        __syncthreads();
+        if (!__builtin_amdgcn_readfirstlane(last_s)) return;   // uniform: the query's last workgroup goes on
+        if (tid < m_first) dist_s[tid] = __hip_atomic_load(meet + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+    } else {
+        rescore(0, m_first);
+    }
 
     // ---- 3. final order, certificate, vote ----
     // every entry that is no candidate has a key at or above the largest candidate's
@@ -1811,16 +1839,18 @@ bool keys_finish_supported(int64_t n_pad, int r)
 
 int keys_finish_cand(int r) { return 32 * r < 2 * kTier1 ? 32 * r : 2 * kTier1; }
 
+size_t keys_finish_meet_entries(int64_t rows) { return rows <= kPartsRows ? (size_t)rows * kMaxRescore : 0; }
+
 size_t keys_finish_workspace_bytes(int64_t rows, int64_t n_pad, int r, size_t align)
 {
     auto up = [&](size_t x) { return (x + align - 1) / align * align; };
     const size_t b = (size_t)rows;
-    return up(b * (size_t)n_pad * 4) + up(b * (size_t)(n_pad / 32) * 8) + up(b * 4) + up(b * (size_t)keys_finish_cand(r) * 8);
+    return up(keys_finish_meet_entries(rows) * 4) + up(b * (size_t)n_pad * 4) + up(b * (size_t)(n_pad / 32) * 8) + up(b * 4) + up(b * (size_t)keys_finish_cand(r) * 8);
 }
 
 // a.part / a.part_count (stride keys_finish_cand(a.r)) are the kernel's outputs for the wider re-scoring
 hipError_t launch_keys_finish(const FinishArgs &a, const float *keys, const uint64_t *bmin, int64_t n_pad, uint64_t *cand,
-                              int32_t *cand_count, hipStream_t s)
+                              int32_t *cand_count, float *meet, int32_t *tickets, int num_cus, hipStream_t s)
 {
     if (!keys_finish_supported(n_pad, a.r) || a.r < 1 || a.r > kMaxRescore || a.k > kMaxK || a.k > a.r || a.b < 1 || !a.flag_count ||
         !a.flag_list || !a.flag_list2 || a.part_stride != keys_finish_cand(a.r))
@@ -1828,8 +1858,22 @@ hipError_t launch_keys_finish(const FinishArgs &a, const float *keys, const uint
     const int64_t nb = n_pad / 32, per_group = (nb + kThrGroups - 1) / kThrGroups;
     int r_sel = 2 * a.r < kMaxRescore ? 2 * a.r : kMaxRescore;
     while (r_sel > a.r && per_group * r_sel > kThrList) --r_sel;   // the gathered minima fit the list
-    KeysFinishArgs ka{a, bmin, keys, nb, n_pad, r_sel, cand, cand_count, first_width(a, a.b > 64)};
-    hipLaunchKernelGGL(keys_finish_kernel, dim3((unsigned)a.b), dim3(kThrThreads), 0, s, ka);
+    KeysFinishArgs ka{a, bmin, keys, nb, n_pad, r_sel, cand, cand_count, first_width(a, a.b > 64), 1, meet, tickets};
+    // Long rows, few queries: a workgroup gets a row out of memory at 50 to 100 GB/s, so up to eight share the rows of a query,
+    // 32 KB each at least; each repeats the selection.  One query,
+    // 50,000 x 16,384: 22 -> 16 us of this kernel; 4 x 3,404 x 16,384 fp32, k = 20: 52 -> 21; 60 x 3,433 x 16,384, k = 20: 40 -> 28; 32 x
+    // 50,000 x 65,536 .. 16,384: 32 -> 17.
+    if (meet && tickets && a.d >= 4096) {
+        const int64_t bytes = (int64_t)ka.m_first * a.d_pad * (a.c_f32 ? 4 : 2);
+        int64_t parts = bytes / 32768;
+        parts = parts < num_cus / a.b ? parts : num_cus / a.b;
+        parts = parts < 8 ? parts : 8;
+        if (parts > 1) {
+            const int per = (int)((ka.m_first + parts - 1) / parts);
+            ka.parts = (ka.m_first + per - 1) / per;
+        }
+    }
+    hipLaunchKernelGGL(keys_finish_kernel, dim3((unsigned)a.b, (unsigned)ka.parts), dim3(kThrThreads), 0, s, ka);
     return hipGetLastError();
 }
 

@@ -193,10 +193,10 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
     const size_t bb = (size_t)(b > 0 ? b : 1);
     const size_t scan_bytes = align_up(kFlagCounts * 4) + 3 * align_up((bb > 2 * kSkinnyRows ? bb : 2 * kSkinnyRows) * 4) +
                               align_up(scan_scratch_entries(b, k, ctx->num_cus) * 8);
+    const bool fast = how == Decomp::best || how == Decomp::lean;
     out->skinny = !cascade && skinny_supported(b, L.n_pad, L.d_pad, r, ctx->num_cus);
     out->keys = false;
     out->blocks = false;
-    const bool fast = how == Decomp::best || how == Decomp::lean;
     const bool next = how == Decomp::best && block_next_pays(ctx, L, b, k);   // block minima with the further bits
     if (out->skinny) {
         DistPlan pl{};
@@ -380,6 +380,7 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
     const uint64_t *keys_bmin = nullptr;
     uint64_t *keys_cand = nullptr;
     int32_t *keys_cand_count = nullptr;
+    float *keys_meet = nullptr;
     const uint64_t *skinny_bmin = nullptr, *skinny_wgmin = nullptr;
     uint64_t *skinny_cand = nullptr, *skinny_samp = nullptr;
     if (sh.skinny) {
@@ -419,6 +420,8 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
             da.bmin = ws.take<uint64_t>(rows * (L.n_pad / 32));
             int32_t *cand_count = ws.take<int32_t>(rows);
             uint64_t *cand = ws.take<uint64_t>(rows * keys_finish_cand(sh.r));
+            const size_t meet = keys_finish_meet_entries((int64_t)rows);
+            keys_meet = meet > 0 ? ws.take<float>(meet) : nullptr;
             da.partial = dist_partial_bytes(sh.plan) > 0 ? ws.take<float>(dist_partial_bytes(sh.plan) / 4) : nullptr;
             if (launch_dist_topr(sh.plan, da, s) != hipSuccess) return FREEZE_EHIP;
             keys = da.keys;
@@ -489,7 +492,7 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
             return FREEZE_EHIP;
     } else if (minima.bkey) {
         if (launch_block_finish(fa, minima, s) != hipSuccess) return FREEZE_EHIP;
-    } else if ((keys ? launch_keys_finish(fa, keys, keys_bmin, L.n_pad, keys_cand, keys_cand_count, s) : launch_finish(fa, s)) !=
+    } else if ((keys ? launch_keys_finish(fa, keys, keys_bmin, L.n_pad, keys_cand, keys_cand_count, keys_meet, tickets, ctx->num_cus, s) : launch_finish(fa, s)) !=
                hipSuccess) {
         return FREEZE_EHIP;
     }
