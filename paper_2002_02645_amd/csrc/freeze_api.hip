@@ -170,6 +170,17 @@ bool block_route(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, i
 // that most CUs would have nothing to do (256 x 2,000 x 512: 52 -> 36 us, 256 x 3,000 x 4,096: 127 -> 81 us).
 constexpr int kStreamRows = 128;
 
+// Whether the small-batch kernel (short activations, up to 16 queries) is faster than the streaming kernel: on large caches,
+// whose keys it does not write out; the re-scoring of whole blocks and the chain of its finishing kernel's steps cost
+// more than the keys of small ones.  One query / 16 queries, k = 10, small-batch against streaming kernel:
+//   2,000 x 512 30, 25 / 35, 25 us; 30,000 x 1,024 55, 31 / 61, 31; 100,000 x 512 42, 35 / 48, 36;
+//   300,000 x 512 75, 81 / 86, 82; 1,000,000 x 512 183, 223 / 196, 223; 1,000,000 x 1,024 341, 408 / 807, 407
+//   (eight queries 799, 407; eight of 700 values 248).
+bool skinny_pays(const LayerCache &L, int64_t b)
+{
+    return L.n >= 250000 && (b <= 4 || (b <= 8 && L.d_pad <= 768) || (L.d_pad <= 512 && L.n >= 500000));
+}
+
 // Which decomposition of the work a look-up is planned with; the result does not depend on it.
 enum class Decomp {
     best,    // the fastest
@@ -194,7 +205,7 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
     const size_t scan_bytes = align_up(kFlagCounts * 4) + 3 * align_up((bb > 2 * kSkinnyRows ? bb : 2 * kSkinnyRows) * 4) +
                               align_up(scan_scratch_entries(b, k, ctx->num_cus) * 8);
     const bool fast = how == Decomp::best || how == Decomp::lean;
-    out->skinny = !cascade && skinny_supported(b, L.n_pad, L.d_pad, r, ctx->num_cus);
+    out->skinny = !cascade && skinny_supported(b, L.n_pad, L.d_pad, r, ctx->num_cus) && (!fast || skinny_pays(L, b));
     out->keys = false;
     out->blocks = false;
     const bool next = how == Decomp::best && block_next_pays(ctx, L, b, k);   // block minima with the further bits
