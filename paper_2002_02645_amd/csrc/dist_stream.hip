@@ -313,27 +313,31 @@ __global__ __launch_bounds__(512, 4) void dist_stream_kernel(StreamArgs p)
     wait_global_loads_le<0>();   // the refills past the end land before the workgroup gives its LDS back
 }
 
-// The tiles cut by the ends of ranges: add up the pieces, then emit.  Block (x, w): wave part w of the tile whose
-// first k-step, but not its last, lies in range x.  Its four waves take a quarter of the pieces each, in the
+// The tiles cut by the ends of ranges: add up the pieces, then emit.  Block (x, w): wave part w of tile x (BY_TILE), or of the
+// tile whose first k-step, but not its last, lies in range x, where there are fewer ranges than tiles.  (By range, tiles of
+// 2^m k-steps begin in ranges that are all on one XCD: 64 queries, 4,000 x 8,192: 48 us of a look-up of 90, which takes 50 by
+// tile; 128 inputs 8,192 -> 1,024 38 -> 20.)  Its four waves take a quarter of the pieces each, in the
 // order of the ranges, and the first adds the quarters up in order (one wave reading the 128 pieces of a
 // 32,768-value projection one after the other took 70 us).
-template <class C>
+template <class C, bool BY_TILE>
 __global__ __launch_bounds__(256) void stream_fixup_kernel(StreamArgs p)
 {
     __shared__ f32x4 part[3][C::EB * C::QB][64];
     const int nq = p.count ? *p.count : p.b;
     const int live_mt = (nq + C::BM - 1) / C::BM;
     const int64_t total = (int64_t)live_mt * p.n_tiles * p.nk;
-    const int64_t g0 = (int64_t)blockIdx.x * p.len;
-    if (g0 >= total) return;
+    const int range = BY_TILE ? (int)((int64_t)blockIdx.x * p.nk / p.len) : (int)blockIdx.x;
+    const int64_t g0 = (int64_t)range * p.len;
+    if ((BY_TILE ? (int64_t)blockIdx.x * p.nk : g0) >= total) return;
     const int64_t g1 = g0 + p.len < total ? g0 + p.len : total;
-    const int64_t tile = (g1 - 1) / p.nk;
+    const int64_t tile = BY_TILE ? (int64_t)blockIdx.x : (g1 - 1) / p.nk;
     const int64_t t0 = tile * p.nk, t1 = t0 + p.nk;
-    if (g1 == t1 || t0 < g0) return;   // uniform: the range ends with a tile, or its last tile starts earlier
+    // uniform: the tile lies in the range, or (by range) the range's last tile starts earlier
+    if (BY_TILE ? g1 >= t1 : g1 == t1 || t0 < g0) return;
     const int w = blockIdx.y, lane = threadIdx.x & 63;
     const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int we = w % C::WE, wq = w / C::WE;
-    const int pieces = (int)((t1 - 1) / p.len) - (int)blockIdx.x + 1;
+    const int pieces = (int)((t1 - 1) / p.len) - range + 1;
     f32x4 acc[C::EB][C::QB];
 #pragma unroll
     for (int i = 0; i < C::EB; ++i)
@@ -344,7 +348,7 @@ __global__ __launch_bounds__(256) void stream_fixup_kernel(StreamArgs p)
 #pragma unroll 2
     for (int n = pieces * v / 4; n < pieces * (v + 1) / 4; ++n) {
         // the first piece is its range's slot 1, the others are slot 0 of theirs
-        const f32x4 *s0 = src + ((size_t)(blockIdx.x + n) * 2 + (n == 0 ? 1 : 0)) * piece;
+        const f32x4 *s0 = src + ((size_t)(range + n) * 2 + (n == 0 ? 1 : 0)) * piece;
 #pragma unroll
         for (int i = 0; i < C::EB; ++i)
 #pragma unroll
@@ -404,7 +408,9 @@ hipError_t launch_cfg(const DistPlan &pl, const DistArgs &a, hipStream_t s)
     hipLaunchKernelGGL((dist_stream_kernel<C>), dim3((unsigned)pl.st_wgs), dim3(512), 0, s, k);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !pl.st_cut) return e;
-    hipLaunchKernelGGL((stream_fixup_kernel<C>), dim3((unsigned)pl.st_wgs, 8), dim3(256), 0, s, k);
+    const int64_t tiles = (int64_t)pl.m_tiles * pl.n_tiles;
+    if (tiles <= pl.st_wgs) hipLaunchKernelGGL((stream_fixup_kernel<C, true>), dim3((unsigned)tiles, 8), dim3(256), 0, s, k);
+    else hipLaunchKernelGGL((stream_fixup_kernel<C, false>), dim3((unsigned)pl.st_wgs, 8), dim3(256), 0, s, k);
     return hipGetLastError();
 }
 
