@@ -12,6 +12,11 @@
 namespace fz {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+// 16-byte loads of what starts on a multiple of its element's size only (rows of odd length): the memory system takes
+// them whole, where eight loads per lane of one element each fetch every line eight times over
+typedef f32x4 __attribute__((aligned(4))) f32x4_any;
+typedef u32x4 __attribute__((aligned(2))) u32x4_any;
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
@@ -50,17 +55,19 @@ __device__ __forceinline__ float block_sum_256(float v, float *scratch4)
 //
 // Column sums and sums of squares of the sampled rows in fp64: block (x, y) takes 512 columns (eight
 // per lane, so that a wave reads 1 KiB, or 2 KiB of fp32, of a row at a time) and a range of the
-// sample; its four waves take every fourth row of that range.
+// sample; its sixteen waves take every sixteenth row of that range.  What bounds it are the fp64 atomic additions that a
+// workgroup ends with (two per column): few, large workgroups.
 constexpr int kStatRows = 8192;
-__global__ __launch_bounds__(256) void col_stats_kernel(const void *entries, int dtype, int64_t n, int64_t d, int64_t d_pad,
+constexpr int kStatWaves = 16;
+__global__ __launch_bounds__(64 * kStatWaves) void col_stats_kernel(const void *entries, int dtype, int64_t n, int64_t d, int64_t d_pad,
                                                         int64_t ns, double *stats)
 {
-    __shared__ double comb[3][64][16];
+    __shared__ double comb[kStatWaves - 1][16][64], own[16][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t col = ((int64_t)blockIdx.x * 64 + lane) * 8;
     const int64_t per = (ns + gridDim.y - 1) / gridDim.y;
     const int64_t i0 = (int64_t)blockIdx.y * per, i1 = i0 + per < ns ? i0 + per : ns;
-    const bool vec = (reinterpret_cast<uintptr_t>(entries) % 16) == 0 && (dtype == 0 ? d % 4 == 0 : d % 8 == 0) && col + 8 <= d;
+    const bool vec = col + 8 <= d;
     const uint64_t step = ((uint64_t)n << 32) / (uint64_t)ns;   // ns <= 8,192, i < ns: no overflow below 2^31 rows
     double s1[8], s2[8];
 #pragma unroll
@@ -70,32 +77,32 @@ __global__ __launch_bounds__(256) void col_stats_kernel(const void *entries, int
         if (vec) {
             // whole groups of values, four rows in flight; sample i of ns is row i * n / ns (n / ns in 32.32 fixed
             // point: distinct rows, for ns <= n)
-            for (; i + 12 < i1; i += 16) {
-                f32x4 f[4][2];
-                uint4 u[4];
+            constexpr int U = 4;
+            for (; i + kStatWaves * (U - 1) < i1; i += kStatWaves * U) {
+                f32x4 f[U][2];
+                u32x4 u[U];
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const int64_t r = (int64_t)(((uint64_t)(i + 4 * t) * step) >> 32);
+                for (int t = 0; t < U; ++t) {
+                    const int64_t r = (int64_t)(((uint64_t)(i + kStatWaves * t) * step) >> 32);
                     if (dtype == 0) {
                         const float *src = reinterpret_cast<const float *>(entries) + r * d + col;
-                        f[t][0] = *reinterpret_cast<const f32x4 *>(src);
-                        f[t][1] = *reinterpret_cast<const f32x4 *>(src + 4);
+                        f[t][0] = *reinterpret_cast<const f32x4_any *>(src);
+                        f[t][1] = *reinterpret_cast<const f32x4_any *>(src + 4);
                     } else {
-                        u[t] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(entries) + r * d + col);
+                        u[t] = *reinterpret_cast<const u32x4_any *>(reinterpret_cast<const uint16_t *>(entries) + r * d + col);
                     }
                 }
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
+                for (int t = 0; t < U; ++t) {
                     float v[8];
                     if (dtype == 0) {
 #pragma unroll
                         for (int e = 0; e < 8; ++e) v[e] = f[t][e >> 2][e & 3];
                     } else {
-                        const uint32_t wv[4] = {u[t].x, u[t].y, u[t].z, u[t].w};
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            v[2 * e] = __uint_as_float(wv[e] << 16);
-                            v[2 * e + 1] = __uint_as_float(wv[e] & 0xffff0000u);
+                            v[2 * e] = __uint_as_float(u[t][e] << 16);
+                            v[2 * e + 1] = __uint_as_float(u[t][e] & 0xffff0000u);
                         }
                     }
 #pragma unroll
@@ -106,20 +113,19 @@ __global__ __launch_bounds__(256) void col_stats_kernel(const void *entries, int
                 }
             }
         }
-        for (; i < i1; i += 4) {
+        for (; i < i1; i += kStatWaves) {
             const int64_t r = (int64_t)(((uint64_t)i * step) >> 32);
             float v[8];
             if (vec && dtype == 0) {
                 const float *src = reinterpret_cast<const float *>(entries) + r * d + col;
-                const f32x4 v0 = *reinterpret_cast<const f32x4 *>(src), v1 = *reinterpret_cast<const f32x4 *>(src + 4);
+                const f32x4 v0 = *reinterpret_cast<const f32x4_any *>(src), v1 = *reinterpret_cast<const f32x4_any *>(src + 4);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     v[e] = v0[e];
                     v[4 + e] = v1[e];
                 }
             } else if (vec) {
-                const uint4 u = *reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(entries) + r * d + col);
-                const uint32_t wv[4] = {u.x, u.y, u.z, u.w};
+                const u32x4 wv = *reinterpret_cast<const u32x4_any *>(reinterpret_cast<const uint16_t *>(entries) + r * d + col);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     v[2 * e] = __uint_as_float(wv[e] << 16);
@@ -142,19 +148,24 @@ __global__ __launch_bounds__(256) void col_stats_kernel(const void *entries, int
     if (w > 0) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            comb[w - 1][lane][e] = s1[e];
-            comb[w - 1][lane][8 + e] = s2[e];
+            comb[w - 1][e][lane] = s1[e];
+            comb[w - 1][8 + e][lane] = s2[e];
+        }
+    }
+    // sum t of 16 of a lane's columns by wave t: the waves' sums in order
+    if (w == 0) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            own[e][lane] = s1[e];
+            own[8 + e][lane] = s2[e];
         }
     }
     __syncthreads();
-    if (w == 0 && col < d) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            if (col + e < d) {
-                atomicAdd(&stats[col + e], s1[e] + (comb[0][lane][e] + comb[1][lane][e] + comb[2][lane][e]));
-                atomicAdd(&stats[d_pad + col + e], s2[e] + (comb[0][lane][8 + e] + comb[1][lane][8 + e] + comb[2][lane][8 + e]));
-            }
-        }
+    const int e = w & 7;
+    if (col + e < d) {
+        double t = own[w][lane];
+        for (int u = 0; u < kStatWaves - 1; ++u) t += comb[u][w][lane];
+        atomicAdd(&stats[(w >> 3) * d_pad + col + e], t);
     }
 }
 
@@ -213,9 +224,6 @@ __global__ __launch_bounds__(256) void cache_build_kernel(const void *entries, i
     if (threadIdx.x < RB && row0 + threadIdx.x < n) labels_out[row0 + threadIdx.x] = labels_in[row0 + threadIdx.x];
     uint4 *tile_base = reinterpret_cast<uint4 *>(c_bf + tile * kTileN * d_pad);
     const int64_t chunks = d_pad / 8;
-    // rows start 16-byte aligned when the batch does and d is a multiple of 8 (bf16) or 4 (fp32):
-    // whole chunks are then fetched with 16-byte loads
-    const bool vec = (reinterpret_cast<uintptr_t>(entries) % 16) == 0 && (dtype == 0 ? d % 4 == 0 : d % 8 == 0);
     constexpr int RPW = RB / 4;   // rows per wave
     float ss[RPW];
 #pragma unroll
@@ -244,10 +252,10 @@ __global__ __launch_bounds__(256) void cache_build_kernel(const void *entries, i
                         h[e] = 0;
                         f[e] = 0.f;
                     }
-                } else if (vec && j * 8 + 8 <= d) {
+                } else if (j * 8 + 8 <= d) {
                     if (dtype == 0) {
                         const float *src = reinterpret_cast<const float *>(entries) + row * d + j * 8;
-                        const f32x4 v0 = *reinterpret_cast<const f32x4 *>(src), v1 = *reinterpret_cast<const f32x4 *>(src + 4);
+                        const f32x4 v0 = *reinterpret_cast<const f32x4_any *>(src), v1 = *reinterpret_cast<const f32x4_any *>(src + 4);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             f[e] = v0[e];
@@ -256,8 +264,7 @@ __global__ __launch_bounds__(256) void cache_build_kernel(const void *entries, i
 #pragma unroll
                         for (int e = 0; e < 8; ++e) h[e] = bf16_rne(f[e]);
                     } else {
-                        const uint4 v = *reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(entries) + row * d + j * 8);
-                        const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
+                        const u32x4 wv = *reinterpret_cast<const u32x4_any *>(reinterpret_cast<const uint16_t *>(entries) + row * d + j * 8);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             h[2 * e] = (uint16_t)(wv[e] & 0xffffu);
@@ -352,13 +359,13 @@ hipError_t launch_cache_build(const void *entries, int dtype, int64_t n, int64_t
         if ((e = launch_fill_i32(reinterpret_cast<int32_t *>(stats), 0, 4 * d_pad, s)) != hipSuccess) return e;
         const int64_t ns = n < kStatRows ? n : kStatRows;   // sampled rows
         const int64_t col_blocks = (d + 511) / 512;
-        // enough workgroups to fill the chip, but at least 128 rows each: every workgroup ends with 1,024 fp64
-        // atomic additions, and 227 per column took most of the time (8,192 x 4,104 sampled: 136 us, now 54; 8,192 x 517: 62, now 45)
-        int64_t row_chunks = 512 / col_blocks;
+        // 256 workgroups, at least 128 rows each: every workgroup ends with 1,024 fp64 atomic additions (with 512
+        // workgroups of four waves 8,192 x 517 fp32 sampled took 45 us, 25 so; 8,191 and 2,047 values of bf16 99 in the mean, 62)
+        int64_t row_chunks = 256 / col_blocks;
         if (row_chunks > (ns + 127) / 128) row_chunks = (ns + 127) / 128;
         if (row_chunks < 1) row_chunks = 1;
         if (row_chunks > 65535) row_chunks = 65535;
-        hipLaunchKernelGGL(col_stats_kernel, dim3((unsigned)col_blocks, (unsigned)row_chunks), dim3(256), 0, s, entries,
+        hipLaunchKernelGGL(col_stats_kernel, dim3((unsigned)col_blocks, (unsigned)row_chunks), dim3(64 * kStatWaves), 0, s, entries,
                            dtype, n, d, d_pad, ns, stats);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         hipLaunchKernelGGL(col_mean_kernel, dim3(1), dim3(1024), 0, s, stats, ns, d, d_pad, centre_mode, mu);
@@ -401,7 +408,6 @@ __global__ __launch_bounds__(256) void query_prep_kernel(const float *queries, c
     const int rsel = (threadIdx.x >> 2) & 1;
     const int row = row0 + rsel, rit = row % bm;
     const float *src = (row < nq) ? queries + (int64_t)(sel ? sel[row] : row) * d : nullptr;
-    const bool vec = (d % 4) == 0;     // rows are then 16-byte aligned (the batch pointer is)
     const int64_t pair_chunks = d_pad / 4;   // 16-byte chunks of the two rows together
     const int64_t per = ((pair_chunks + gridDim.y - 1) / gridDim.y + 255) / 256 * 256;   // chunks per block of the pair
     const int64_t jj_end = (blockIdx.y + 1) * per < pair_chunks ? (blockIdx.y + 1) * per : pair_chunks;
@@ -430,18 +436,19 @@ __global__ __launch_bounds__(256) void query_prep_kernel(const float *queries, c
         tile_base[tiled_chunk_offset(rit, j, bm)] = v;
     };
     int64_t jj = blockIdx.y * per + threadIdx.x;
-    // whole rows of 16-byte aligned values: four steps' loads are issued before the first is
+    // four steps' loads are issued before the first is
     // converted, so that a thread keeps 128 bytes of reads in flight
-    if (src && vec && d == d_pad) {
-        for (; jj + 3 * 256 < jj_end; jj += 4 * 256) {
+    if (src) {
+        const int64_t last = d / 8 - 1;   // whole chunks
+        for (; jj + 3 * 256 < jj_end && ((jj + 3 * 256) >> 3) * 4 + 3 <= last; jj += 4 * 256) {
             f32x4 v0[4], v1[4];
             int64_t jc[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int64_t ju = jj + u * 256;
                 jc[u] = (ju >> 3) * 4 + (ju & 3);
-                v0[u] = *reinterpret_cast<const f32x4 *>(src + jc[u] * 8);
-                v1[u] = *reinterpret_cast<const f32x4 *>(src + jc[u] * 8 + 4);
+                v0[u] = *reinterpret_cast<const f32x4_any *>(src + jc[u] * 8);
+                v1[u] = *reinterpret_cast<const f32x4_any *>(src + jc[u] * 8 + 4);
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -454,9 +461,9 @@ __global__ __launch_bounds__(256) void query_prep_kernel(const float *queries, c
         const int64_t j = (jj >> 3) * 4 + (jj & 3);   // chunk of 8 elements within the row
         const int64_t i0 = j * 8;
         float x[8];
-        if (src && vec && i0 + 8 <= d) {
-            const f32x4 v0 = *reinterpret_cast<const f32x4 *>(src + i0);
-            const f32x4 v1 = *reinterpret_cast<const f32x4 *>(src + i0 + 4);
+        if (src && i0 + 8 <= d) {
+            const f32x4 v0 = *reinterpret_cast<const f32x4_any *>(src + i0);
+            const f32x4 v1 = *reinterpret_cast<const f32x4_any *>(src + i0 + 4);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 x[e] = v0[e];
