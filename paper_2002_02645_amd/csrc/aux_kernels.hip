@@ -1904,7 +1904,7 @@ hipError_t launch_keys_finish(const FinishArgs &a, const float *keys, const uint
 //     matrix cores' additions, at most one ulp of a partial sum per k-step, the margin's floor covers.
 //     Entries outside the blocks taken have a key at or above the next minimum, and so have those that were passed over in
 //     them.  A query that fails takes R blocks, then all that were gathered (up to 64), then up to 256.
-//  5. The 256 are selected anew and re-scored whole.  The first kMeetQueries queries that get here leave that to the
+//  5. The 256 are selected anew and re-scored like the first ones.  The first kMeetQueries queries that get here leave that to the
 //     follow-up kernel, where sixteen workgroups share each: that is all of them on most inputs, and a single workgroup would
 //     be the last to finish by far.  With more (duplicates, neighbours closer than the key's error) the chip is busy
 //     anyway, and each goes on here.
@@ -2247,7 +2247,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
     __shared__ uint64_t kth_s;
     __shared__ int list_n, near_n, open_n, distinct_s, verdict_s, flagged_s;
     __shared__ float others_s[RMAX];                  // bound of the keys of a block's other entries; +inf: re-scored too
-    __shared__ uint8_t at_s[RMAX];                    // which of a block's entries has the smallest key
+    __shared__ uint8_t at_s[kTier1];                  // which of a block's entries has the smallest key; step 5: 8 more, all of them
     __shared__ uint16_t work_s[RMAX * 9];             // slots to re-score
     const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2543,13 +2543,44 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
                 const int all = got < kTier1 ? got : kTier1;
                 constexpr int CH = 16, STEP = 64;   // blocks between two merges, and between two certificates
                 if (tid < kMaxK) best_s[tid] = kSentinel;
+                if constexpr (NEXT) {
+                    // all eight where the others may come before what is left out of the `all` blocks
+                    const uint32_t nxt = got > all ? (uint32_t)(list[all] >> 32) : 0xffffffffu, out = tk < nxt ? tk : nxt;
+                    const float outf = out >= kInf ? inf : from_ordered_bits(out);
+                    for (int i = tid; i < all; i += NT) {
+                        const uint32_t next = ba.bnext[(size_t)q * ba.nb + (uint32_t)list[i]];
+                        const float others = block_others(from_ordered_bits((uint32_t)(list[i] >> 32)), next);
+                        at_s[i] = (uint8_t)((next & 7u) | (others >= outf ? 0u : 8u));
+                    }
+                }
                 for (int from = 0;;) {
                     const int end = from + STEP < all ? from + STEP : all;
                     for (int c0 = from; c0 < end; c0 += CH) {
-                        if (tid == 0) near_n = 0;
+                        if (tid == 0) near_n = open_n = 0;
                         __syncthreads();
                         const uint64_t tau = best_s[a.k - 1];
-                        for (int b = c0 + w; b < c0 + CH && b < end; b += NW) {
+                        if constexpr (NEXT) {
+                            if (tid < CH && c0 + tid < end) {
+                                const int b = c0 + tid, at = at_s[b], m = at & 8 ? 8 : 1;
+                                const int pos = atomicAdd(&open_n, m);
+                                for (int e = 0; e < m; ++e) work_s[pos + e] = (uint16_t)(b * 8 + (m == 8 ? e : at));
+                            }
+                            __syncthreads();
+                            const int work = __builtin_amdgcn_readfirstlane(open_n);   // <= 8 CH
+                            for (int g0 = 8 * w; g0 < work; g0 += 8 * NW) {
+                                auto slot = [&](int j) { return (int)work_s[g0 + j < work ? g0 + j : work - 1]; };
+                                auto entry = [&](int j) { return entry_of(slot(j)); };
+                                ListRows<decltype(entry)> rows{entry, {}};
+#pragma unroll
+                                for (int j = 0; j < 8; ++j) rows.first[j] = __builtin_amdgcn_readfirstlane(entry(j));
+                                const uint64_t x = rescore_rows8(a, qrow, rows, lane);
+                                if ((lane & 7) == 0 && g0 + (lane >> 3) < work) {
+                                    if (x < tau) ent[atomicAdd(&near_n, 1)] = x;
+                                    const int sl = slot(lane >> 3), b = sl >> 3;
+                                    if ((sl & 7) == (at_s[b] & 7)) sdist_s[b] = from_ordered_bits((uint32_t)(x >> 32));
+                                }
+                            }
+                        } else for (int b = c0 + w; b < c0 + CH && b < end; b += NW) {
                             const uint64_t x =
                                 rescore_rows8(a, qrow, BlockRows{block_first_entry(__builtin_amdgcn_readfirstlane((int)(uint32_t)list[b]))}, lane);
                             if ((lane & 7) == 0 && x < tau) ent[atomicAdd(&near_n, 1)] = x;   // <= 8 CH
@@ -2571,7 +2602,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
                         }
                         __syncthreads();
                     }
-                    for (int b = from + w * 4; b < end; b += 4 * NW) {
+                    for (int b = from + w * 4; !NEXT && b < end; b += 4 * NW) {
                         const float dot = coarse_dot4(a, ba.mu, qrow, sidx_s, b, end, lane);
                         const int bj = b + (lane >> 4);
                         if ((lane & 15) == 0 && bj < end)
@@ -2596,8 +2627,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
                     }
                     __syncthreads();
                     const uint32_t out = tk >= kInf ? 0xffffffffu : tk, nxt = got > end ? (uint32_t)(list[end] >> 32) : 0xffffffffu;
-                    ok = __builtin_amdgcn_readfirstlane((int)certificate(samp_s, sdist_s, end, dsel_s[a.k - 1], nxt < out ? nxt : out,
-                                                                         distinct_s, tid, &verdict_s, 4.0 + 2.0 * ba.nk)) != 0;
+                    ok = __builtin_amdgcn_readfirstlane((int)certificate(NEXT ? list : samp_s, sdist_s, end, dsel_s[a.k - 1], nxt < out ? nxt : out,
+                                                                         distinct_s, tid, &verdict_s, NEXT ? 4.0 : 4.0 + 2.0 * ba.nk)) != 0;
                     if (ok || end >= all) break;   // uniform
                     from = end;
                     __syncthreads();

@@ -57,3 +57,33 @@ def test_near_entries_share_blocks(n, d, copies, noise, k, dtype):
     lab = torch.randint(0, 10, (ent.shape[0],), generator=g, dtype=torch.int32)
     q = base[torch.randint(0, n // copies, (300,), generator=g)] + 0.3 * torch.randn(300, d, generator=g)
     check_case(ent, lab, q, 10, k, max(1, k - 3))
+
+
+@pytest.mark.parametrize("n,d,copies,k,dtype", [
+    (4200, 512, 21, 10, torch.bfloat16),     # ten of 21 equal entries in 21 blocks: too few distances for a certificate in 64 blocks
+    (4200, 1024, 21, 20, torch.float32),
+    (2600, 4096, 13, 10, torch.bfloat16),
+    (4200, 512, 21, 64, torch.bfloat16),
+])
+def test_copies_in_many_blocks(n, d, copies, k, dtype):
+    """Every query needs the 256 blocks with the smallest keys, and more queries than the follow-up takes."""
+    g = torch.Generator().manual_seed(n + d + k)
+    ent = torch.randn(n // copies, d, generator=g).repeat(copies, 1).to(dtype)
+    lab = torch.randint(0, 10, (n,), generator=g, dtype=torch.int32)
+    q = torch.randn(1100 if d == 4096 else 300, d, generator=g)
+    some = torch.arange(0, q.shape[0], 5)
+    fc = binding.FreezeCache(1)
+    try:
+        counters = torch.zeros(3, dtype=torch.int64, device="cuda")
+        binding.freeze_lookup_stats_attach(fc.ctx, counters)
+        fc.build_layer(0, ent.cuda(), lab.cuda(), 10)
+        out = fc.lookup(0, q.cuda(), k, 1)
+        torch.cuda.synchronize()
+        got = {key: v.cpu().numpy()[some.numpy()] for key, v in out.items()}
+        c = counters.tolist()
+    finally:
+        fc.close()
+    e_h, l_h, q_h = _host_entries(ent), lab.numpy(), q[some].numpy()
+    ref = parity.oracle_reference(q_h, e_h, l_h, 10, k, 1)
+    parity.assert_lookup_matches(got, ref, q_h, e_h, l_h, 10, k, 1, rel=1e-5, dist_rel=1e-5)
+    assert sum(c) == q.shape[0] and c[1] + c[2] > 32, c
