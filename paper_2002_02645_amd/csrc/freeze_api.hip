@@ -176,8 +176,10 @@ constexpr int kStreamRows = 128;
 //   2,000 x 512 30, 25 / 35, 25 us; 30,000 x 1,024 55, 31 / 61, 31; 100,000 x 512 42, 35 / 48, 36;
 //   300,000 x 512 75, 81 / 86, 82; 1,000,000 x 512 183, 223 / 196, 223; 1,000,000 x 1,024 341, 408 / 807, 407
 //   (eight queries 799, 407; eight of 700 values 248).
+// Rows of fewer than 193 values were not measured and stay with it.
 bool skinny_pays(const LayerCache &L, int64_t b)
 {
+    if (L.d_pad < 256) return true;
     return L.n >= 250000 && (b <= 4 || (b <= 8 && L.d_pad <= 768) || (L.d_pad <= 512 && L.n >= 500000));
 }
 
