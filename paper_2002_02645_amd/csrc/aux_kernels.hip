@@ -2360,9 +2360,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
     const float *qrow = a.queries + (int64_t)(a.sel ? a.sel[q] : q) * a.d;
     // slot 8 b + e: entry e of block b of the list
     auto entry_of = [&](int slot) { return block_first_entry((int)(uint32_t)list[slot >> 3]) + (slot & 3) + (slot >> 2 & 1) * 16; };
-    if (!NEXT) {
-        if (tid < RMAX) others_s[tid] = __builtin_nanf("");
-    } else if (tid < RMAX && tid < cnt) {
+    if (NEXT && tid < RMAX && tid < cnt) {
         const uint32_t next = ba.bnext[(size_t)q * ba.nb + (uint32_t)list[tid]];
         others_s[tid] = block_others(from_ordered_bits((uint32_t)(list[tid] >> 32)), next);
         at_s[tid] = (uint8_t)(next & 7u);
@@ -2382,50 +2380,57 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
             excl = nxt < excl ? nxt : excl;
         }
         const float exclf = excl >= kInf ? inf : from_ordered_bits(excl);
-        if (tid == 0) open_n = 0;
-        for (int i = done * 8 + tid; i < nblk * 8; i += NT) ent[i] = kSentinel;
-        __syncthreads();
         // ---- 2. exact re-scoring: of blocks [done, nblk) the entry with the smallest key; of blocks whose other entries
-        // may come before what is left out, all of them ----
-        if (tid < nblk) {
-            if (NEXT && tid >= done) {
-                work_s[tid - done] = (uint16_t)(tid * 8 + at_s[tid]);
-                sidx_s[tid] = entry_of(tid * 8 + at_s[tid]);
-            }
-            if (!(others_s[tid] >= exclf)) {   // (also no number)
-                const int at = (NEXT ? nblk - done : 0) + 8 * atomicAdd(&open_n, 1);
+        // may come before what is left out, all of them.  Packed (distance, index) by slot ----
+        if constexpr (NEXT) {
+            if (tid == 0) open_n = 0;
+            for (int i = done * 8 + tid; i < nblk * 8; i += NT) ent[i] = kSentinel;
+            __syncthreads();
+            if (tid < nblk) {
+                if (tid >= done) {
+                    work_s[tid - done] = (uint16_t)(tid * 8 + at_s[tid]);
+                    sidx_s[tid] = entry_of(tid * 8 + at_s[tid]);
+                }
+                if (!(others_s[tid] >= exclf)) {   // (also no number)
+                    const int at = nblk - done + 8 * atomicAdd(&open_n, 1);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) work_s[at + e] = (uint16_t)(tid * 8 + e);
-                others_s[tid] = inf;   // done with
+                    for (int e = 0; e < 8; ++e) work_s[at + e] = (uint16_t)(tid * 8 + e);
+                    others_s[tid] = inf;   // done with
+                }
             }
-        }
-        __syncthreads();
-        const int work = __builtin_amdgcn_readfirstlane((NEXT ? nblk - done : 0) + 8 * open_n);
-        for (int c0 = 8 * w; c0 < work; c0 += 8 * NW) {
-            auto slot = [&](int j) { return (int)work_s[c0 + j < work ? c0 + j : work - 1]; };
-            auto entry = [&](int j) { return entry_of(slot(j)); };
-            ListRows<decltype(entry)> rows{entry, {}};
+            __syncthreads();
+            const int work = __builtin_amdgcn_readfirstlane(nblk - done + 8 * open_n);
+            for (int c0 = 8 * w; c0 < work; c0 += 8 * NW) {
+                auto slot = [&](int j) { return (int)work_s[c0 + j < work ? c0 + j : work - 1]; };
+                auto entry = [&](int j) { return entry_of(slot(j)); };
+                ListRows<decltype(entry)> rows{entry, {}};
 #pragma unroll
-            for (int j = 0; j < 8; ++j) rows.first[j] = __builtin_amdgcn_readfirstlane(entry(j));
-            const uint64_t x = rescore_rows8(a, qrow, rows, lane);
-            if ((lane & 7) == 0) ent[slot(lane >> 3)] = x;
+                for (int j = 0; j < 8; ++j) rows.first[j] = __builtin_amdgcn_readfirstlane(entry(j));
+                const uint64_t x = rescore_rows8(a, qrow, rows, lane);
+                if ((lane & 7) == 0) ent[slot(lane >> 3)] = x;
+            }
+        } else {
+            for (int b = done + w; b < nblk; b += NW) {
+                uint64_t x = rescore_rows8(a, qrow, BlockRows{block_first_entry(__builtin_amdgcn_readfirstlane((int)(uint32_t)list[b]))}, lane);
+                if ((lane & 7) == 0) ent[b * 8 + (lane >> 3)] = x;
+                x = block_nearest(x);   // the certificate's sample
+                if (lane == 0) {
+                    // (a block that was taken holds a real entry; the marker only with non-finite inputs)
+                    sidx_s[b] = (uint32_t)x < (uint32_t)a.n ? (int32_t)(uint32_t)x : 0;
+                    sdist_s[b] = from_ordered_bits((uint32_t)(x >> 32));
+                }
+            }
         }
         if (tid == 0) {
             distinct_s = 0;
             near_n = 0;
         }
         __syncthreads();
-        if (tid >= done && tid < nblk) {   // the certificate's samples
-            uint64_t x = ent[tid * 8 + (NEXT ? at_s[tid] : 0)];
-            if (!NEXT) {   // the nearest entry; its key is formed again below
-#pragma unroll
-                for (int e = 1; e < 8; ++e) x = ent[tid * 8 + e] < x ? ent[tid * 8 + e] : x;
-                // (a block that was taken holds a real entry; the marker only with non-finite inputs)
-                sidx_s[tid] = (uint32_t)x < (uint32_t)a.n ? (int32_t)(uint32_t)x : 0;
-            }
-            sdist_s[tid] = from_ordered_bits((uint32_t)(x >> 32));
+        if constexpr (NEXT) {
+            if (tid >= done && tid < nblk)   // the certificate's samples
+                sdist_s[tid] = from_ordered_bits((uint32_t)(ent[tid * 8 + at_s[tid]] >> 32));
+            __syncthreads();
         }
-        __syncthreads();
 
         // ---- 3. the k nearest ----
         // The k-th smallest of the blocks' nearest distances bounds the k-th neighbour: usually a few more

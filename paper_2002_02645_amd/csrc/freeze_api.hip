@@ -122,6 +122,15 @@ int lists_per_query(const DistPlan &pl, bool device_count)
     return pl.bal_f > 0 ? pl.bal_lists : pl.n_splits;
 }
 
+// Rows beyond the first of blocks that are re-scored whole although it is known where their smallest keys lie: a block holds
+// another of the m nearest with probability m / blocks (10,000 queries x 200 centres of 8,192 values, k = 1: 25 blocks in
+// all; 0.94 ms to finish with block minima).
+double whole_block_rows(const LayerCache &L, int64_t b, int k)
+{
+    const double m = k + 2 > 8 ? k + 2 : 8, blocks = ((double)L.n + 7.0) / 8.0;
+    return (double)b * 7.0 * m * (m < blocks ? m / blocks : 1.0);
+}
+
 // Whether a block leaves where its smallest key lies and a bound of the other seven, so that one row of it is
 // re-scored in place of eight: 2.4 us per tile of a workgroup, and a quarter more to write, against the rows (4,096 x 50,000 x
 // 512, k = 10: 31 us more in the matrix kernel, 75 less in the finishing one; 600 x 1,000,000 x 512: 100 more, 10 less).
@@ -130,7 +139,7 @@ bool block_next_pays(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int 
     const double tiles = (double)((b + 255) / 256) * (double)(L.n_pad / kTileN);
     const double row = (double)L.d_pad * (L.entries_dtype == FREEZE_F32 ? 4.0 : 2.0);
     const double per_us = (double)L.n * row <= 16e6 ? 8e6 : 5.3e6;
-    const double rows = (double)b * 7.0 * (k + 2 > 8 ? k + 2 : 8) * row / per_us;
+    const double rows = ((double)b * 7.0 * (k + 2 > 8 ? k + 2 : 8) - whole_block_rows(L, b, k)) * row / per_us;
     return 2.4 * (1.0 + (double)(int64_t)(tiles / ctx->num_cus)) < rows;
 }
 
@@ -158,8 +167,12 @@ bool block_route(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, i
     const double row = (double)L.d_pad * (L.entries_dtype == FREEZE_F32 ? 4.0 : 2.0);
     // (all eight rows of a block where one is not known to do: longer ones lose too much)
     if (!next && L.d_pad > 3072) return false;
+    // (few neighbours of few entries: eight samples often do not confirm, and then nearly all blocks are taken.  3,000 x 400 x
+    // 8,192, k = 1: 296 us with lists, 611 with blocks; 2,000 x 300 x 8,192, k = 5 goes the other way, 272, 238, and so does
+    // 2,000 x 2,000 x 4,096, k = 1: 183, 147)
+    if (L.d_pad > 3072 && k < 5 && L.n < 1024) return false;
     const double per_us = (double)L.n * row <= 16e6 ? 8e6 : 5.3e6;
-    const double rows = next ? (L.d_pad > 4096 ? (double)b * (k + 2) * row * (double)L.d_pad / 3e14 : 0.0)
+    const double rows = next ? (L.d_pad > 4096 ? (double)b * (k + 2) * row * (double)L.d_pad / 3e14 : 0.0) + whole_block_rows(L, b, k) * row / per_us
                              : (double)b * 8.0 * (k + 2 > 8 ? k + 2 : 8) * row / per_us;
     return 20.0 + matrix / (r <= 16 ? 12.0 : 24.0) + minima + rows < lists;
 }
