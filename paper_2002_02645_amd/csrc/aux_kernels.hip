@@ -984,6 +984,7 @@ __device__ __forceinline__ int gather_entries(const FinishArgs &a, int q, int nq
 struct FinishKernelArgs {
     FinishArgs a;
     int sort_cap;   // power of two >= the largest number of entries gathered per query (LDS allocation)
+    int m_first;    // candidates re-scored at first (first_width)
 };
 
 // Exactness certificate of the bf16 pre-filter, by the first wave of the block (every thread
@@ -1104,7 +1105,7 @@ __global__ __launch_bounds__(NT, NT == 256 ? 4 : 1) void finish_kernel(FinishKer
     const float *qrow = a.queries + (int64_t)(a.sel ? a.sel[q] : q) * a.d;
     // the others are re-scored only when the certificate over the first ones, which then counts them among the
     // excluded entries, does not confirm the result (first_width)
-    const int m_first = first_width(a, true);
+    const int m_first = fa.m_first;
 
     for (int c = tid; c < r; c += NT) {
         // With finite inputs every one of the first r entries is a real cache row.  Non-finite
@@ -1118,14 +1119,14 @@ __global__ __launch_bounds__(NT, NT == 256 ? 4 : 1) void finish_kernel(FinishKer
     // 2. exact fp32 re-scoring: each wave takes a group of candidates and needs no block barrier
     if (a.d >= 4096 && a.d % 8 == 0) {
         // long activations: the whole block per candidate, the query row read once
-        if (m_first <= 16) {
+        if (r <= 16) {
             rescore_block_all<NT, 16, true>(a, qrow, idx_s, dist_s, red, m_first, tid);
-        } else if (m_first <= 32) {
+        } else if (r <= 32) {
             rescore_block_all<NT, 32, true>(a, qrow, idx_s, dist_s, red, m_first, tid);
         } else {
             // (two passes of 32: 64 accumulators per thread spill, and the pass is 8 % slower for it)
-            rescore_block_all<NT, 32>(a, qrow, idx_s, dist_s, red, 32, tid);
-            rescore_block_all<NT, 32>(a, qrow, idx_s + 32, dist_s + 32, red, m_first - 32, tid);
+            for (int c0 = 0; c0 < m_first; c0 += 32)
+                rescore_block_all<NT, 32>(a, qrow, idx_s + c0, dist_s + c0, red, m_first - c0 < 32 ? m_first - c0 : 32, tid);
         }
     } else if (tid < 256) {   // short activations: four waves, one group of candidates each
         if (r <= 16)
@@ -1148,8 +1149,7 @@ __global__ __launch_bounds__(NT, NT == 256 ? 4 : 1) void finish_kernel(FinishKer
         const uint32_t nxt = (uint32_t)(ent[m_first] >> 32);   // (real >= r > m_first with finite inputs; else the marker)
         ok = certificate(ent, dist_s, m_first, dsel_s[a.k - 1], nxt < excl_s ? nxt : excl_s, distinct_s, tid, &verdict_s);
         if (!ok) {   // uniform
-            for (int c0 = m_first; c0 < r; c0 += 16)
-                rescore_block_all<NT, 16, true>(a, qrow, idx_s + c0, dist_s + c0, red, r - c0 < 16 ? r - c0 : 16, tid);
+            rescore_block_all<NT, 16, true>(a, qrow, idx_s + m_first, dist_s + m_first, red, r - m_first, tid);
             if (tid == 0) distinct_s = 0;
             __syncthreads();
         }
@@ -2686,7 +2686,9 @@ hipError_t launch_finish(const FinishArgs &a, hipStream_t s)
     const int total = a.alloc_splits * a.r;   // (candidate lists with a count are keys_finish_kernel's)
     if (a.part_count || total > kMaxMergeEntries || a.r > kMaxRescore || a.k > kMaxK || a.k > a.r) return hipErrorInvalidValue;
     if (!a.flag_count || !a.flag_list || !a.flag_list2) return hipErrorInvalidValue;
-    FinishKernelArgs fa{a, 2};
+    // (the second step takes sixteen candidates at most: a loop there costs the whole kernel registers)
+    const int first = first_width(a, true);
+    FinishKernelArgs fa{a, 2, first > a.r - 16 ? first : a.r - 16};
     while (fa.sort_cap < total) fa.sort_cap <<= 1;
     const size_t lds = (size_t)fa.sort_cap * sizeof(uint64_t);
     // a block per query: with few queries and long activations use 1024-thread blocks
