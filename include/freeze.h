@@ -104,8 +104,8 @@ int freeze_cache_build(freeze_ctx *ctx, int layer, const void *entries, int entr
 int freeze_set_centring(freeze_ctx *ctx, int mode);
 
 /* Bytes of workspace with which freeze_lookup runs a batch of b queries at full speed. 0 on invalid
- * arguments.  The keys or block minima of a batch (4,096 queries against 300,000 x 512 entries: 0.6 GiB; minima take
- * 2 GiB at most) and the accumulators of tiles that several workgroups share lie in it, and a smaller batch
+ * arguments.  The keys or block minima of a batch (4,096 queries against 300,000 x 512 entries: 0.9 GiB; minima take
+ * 3 GiB at most) and the accumulators of tiles that several workgroups share lie in it, and a smaller batch
  * may ask for more than a larger one (50,000 x 8,192: 1,024 queries 546 MiB, 10,000 queries 171 MiB).  The look-up takes a smaller workspace too as long as a slower
  * decomposition of the same work fits it (candidate lists, tiles of one workgroup each; the results are the
  * same), and else returns FREEZE_EWORKSPACE. */
