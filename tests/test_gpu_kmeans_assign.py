@@ -111,3 +111,37 @@ def test_points_that_are_no_numbers():
     hit = ~np.isfinite(got).all(axis=1)                               # centres that took one of the three
     assert hit.sum() <= 3
     np.testing.assert_allclose(got[~hit], exp[~hit], rtol=1e-6, atol=1e-7)
+
+
+@pytest.mark.parametrize("n,d,kc,shape", [
+    (32768, 65536, 512, "constant"),      # two tiles of centres, as many tiles as CUs: a sum runs over the whole row
+    (16384, 65536, 100, "constant"),      # ... over a quarter of it
+    (32768, 65536, 300, "blocks"),        # runs of equal values, every other run small: sums that grow evenly too
+    (66000, 16384, 60, "constant"),
+])
+def test_rows_whose_sums_round_one_way(n, d, kc, shape):
+    # The addends of a point's sums are all alike, so within a binade every addition rounds the same way and the errors
+    # of a key add up over the row's length.  Centres close together in value: keys that are off by that are wrong.  With the
+    # index of its nearest centre as every point's label, clusters that took no other points have a share of exactly 1.
+    g = torch.Generator().manual_seed(n + d + kc)
+    cval = torch.sort(0.5 + 1.5 * torch.rand(kc, generator=g, dtype=torch.float64))[0].float().double()
+    gap = torch.minimum(torch.diff(cval, prepend=cval[:1] - 1), torch.diff(cval, append=cval[-1:] + 1))
+    want = torch.randint(0, kc, (n,), generator=g)
+    want[:kc] = torch.arange(kc)
+    # at most 0.4 of the way to the next centre: squared distances 1 : 2.25 at least, where fp32 ones are good to 1e-3
+    pval = (cval[want] + gap[want] * 0.8 * (torch.rand(n, generator=g, dtype=torch.float64) - 0.5)).float()
+    keep = torch.ones(d, device="cuda")
+    if shape == "blocks":
+        keep = 1.0 - 0.9375 * ((torch.arange(d, device="cuda") // 512) % 2).float()
+    pts = torch.empty(n, d, device="cuda")
+    torch.mul(pval.cuda()[:, None], keep[None, :], out=pts)
+    cen = cval.float().cuda()[:, None] * keep[None, :]
+    fc = binding.FreezeCache(1)
+    try:
+        got = fc.build_kmeans_layer(0, pts, want.to(torch.int32).cuda(), kc, cen.contiguous(), 0)
+        torch.cuda.synchronize()
+        share, label = got["fraction"].cpu(), got["majority"].cpu()
+    finally:
+        fc.close()
+    wrong = (share != 1.0) | (label != torch.arange(kc))
+    assert not wrong.any(), (int(wrong.sum()), share[wrong][:5], torch.nonzero(wrong)[:5, 0])
