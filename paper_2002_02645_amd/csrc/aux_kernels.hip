@@ -1895,7 +1895,7 @@ hipError_t launch_keys_finish(const FinishArgs &a, const float *keys, const uint
 //     matrix kernel has left that (NEXT), and all eight where the bound of the others' keys lies under the smallest key that is
 //     left out (two of the nearest in one block; no lead, i.e. equal keys).  Without it, all eight of every block.  Eight rows
 //     in flight per lane, and one transposed reduction for the eight sums (ten shuffles instead of 48).  Same order of
-//     additions as in the other kernels, for rows of any length, hence the same distances bit for bit.
+//     additions as in the other kernels (rescore_rows8), hence the same distances bit for bit.
 //  3. The k nearest by (distance, index).
 //  4. The certificate.  Its samples are the blocks' smallest keys and the distances of the entries that have them (NEXT).
 //     Without NEXT it is not known which that is: the coarse key of
@@ -1970,8 +1970,9 @@ struct ListRows {
 };
 
 // Exact distances of the eight entries rows(0 .. 7), by one wave: the packed (distance, index) of row lane >> 3 in every
-// lane, the marker where that is no entry.  Same order of additions as in the other kernels for rows of any length:
-// rescore_block_all<256, .>'s four waves' chains, one after the other, from 4,096 on, rescore_wave's else.
+// lane, the marker where that is no entry.  Same order of additions as in the other kernels for rows of any length (the
+// longest of few queries, wide_order, do not come here): rescore_block_all<256, .>'s four waves' chains, one after the other,
+// from 4,096 on, rescore_wave's else.
 template <class Rows>
 __device__ __forceinline__ uint64_t rescore_rows8(const FinishArgs &a, const float *qrow, const Rows &rows, int lane)
 {
@@ -2692,7 +2693,7 @@ hipError_t launch_finish(const FinishArgs &a, hipStream_t s)
     while (fa.sort_cap < total) fa.sort_cap <<= 1;
     const size_t lds = (size_t)fa.sort_cap * sizeof(uint64_t);
     // a block per query: with few queries and long activations use 1024-thread blocks
-    if (a.b <= 1024 && a.d >= 16384 && a.d % 8 == 0)
+    if (wide_order(a.b, a.d))
         hipLaunchKernelGGL((finish_kernel<1024>), dim3((unsigned)a.b), dim3(1024), lds, s, fa);
     else
         hipLaunchKernelGGL((finish_kernel<256>), dim3((unsigned)a.b), dim3(256), lds, s, fa);

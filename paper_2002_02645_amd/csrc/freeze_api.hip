@@ -158,6 +158,9 @@ bool block_route(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, i
 {
     // 1.5 GiB of minima at most (3 with the padding of the last query tile); longer rows than measured
     if (b * L.n_pad > (int64_t)1 << 31 || L.d_pad > 16384) return false;
+    // The other finishing kernels add up the longest rows' distances by all 1,024 threads for up to 1,024 queries
+    // (wide_order), the kernel of this route in the order of four waves: a result must not depend on the route.
+    if (wide_order(b, L.d)) return false;
     // (600 x 250,000 x 3,000: 1,011 us with lists, 1,091 with blocks)
     if (L.d_pad > 2048 && L.n_pad * L.d_pad * 2 > (int64_t)512 << 20 && b <= 1280) return false;
     const double tiles = (double)((b + 255) / 256) * (double)(L.n_pad / kTileN);

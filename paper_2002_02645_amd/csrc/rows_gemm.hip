@@ -467,7 +467,7 @@ constexpr int kPickPoints = 4;   // points per wave
 
 // fp32 distances of point row q to the m centres cand_s, by 256 threads, in the order of additions that the look-ups'
 // re-scoring has for rows of this length (rescore_block_all<256, .> and rescore_wave): whoever assigns a point, nearly equal
-// distances compare alike.
+// distances compare alike.  (Not always those of up to 1,024 points of 16,384 values and more: see wide_order.)
 __device__ inline void exact_distances(const float *q, const float *centers, int64_t d, const int32_t *cand_s, int m, float *dist_s, float *red_s, int tid)
 {
     const int lane = tid & 63, w = tid >> 6;

@@ -79,6 +79,7 @@ def test_buffer_sized_for_the_full_batch_serves_the_last(n, d, dtype, full, last
     (50000, 2048, 64, 10, 0, torch.bfloat16),    # cut tiles -> whole tiles, 64 queries per tile
     (36000, 2080, 200, 10, 64, torch.float32),   # ... of the 256-query kernel
     (300, 40, 1, 1, 0, torch.float32),
+    (700, 16384, 900, 10, 0, torch.bfloat16),    # the longest rows, whose distances 1,024 threads add up on every route
 ])
 def test_smaller_buffers_give_the_same_result_or_are_refused(n, d, b, k, r, dtype):
     L, q = _layer(n, d, b, k, dtype, 23 + n)
@@ -105,7 +106,7 @@ def test_smaller_buffers_give_the_same_result_or_are_refused(n, d, b, k, r, dtyp
             _equal(got, want)
             assert ws.intact()
             served += 1
-            size -= max(256, size // 6)
+            size -= max(256, size // (256 if d == 16384 else 6))   # (there the routes' buffers differ by little)
         assert served >= 1
     finally:
         fc.close()
