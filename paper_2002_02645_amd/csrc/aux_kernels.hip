@@ -2247,9 +2247,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
     __shared__ int32_t nearest_s;
     __shared__ uint64_t kth_s;
     __shared__ int list_n, near_n, open_n, distinct_s, verdict_s, flagged_s;
-    __shared__ float others_s[RMAX];                  // bound of the keys of a block's other entries; +inf: re-scored too
+    __shared__ float others_s[RMAX];                  // bound of the keys of a block's other entries; +inf: they have been re-scored, too
     __shared__ uint8_t at_s[kTier1];                  // which of a block's entries has the smallest key; step 5: 8 more, all of them
-    __shared__ uint16_t work_s[RMAX * 9];             // slots to re-score
+    __shared__ uint16_t work_s[RMAX * 8];             // slots to re-score
     const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (a.count && q >= *a.count) return;   // uniform
@@ -2384,23 +2384,27 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
         // ---- 2. exact re-scoring: of blocks [done, nblk) the entry with the smallest key; of blocks whose other entries
         // may come before what is left out, all of them.  Packed (distance, index) by slot ----
         if constexpr (NEXT) {
-            if (tid == 0) open_n = 0;
             for (int i = done * 8 + tid; i < nblk * 8; i += NT) ent[i] = kSentinel;
             __syncthreads();
-            if (tid < nblk) {
-                if (tid >= done) {
-                    work_s[tid - done] = (uint16_t)(tid * 8 + at_s[tid]);
-                    sidx_s[tid] = entry_of(tid * 8 + at_s[tid]);
+            if (w == 0) {   // a lane per block (RMAX of them at most); first the blocks of which one entry does
+                const bool fresh = lane >= done && lane < nblk, open = lane < nblk && !(others_s[lane] >= exclf);   // (also no number)
+                const uint64_t ones = __ballot(fresh && !open), wholes = __ballot(open), below = (1ull << lane) - 1ull;
+                const int base = __builtin_popcountll(ones);
+                if (fresh) {
+                    const int slot = lane * 8 + at_s[lane];
+                    sidx_s[lane] = entry_of(slot);
+                    if (!open) work_s[__builtin_popcountll(ones & below)] = (uint16_t)slot;
                 }
-                if (!(others_s[tid] >= exclf)) {   // (also no number)
-                    const int at = nblk - done + 8 * atomicAdd(&open_n, 1);
+                if (open) {
+                    const int at = base + 8 * __builtin_popcountll(wholes & below);
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) work_s[at + e] = (uint16_t)(tid * 8 + e);
-                    others_s[tid] = inf;   // done with
+                    for (int e = 0; e < 8; ++e) work_s[at + e] = (uint16_t)(lane * 8 + e);
+                    others_s[lane] = inf;   // done with
                 }
+                if (lane == 0) open_n = base + 8 * __builtin_popcountll(wholes);
             }
             __syncthreads();
-            const int work = __builtin_amdgcn_readfirstlane(nblk - done + 8 * open_n);
+            const int work = __builtin_amdgcn_readfirstlane(open_n);
             for (int c0 = 8 * w; c0 < work; c0 += 8 * NW) {
                 auto slot = [&](int j) { return (int)work_s[c0 + j < work ? c0 + j : work - 1]; };
                 auto entry = [&](int j) { return entry_of(slot(j)); };
@@ -2515,7 +2519,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
         if (flagged < kMeetQueries) {
             if (tid == 0) a.flag_list[flagged] = q;   // (and counted in the statistics there)
         } else {
-            // ---- 5. the 256 blocks with the smallest minima, all their entries ----
+            // ---- 5. the 256 blocks with the smallest minima; the first nblk of them are done ----
             // T = the kTier1-th smallest of kBlkList group minima: at least that many blocks (or all) are <= T
             auto minimum = [&](int64_t blk) { return ((uint64_t)ordered_bits(bq[blk]) << 32) | (uint32_t)blk; };
             for (int g = tid; g < kBlkList; g += NT) {
@@ -2547,29 +2551,34 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
                 __syncthreads();
                 bitonic_sort_lds(list, n2, tid, NT);
                 const int all = got < kTier1 ? got : kTier1;
-                constexpr int CH = 16, STEP = 64;   // blocks between two merges, and between two certificates
-                if (tid < kMaxK) best_s[tid] = kSentinel;
+                // blocks between two merges, and between two certificates (NEXT: mostly one row each)
+                constexpr int CH = NEXT ? 64 : 16, STEP = 64;
+                static_assert(8 * CH + kMaxK <= RMAX * 16 && CH <= RMAX && CH <= NT, "ent, work_s");
                 if constexpr (NEXT) {
-                    // all eight where the others may come before what is left out of the `all` blocks
+                    // all eight where the others may come before what is left out of the `all` blocks (of the first nblk: all but
+                    // the one that has been re-scored, where the others have not)
                     const uint32_t nxt = got > all ? (uint32_t)(list[all] >> 32) : 0xffffffffu, out = tk < nxt ? tk : nxt;
                     const float outf = out >= kInf ? inf : from_ordered_bits(out);
                     for (int i = tid; i < all; i += NT) {
                         const uint32_t next = ba.bnext[(size_t)q * ba.nb + (uint32_t)list[i]];
                         const float others = block_others(from_ordered_bits((uint32_t)(list[i] >> 32)), next);
-                        at_s[i] = (uint8_t)((next & 7u) | (others >= outf ? 0u : 8u));
+                        const bool whole = !(others >= outf) && !(i < nblk && others_s[i] == inf);
+                        at_s[i] = (uint8_t)((next & 7u) | (whole ? 8u : 0u));
                     }
                 }
-                for (int from = 0;;) {
-                    const int end = from + STEP < all ? from + STEP : all;
+                for (int from = NEXT ? 0 : nblk, end = nblk;;) {
+                    end = end + STEP < all ? end + STEP : all;
                     for (int c0 = from; c0 < end; c0 += CH) {
                         if (tid == 0) near_n = open_n = 0;
                         __syncthreads();
                         const uint64_t tau = best_s[a.k - 1];
                         if constexpr (NEXT) {
                             if (tid < CH && c0 + tid < end) {
-                                const int b = c0 + tid, at = at_s[b], m = at & 8 ? 8 : 1;
-                                const int pos = atomicAdd(&open_n, m);
-                                for (int e = 0; e < m; ++e) work_s[pos + e] = (uint16_t)(b * 8 + (m == 8 ? e : at));
+                                const int b = c0 + tid, at = at_s[b] & 7;
+                                const bool whole = at_s[b] & 8, fresh = b >= nblk;
+                                int pos = atomicAdd(&open_n, (fresh ? 1 : 0) + (whole ? 7 : 0));
+                                for (int e = 0; e < 8; ++e)
+                                    if (e == at ? fresh : whole) work_s[pos++] = (uint16_t)(b * 8 + e);
                             }
                             __syncthreads();
                             const int work = __builtin_amdgcn_readfirstlane(open_n);   // <= 8 CH
@@ -2600,7 +2609,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void bl
                         const int c = __builtin_amdgcn_readfirstlane(near_n);
                         if (c > 0) {   // uniform
                             int m2 = 2;
-                            while (m2 < c + a.k) m2 <<= 1;   // <= 256
+                            while (m2 < c + a.k) m2 <<= 1;   // <= RMAX * 16
                             for (int i = c + tid; i < m2; i += NT) ent[i] = i < c + a.k ? best_s[i - c] : kSentinel;
                             __syncthreads();
                             bitonic_sort_lds(ent, m2, tid, NT);
