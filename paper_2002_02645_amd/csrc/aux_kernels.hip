@@ -1578,18 +1578,19 @@ __global__ __launch_bounds__(kThrThreads) void keys_finish_kernel(KeysFinishArgs
     }
     if (tid < kThrGroups) rank_s[tid] = 0;
     uint64_t t = kSentinel;   // threshold on (key, index) pairs
-    int nblk;
-    if (r_sel >= nb) {        // fewer blocks than that: all of them, everything passes
-        if (tid < (int)nb) pick_s[tid] = bq[tid];
-        nblk = (int)nb;
-        __syncthreads();
-    } else {
+    const float *kq = ka.keys + (size_t)q * ka.n_pad;
+    const bool by_entry = r_sel >= nb;   // as few blocks as that: groups of entries in their place
+    int nblk = 0;
+    {
         constexpr int NV = 8;   // minima per thread kept in registers
+        static_assert(kMaxRescore * 32 <= NV * kThrThreads, "all entries by entry");
+        const int64_t values = by_entry ? a.n : nb;
         uint64_t v[NV], m = kSentinel;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             const int64_t j = (int64_t)i * kThrThreads + tid;
-            v[i] = j < nb ? bq[j] : kSentinel;
+            v[i] = kSentinel;
+            if (j < values) v[i] = by_entry ? ((uint64_t)ordered_bits(kq[j]) << 32) | (uint32_t)j : bq[j];
             m = v[i] < m ? v[i] : m;
         }
         for (int64_t j = (int64_t)NV * kThrThreads + tid; j < nb; j += kThrThreads) {
@@ -1617,8 +1618,8 @@ __global__ __launch_bounds__(kThrThreads) void keys_finish_kernel(KeysFinishArgs
             atomicAdd(&rank_s[tid & (kThrGroups - 1)], c);
         }
         __syncthreads();
-        // (groups without a value hold the marker; r_sel < nb values exist, but they may lie in fewer than
-        // r_sel groups: then T stays the marker and everything passes)
+        // (groups without a value hold the marker; where the values lie in fewer than r_sel groups T stays the marker and
+        // everything passes)
         if (tid == 0) sel_s = kSentinel;
         __syncthreads();
         if (tid < kThrGroups && rank_s[tid] == r_sel - 1 && grp_s[tid] != kSentinel) sel_s = grp_s[tid];
@@ -1640,7 +1641,9 @@ __global__ __launch_bounds__(kThrThreads) void keys_finish_kernel(KeysFinishArgs
         }
         __syncthreads();
         const int cnt = list_n < kThrList ? list_n : kThrList;
-        if (cnt <= kMaxRescore) {
+        if (by_entry) {   // uniform
+            if (tid == 0) cand_n = cnt;
+        } else if (cnt <= kMaxRescore) {
             if (tid < cnt) pick_s[tid] = list[tid];
             nblk = cnt;
         } else {   // uniform
@@ -1659,7 +1662,6 @@ __global__ __launch_bounds__(kThrThreads) void keys_finish_kernel(KeysFinishArgs
     }
 
     // ---- their entries at or under the threshold, in order of their keys ----
-    const float *kq = ka.keys + (size_t)q * ka.n_pad;
     for (int c = tid; c < nblk * 32; c += kThrThreads) {
         const uint32_t idx = ((uint32_t)pick_s[c >> 5] & ~31u) + (c & 31);
         const uint64_t pr = ((uint64_t)ordered_bits(kq[idx]) << 32) | idx;
@@ -1864,6 +1866,10 @@ hipError_t launch_keys_finish(const FinishArgs &a, const float *keys, const uint
         return hipErrorInvalidValue;
     const int64_t nb = n_pad / 32, per_group = (nb + kThrGroups - 1) / kThrGroups;
     int r_sel = 2 * a.r < kMaxRescore ? 2 * a.r : kMaxRescore;
+    // Not more than half of few blocks where that leaves the width: the threshold is the r_sel-th smallest block minimum, and near
+    // the largest it lets in a good part of the cache, which is sorted.  One query, 2,000 x 512 (64 blocks), k = 20: 41 us with
+    // all blocks, 26 with half of them; k = 40, by entries, 45 -> 33.
+    if (r_sel > nb / 2) r_sel = a.r > nb / 2 ? a.r : (int)(nb / 2);
     while (r_sel > a.r && per_group * r_sel > kThrList) --r_sel;   // the gathered minima fit the list
     KeysFinishArgs ka{a, bmin, keys, nb, n_pad, r_sel, cand, cand_count, first_width(a, a.b > 64), 1, meet, tickets};
     // Long rows, few queries: a workgroup gets a row out of memory at 50 to 100 GB/s, so up to eight share the rows of a query,

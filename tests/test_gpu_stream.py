@@ -57,6 +57,22 @@ def test_keys_out_for_several_query_tiles(n, d, b, k, dtype):
     check_case(L.entries, L.labels, q, 10, k, max(1, k - 2))
 
 
+@pytest.mark.parametrize("n,k,r", [
+    (2000, 20, 0),     # 64 blocks of 32 entries: half of them, the width itself, are let in and not all
+    (1280, 20, 0),     # 40: the width is more than half
+    (1025, 20, 0),     # ... the last eight of which hold one entry
+    (1024, 20, 0),     # 32, as many as the width: groups of entries in their place
+    (2000, 40, 0),     # ... width 64, two entries per thread
+    (40, 10, 0), (17, 10, 0),   # ... hardly more entries than the width
+    (2000, 20, 33),    # a width beyond half
+    (700, 10, 0),      # 24 blocks, width 16
+    (500, 1, 0),       # 16, width 8
+])
+def test_keys_of_few_blocks(n, k, r):
+    L, q = _inputs(n, 512, 40, k, torch.bfloat16, 40 + n + k + r)
+    check_case(L.entries, L.labels, q, 10, k, max(1, k - 2), r)
+
+
 @pytest.mark.parametrize("batch,thresholds", [(1, (8, 8, 8, 8)), (40, (10, 10, 10, 10)), (128, (8, 8, 8, 8))])
 def test_small_cascade(batch, thresholds):
     """All layers by the streaming kernel; with thresholds of 10 of 10 many requests go all the way."""
