@@ -737,18 +737,6 @@ const LayerCache *get_projection(const freeze_ctx *ctx, int slot, int *err)
     *err = FREEZE_OK;
     return &ctx->layers[slot];
 }
-// The projection straight from the fp32 rows; off: by a bf16 copy of them (projection_plan): for few k-steps in all, where
-// the sums of cut tiles cost more than the copy (512 x 4,096 -> 256: 26 us so, 25 by the copy; 257 x 512 -> 1,024 22, 14; 2,500 x
-// 517 -> 1,001 43, 40), unless there are many tiles (10,000 x 512 -> 128: 20, 38).
-RowsPlan projection_rows(const freeze_ctx *ctx, const LayerCache &P, int64_t b)
-{
-    if (b <= 256) return RowsPlan{};
-    RowsPlan pl = plan_projection(b, P.d, P.n, ctx->num_cus);
-    const int64_t tiles = (int64_t)pl.m_tiles * pl.n_tiles;
-    if (tiles * pl.nk < 4 * (int64_t)ctx->num_cus && (tiles < 20 || P.d % 4 != 0)) pl.on = false;
-    return pl;
-}
-
 // Up to 256 inputs, and up to 512 where their 256 x 256 tiles would go without stream-K: the streaming kernel, which
 // cuts the few output tiles along the depth for small input tiles too (8,192 -> 1,024 outputs: 1 input 155 -> 20 us,
 // 128 inputs 155 -> 39 us; 384 x 16,384, where stream-K applies: 124 us against 133).  Else a workgroup per (tile
@@ -773,6 +761,21 @@ DistPlan projection_plan(const freeze_ctx *ctx, const LayerCache &P, int64_t b, 
     const int64_t k_steps = (int64_t)pl.m_tiles * pl.n_tiles * (P.d_pad / kKB);
     if (!whole) plan_stream_k(pl, ctx->num_cus, P.d_pad, k_steps < 16 * (int64_t)ctx->num_cus ? 90.0 : 0.0);
     if (b <= 512 && pl.sk_wgs == 0) return plan_stream(b, P.n, 1, ctx->num_cus, P.d_pad, whole ? StreamCut::none : StreamCut::always);
+    return pl;
+}
+
+// The projection straight from the fp32 rows; off: by a bf16 copy of them (projection_plan): for few k-steps in all, where
+// the sums of cut tiles cost more than the copy (512 x 4,096 -> 256: 26 us so, 25 by the copy; 257 x 512 -> 1,024 22, 14; 2,500 x
+// 517 -> 1,001 43, 40), unless there are many tiles (10,000 x 512 -> 128: 20, 38).
+RowsPlan projection_rows(const freeze_ctx *ctx, const LayerCache &P, int64_t b)
+{
+    if (b <= 256) return RowsPlan{};
+    // (no longer sums than by the bf16 copy: smaller buffers get that, and are not to be the more precise)
+    const DistPlan copy = projection_plan(ctx, P, b, false);
+    const int64_t nk = P.d_pad / kKB, cut = copy.variant == 4 ? copy.st_len : (copy.sk_wgs > 0 ? copy.sk_len : nk);
+    RowsPlan pl = plan_projection(b, P.d, P.n, ctx->num_cus, cut < nk ? cut : nk);
+    const int64_t tiles = (int64_t)pl.m_tiles * pl.n_tiles;
+    if (tiles * pl.nk < 4 * (int64_t)ctx->num_cus && (tiles < 20 || P.d % 4 != 0)) pl.on = false;
     return pl;
 }
 

@@ -341,7 +341,7 @@ struct RowsPlan {
     int ncb, nc;        // blocks of 16 centres and centres per tile
     int n_tiles, m_tiles, nk, slots, wgs;
     int rows;           // projection: rows per tile
-    int groups;         // ... groups of n_tiles workgroups per XCD
+    int groups;         // ... groups of n_tiles workgroups within an XCD
     int64_t len;        // k-steps per workgroup of the flattened (point tile, centre tile, k-step) space; projection: per
                         // group of the (row tile, k-step) space
     size_t part, sq;    // floats of the sums and of the points' sums of squares
@@ -349,7 +349,7 @@ struct RowsPlan {
 RowsPlan plan_rows(int64_t n, int64_t d, int64_t kc, int num_cus);
 // The dense layer in front of a look-up by the same kernel: out = x w^T + bias of fp32 rows x [n, d] and the tiled bf16
 // rows w (m of m_pad).  part: plan's floats of scratch (none: null).  on == false: not for this shape.
-RowsPlan plan_projection(int64_t n, int64_t d, int64_t m, int num_cus);
+RowsPlan plan_projection(int64_t n, int64_t d, int64_t m, int num_cus, int64_t most);   // most: k-steps that a sum should have at most
 hipError_t launch_project(const RowsPlan &pl, const float *x, int64_t n, int64_t d, int64_t d_pad, const uint16_t *w, int64_t m, int64_t m_pad,
                           const float *bias, bool relu, float *part, float *out, hipStream_t s);
 // hi, lo [n_pad * d_pad] and norm [n_pad] of the centres (n_pad: kc rounded up to kTileN)

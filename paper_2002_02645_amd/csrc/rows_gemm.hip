@@ -30,15 +30,17 @@
 // Projection: one bf16 value per element on both sides, as the layer is defined.  A bf16 copy of the inputs first cost 82 us
 // at 10,000 x 8,192 -> 1,024 (and the product 148, the sums of cut tiles 36).
 //   - Ranges of the (row tile, k-step) space, each for a group of workgroups of one XCD, one per column tile: they take the
-//     same fp32 rows at about the same time, out of HBM once and out of the XCD's L2 for the others.
+//     same fp32 rows at about the same time, out of HBM once and out of the XCD's L2 for the others.  (What is left of the XCDs'
+//     workgroups forms groups across them: 5 of 85 with three column tiles.)
 //   - Bound by what reaches the CUs out of L2, 48 KiB per k-step and workgroup, at 10 TB/s: 195 us there for 168 GFLOP (0.86
 //     PFLOP/s).  Whole calls 265 -> 209 us; 10,000 x 32,768 -> 256 604 -> 319; 10,000 x 1,000 -> 1,500 75 -> 41; 300 x 30,000 ->
-//     300 176 -> 35; 1,500 x 8,192 -> 1,024 87 -> 46.
+//     300 176 -> 35; 1,500 x 8,192 -> 1,024 87 -> 59 (47 with the longer sums that plan_projection no longer takes).
 //
 // Paper: Sec. 4 "k-means"; Sec. 3 (one-layer dimensionality reduction).
 #include "freeze_internal.h"
 #include "select_common.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace fz {
@@ -146,8 +148,10 @@ __global__ __launch_bounds__(512) void rows_gemm_kernel(RowsGemmArgs p)
     // ranges of the flattened (row tile, column tile, k-step) space; the projection: of (row tile, k-step), a range for
     // the n_tiles workgroups of a group, one per column tile (block id modulo 8: the XCD)
     const int across = SPLIT ? p.n_tiles : 1;
-    const int place = (int)blockIdx.x >> 3;
-    const int range = SPLIT ? (int)blockIdx.x : (int)(blockIdx.x & 7) * p.groups + place / p.n_tiles;
+    // (an XCD's workgroups beyond its groups form groups across the XCDs)
+    const int xcd = (int)blockIdx.x & 7, place = (int)blockIdx.x >> 3, left = place - p.groups * p.n_tiles;
+    const int member = left < 0 ? place : left * 8 + xcd;   // of the XCD's groups, or of the others
+    const int range = SPLIT ? (int)blockIdx.x : (left < 0 ? xcd : 8) * p.groups + member / p.n_tiles;
     const int64_t total = (int64_t)p.m_tiles * across * nk;
     const int64_t g_begin = (int64_t)range * p.len;
     const int64_t g_end = g_begin + p.len < total ? g_begin + p.len : total;
@@ -170,7 +174,7 @@ __global__ __launch_bounds__(512) void rows_gemm_kernel(RowsGemmArgs p)
         const int64_t tile = g / nk;
         const int ka = (int)(g - tile * nk);
         const int kb = g_end - tile * nk < nk ? (int)(g_end - tile * nk) : nk;
-        const int nt = SPLIT ? (int)(tile % p.n_tiles) : place % p.n_tiles;
+        const int nt = SPLIT ? (int)(tile % p.n_tiles) : member % p.n_tiles;
         const int64_t mt = tile / across;
         // slot: how many ranges before this one touch the tile
         const int slot = (int)(range - (tile * nk) / p.len);
@@ -405,16 +409,17 @@ __global__ __launch_bounds__(256) void project_sum_kernel(RowsGemmArgs p, int nc
         if (row0 + r < mt * rows || (int64_t)nt * nc + c >= p.m) continue;
         const float *src = p.part + (tile * p.slots * rows + r) * nc + c;
         const int64_t step = (int64_t)rows * nc;
-        f32x4 v = *reinterpret_cast<const f32x4 *>(src);
-        int s = 1;
-        for (; s + 3 < ns; s += 4) {   // four in flight
+        // four in flight, and four summed before they are added: one after the other, the error of sums of 40 slots was a quarter larger
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+        for (int s = 0; s < ns; s += 4) {
             f32x4 t[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) t[u] = *reinterpret_cast<const f32x4 *>(src + (s + u) * step);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v += t[u];
+            for (int u = 0; u < 4; ++u) {
+                t[u] = *reinterpret_cast<const f32x4 *>(src + (s + u < ns ? s + u : s) * step);
+                if (s + u >= ns) t[u] = f32x4{0.f, 0.f, 0.f, 0.f};   // uniform
+            }
+            v += (t[0] + t[1]) + (t[2] + t[3]);
         }
-        for (; s < ns; ++s) v += *reinterpret_cast<const f32x4 *>(src + s * step);
         store_projected(p, row0 + r, (int64_t)nt * nc + c, v);
     }
 }
@@ -776,7 +781,8 @@ hipError_t launch_kmeans_assign(const RowsPlan &pl, const float *points, int64_t
     return hipGetLastError();
 }
 
-static RowsPlan plan_projection_rows(int64_t n, int64_t d, int64_t m, int num_cus, int rows)
+// across: with the workgroups beyond the groups of their XCD, in groups across the XCDs
+static RowsPlan plan_projection_rows(int64_t n, int64_t d, int64_t m, int num_cus, int rows, bool across)
 {
     RowsPlan pl{};
     pl.rows = rows;
@@ -789,15 +795,16 @@ static RowsPlan plan_projection_rows(int64_t n, int64_t d, int64_t m, int num_cu
     pl.m_tiles = (int)((n + rows - 1) / rows);
     pl.nk = (int)((d + kKB - 1) / kKB);
     pl.groups = per_xcd / pl.n_tiles;
-    const int64_t total = (int64_t)pl.m_tiles * pl.nk, ranges = 8 * (int64_t)pl.groups;
-    if (pl.m_tiles >= 8 * ranges) {
-        pl.len = (pl.m_tiles + ranges - 1) / ranges * pl.nk;   // whole tiles: an idle eighth at most
-    } else {
-        pl.len = (total + ranges - 1) / ranges;
-        const int64_t least = pl.nk < 8 ? pl.nk : 8;           // a slot is written and read for it
-        if (pl.len < least) pl.len = least;
-    }
-    pl.wgs = 8 * pl.groups * pl.n_tiles;   // (ranges past the end return at once)
+    const int64_t total = (int64_t)pl.m_tiles * pl.nk;
+    auto range_len = [&](int64_t ranges) {
+        if (pl.m_tiles >= 8 * ranges) return (pl.m_tiles + ranges - 1) / ranges * pl.nk;   // whole tiles: an idle eighth at most
+        const int64_t len = (total + ranges - 1) / ranges, least = pl.nk < 8 ? pl.nk : 8;   // a slot is written and read for it
+        return len < least ? least : len;
+    };
+    pl.len = range_len(8 * pl.groups);
+    // (not where ranges are whole tiles without them)
+    if (across && pl.len % pl.nk != 0) pl.len = range_len(8 * pl.groups + 8 * (per_xcd - pl.groups * pl.n_tiles) / pl.n_tiles);
+    pl.wgs = 8 * per_xcd;   // (ranges past the end return at once)
     pl.slots = pl.len % pl.nk == 0 ? 1 : (int)((pl.nk + pl.len - 2) / pl.len) + 1;
     pl.part = pl.slots == 1 ? 0 : (size_t)pl.m_tiles * pl.n_tiles * pl.slots * rows * pl.nc;
     pl.on = pl.part * 4 <= (size_t)1 << 30;
@@ -807,11 +814,18 @@ static RowsPlan plan_projection_rows(int64_t n, int64_t d, int64_t m, int num_cu
 // Tiles of 256 rows take 1.22 us a k-step, of 192 rows 0.94 where the chip is busy (10,000 x 8,192 -> 1,024: what L2
 // hands to the CUs, 10 TB/s, bounds both: 210, 219 us) and about 0.8 in short ranges (1,500 x 8,192 -> 1,024, 24 and 32 k-steps: 55, 46;
 // 3,000 x 8,192 -> 700 67, 60; but 2,000 x 16,384 -> 256, 16 and 22 k-steps: 53, 58).
-RowsPlan plan_projection(int64_t n, int64_t d, int64_t m, int num_cus)
+// The length of a chain of additions is part of the projection's precision: where the faster one's is more than `most` k-steps, the
+// one with shorter sums (6,079 x 8,192 -> 1,024: 129 us with an error of 3.2e-7 against 64 bits, 148 with 2.56e-7, that of
+// 256 x 256 tiles dealt evenly to the CUs).
+RowsPlan plan_projection(int64_t n, int64_t d, int64_t m, int num_cus, int64_t most)
 {
-    const RowsPlan p4 = plan_projection_rows(n, d, m, num_cus, 256), p3 = plan_projection_rows(n, d, m, num_cus, 192);
-    if (!p4.on || !p3.on) return p4.on ? p4 : p3;
-    return p3.len * 100 >= p4.len * (p4.len >= 128 || p4.slots == 1 ? 130 : 136) ? p4 : p3;
+    const RowsPlan p4 = plan_projection_rows(n, d, m, num_cus, 256, false), p3 = plan_projection_rows(n, d, m, num_cus, 192, false);
+    if (!p4.on || !p3.on) return plan_projection_rows(n, d, m, num_cus, p4.on ? 256 : 192, true);
+    const bool large = p3.len * 100 >= p4.len * (p4.len >= 128 || p4.slots == 1 ? 130 : 136);
+    const RowsPlan fast = plan_projection_rows(n, d, m, num_cus, large ? 256 : 192, true);
+    if (std::min<int64_t>(fast.len, fast.nk) <= most) return fast;
+    const RowsPlan other = plan_projection_rows(n, d, m, num_cus, large ? 192 : 256, true);
+    return other.len < fast.len ? other : fast;
 }
 
 hipError_t launch_project(const RowsPlan &pl, const float *x, int64_t n, int64_t d, int64_t d_pad, const uint16_t *w, int64_t m, int64_t m_pad,

@@ -68,3 +68,23 @@ def test_no_finite_numbers(d):
         assert torch.equal(a.isnan(), part.isnan()) and torch.equal(a.isinf(), part.isinf())
         assert torch.equal(a[a.isinf()], part[part.isinf()])
     assert whole[0].isinf().all() and whole[1].isnan().all() and whole[10].isfinite().all()
+
+
+@pytest.mark.parametrize("b,d,m,most", [
+    (6079, 8192, 1024, 2.56e-7),     # sums of 96 k-steps; of 128, as tiles of 192 rows have them, 3.2e-7
+    (1500, 8192, 1024, 1.38e-7),
+    (3000, 8192, 700, 1.58e-7),      # three column tiles: groups of workgroups across the XCDs
+    (1050, 16384, 1190, 1.94e-7),    # five
+    (766, 16384, 256, 1.43e-7),      # many slots per tile
+    (544, 25600, 256, 1.62e-7),
+])
+def test_error_of_the_sums(b, d, m, most):
+    # The length of a chain of fp32 additions, and of the sums of its pieces, is the error of the result.  most: relative error
+    # (2-norm) on these inputs with tiles of 256 x 256 whose k-steps are dealt evenly to 256 CUs; 5 % for other random inputs.
+    g = torch.Generator(device="cuda").manual_seed(b)
+    x = torch.randn(b, d, device="cuda", generator=g).clamp_(min=0.0)
+    w = (torch.randn(m, d, device="cuda", generator=g) / d ** 0.5).to(torch.bfloat16)
+    bias = 0.1 * torch.randn(m, device="cuda", generator=g)
+    y = _project(x, w, bias, False)
+    ref = x.to(torch.bfloat16).double() @ w.double().t() + bias.double()
+    assert ((y.double() - ref).norm() / ref.norm()).item() <= 1.05 * most
