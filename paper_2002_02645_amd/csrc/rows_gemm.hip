@@ -709,10 +709,12 @@ RowsPlan plan_rows(int64_t n, int64_t d, int64_t kc, int num_cus)
     if (n < kRowsTile || d < 1 || d > (int64_t)1 << 20 || kc < 1 || kc > kRowsMaxTiles * kTileN) return pl;
     pl.n_tiles = (int)((kc + kTileN - 1) / kTileN);
     const int per = (int)((kc + pl.n_tiles - 1) / pl.n_tiles);
-    for (int b : {4, 6, 8, 10, 12, 13, 14, 16}) {
-        pl.ncb = b;
-        if (16 * b >= per) break;
-    }
+    // As many blocks of columns as are needed, four at least.  An odd number's waves differ, which costs registers and still is 1
+    // to 5 % of a build less than the next even one (50,000 x 8,192 with 136 centres 1,937 -> 1,880 us, 168 2,068 -> 2,010, 200
+    // 2,230 -> 2,151, 280 3,156 -> 3,043; 9,000 x 1,023 with 104 250 -> 242); of 15 blocks 18 registers spill: 50,000 x 8,192
+    // with 232 2,312 -> 2,264, but 20,000 x 4,100 with 480 1,320 -> 1,332, 50,000 x 517 with 232 524 -> 536.
+    pl.ncb = per <= 64 ? 4 : (per + 15) / 16;
+    if (pl.ncb == 15) pl.ncb = 16;
     pl.nc = 16 * pl.ncb;
     pl.m_tiles = (int)((n + kRowsTile - 1) / kRowsTile);
     pl.nk = (int)((d + kKB - 1) / kKB);
@@ -764,9 +766,13 @@ hipError_t launch_kmeans_assign(const RowsPlan &pl, const float *points, int64_t
     hipError_t e;
     switch (pl.ncb) {
     case 4: e = launch_gemm<4, true>(pl, a, s); break;
+    case 5: e = launch_gemm<5, true>(pl, a, s); break;
     case 6: e = launch_gemm<6, true>(pl, a, s); break;
+    case 7: e = launch_gemm<7, true>(pl, a, s); break;
     case 8: e = launch_gemm<8, true>(pl, a, s); break;
+    case 9: e = launch_gemm<9, true>(pl, a, s); break;
     case 10: e = launch_gemm<10, true>(pl, a, s); break;
+    case 11: e = launch_gemm<11, true>(pl, a, s); break;
     case 12: e = launch_gemm<12, true>(pl, a, s); break;
     case 13: e = launch_gemm<13, true>(pl, a, s); break;
     case 14: e = launch_gemm<14, true>(pl, a, s); break;

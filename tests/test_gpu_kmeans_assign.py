@@ -48,9 +48,12 @@ def _build(pts, cen, iters=1):
     (256, 32, 1),         # one tile of points, one k-step, one centre
     (257, 33, 16),        # the second tile reaches back over 255 rows of the first
     (300, 4, 64), (511, 100, 65), (1021, 31, 97),
-    (2051, 36, 200),      # 13 column blocks: the waves of a pair differ
+    (300, 132, 80), (411, 33, 112), (290, 68, 131), (310, 65, 176),   # 5, 7, 9 and 11 column blocks: the waves of a pair differ
+    (2051, 36, 200),      # 13
+    (400, 70, 230),       # 15: as 16
     (700, 520, 256),      # the widest tile
     (900, 68, 257), (1500, 98, 512),       # two tiles of centres
+    (600, 100, 343),      # ... of 11 column blocks
     (1300, 60, 513),      # more centres than the product takes
     (601, 4104, 13),      # re-scored by the whole workgroup, ranges that cut tiles in several places
     (600, 4099, 33),      # ... by waves, rows on any boundary
