@@ -83,7 +83,8 @@ def test_config1_confidence_full_batch():
 @pytest.mark.parametrize("n,d,b,k,r,dtype", [
     (777, 100, 37, 7, 0, torch.float32),       # streaming kernel, ragged everything
     (5000, 1024, 600, 10, 0, torch.bfloat16),  # ... ten query tiles
-    (20000, 512, 8, 20, 0, torch.bfloat16),    # small-batch kernel
+    (20000, 512, 8, 20, 0, torch.bfloat16),    # streaming kernel, few queries
+    (250001, 512, 8, 20, 0, torch.bfloat16),   # small-batch kernel
     (3000, 2048, 100, 10, 0, torch.bfloat16),  # long rows
     (1500, 192, 9, 33, 0, torch.bfloat16),     # k > 24
     (300, 64, 1, 1, 0, torch.float32),         # k = 1: confidence = 1 / distance

@@ -54,7 +54,10 @@ def _make(n, d, b, k, r, dtype, seed):
     (3001, 333, 301, 20, 0, torch.float32),      # ... R = 32, fp32 cache
     (2500, 4160, 37, 10, 64, torch.float32),     # streaming kernel, R = 64
     (50000, 2048, 64, 10, 0, torch.bfloat16),    # ... tiles cut along the depth
-    (20001, 500, 7, 20, 0, torch.bfloat16),      # small-batch kernel
+    (20001, 500, 7, 20, 0, torch.bfloat16),      # streaming kernel, one query tile
+    (20001, 100, 7, 20, 0, torch.bfloat16),      # small-batch kernel
+    (250001, 500, 7, 20, 0, torch.bfloat16),     # ...
+    (250001, 700, 5, 10, 0, torch.bfloat16),     # ... its configuration for longer rows
     (4000, 64, 50, 10, 10, torch.bfloat16),      # no spare candidates: the wider re-scoring and the exact scan run
     (300, 40, 1, 1, 0, torch.float32),           # one query, one neighbour
 ])

@@ -254,7 +254,8 @@ def _distance_in_order(q, row):
     (3000, 517, 100, 20, torch.bfloat16),     # keys: one or two rows per wave
     (3000, 517, 100, 40, torch.float32),      # ... four
     (3000, 517, 100, 1, torch.bfloat16),      # fewer rows than waves
-    (3000, 517, 9, 10, torch.bfloat16),       # small-batch kernel
+    (3000, 517, 9, 10, torch.bfloat16),       # keys, few queries
+    (3000, 117, 9, 10, torch.bfloat16),       # small-batch kernel
     (1500, 4101, 1030, 10, torch.bfloat16),   # lists: four rows per wave
     (1500, 4101, 1030, 20, torch.float32),    # ... eight
     (1500, 4101, 1030, 40, torch.bfloat16),   # ... sixteen

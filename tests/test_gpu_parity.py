@@ -73,14 +73,14 @@ def test_hand_example_on_gpu():
     (40, 64, 5, 40, 0, torch.bfloat16),        # k = N
     (300, 64, 1, 1, 0, torch.float32),         # batch 1, k = 1
     (1500, 192, 9, 33, 0, torch.bfloat16),     # k > 24 -> default R = 64
-    (20000, 512, 8, 20, 0, torch.bfloat16),    # small-batch kernel, many tiles per workgroup
-    (5000, 1024, 16, 10, 0, torch.bfloat16),   # small-batch kernel, longest supported activation
-    (3000, 960, 3, 5, 0, torch.float32),       # small-batch kernel, fp32 cache, d not a multiple of 64
-    (5000, 512, 4, 40, 0, torch.bfloat16),     # small-batch kernel, R = 64 and k > 32: the selection's fallbacks
+    (20000, 512, 8, 20, 0, torch.bfloat16),    # streaming kernel (the small-batch kernel takes such rows from 250,000 entries on: test_gpu_small_batch_large_cache.py)
+    (5000, 1024, 16, 10, 0, torch.bfloat16),   # ... a full tile of 16 queries
+    (3000, 960, 3, 5, 0, torch.float32),       # ... fp32 cache, d not a multiple of 64
+    (5000, 512, 4, 40, 0, torch.bfloat16),     # ... R = 64 and k > 32
     (3000, 100, 2, 5, 0, torch.float32),       # small-batch kernel, d not a multiple of 8
     (2000, 128, 5, 10, 0, torch.bfloat16),     # small-batch kernel, fewer workgroups than blocks to take
-    (70000, 256, 16, 10, 0, torch.bfloat16),   # small-batch kernel, one tile per workgroup
-    (3000, 1100, 3, 5, 0, torch.bfloat16),     # d too long for the small-batch kernel -> streaming kernel
+    (70000, 256, 16, 10, 0, torch.bfloat16),   # streaming kernel
+    (3000, 1100, 3, 5, 0, torch.bfloat16),     # ... d too long for the small-batch kernel whatever the cache
     (3000, 2048, 100, 10, 0, torch.bfloat16),  # long activation: every key is written out, by the streaming kernel
     (2500, 4160, 200, 10, 64, torch.float32),  # ... R = 64, fp32 cache, ragged everything
     (1000, 640, 20, 5, 0, torch.bfloat16),     # ... few cache tiles
@@ -209,7 +209,8 @@ def test_cascade_on_clusters_far_from_the_origin():
 
 @pytest.mark.parametrize("n,d,b,k,dtype", [
     (3000, 256, 300, 10, torch.bfloat16),    # block minima
-    (20000, 512, 8, 20, torch.bfloat16),     # small-batch kernel (the queries are converted inside the streaming kernel)
+    (20000, 512, 8, 20, torch.bfloat16),     # streaming kernel
+    (250001, 200, 8, 20, torch.bfloat16),    # small-batch kernel (converts its queries itself)
     (2500, 4160, 100, 10, torch.float32),    # streaming kernel, fp32 cache, ragged depth
 ])
 def test_forced_centring_keeps_results_exact(n, d, b, k, dtype):

@@ -37,7 +37,8 @@ def _both(fc, q, k, thr, r):
 
 @pytest.mark.parametrize("n,d,b1,b2,k,r,dtype", [
     (3000, 256, 300, 41, 10, 0, torch.bfloat16),     # block minima, two query tiles, then the streaming kernel
-    (20000, 512, 8, 3, 20, 0, torch.bfloat16),       # small-batch kernel twice
+    (20000, 512, 8, 3, 20, 0, torch.bfloat16),       # streaming kernel twice
+    (250001, 512, 8, 3, 20, 0, torch.bfloat16),      # small-batch kernel twice
     (2000, 512, 256, 100, 5, 0, torch.float32),      # streaming kernel, fp32 cache
 ])
 def test_static_scratch_matches_workspace_variant(n, d, b1, b2, k, r, dtype):
