@@ -25,8 +25,9 @@
 //     query tiles, cache tile, query tile of the group): a workgroup uses a cache tile for all query tiles
 //     of a group in a row, and a group's queries (1 or 2 MB) stay in the XCD's L2.
 //
-// 4,096 x 50,000 x 512, k = 10: whole look-ups 510 us with lists, 330 with minima alone, 261 with the further bits;
-// 300 queries 170, 64, 59 us; 20,011 x 517 fp32, 1,537 queries, k = 20 323, 185, 98.
+// 4,096 x 50,000 x 512, k = 10: whole look-ups 503 us with lists, 327 with minima alone, 286 with the further bits (where the
+// first blocks confirm more of the queries 493, 292, 280); 300 queries 172, 62, 62 us; 20,011 x 517 fp32, 1,537 queries, k = 20
+// 320, 189, 102.
 //
 // Paper: Sec. 3 (k nearest neighbours), Sec. 4 "Computational Complexity".
 #include "freeze_internal.h"

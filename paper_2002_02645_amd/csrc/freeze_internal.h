@@ -327,7 +327,7 @@ hipError_t launch_cascade_scatter(const int32_t *labels, const uint8_t *hit, con
                                   const int32_t *count, int64_t b, int layer_pos, int32_t *out_labels,
                                   int32_t *out_exit, hipStream_t s);
 
-// k-means cache build (the assignment step is the look-up itself)
+// k-means cache build: update and majority (the assignment: launch_kmeans_assign, or a look-up with k = 1)
 // sizes [k], offsets [k + 1], rank [k] and members [n] int32 are scratch
 // (members: the points grouped by the centre they are assigned to, each group ascending)
 hipError_t launch_kmeans_update(const float *points, const int32_t *assign, int64_t n, int64_t d, int64_t k,

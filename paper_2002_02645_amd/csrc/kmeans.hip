@@ -2,9 +2,10 @@
 // and each cluster is represented by its centre; a cache item is the centre, the majority
 // label of the cluster and the fraction of the cluster that carries it.
 //
-// The assignment step of Lloyd's iterations is the batched look-up itself (every point against
-// the centres, k = 1) and is driven from the API file; this file holds what is left: the update
-// of the centres, the majority label and fraction of every cluster, and a read-out.  gfx950 only.
+// The assignment step of Lloyd's iterations is a product of the points with split centres (rows_gemm.hip) from 256
+// points and up to 512 centres; else, and in a workspace without room for its sums, the batched look-up (every point
+// against the centres, k = 1).  Both are driven from the API file; this file holds what is left: the update of the
+// centres, the majority label and fraction of every cluster, and a read-out.  gfx950 only.
 #include "freeze_internal.h"
 
 namespace fz {

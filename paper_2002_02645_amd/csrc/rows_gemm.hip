@@ -10,8 +10,8 @@
 // so that the keys are good to 2^-12 of |q||c|, mostly far better, instead of 2^-7 and most points' nearest
 // centre is known from them alone (kmeans_pick_kernel, which re-scores what the bound of key_error leaves open).
 // Three matrix instructions per block instead of one: 0.51 TFLOP in that case, 400 to 470 us (1.1 to 1.25 PFLOP/s; the matrix
-// pipes are busy 60 % of the time at 2.0 GHz, and it is the power limit that sets the clock), and 85 to 105 us for the choice, which
-// re-scores a tenth of the points.  The whole build, two rounds, 4,710 -> 2,200 us; 50,000 x 512 1,590 -> 437, 50,000 x 8,191
+// pipes are busy 60 % of the time at 2.0 GHz, and it is the power limit that sets the clock), and 90 to 115 us for the choice, which
+// re-scores a tenth of the points.  The whole build, two rounds, 4,710 -> 2,240 us; 50,000 x 512 1,590 -> 437, 50,000 x 8,191
 // 6,810 -> 2,640, 50,000 x 8,192 with 400 centres 5,680 -> 3,600, 3,000 x 300 with 20 centres 232 -> 152.
 // (Sums cut at half the length, with half the error: 70 us for the choice, 25 more for the product, 2,195.)
 //
