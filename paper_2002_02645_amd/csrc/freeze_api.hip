@@ -1216,7 +1216,9 @@ int freeze_project(freeze_ctx *ctx, int slot, const float *x, int64_t b, int rel
         return FREEZE_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const RowsPlan rows = projection_rows(ctx, *P, b);
-    if (rows.on && rows.part * 4 <= workspace_bytes && (reinterpret_cast<uintptr_t>(workspace) % kAlign) == 0)
+    // outputs over the inputs: by the bf16 copy of these, which is complete before the first output is written
+    const bool apart = x + b * P->d <= out || out + b * P->n <= x;
+    if (rows.on && apart && rows.part * 4 <= workspace_bytes && (reinterpret_cast<uintptr_t>(workspace) % kAlign) == 0)
         return launch_project(rows, x, b, P->d, P->d_pad, P->c_bf, P->n, P->n_pad, P->bias, relu != 0, static_cast<float *>(workspace), out, s) ==
                        hipSuccess
                    ? FREEZE_OK

@@ -88,3 +88,28 @@ def test_error_of_the_sums(b, d, m, most):
     y = _project(x, w, bias, False)
     ref = x.to(torch.bfloat16).double() @ w.double().t() + bias.double()
     assert ((y.double() - ref).norm() / ref.norm()).item() <= 1.05 * most
+
+
+@pytest.mark.parametrize("b,d,m,first", [
+    (700, 8192, 1024, 0),            # the outputs over the first inputs
+    (700, 8192, 1024, 699 * 8192),   # ... over the last row and past it
+    (400, 16384, 256, 12),
+])
+def test_outputs_over_inputs(b, d, m, first):
+    g = torch.Generator(device="cuda").manual_seed(b + first)
+    buf = torch.randn(b * d + b * m, device="cuda", generator=g)
+    x, out = buf[:b * d].view(b, d), buf[first:first + b * m].view(b, m)
+    w = (torch.randn(m, d, device="cuda", generator=g) / d ** 0.5).to(torch.bfloat16)
+    bias = 0.1 * torch.randn(m, device="cuda", generator=g)
+    xr = x.to(torch.bfloat16).double()
+    ref = xr @ w.double().t() + bias.double()
+    scale = xr.abs() @ w.double().abs().t() + bias.double().abs()
+    fc = binding.FreezeCache(1)
+    try:
+        fc.build_projection(0, w, bias)
+        ws = torch.empty(binding.freeze_project_workspace_bytes(fc.ctx, 0, b), dtype=torch.uint8, device="cuda")
+        binding.freeze_project(fc.ctx, 0, x, False, out, ws)
+        torch.cuda.synchronize()
+    finally:
+        fc.close()
+    assert ((out.double() - ref).abs() <= 4e-6 * scale).all()   # as in test_rows
