@@ -141,15 +141,16 @@ __global__ __launch_bounds__(1024) void kmeans_members_kernel(const int32_t *ass
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 template <bool VEC>
 __global__ __launch_bounds__(256) void kmeans_update_kernel(const float *points, const int32_t *offsets, const int32_t *members,
-                                                            const int32_t *rank, int64_t d, const float *old_centers, float *new_centers)
+                                                            const int32_t *rank, int64_t k, int64_t d, const float *old_centers, float *new_centers)
 {
     constexpr int U = 16;                     // rows per wave and batch
     __shared__ __attribute__((aligned(16))) float rows_s[4 * U][256];
-    const uint32_t chunks = (uint32_t)((d + 255) / 256);
-    const int c = rank[blockIdx.x / chunks];
+    const int64_t place = (int64_t)blockIdx.z * gridDim.y + blockIdx.y;
+    if (place >= k) return;                   // uniform
+    const int c = rank[place];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t dim0 = (int64_t)(blockIdx.x % chunks) * 256;
+    const int64_t dim0 = (int64_t)blockIdx.x * 256;
     const int m0 = offsets[c], m1 = offsets[c + 1];
     // the lane's four dimensions of a piece: consecutive, or 64 apart; past the row's end any will do
     int at[4];
@@ -221,11 +222,13 @@ hipError_t launch_kmeans_update(const float *points, const int32_t *assign, int6
     hipError_t e = launch_kmeans_group(assign, n, k, sizes, offsets, rank, members, s);
     if (e != hipSuccess) return e;
     // (points, centres: 16-byte aligned by contract and by the workspace's layout)
-    const dim3 grid((unsigned)(k * ((d + 255) / 256)));
+    // (a cluster's workgroups in a row; in one dimension 4,097 centres of 2^20 values would be more than its 2^32 threads)
+    const int64_t rows = k < 32768 ? k : 32768;
+    const dim3 grid((unsigned)((d + 255) / 256), (unsigned)rows, (unsigned)((k + rows - 1) / rows));
     if (d % 4 == 0)
-        hipLaunchKernelGGL(kmeans_update_kernel<true>, grid, dim3(256), 0, s, points, offsets, members, rank, d, old_centers, new_centers);
+        hipLaunchKernelGGL(kmeans_update_kernel<true>, grid, dim3(256), 0, s, points, offsets, members, rank, k, d, old_centers, new_centers);
     else
-        hipLaunchKernelGGL(kmeans_update_kernel<false>, grid, dim3(256), 0, s, points, offsets, members, rank, d, old_centers, new_centers);
+        hipLaunchKernelGGL(kmeans_update_kernel<false>, grid, dim3(256), 0, s, points, offsets, members, rank, k, d, old_centers, new_centers);
     return hipGetLastError();
 }
 
@@ -306,16 +309,17 @@ hipError_t launch_kmeans_majority(const int32_t *assign, const int32_t *labels, 
 // dst[i] = src[i] for float arrays; rows of a [rows, d] matrix out of a [rows, d_pad] one
 __global__ void copy_rows_f32_kernel(const float *src, int64_t src_stride, float *dst, int64_t rows, int64_t d)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < rows * d) dst[i] = src[(i / d) * src_stride + i % d];
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < rows * d; i += (int64_t)gridDim.x * blockDim.x)
+        dst[i] = src[(i / d) * src_stride + i % d];
 }
 
 hipError_t launch_copy_rows_f32(const float *src, int64_t src_stride, float *dst, int64_t rows, int64_t d, hipStream_t s)
 {
     const int64_t total = rows * d;
     if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(copy_rows_f32_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, src, src_stride, dst,
-                       rows, d);
+    // (a grid of 2^32 threads and more is cut off without an error)
+    const int64_t blocks = (total + 255) / 256 < (1 << 20) ? (total + 255) / 256 : 1 << 20;
+    hipLaunchKernelGGL(copy_rows_f32_kernel, dim3((unsigned)blocks), dim3(256), 0, s, src, src_stride, dst, rows, d);
     return hipGetLastError();
 }
 

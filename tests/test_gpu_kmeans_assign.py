@@ -148,3 +148,38 @@ def test_rows_whose_sums_round_one_way(n, d, kc, shape):
         fc.close()
     wrong = (share != 1.0) | (label != torch.arange(kc))
     assert not wrong.any(), (int(wrong.sum()), share[wrong][:5], torch.nonzero(wrong)[:5, 0])
+
+
+def test_update_of_many_centres():
+    # more centres than the update's grid has in one dimension; two points each to the last 7,000
+    n, kc, d = 40000, 33000, 8
+    pts = torch.zeros(n, d)
+    i = torch.arange(kc)
+    pts[:kc, 0], pts[:kc, 1] = 8.0 * (i % 200), 8.0 * (i // 200)
+    pts[kc:] = pts[kc - (n - kc):kc] + 1.0
+    cen = pts[:kc].clone()
+    want = cen.clone()
+    want[kc - (n - kc):] += 0.5
+    assert np.array_equal(_build(pts.numpy(), cen.numpy())["centers"], want.numpy())
+
+
+def test_centres_of_more_than_2_to_the_32_values():
+    # more threads than a grid takes, were there one per value.  Every centre is a point and stays where it is.
+    if torch.cuda.mem_get_info()[0] < 180e9:
+        pytest.skip("needs 180 GB of device memory")
+    n, d = 4097, 1 << 20
+    fc = binding.FreezeCache(1)
+    got = None
+    try:
+        pts = torch.empty(n, d, device="cuda")
+        for i in range(0, n, 256):
+            pts[i:i + 256].normal_()
+        lab = torch.arange(n, dtype=torch.int32, device="cuda")
+        got = fc.build_kmeans_layer(0, pts, lab, n, pts, 1)
+        torch.cuda.synchronize()
+        assert all(torch.equal(got["centers"][i:i + 256], pts[i:i + 256]) for i in range(0, n, 256))
+        assert torch.equal(got["majority"], lab)
+    finally:
+        fc.close()
+        del pts, got, fc
+        torch.cuda.empty_cache()
