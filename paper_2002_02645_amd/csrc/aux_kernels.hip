@@ -1854,7 +1854,7 @@ size_t keys_finish_workspace_bytes(int64_t rows, int64_t n_pad, int r, size_t al
 {
     auto up = [&](size_t x) { return (x + align - 1) / align * align; };
     const size_t b = (size_t)rows;
-    return up(keys_finish_meet_entries(rows) * 4) + up(b * (size_t)n_pad * 4) + up(b * (size_t)(n_pad / 32) * 8) + up(b * 4) + up(b * (size_t)keys_finish_cand(r) * 8);
+    return up(b * (size_t)n_pad * 4) + up(b * (size_t)(n_pad / 32) * 8) + up(b * 4) + up(b * (size_t)keys_finish_cand(r) * 8);
 }
 
 // a.part / a.part_count (stride keys_finish_cand(a.r)) are the kernel's outputs for the wider re-scoring

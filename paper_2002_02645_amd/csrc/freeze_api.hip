@@ -109,6 +109,7 @@ struct LookupShape {
     int r;
     bool skinny;   // small-batch bandwidth-bound kernel instead of the tiled matrix-core kernel
     bool keys;     // every key is written out; selection and everything after it by keys_finish_kernel
+    bool meet;     // ... of which several may share a query
     bool blocks;   // tiled kernel writes block minima; selection and re-scoring by block_finish_kernel
     bool cascade;  // sized for a look-up whose live count may sit on the device
     DistPlan plan;
@@ -202,7 +203,8 @@ bool skinny_pays(const LayerCache &L, int64_t b)
 // Which decomposition of the work a look-up is planned with; the result does not depend on it.
 enum class Decomp {
     best,    // the fastest
-    lean,    // the fastest, but block minima without the further bits: where the workspace does not hold those
+    lean,    // the fastest, but block minima without the further bits, and materialised keys finished by a workgroup per
+             // query: where the workspace does not hold what those take
     small,   // whole tiles only, no accumulator slots, no block minima: where the workspace does not hold the fastest
     plain    // the 256-query kernel alone, as `small` (only its size is asked for: see asked_bytes)
 };
@@ -225,6 +227,7 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
     const bool fast = how == Decomp::best || how == Decomp::lean;
     out->skinny = !cascade && skinny_supported(b, L.n_pad, L.d_pad, r, ctx->num_cus) && (!fast || skinny_pays(L, b));
     out->keys = false;
+    out->meet = false;
     out->blocks = false;
     const bool next = how == Decomp::best && block_next_pays(ctx, L, b, k);   // block minima with the further bits
     if (out->skinny) {
@@ -278,9 +281,10 @@ bool lookup_shape(const freeze_ctx *ctx, const LayerCache &L, int64_t b, int k, 
         else
             out->plan = plan_dist(b, L.n, r, ctx->num_cus, out->keys, fast ? L.d_pad : 0);   // depth 0: no cut tiles, no slots
         out->ws_bytes = align_up((size_t)out->plan.b_pad * L.d_pad * 2);
+        out->meet = out->keys && how == Decomp::best && keys_finish_meet_entries(out->plan.b_pad) > 0;
         if (out->keys)
             out->ws_bytes += keys_finish_workspace_bytes(out->plan.b_pad, L.n_pad, r, kAlign) +
-                             align_up(dist_partial_bytes(out->plan));
+                             (out->meet ? align_up(keys_finish_meet_entries(out->plan.b_pad) * 4) : 0) + align_up(dist_partial_bytes(out->plan));
         else if (out->blocks)
             out->ws_bytes += align_up((size_t)out->plan.b_pad * (L.n_pad / 8) * 4) +
                              (out->plan.next ? align_up((size_t)out->plan.b_pad * (L.n_pad / 16) * 4) : 0) +
@@ -449,8 +453,7 @@ int enqueue_lookup(freeze_ctx *ctx, const LayerCache &L, const LookupShape &sh, 
             da.bmin = ws.take<uint64_t>(rows * (L.n_pad / 32));
             int32_t *cand_count = ws.take<int32_t>(rows);
             uint64_t *cand = ws.take<uint64_t>(rows * keys_finish_cand(sh.r));
-            const size_t meet = keys_finish_meet_entries((int64_t)rows);
-            keys_meet = meet > 0 ? ws.take<float>(meet) : nullptr;
+            keys_meet = sh.meet ? ws.take<float>(keys_finish_meet_entries((int64_t)rows)) : nullptr;
             da.partial = dist_partial_bytes(sh.plan) > 0 ? ws.take<float>(dist_partial_bytes(sh.plan) / 4) : nullptr;
             if (launch_dist_topr(sh.plan, da, s) != hipSuccess) return FREEZE_EHIP;
             keys = da.keys;

@@ -290,7 +290,7 @@ bool keys_finish_supported(int64_t n_pad, int r);
 int keys_finish_cand(int r);
 constexpr int kPartsRows = 128;   // queries (padded) up to which several workgroups may share one
 size_t keys_finish_meet_entries(int64_t rows);   // floats of scratch for these (0: none)
-size_t keys_finish_workspace_bytes(int64_t rows, int64_t n_pad, int r, size_t align);   // that included
+size_t keys_finish_workspace_bytes(int64_t rows, int64_t n_pad, int r, size_t align);   // without these
 // meet: keys_finish_meet_entries(rows) floats or null; tickets [b] int32, zero on entry, left zero
 hipError_t launch_keys_finish(const FinishArgs &a, const float *keys, const uint64_t *bmin, int64_t n_pad, uint64_t *cand,
                               int32_t *cand_count, float *meet, int32_t *tickets, int num_cus, hipStream_t s);

@@ -112,6 +112,28 @@ def test_smaller_buffers_give_the_same_result_or_are_refused(n, d, b, k, r, dtyp
         fc.close()
 
 
+@pytest.mark.parametrize("n,d,b,k,r", [(3000, 8192, 100, 10, 16), (3000, 512, 128, 1, 8), (5000, 16384, 70, 20, 32)])
+def test_materialised_keys_on_the_smallest_buffer(n, d, b, k, r):
+    """Few queries take no more than their bf16 copy, the keys, block minima, candidates, and the exact scan's lists."""
+    L, q = _layer(n, d, b, k, torch.bfloat16, 41 + n)
+    thr = max(1, k - 2)
+    rows, n_pad, cus = 128, (n + 255) // 256 * 256, torch.cuda.get_device_properties(0).multi_processor_count
+    parts = [rows * d * 2, rows * n_pad * 4, rows * (n_pad // 32) * 8, rows * 4, rows * min(32 * r, 512) * 8, 16, b * 4, b * 4, b * 4,
+             max(b, 2 * cus) * k * 8]
+    fc = binding.FreezeCache(1)
+    try:
+        fc.build_layer(0, L.entries.cuda(), L.labels.cuda(), 10)
+        q = q.cuda()
+        want = fc.lookup(0, q, k, thr)
+        ws = Guarded(sum((x + 255) // 256 * 256 for x in parts))
+        got = fc.alloc_outputs(b, k)
+        binding.freeze_lookup(fc.ctx, 0, q, k, thr, 0, got["label"], got["hit"], got["votes"], got["idx"], got["dist"], ws.payload)
+        _equal(got, want)
+        assert ws.intact()
+    finally:
+        fc.close()
+
+
 def test_cascade_and_thresholds_on_a_buffer_sized_for_the_full_batch():
     wl = synth.scaled(synth.WORKLOADS["c4_cascade_noisy"], n=2600, d_div=8, batch=1100)
     data = synth.make_workload(wl)
