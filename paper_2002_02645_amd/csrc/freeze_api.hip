@@ -1069,7 +1069,7 @@ int freeze_kmeans_build(freeze_ctx *ctx, int layer, const float *points, int64_t
     LayerCache centres;
     LookupShape sh;
     centres_shape(kc, d, &centres);
-    if ((reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0 || (!by_rows && !fit_shape(ctx, centres, n, 1, 0, false, room, &sh)))
+    if ((reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0 || !fit_shape(ctx, centres, n, 1, 0, false, room, &sh))
         return FREEZE_EWORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
 
@@ -1218,18 +1218,18 @@ int freeze_project(freeze_ctx *ctx, int slot, const float *x, int64_t b, int rel
         (reinterpret_cast<uintptr_t>(out) % 16) != 0)
         return FREEZE_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const RowsPlan rows = projection_rows(ctx, *P, b);
-    // outputs over the inputs: by the bf16 copy of these, which is complete before the first output is written
-    const bool apart = x + b * P->d <= out || out + b * P->n <= x;
-    if (rows.on && apart && rows.part * 4 <= workspace_bytes && (reinterpret_cast<uintptr_t>(workspace) % kAlign) == 0)
-        return launch_project(rows, x, b, P->d, P->d_pad, P->c_bf, P->n, P->n_pad, P->bias, relu != 0, static_cast<float *>(workspace), out, s) ==
-                       hipSuccess
-                   ? FREEZE_OK
-                   : FREEZE_EHIP;
     DistPlan pl = projection_plan(ctx, *P, b, false);
     if (projection_bytes(*P, b, pl) > workspace_bytes) pl = projection_plan(ctx, *P, b, true);
     if (projection_bytes(*P, b, pl) > workspace_bytes || (reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0)
         return FREEZE_EWORKSPACE;
+    const RowsPlan rows = projection_rows(ctx, *P, b);
+    // outputs over the inputs: by the bf16 copy of these, which is complete before the first output is written
+    const bool apart = x + b * P->d <= out || out + b * P->n <= x;
+    if (rows.on && apart && rows.part * 4 <= workspace_bytes)
+        return launch_project(rows, x, b, P->d, P->d_pad, P->c_bf, P->n, P->n_pad, P->bias, relu != 0, static_cast<float *>(workspace), out, s) ==
+                       hipSuccess
+                   ? FREEZE_OK
+                   : FREEZE_EHIP;
     Carver ws(workspace);
     uint16_t *x_bf = ws.take<uint16_t>((size_t)pl.b_pad * P->d_pad);
     const bool streamed = pl.variant == 4;

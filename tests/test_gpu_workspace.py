@@ -212,3 +212,25 @@ def test_kmeans_build_on_smaller_buffers():
         assert served >= 2
     finally:
         fc.close()
+
+
+def test_buffers_without_room_for_the_bf16_copy_are_refused():
+    """Also where the call would not make the copy of its inputs: what a buffer has to hold does not depend on the kernel."""
+    b, d, m = 4096, 8192, 1024
+    x = torch.randn(b, d, device="cuda")
+    small = torch.empty(b * d * 2 - 4096, dtype=torch.uint8, device="cuda")
+    fc = binding.FreezeCache(2)
+    try:
+        fc.build_projection(0, torch.randn(m, d, device="cuda"), torch.zeros(m, device="cuda"))
+        out = torch.full((b, m), 7.0, device="cuda")
+        with pytest.raises(binding.FreezeError) as e:
+            binding.freeze_project(fc.ctx, 0, x, False, out, small)
+        assert e.value.code == binding.FREEZE_EWORKSPACE
+        st = torch.empty(binding.freeze_kmeans_storage_bytes(20, d), dtype=torch.uint8, device="cuda")
+        with pytest.raises(binding.FreezeError) as e:
+            binding.freeze_kmeans_build(fc.ctx, 1, x, torch.zeros(b, dtype=torch.int32, device="cuda"), 3, x[:20].clone(), 1, st, small)
+        assert e.value.code == binding.FREEZE_EWORKSPACE
+        torch.cuda.synchronize()
+        assert bool((out == 7.0).all())
+    finally:
+        fc.close()
