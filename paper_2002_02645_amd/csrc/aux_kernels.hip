@@ -741,14 +741,15 @@ __device__ __forceinline__ void rescore_short(const FinishArgs &a, const float *
 // look-ups 2,227 us without, 2,087 with; width 64, i.e. two passes of 32, 3,000 x 286 x 44,976: 3,024 without, 4,294 with
 // (workgroups that drift apart share less of L2).
 // GS: rows whose loads are in flight at once; fewer than eight where fewer are asked for (RG = GS).
-template <int NT, int RG, bool BATCHED = false, int GS = 8>
+// PARTS > 1: part `part` of the order that PARTS * NT threads have, their chains part * NT .. + NT; parts are added up in turn.
+template <int NT, int RG, bool BATCHED = false, int GS = 8, int PARTS = 1>
 __device__ __forceinline__ void rescore_block_all(const FinishArgs &a, const float *qrow, const int32_t *idx_s,
-                                                  float *dist_s, float (*red)[8], int r, int tid)
+                                                  float *dist_s, float (*red)[8], int r, int tid, int part = 0)
 {
     float acc[RG];
 #pragma unroll
     for (int j = 0; j < RG; ++j) acc[j] = 0.f;
-    for (int64_t i = (int64_t)tid * 8; i < a.d; i += NT * 8) {
+    for (int64_t i = (int64_t)(PARTS > 1 ? part * NT + tid : tid) * 8; i < a.d; i += PARTS * NT * 8) {
         const f32x4 q0 = *reinterpret_cast<const f32x4 *>(qrow + i);
         const f32x4 q1 = *reinterpret_cast<const f32x4 *>(qrow + i + 4);
         const float qv[8] = {q0[0], q0[1], q0[2], q0[3], q1[0], q1[1], q1[2], q1[3]};
@@ -821,7 +822,7 @@ __device__ __forceinline__ void rescore_block_all(const FinishArgs &a, const flo
             }
             __syncthreads();
             if (tid < GS && g + tid < r) {
-                float t = 0.f;
+                float t = PARTS > 1 && part > 0 ? dist_s[g + tid] : 0.f;
 #pragma unroll
                 for (int wv = 0; wv < NT / 64; wv += 4)   // fixed order: groups of four waves
                     t += (red[wv][tid] + red[wv + 1][tid]) + (red[wv + 2][tid] + red[wv + 3][tid]);
@@ -829,6 +830,19 @@ __device__ __forceinline__ void rescore_block_all(const FinishArgs &a, const flo
             }
             __syncthreads();
         }
+    }
+}
+
+// The same by 256 threads in the order that the batch's finishing kernel has (wide_order): a distance does not depend on
+// whether the first candidates confirmed the query.
+template <int RG>
+__device__ __forceinline__ void rescore_block_any(const FinishArgs &a, const float *qrow, const int32_t *idx_s, float *dist_s, float (*red)[8],
+                                                  int r, int tid)
+{
+    if (wide_order(a.b, a.d)) {   // uniform
+        for (int part = 0; part < 4; ++part) rescore_block_all<256, RG, false, 8, 4>(a, qrow, idx_s, dist_s, red, r, tid, part);
+    } else {
+        rescore_block_all<256, RG>(a, qrow, idx_s, dist_s, red, r, tid);
     }
 }
 
@@ -2950,7 +2964,7 @@ __global__ __launch_bounds__(256) void follow_up_kernel(ScanArgs sa)
                 auto rescore = [&](int m0, int m) {   // candidates [m0, m)
                     if (whole_block) {
                         for (int c0 = m0; c0 < m; c0 += 16)
-                            rescore_block_all<256, 16>(a, qrow, idx_s + c0, dist_s + c0, red, m - c0 < 16 ? m - c0 : 16, tid);
+                            rescore_block_any<16>(a, qrow, idx_s + c0, dist_s + c0, red, m - c0 < 16 ? m - c0 : 16, tid);
                     } else {
                         // (sixteen rows in flight per wave where there are enough: 4,538 x 29,747 fp32, 47 queries 901 us, 1,474 with four)
                         if (m - m0 > 32) rescore_wave<16>(a, qrow, idx_s + m0, dist_s + m0, m - m0, tid >> 6, tid & 63);
@@ -3044,7 +3058,7 @@ __global__ __launch_bounds__(256) void follow_up_kernel(ScanArgs sa)
             __syncthreads();
             if (a.d >= 4096 && a.d % 8 == 0) {
                 for (int c0 = 0; c0 < m; c0 += 32)
-                    rescore_block_all<256, 32>(a, qrow, idx_s + c0, dist_s + c0, red, m - c0 < 32 ? m - c0 : 32, tid);
+                    rescore_block_any<32>(a, qrow, idx_s + c0, dist_s + c0, red, m - c0 < 32 ? m - c0 : 32, tid);
             } else
                 rescore_wave<16>(a, qrow, idx_s, dist_s, m, tid >> 6, tid & 63);
             __syncthreads();

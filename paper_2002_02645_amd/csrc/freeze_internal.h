@@ -281,7 +281,7 @@ struct FinishArgs {
 
 // Whether the distances of a batch are added up by 1,024 threads (workgroups as large as that pay for few queries on the longest
 // rows) and not in the order of four waves.
-inline bool wide_order(int64_t b, int64_t d) { return b <= 1024 && d >= 16384 && d % 8 == 0; }
+__host__ __device__ inline bool wide_order(int64_t b, int64_t d) { return b <= 1024 && d >= 16384 && d % 8 == 0; }
 hipError_t launch_finish(const FinishArgs &a, hipStream_t s);
 // Keys-out routes: selection from the materialised keys and block minima, and everything launch_finish
 // does.  rows = query rows of the key buffers; cand [b, keys_finish_cand(r)] and cand_count [b] receive the

@@ -77,3 +77,51 @@ def test_wider_width_on_lists(n, d, b, k, r, offset, dtype):
     e_h, l_h, q_h = _host_entries(ent), lab.numpy(), q[some].numpy()
     ref = parity.oracle_reference(q_h, e_h, l_h, 10, k, thr)
     parity.assert_lookup_matches(got, ref, q_h, e_h, l_h, 10, k, thr, rel=1e-5, dist_rel=1e-5)
+
+
+def _by_1024_threads(q, c):
+    """fp32 distances of the rows of q to those of c, added up by 1,024 threads: chains of every 1,024th piece of eight values, a
+    butterfly over a wave's, four waves' at a time.  (Inputs: squares of 24 bits, so that float64 rounds like a fused step.)"""
+    x = (q - c).view(q.shape[0], -1, 1024, 8).double()
+    acc = torch.zeros(q.shape[0], 1024, device=q.device)
+    for s in range(x.shape[1]):
+        for e in range(8):
+            acc = (acc.double() + x[:, s, :, e] ** 2).float()
+    acc, lane = acc.view(-1, 16, 64), torch.arange(64, device=q.device)
+    for off in (32, 16, 8, 4, 2, 1):
+        acc = acc + acc[:, :, lane ^ off]
+    wave, t = acc[:, :, 0], torch.zeros(q.shape[0], device=q.device)
+    for w in range(0, 16, 4):
+        t = t + ((wave[:, w] + wave[:, w + 1]) + (wave[:, w + 2] + wave[:, w + 3]))
+    return t
+
+
+@pytest.mark.parametrize("points,copies,b,k,stage", [
+    (256, 2, 512, 1, 1),      # a workgroup per query that the first candidates do not confirm
+    (256, 2, 16, 1, 1),       # ... several, that meet
+    (1, 600, 12, 5, 2),       # the exact scan
+])
+def test_longest_rows_have_one_order_of_additions(points, copies, b, k, stage):
+    """Entries as far from a query as each other but for the roundings of the sums: permutations of the same differences.  Up to
+    1,024 queries on 16,384 values: what re-scores later candidates adds up like what re-scores the first ones."""
+    d = 16384
+    g = torch.Generator().manual_seed(points + b)
+    at = torch.randint(-32, 33, (points, d), generator=g) / 16.0
+    off = torch.randint(-4095, 4096, (points, d), generator=g) / 4096.0
+    ent = torch.stack([at + off[:, torch.randperm(d, generator=g)] for _ in range(copies)], 1).view(points * copies, d).cuda()
+    q = at[torch.arange(b) % points].cuda().contiguous()
+    fc = binding.FreezeCache(1)
+    try:
+        stats = torch.zeros(3, dtype=torch.int64, device="cuda")
+        binding.freeze_lookup_stats_attach(fc.ctx, stats)
+        fc.build_layer(0, ent, torch.zeros(points * copies, dtype=torch.int32, device="cuda"), 2)
+        got = fc.lookup(0, q, k, 1)
+        torch.cuda.synchronize()
+        binding.freeze_lookup_stats_attach(fc.ctx, None)
+    finally:
+        fc.close()
+    assert stats[stage] > 0, stats
+    dist = torch.stack([_by_1024_threads(q, ent[torch.arange(b, device="cuda") % points * copies + j]) for j in range(copies)], 1)
+    want, place = torch.sort(dist, dim=1, stable=True)
+    assert torch.equal(got["dist"], want[:, :k])
+    assert torch.equal(got["idx"].long(), (torch.arange(b, device="cuda") % points * copies)[:, None] + place[:, :k])
