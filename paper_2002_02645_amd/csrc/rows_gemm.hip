@@ -466,14 +466,15 @@ struct PickArgs {
     uint32_t len;               // (the flattened space has fewer than 2^31 k-steps)
     int nk, n_tiles, slots, nc;
     float eps;                  // bound of a key's error, in units of 2 |q||c| (key_error)
+    bool wide;                  // wide_order(n, d)
 };
 
 constexpr int kPickPoints = 4;   // points per wave
 
 // fp32 distances of point row q to the m centres cand_s, by 256 threads, in the order of additions that the look-ups'
-// re-scoring has for rows of this length (rescore_block_all<256, .> and rescore_wave): whoever assigns a point, nearly equal
-// distances compare alike.  (Not always those of up to 1,024 points of 16,384 values and more: see wide_order.)
-__device__ inline void exact_distances(const float *q, const float *centers, int64_t d, const int32_t *cand_s, int m, float *dist_s, float *red_s, int tid)
+// re-scoring has for rows of this length (rescore_block_all<256, .> and rescore_wave; wide: rescore_block_all<1024, .>, four
+// threads' chains by each): whoever assigns a point, nearly equal distances compare alike.
+__device__ inline void exact_distances(const float *q, const float *centers, int64_t d, bool wide, const int32_t *cand_s, int m, float *dist_s, float *red_s, int tid)
 {
     const int lane = tid & 63, w = tid >> 6;
     auto wave_sum = [](float v) {
@@ -513,13 +514,19 @@ __device__ inline void exact_distances(const float *q, const float *centers, int
         return acc;
     };
     if (d >= 4096 && d % 8 == 0) {   // (rows start on 16-byte boundaries)
+        const int parts = wide ? 4 : 1;
         for (int j = 0; j < m; ++j) {
-            const float v = wave_sum(chain(centers + cand_s[j] * d, (int64_t)tid * 8, 256 * 8));
-            if (lane == 0) red_s[w] = v;
-            __syncthreads();
-            if (tid == 0) dist_s[j] = (red_s[0] + red_s[1]) + (red_s[2] + red_s[3]);
-            __syncthreads();
+            float t = 0.f;
+            for (int part = 0; part < parts; ++part) {
+                const float v = wave_sum(chain(centers + cand_s[j] * d, (int64_t)(part * 256 + tid) * 8, parts * 256 * 8));
+                if (lane == 0) red_s[w] = v;
+                __syncthreads();
+                t += (red_s[0] + red_s[1]) + (red_s[2] + red_s[3]);
+                __syncthreads();
+            }
+            if (tid == 0) dist_s[j] = t;
         }
+        __syncthreads();
         return;
     }
     for (int j = w; j < m; j += 4) {
@@ -671,7 +678,7 @@ __global__ __launch_bounds__(256) void kmeans_pick_kernel(PickArgs p)
         }
         __syncthreads();
         const int m = count_s;
-        exact_distances(p.x + i * p.d, p.centers, p.d, cand_s, m, dist_s, red_s, (int)threadIdx.x);
+        exact_distances(p.x + i * p.d, p.centers, p.d, p.wide, cand_s, m, dist_s, red_s, (int)threadIdx.x);
         if (w == 0) {   // the nearest, equal distances the lower index (which comes first)
             uint64_t best = kSentinel;
             for (int j = lane; j < m; j += 64) {
@@ -780,7 +787,7 @@ hipError_t launch_kmeans_assign(const RowsPlan &pl, const float *points, int64_t
     default: return hipErrorInvalidValue;
     }
     if (e != hipSuccess) return e;
-    PickArgs k{points, centers, part, sq, norm, assign, n, d, kc, (uint32_t)pl.len, pl.nk, pl.n_tiles, pl.slots, pl.nc, key_error(pl)};
+    PickArgs k{points, centers, part, sq, norm, assign, n, d, kc, (uint32_t)pl.len, pl.nk, pl.n_tiles, pl.slots, pl.nc, key_error(pl), wide_order(n, d)};
     const dim3 grid((unsigned)((n + 4 * kPickPoints - 1) / (4 * kPickPoints)));
     if (pl.n_tiles == 1) hipLaunchKernelGGL(kmeans_pick_kernel<1>, grid, dim3(256), 0, s, k);
     else hipLaunchKernelGGL(kmeans_pick_kernel<kRowsMaxTiles>, grid, dim3(256), 0, s, k);

@@ -185,11 +185,24 @@ def test_projection_on_a_buffer_sized_for_the_full_batch():
         fc.close()
 
 
-def test_kmeans_build_on_smaller_buffers():
-    n, d, kc, iters = 3000, 520, 300, 2
+@pytest.mark.parametrize("n,d,kc,twins", [
+    (3000, 520, 300, False),
+    (512, 16384, 512, True), (512, 16392, 500, True),   # the longest rows of few points, whose distances 1,024 threads add up
+    (1030, 16384, 400, True), (600, 4104, 200, True), (700, 515, 260, True),
+])
+def test_kmeans_build_on_smaller_buffers(n, d, kc, twins):
+    iters = 2
     g = torch.Generator().manual_seed(12)
     pts, lab = torch.randn(n, d, generator=g).cuda(), torch.randint(0, 7, (n,), generator=g, dtype=torch.int32).cuda()
     init = pts[:kc].clone()
+    if twins:
+        # two centres for every point, whose distances are sums of the same squares in another order: the nearer one is
+        # a matter of the roundings
+        iters = 0
+        at = torch.randint(-32, 33, (kc // 2, d), generator=g) / 16.0
+        off = torch.randint(-4095, 4096, (kc // 2, d), generator=g) / 4096.0
+        init = torch.stack([at + off, at + off[:, torch.randperm(d, generator=g)]], 1).view(kc, d).cuda()
+        pts = at[torch.arange(n) % (kc // 2)].cuda()
     fc = binding.FreezeCache(1)
     try:
         want = fc.build_kmeans_layer(0, pts, lab, 7, init, iters)
