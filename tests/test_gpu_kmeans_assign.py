@@ -183,3 +183,17 @@ def test_centres_of_more_than_2_to_the_32_values():
         fc.close()
         del pts, got, fc
         torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("n,d,kc", [(600, 4100, 33), (700, 4099, 50), (900, 33, 20), (520, 36, 300), (513, 95, 70), (400, 64, 16)])
+def test_large_first_value(n, d, kc):
+    # The row's first values stand in for what lies past its end, and are taken off the sums of squares again: the bound of the
+    # keys' errors must not fall short.  The large value is the same everywhere, so that distances are those of the others.
+    rng = np.random.default_rng(n + d)
+    centre = 2.0 * rng.standard_normal((5, d))
+    pts = (centre[rng.integers(0, 5, n)] + rng.standard_normal((n, d))).astype(np.float32)
+    pts[:, 0] = 3000.37
+    cen = pts[rng.permutation(n)[:kc]].copy()
+    want, gap = _nearest64(pts, cen)
+    assert gap > 4e-6
+    np.testing.assert_allclose(_build(pts, cen)["centers"], _means(pts, want, cen), rtol=1e-6, atol=1e-7)
