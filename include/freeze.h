@@ -246,7 +246,7 @@ int freeze_compute_thresholds(freeze_ctx *ctx, int num_layers, const int *layers
  * k-means cache (Sec. 4, "k-means"): the points of a layer are clustered and a cache item is
  * a cluster centre with the majority label of its cluster and the share of the cluster that
  * carries it.  freeze_kmeans_build runs `iters` rounds of Lloyd's iterations from the given
- * centres (assignment = the batched look-up of every point against the centres with k = 1,
+ * centres (assignment = every point to its nearest centre by fp32 distances, as a look-up with k = 1,
  * equal distances -> the lower centre; update = mean of the assigned points, summed in point
  * order in fp64 and rounded once to fp32; a cluster that loses all its points keeps its
  * centre, gets label 0 and share 0), then assigns once more for the labels and shares, and
@@ -282,7 +282,7 @@ int freeze_kmeans_read(freeze_ctx *ctx, int layer, float *out_centers, int32_t *
  *   weights  [m, d] row-major, fp32 or bf16 (weights_dtype); bias [m] fp32.
  *   storage  >= freeze_projection_storage_bytes() bytes, 256-byte aligned, must outlive the
  *            calls of freeze_project on the slot; build workspace: >= 256 + 4 m bytes.
- *   x        [b, d] fp32, 16-byte aligned;  out [b, m] fp32, 16-byte aligned.
+ *   x        [b, d] fp32, 16-byte aligned;  out [b, m] fp32, 16-byte aligned; it may lie over x.
  *   workspace of freeze_project: freeze_project_workspace_bytes() bytes; a smaller one is taken while it
  *            holds the bf16 copy of x and, for larger batches, the padded outputs.
  * b == 0 is a no-op.
